@@ -46,6 +46,8 @@ struct Plan {
     size_t o_state = 0, o_transits = 0;
     int window = 0;            // walks grouped per window of this many samples (0: GPU-wide grouping)
     uint32_t heavy_min = 64;   // pairs of one transit in a window from which the workgroup class serves it
+    bool free_walk = false;    // walks over the graph's links, one lane per walk (nd_walk_free.hip)
+    size_t o_flags = 0, o_parts = 0;  // per workgroup: flag, live pairs per step
 };
 
 int64_t step_fanout(int app, const nd_params* p, int i) {
@@ -192,6 +194,7 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
         const bool overridden = p->sched_force_class != ND_CLASS_AUTO || p->sched_sub_max != 0 ||
                                 p->sched_wg_max != 0 || p->sched_group_bits != 0;
         if (p->sched_window > 0) pl->window = p->sched_window;
+        else if (p->sched_window == 0 && !overridden && g.links && (app == ND_DEEPWALK || app == ND_PPR)) pl->free_walk = true;
         else if (p->sched_window == 0 && !overridden) pl->window = walk_window_auto(pl->S);
         if (pl->window > 0 && p->sched_window > 0 && p->sched_sub_max > 0)
             pl->heavy_min = (uint32_t)p->sched_sub_max + 1u;
@@ -232,7 +235,11 @@ void layout(Plan* pl, int64_t V) {
         pl->o_state = o; o = align_up(o + (size_t)(pl->state_len > 0 ? pl->state_len : 1) * 4);
         pl->o_transits = o; o = align_up(o + (size_t)(pl->S > 0 ? pl->S : 1) * 4);
     }
-    if (pl->mode == ND_MODE_TRANSIT_PARALLEL && !pl->collective && pl->window == 0) {
+    if (pl->free_walk) {
+        const size_t groups = (size_t)walk_free_groups(pl->S);
+        pl->o_flags = o; o = align_up(o + groups * 4);
+        pl->o_parts = o; o = align_up(o + groups * (size_t)pl->k * 4);
+    } else if (pl->mode == ND_MODE_TRANSIT_PARALLEL && !pl->collective && pl->window == 0) {
         const size_t n = (size_t)(pl->max_slots > 0 ? pl->max_slots : 1);
         pl->o_keysA = o; o = align_up(o + n * 4);
         pl->o_valsA = o; o = align_up(o + n * 4);
@@ -263,8 +270,7 @@ __global__ void init_header_kernel(WsHeader* h, uint32_t num_steps, StepCtl* ctl
                                    int64_t bit_words) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) {
-        h->status = 0;
-        h->num_steps = num_steps;
+        write_header(h, num_steps, 0, 0, 0);
     }
     if (i < num_steps) ctl[i] = StepCtl{};
     if (i < bit_words) bits[i] = 0;
@@ -506,8 +512,9 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     char* ws = (char*)workspace_dev;
     WsHeader* hdr = (WsHeader*)ws;
     StepCtl* ctl = (StepCtl*)(ws + pl.o_ctl);
-    mark_phase(ND_PHASE_INIT, stream);
-    {
+    const bool own_header = pl.free_walk && pl.S > 0;  // its first kernel writes the header
+    if (!own_header) {
+        mark_phase(ND_PHASE_INIT, stream);
         const int64_t n_init = pl.bit_words > pl.k ? pl.bit_words : pl.k;
         hipLaunchKernelGGL(init_header_kernel, dim3((unsigned)((n_init + 255) / 256)), dim3(256), 0,
                            stream, hdr, (uint32_t)pl.k, ctl, (uint32_t*)(ws + pl.o_bits), pl.bit_words);
@@ -572,6 +579,12 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     int32_t* mrw_state = (int32_t*)(ws + pl.o_state);
     int32_t* mrw_transits = (int32_t*)(ws + pl.o_transits);
     const uint32_t mrw_R = (uint32_t)params->roots_per_sample;
+    if (pl.free_walk) {
+        rc = walk_free(g, draw, a, pl.S, pl.k, roots_dev, step_out_dev, ws, pl.o_flags, pl.o_parts, stream);
+        if (rc != ND_OK) return rc;
+        mark_phase(ND_PHASE_NONE, stream);
+        return ND_OK;
+    }
     if (pl.window > 0) {  // walks grouped per window of samples, inside LDS
         rc = walk_windows(g, draw, multirw, a, pl.S, pl.k, pl.window, pl.heavy_min, params->sched_force_class,
                           roots_dev, 1, step_out_dev, &hdr->status, ctl, multirw ? mrw_state : nullptr,
@@ -707,8 +720,12 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};
 
-__global__ void publish_status_kernel(const WsHeader* hdr, uint32_t* status_out) {
-    *status_out = hdr->status;
+__global__ __launch_bounds__(256) void publish_status_kernel(const WsHeader* hdr, uint32_t* status_out) {
+    const uint32_t* flags = (const uint32_t*)((const char*)hdr + hdr->o_flags);
+    uint32_t any = hdr->status;
+    for (uint32_t i = threadIdx.x; i < hdr->n_groups; i += 256) any |= flags[i];
+    const int all = __syncthreads_or((int)any);
+    if (threadIdx.x == 0) *status_out = all ? 1u : 0u;
 }
 
 // Device address of the current device's copy of the array (looked up on first use).
@@ -756,7 +773,7 @@ int nd_sample_static(const nd_graph* h, int app, const nd_params* params, const 
                      (size_t)ND_STATIC_SCRATCH_BYTES, true, stream);
     if (rc != ND_OK) return rc;
     if (status_dev) {
-        hipLaunchKernelGGL(publish_status_kernel, dim3(1), dim3(1), 0, stream, (const WsHeader*)scratch,
+        hipLaunchKernelGGL(publish_status_kernel, dim3(1), dim3(256), 0, stream, (const WsHeader*)scratch,
                            status_dev);
         ND_HIP_CHECK(hipGetLastError());
     }
@@ -768,10 +785,17 @@ int nd_sample_status(const void* workspace_dev, void* hip_stream) {
         set_error("workspace is NULL");
         return ND_ERR_NULL_POINTER;
     }
-    uint32_t status = 0;
-    ND_HIP_CHECK(hipMemcpyAsync(&status, workspace_dev, sizeof(status), hipMemcpyDeviceToHost,
-                                (hipStream_t)hip_stream));
+    WsHeader hdr;
+    ND_HIP_CHECK(hipMemcpyAsync(&hdr, workspace_dev, sizeof(hdr), hipMemcpyDeviceToHost, (hipStream_t)hip_stream));
     ND_HIP_CHECK(hipStreamSynchronize((hipStream_t)hip_stream));
+    uint32_t status = hdr.status;
+    if (hdr.n_groups > 0) {
+        std::vector<uint32_t> flags(hdr.n_groups);
+        ND_HIP_CHECK(hipMemcpyAsync(flags.data(), (const char*)workspace_dev + hdr.o_flags, flags.size() * 4,
+                                    hipMemcpyDeviceToHost, (hipStream_t)hip_stream));
+        ND_HIP_CHECK(hipStreamSynchronize((hipStream_t)hip_stream));
+        for (uint32_t f : flags) status |= f;
+    }
     if (status & 1u) {
         set_error("a root was outside [0, V); it was treated as NULL");
         return ND_ERR_BAD_ROOT;
@@ -795,7 +819,16 @@ int nd_sample_stats(const void* workspace_dev, void* hip_stream, int32_t max_ste
     int n = (int)hdr.num_steps < max_steps ? (int)hdr.num_steps : max_steps;
     if (n > ND_MAX_WALK_STEPS) n = ND_MAX_WALK_STEPS;
     static thread_local StepCtl host_ctl[ND_MAX_WALK_STEPS];
-    if (n > 0) {
+    if (n > 0 && hdr.n_groups > 0) {  // only the live pairs are counted on these routes
+        std::vector<uint32_t> parts((size_t)hdr.n_groups * hdr.num_steps);
+        ND_HIP_CHECK(hipMemcpyAsync(parts.data(), (const char*)workspace_dev + hdr.o_parts, parts.size() * 4,
+                                    hipMemcpyDeviceToHost, stream));
+        ND_HIP_CHECK(hipStreamSynchronize(stream));
+        for (int i = 0; i < n; ++i) {
+            host_ctl[i] = StepCtl{};
+            for (uint32_t b = 0; b < hdr.n_groups; ++b) host_ctl[i].P += parts[(size_t)b * hdr.num_steps + (size_t)i];
+        }
+    } else if (n > 0) {
         ND_HIP_CHECK(hipMemcpyAsync(host_ctl, (const char*)workspace_dev + sizeof(WsHeader),
                                     sizeof(StepCtl) * (size_t)n, hipMemcpyDeviceToHost, stream));
         ND_HIP_CHECK(hipStreamSynchronize(stream));

@@ -5,6 +5,9 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <atomic>
+#include <mutex>
+
 #include "../../include/nd.h"
 
 namespace nd {
@@ -29,6 +32,28 @@ void set_error(const char* fmt, ...);
 void mark_phase(int phase, hipStream_t stream);
 
 // ---------------------------------------------------------------- graph
+// What a walk needs of the edge it draws, in one aligned 16-byte piece: the vertex at its end and
+// where that vertex's row lies, so that a step is one scattered fetch instead of two dependent ones
+// (row offsets, then the entry).  The quantised weight sits in the fourth word.
+struct Link {
+    int32_t v;
+    uint32_t rs, deg;   // the row of v: first entry and length
+    uint32_t wq;        // quantised weight of this edge (0 on an unweighted graph)
+};
+static_assert(sizeof(Link) == 16, "one 16-byte load");
+// On a weighted graph every Link is followed by what the inverse transform needs (32 bytes per edge).
+// Entry j of a row with running sums cum and total T is drawn when mulhi64(R, T) < cum[j] for the
+// first time, R being the draw's 64-bit word, and that is R < ceil(cum[j] * 2^64 / T): `thr`, so the
+// total is not looked up and nothing is multiplied.  The words with mulhi32(high word, deg) == i
+// start the search at entry `guide` of cell i (Chen and Asau's guide table: on average about one
+// entry is looked at, whatever the row's length).
+struct WeightLink {
+    uint64_t thr;
+    uint32_t guide;
+    uint32_t always;    // 1: thr would be 2^64 (only zero weights follow)
+};
+static_assert(sizeof(WeightLink) == 16, "one 16-byte load");
+
 struct Graph {
     int64_t V = 0, E = 0;
     int off64 = 0;              // width of row offsets as stored
@@ -40,6 +65,29 @@ struct Graph {
     int device = 0;
     int num_cus = 256;
     int64_t max_degree = 0;
+    // E links, each followed by its WeightLink on a weighted graph; null when E >= 2^31 or when the
+    // device had no room for them (walks then take the window kernel)
+    Link* links = nullptr;
+    // Membership table of every row (see RowSet): built when node2vec is first asked for
+    mutable std::atomic<int32_t*> rowset{nullptr};
+    mutable std::mutex rowset_mutex;
+    mutable bool rowset_failed = false;
+};
+void graph_need_rowset(const Graph& g);
+
+// Is u in the row of v?  Every row owns a hash table of at least 2 deg + 1 places in groups of four
+// (16 bytes), open addressing by groups, empty places -1: one fetch answers most questions where a
+// search down the row takes log2(deg) dependent ones.  Row v's groups start at rs / 2 + v.
+struct RowSet {
+    const int32_t* table;
+    __host__ __device__ static uint64_t first_group(int64_t v, uint64_t rs) { return rs / 2 + (uint64_t)v; }
+    __host__ __device__ static uint32_t groups(uint64_t rs, uint32_t deg) {
+        return (uint32_t)((rs + deg) / 2 - rs / 2) + 1u;
+    }
+    __host__ __device__ static uint32_t hash(int32_t u) {
+        const uint32_t x = (uint32_t)u * 0x9E3779B1u;
+        return x ^ (x >> 15);
+    }
 };
 
 // Device-side view passed to kernels by value.
@@ -114,9 +162,23 @@ static_assert(sizeof(StepCtl) == 64, "one control block per 64 bytes");
 struct WsHeader {
     uint32_t status;        // bit 0: a root was out of range
     uint32_t num_steps;
-    uint32_t pad[62];
+    // Routes that need no kernel to clear counters: every workgroup writes what it found to places of
+    // its own, and whoever asks (nd_sample_status, nd_sample_stats) adds up.  0 groups: not that route.
+    uint32_t n_groups;
+    uint32_t pad0;
+    uint64_t o_flags;       // n_groups words: a root was out of range
+    uint64_t o_parts;       // [n_groups][num_steps] words: live pairs
+    uint32_t pad[56];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
+__device__ __forceinline__ void write_header(WsHeader* h, uint32_t num_steps, uint32_t n_groups, uint64_t o_flags,
+                                             uint64_t o_parts) {
+    h->status = 0;
+    h->num_steps = num_steps;
+    h->n_groups = n_groups;
+    h->o_flags = o_flags;
+    h->o_parts = o_parts;
+}
 
 // ---------------------------------------------------------------- radix sort plan
 constexpr int kSortThreads = 512;       // large inputs: 8,192 keys per tile

@@ -69,6 +69,12 @@ int walk_windows(const Graph& gr, int draw, bool multirw, const DrawArgs& d, int
                  int32_t* const* step_out, uint32_t* status, StepCtl* ctl, int32_t* mrw_state, uint32_t R,
                  hipStream_t stream);
 
+// Random walks over the graph's links (nd_walk_free.hip): DeepWalk and PPR.  The call's header, one flag
+// per workgroup (o_flags) and the live walks per workgroup and step (o_parts) go to the workspace.
+int64_t walk_free_groups(int64_t S);
+int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t num_steps, const int32_t* roots,
+              int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, hipStream_t stream);
+
 // Unique neighbours (Section 6.3) for one k-hop step whose first draw round has already been
 // written to `out`: per sample, duplicates are removed (the lowest slot keeps the vertex) and
 // the slots that lost draw again, sample-parallel, for rounds - 1 further attempts.
