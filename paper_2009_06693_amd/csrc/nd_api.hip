@@ -47,6 +47,7 @@ struct Plan {
     int window = 0;            // walks grouped per window of this many samples (0: GPU-wide grouping)
     uint32_t heavy_min = 64;   // pairs of one transit in a window from which the workgroup class serves it
     bool free_walk = false;    // walks over the graph's links, one lane per walk (nd_walk_free.hip)
+    bool fused = false;        // k-hop: all hops in one launch (nd_khop.hip)
     size_t o_flags = 0, o_parts = 0;  // per workgroup: flag, live pairs per step
 };
 
@@ -189,16 +190,20 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
             }
         }
     }
+    // what asks for the scheduling index of Section 6.1.2 as such
+    const bool overridden = p->sched_force_class != ND_CLASS_AUTO || p->sched_sub_max != 0 || p->sched_wg_max != 0 ||
+                            p->sched_group_bits != 0;
     pl->window = 0;
     if (walk && p->mode == ND_MODE_TRANSIT_PARALLEL) {
-        const bool overridden = p->sched_force_class != ND_CLASS_AUTO || p->sched_sub_max != 0 ||
-                                p->sched_wg_max != 0 || p->sched_group_bits != 0;
         if (p->sched_window > 0) pl->window = p->sched_window;
         else if (p->sched_window == 0 && !overridden && g.links && (app == ND_DEEPWALK || app == ND_PPR)) pl->free_walk = true;
         else if (p->sched_window == 0 && !overridden) pl->window = walk_window_auto(pl->S);
         if (pl->window > 0 && p->sched_window > 0 && p->sched_sub_max > 0)
             pl->heavy_min = (uint32_t)p->sched_sub_max + 1u;
     }
+    pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
+                p->unique_rounds == 0 &&
+                khop_fused_fits(g, p->fanout, p->num_steps);
     pl->max_slots = 0;
     pl->max_out = 0;
     double guard = 1.0;
@@ -227,7 +232,8 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     return ND_OK;
 }
 
-void layout(Plan* pl, int64_t V) {
+void layout(Plan* pl, const Graph& g, const nd_params* p) {
+    const int64_t V = g.V;
     size_t o = sizeof(WsHeader);
     pl->o_ctl = o;
     o = align_up(o + sizeof(StepCtl) * (size_t)pl->k);
@@ -262,6 +268,13 @@ void layout(Plan* pl, int64_t V) {
         pl->o_chunk_idx = o; o = align_up(o + (size_t)pl->cap_chunks * 4);
         pl->bit_words = (V + 31) / 32;
         pl->o_bits = o; o = align_up(o + (size_t)pl->bit_words * 4);
+    }
+    if (pl->fused) {  // inside what the call may use when it groups
+        const size_t groups = (size_t)khop_fused_groups(g, p->fanout, pl->k, pl->S);
+        size_t f = pl->o_ctl;
+        pl->o_flags = f; f = align_up(f + groups * 4);
+        pl->o_parts = f; f = align_up(f + groups * (size_t)pl->k * 4);
+        if (f > o) o = f;
     }
     pl->total = o;
 }
@@ -467,7 +480,7 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
     Plan pl;
     const int rc = check_params(*h->g, app, params, num_roots, &pl);
     if (rc != ND_OK) return rc;
-    layout(&pl, h->g->V);
+    layout(&pl, *h->g, params);
     if (num_steps) *num_steps = pl.k;
     if (step_len) {
         for (int i = 0; i < pl.k; ++i) {
@@ -482,15 +495,16 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
 
 // The body of nd_sample and nd_sample_static.  fixed_scratch: the workspace is the library's
 // own array of a fixed size, so a call that needs more is told the limit, not a size to bring.
+// status_dev (may be null): *status_done tells whether the call's own kernel wrote the status there.
 static int sample_impl(const nd_graph* h, int app, const nd_params* params, const int32_t* roots_dev,
                        int64_t num_roots, uint64_t seed, int32_t* const* step_out_dev,
-                       void* workspace_dev, size_t workspace_bytes, bool fixed_scratch,
-                       hipStream_t stream) {
+                       void* workspace_dev, size_t workspace_bytes, bool fixed_scratch, uint32_t* status_dev,
+                       bool* status_done, hipStream_t stream) {
     const Graph& g = *h->g;
     Plan pl;
     int rc = check_params(g, app, params, num_roots, &pl);
     if (rc != ND_OK) return rc;
-    layout(&pl, g.V);
+    layout(&pl, g, params);
     if (fixed_scratch && workspace_bytes < pl.total) {
         set_error("this call needs %zu bytes of scratch; nd_sample_static has %zu (ND_STATIC_SCRATCH_BYTES): "
                   "use fewer roots per call or nd_sample with a workspace", pl.total, workspace_bytes);
@@ -512,7 +526,7 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     char* ws = (char*)workspace_dev;
     WsHeader* hdr = (WsHeader*)ws;
     StepCtl* ctl = (StepCtl*)(ws + pl.o_ctl);
-    const bool own_header = pl.free_walk && pl.S > 0;  // its first kernel writes the header
+    const bool own_header = (pl.free_walk || pl.fused) && pl.S > 0;  // its first kernel writes the header
     if (!own_header) {
         mark_phase(ND_PHASE_INIT, stream);
         const int64_t n_init = pl.bit_words > pl.k ? pl.bit_words : pl.k;
@@ -579,6 +593,15 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     int32_t* mrw_state = (int32_t*)(ws + pl.o_state);
     int32_t* mrw_transits = (int32_t*)(ws + pl.o_transits);
     const uint32_t mrw_R = (uint32_t)params->roots_per_sample;
+    if (pl.fused) {
+        const bool few = num_roots <= kKhopStatusRoots;
+        rc = khop_fused(g, a, params->fanout, pl.k, pl.S, roots_dev, step_out_dev, ws, pl.o_flags, pl.o_parts,
+                        few ? status_dev : nullptr, stream);
+        if (rc != ND_OK) return rc;
+        if (few && status_done) *status_done = true;
+        mark_phase(ND_PHASE_NONE, stream);
+        return ND_OK;
+    }
     if (pl.free_walk) {
         rc = walk_free(g, draw, a, pl.S, pl.k, roots_dev, step_out_dev, ws, pl.o_flags, pl.o_parts, stream);
         if (rc != ND_OK) return rc;
@@ -706,7 +729,7 @@ int nd_sample(const nd_graph* h, int app, const nd_params* params, const int32_t
         return ND_ERR_NULL_POINTER;
     }
     return sample_impl(h, app, params, roots_dev, num_roots, seed, step_out_dev, workspace_dev,
-                       workspace_bytes, false, (hipStream_t)hip_stream);
+                       workspace_bytes, false, nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
 // ---------------------------------------------------------------- scratch owned by the library
@@ -769,10 +792,11 @@ int nd_sample_static(const nd_graph* h, int app, const nd_params* params, const 
     int rc = static_scratch(&scratch);
     if (rc != ND_OK) return rc;
     hipStream_t stream = (hipStream_t)hip_stream;
+    bool status_done = false;
     rc = sample_impl(h, app, params, roots_dev, num_roots, seed, step_out_dev, scratch,
-                     (size_t)ND_STATIC_SCRATCH_BYTES, true, stream);
+                     (size_t)ND_STATIC_SCRATCH_BYTES, true, status_dev, &status_done, stream);
     if (rc != ND_OK) return rc;
-    if (status_dev) {
+    if (status_dev && !status_done) {
         hipLaunchKernelGGL(publish_status_kernel, dim3(1), dim3(256), 0, stream, (const WsHeader*)scratch,
                            status_dev);
         ND_HIP_CHECK(hipGetLastError());
