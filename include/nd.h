@@ -132,17 +132,22 @@ typedef struct nd_params {
                                /* segment scan or classification; every draw then goes    */
                                /* through the lane-per-draw kernel, which needs transits  */
                                /* to be near each other, not equal.  Same output.         */
-    int32_t sched_window;      /* random walks: scope of the grouping by transit.              */
+    int32_t sched_window;      /* walks and k-hop: scope of the grouping by transit.           */
                                /* -1: all samples of the call (GPU-wide sort and scan, three   */
                                /* classes); 256, 1024 or 2048: windows of that many            */
-                               /* consecutive samples, each kept by one workgroup for the      */
-                               /* whole walk (pairs per transit counted in LDS; a transit with */
+                               /* consecutive samples (walks), each kept by one workgroup for  */
+                               /* the whole walk (pairs per transit counted in LDS; a transit with */
                                /* many pairs in its window is sorted out, grouped and served   */
                                /* workgroup-wide from LDS, the others lane-per-pair;           */
                                /* sched_sub_max then is the largest number of pairs of one     */
                                /* transit in a window served lane-per-pair, default 63; no     */
-                               /* grid class); 0: windows for walks unless sched_force_class,  */
-                               /* sched_sub_max, sched_wg_max or sched_group_bits is set.      */
+                               /* grid class); 0: the library's choice unless                  */
+                               /* sched_force_class, sched_sub_max, sched_wg_max or            */
+                               /* sched_group_bits is set: walks run one lane per walk over    */
+                               /* the graph's links, ungrouped (windows where the device has   */
+                               /* no room for links); k-hop runs all hops in one launch where  */
+                               /* draws seldom meet in a line of the graph, and groups GPU-    */
+                               /* wide on dense graphs with many pairs per vertex.             */
                                /* Same output.                                                 */
     int32_t reserved[2];
 } nd_params;

@@ -201,9 +201,6 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
         if (pl->window > 0 && p->sched_window > 0 && p->sched_sub_max > 0)
             pl->heavy_min = (uint32_t)p->sched_sub_max + 1u;
     }
-    pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
-                p->unique_rounds == 0 &&
-                khop_fused_fits(g, p->fanout, p->num_steps);
     pl->max_slots = 0;
     pl->max_out = 0;
     double guard = 1.0;
@@ -229,6 +226,8 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
         const size_t hb = sort_hist_bytes(make_sort_plan(ns, g.V, p->sched_group_bits));
         if (hb > pl->hist_bytes) pl->hist_bytes = hb;
     }
+    pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
+                p->unique_rounds == 0 && khop_fused_fits(g, p->fanout, p->num_steps, pl->S);
     return ND_OK;
 }
 

@@ -1,14 +1,8 @@
 // k-hop sampling (Section 3 and Section 6.1 of the paper: `stepSize(i)` uniform neighbours of every
-// transit) by two routes that need no exact grouping by transit:
-//
-//   fused    every workgroup carries a few samples through all hops: what a hop draws is a Link, which
-//            holds the row of the drawn vertex, so the next hop finds its rows in LDS.  One launch,
-//            nothing read back from the outputs, no sort.  For calls that draw too little of the
-//            graph for two draws to meet in a cache line.
-//   grouped  a step with many draws per line of the graph: its (transit, slot) pairs are brought into
-//            256 buckets of neighbouring transits by one stable radix pass, drawn bucket by bucket while
-//            the bucket's rows sit in L2, written in that order, and put back into slot order by a pass
-//            that reads 256 rising streams and writes whole lines (NULL included).
+// transit) in one launch: every workgroup carries a few samples through all hops.  What a hop draws is
+// a Link, which holds the row of the drawn vertex, so the next hop finds its rows in LDS; nothing is
+// read back from the outputs and nothing is sorted.  Grouping by transit (nd_sort.hip, nd_sched.hip,
+// nd_sample.hip) remains for calls whose draws meet often enough in a line of the graph.
 #include "nd_common.h"
 #include "nd_philox.h"
 #include "nd_wave.h"
@@ -40,12 +34,20 @@ struct FusedArgs {
     uint32_t* status_out;       // may be null
 };
 
+// R consecutive entries (R = 2: eight bytes, aligned).
+template <int R>
+__device__ __forceinline__ void store_run(int32_t* p, const int32_t* v) {
+    if (R == 2) *reinterpret_cast<int2*>(p) = make_int2(v[0], v[1]);
+    else *p = v[0];
+}
+
 // A place in a buffer of rows: where the row of a slot's vertex lies.
 __device__ __forceinline__ uint2 row_of_link(const Link& l) { return make_uint2(l.rs, l.deg); }
 
 // Bound by latency (small calls: a hop is generator, link, row; 37 roots of three hops take one launch
 // instead of 26) or by the rate of scattered fetches (large ones).
-template <int STRIDE, typename OffT>
+// R: draws per lane of the last hop, a divisor of its fanout.
+template <int STRIDE, int R, typename OffT>
 __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<OffT> g, FusedArgs a) {
     extern __shared__ uint2 s_rows[];  // rows of the parents of this hop, of the next, in turn
     __shared__ uint32_t s_live[ND_MAX_FANOUT_STEPS];
@@ -84,12 +86,12 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
             for (uint32_t d = tid; d < total; d += T) {
                 const uint32_t s = fastdiv(d, a.div_w[hop]);
                 const uint2 row = rows[fastdiv(d, a.div_m[hop])];
-                const Rand4 r = draw4(a.seed, a.sample_base + s0 + s, d - s * W, (uint32_t)hop, 0u);
                 Link l;
                 l.v = ND_NULL_VERTEX;
                 l.rs = 0;
                 l.deg = 0;
                 if (row.y > 0u) {
+                    const Rand4 r = draw4(a.seed, a.sample_base + s0 + s, d - s * W, (uint32_t)hop, 0u);
                     l = a.links[(uint64_t)(row.x + mulhi32(r.r0, row.y)) * STRIDE];
                     ++live;
                 }
@@ -98,33 +100,40 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
             }
             if (live) atomicAdd(&s_live[hop + 1], live);
         } else {
-            // four independent draws per lane and round
-            const uint32_t share = ((total + a.splits - 1u) / a.splits + T - 1u) / T * T;
+            // kInFlight independent pieces per lane and round, of R consecutive draws of one parent each
+            constexpr uint32_t kInFlight = 4 / R;
+            const uint32_t pieces = total / R;
+            const uint32_t share = ((pieces + a.splits - 1u) / a.splits + T - 1u) / T * T;
             const uint32_t begin = part * share;
-            const uint32_t end = begin + share < total ? begin + share : total;
-            for (uint32_t d0 = begin + tid; d0 < end; d0 += 4u * T) {
-                uint2 row[4];
-                uint32_t e[4];
-                int32_t v[4];
+            const uint32_t end = begin + share < pieces ? begin + share : pieces;
+            for (uint32_t d0 = begin + tid; d0 < end; d0 += kInFlight * T) {
+                uint2 row[kInFlight];
+                uint32_t e[kInFlight][R];
+                int32_t v[kInFlight][R];
 #pragma unroll
-                for (uint32_t u = 0; u < 4u; ++u) {
-                    const uint32_t d = d0 + u * T < end ? d0 + u * T : d0;
-                    row[u] = rows[fastdiv(d, a.div_m[hop])];
-                    const uint32_t s = fastdiv(d, a.div_w[hop]);
-                    e[u] = 0;
-                    if (u == 0 || d != d0) {
-                        const Rand4 r = draw4(a.seed, a.sample_base + s0 + s, d - s * W, (uint32_t)hop, 0u);
-                        e[u] = row[u].x + mulhi32(r.r0, row[u].y);
+                for (uint32_t u = 0; u < kInFlight; ++u) {
+                    const uint32_t d = (d0 + u * T) * R;
+                    row[u] = d0 + u * T < end ? rows[fastdiv(d, a.div_m[hop])] : make_uint2(0u, 0u);
+                    // the draws of a sample without live parents are neighbours: whole wavefronts skip this
+                    if (row[u].y > 0u) {
+                        const uint32_t s = fastdiv(d, a.div_w[hop]);
+#pragma unroll
+                        for (uint32_t i = 0; i < R; ++i) {
+                            const Rand4 r = draw4(a.seed, a.sample_base + s0 + s, d - s * W + i, (uint32_t)hop, 0u);
+                            e[u][i] = row[u].x + mulhi32(r.r0, row[u].y);
+                        }
                     }
                 }
 #pragma unroll
-                for (uint32_t u = 0; u < 4u; ++u) {
-                    v[u] = ND_NULL_VERTEX;
-                    if (row[u].y > 0u && d0 + u * T < end) v[u] = g.col[e[u]];
-                }
+                for (uint32_t u = 0; u < kInFlight; ++u)
 #pragma unroll
-                for (uint32_t u = 0; u < 4u; ++u)
-                    if (d0 + u * T < end) out[d0 + u * T] = v[u];
+                    for (uint32_t i = 0; i < R; ++i) {
+                        v[u][i] = ND_NULL_VERTEX;
+                        if (row[u].y > 0u) v[u][i] = g.col[e[u][i]];
+                    }
+#pragma unroll
+                for (uint32_t u = 0; u < kInFlight; ++u)
+                    if (d0 + u * T < end) store_run<R>(out + (d0 + u * T) * R, v[u]);
             }
         }
         __syncthreads();
@@ -183,6 +192,10 @@ FusedShape fused_shape(const Graph& gr, int32_t k, const int64_t* W, int64_t S) 
     return f;
 }
 
+// Two draws per lane where the fanout is even and the output aligned: what a lane looks up about its
+// pair (slot, row) and works out about its place then serves two draws, and they leave in one store.
+bool khop_in_pairs(uint32_t m, const int32_t* out) { return m % 2u == 0u && ((uintptr_t)out & 7u) == 0; }
+
 void slots_per_sample(const int32_t* fanout, int32_t k, int64_t* W) {
     int64_t w = 1;
     for (int32_t i = 0; i < k; ++i) W[i] = w = w * fanout[i];
@@ -190,8 +203,19 @@ void slots_per_sample(const int32_t* fanout, int32_t k, int64_t* W) {
 
 }  // namespace
 
-bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k) {
+// Whether the fused kernel takes the call.  Its limits are the rows in LDS and the links.  Its cost is one
+// scattered fetch per line a pair's draws touch, whatever other pairs touch; grouping by transit fetches a
+// line once for all its draws and pays for it with the sort and with scattered stores.  Measured from
+// all, a tenth and a fiftieth of the vertices of ten graphs with fanouts [25,10], [10,10], [10,25], [20] and
+// [15,10,5]: grouping wins, by up to 1.4x, on dense graphs (rows that ten draws rarely share a line of)
+// with many pairs per vertex and enough draws to pay for its 26 launches; elsewhere it loses, by up to 9x.
+bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
     if (!gr.links) return false;
+    int64_t pairs = S;
+    for (int32_t i = 0; i + 1 < k; ++i) pairs *= fanout[i];  // below 2^31 by the call's plan
+    if (pairs * fanout[k - 1] >= 20000000 &&
+        ((gr.E >= 300 * gr.V && pairs >= 8 * gr.V) || (gr.E >= 80 * gr.V && pairs >= 16 * gr.V)))
+        return false;
     int64_t w = 1, prev = 1;
     for (int32_t i = 0; i + 1 < k; ++i) {
         prev = w;
@@ -239,8 +263,14 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     a.status_out = status_out;
     mark_phase(ND_PHASE_SAMPLE_SUB, stream);
     const dim3 grid((unsigned)f.groups), block(kFusedThreads);
-#define ND_FUSED_LAUNCH(STRIDE, OFFT) \
-    hipLaunchKernelGGL((khop_fused_kernel<STRIDE, OFFT>), grid, block, f.lds, stream, view_of<OFFT>(gr), a)
+    const bool pairs = khop_in_pairs(a.m[k - 1], step_out[k - 1]);
+#define ND_FUSED_LAUNCH(STRIDE, OFFT)                                                                              \
+    do {                                                                                                           \
+        if (pairs)                                                                                                 \
+            hipLaunchKernelGGL((khop_fused_kernel<STRIDE, 2, OFFT>), grid, block, f.lds, stream, view_of<OFFT>(gr), a); \
+        else                                                                                                       \
+            hipLaunchKernelGGL((khop_fused_kernel<STRIDE, 1, OFFT>), grid, block, f.lds, stream, view_of<OFFT>(gr), a); \
+    } while (0)
     if (gr.off64) {
         if (gr.wq) ND_FUSED_LAUNCH(2, int64_t);
         else ND_FUSED_LAUNCH(1, int64_t);
