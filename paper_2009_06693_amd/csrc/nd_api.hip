@@ -196,7 +196,7 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     pl->window = 0;
     if (walk && p->mode == ND_MODE_TRANSIT_PARALLEL) {
         if (p->sched_window > 0) pl->window = p->sched_window;
-        else if (p->sched_window == 0 && !overridden && g.links && (app == ND_DEEPWALK || app == ND_PPR)) pl->free_walk = true;
+        else if (p->sched_window == 0 && !overridden && g.links) pl->free_walk = true;
         else if (p->sched_window == 0 && !overridden) pl->window = walk_window_auto(pl->S);
         if (pl->window > 0 && p->sched_window > 0 && p->sched_sub_max > 0)
             pl->heavy_min = (uint32_t)p->sched_sub_max + 1u;
@@ -241,7 +241,7 @@ void layout(Plan* pl, const Graph& g, const nd_params* p) {
         pl->o_transits = o; o = align_up(o + (size_t)(pl->S > 0 ? pl->S : 1) * 4);
     }
     if (pl->free_walk) {
-        const size_t groups = (size_t)walk_free_groups(pl->S);
+        const size_t groups = (size_t)walk_free_groups(pl->S, pl->app == ND_MULTIRW ? (uint32_t)p->roots_per_sample : 0u);
         pl->o_flags = o; o = align_up(o + groups * 4);
         pl->o_parts = o; o = align_up(o + groups * (size_t)pl->k * 4);
     } else if (pl->mode == ND_MODE_TRANSIT_PARALLEL && !pl->collective && pl->window == 0) {
@@ -480,6 +480,7 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
     const int rc = check_params(*h->g, app, params, num_roots, &pl);
     if (rc != ND_OK) return rc;
     layout(&pl, *h->g, params);
+    if (app == ND_NODE2VEC && pl.free_walk) graph_need_rowset(*h->g);
     if (num_steps) *num_steps = pl.k;
     if (step_len) {
         for (int i = 0; i < pl.k; ++i) {
@@ -602,7 +603,8 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
         return ND_OK;
     }
     if (pl.free_walk) {
-        rc = walk_free(g, draw, a, pl.S, pl.k, roots_dev, step_out_dev, ws, pl.o_flags, pl.o_parts, stream);
+        rc = walk_free(g, draw, a, pl.S, pl.k, roots_dev, step_out_dev, ws, pl.o_flags, pl.o_parts,
+                       multirw ? mrw_R : 0u, mrw_state, stream);
         if (rc != ND_OK) return rc;
         mark_phase(ND_PHASE_NONE, stream);
         return ND_OK;

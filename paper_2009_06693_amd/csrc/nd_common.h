@@ -50,7 +50,9 @@ static_assert(sizeof(Link) == 16, "one 16-byte load");
 struct WeightLink {
     uint64_t thr;
     uint32_t guide;
-    uint32_t always;    // 1: thr would be 2^64 (only zero weights follow)
+    uint32_t top;       // bits 0-30: largest quantised weight in the row of the link's vertex (node2vec's
+                        // envelope); bit 31: thr would be 2^64 (only zero weights follow)
+    __host__ __device__ bool always() const { return (top >> 31) != 0u; }
 };
 static_assert(sizeof(WeightLink) == 16, "one 16-byte load");
 

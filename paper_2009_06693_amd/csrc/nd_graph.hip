@@ -127,7 +127,8 @@ constexpr int kLinkTile = 256;
 template <typename OffT>
 __global__ __launch_bounds__(256) void build_links_kernel(const OffT* __restrict__ off, const int32_t* __restrict__ col,
                                                           const uint32_t* __restrict__ wq,
-                                                          const uint64_t* __restrict__ cumq, int64_t V, int64_t E,
+                                                          const uint64_t* __restrict__ cumq,
+                                                          const uint32_t* __restrict__ maxwq, int64_t V, int64_t E,
                                                           Link* __restrict__ links, uint32_t* __restrict__ flags) {
     const int64_t first = (int64_t)blockIdx.x * kLinkTile;
     const int64_t last = first + kLinkTile < E ? first + kLinkTile - 1 : E - 1;
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(256) void build_links_kernel(const OffT* __restrict
         } else {
             const uint64_t T = cumq[lo + deg - 1u], c = cumq[e];
             WeightLink w;
-            w.always = c == T && T > 0 ? 1u : 0u;
+            w.top = maxwq[u] | (c == T && T > 0 ? 0x80000000u : 0u);
             w.thr = c == T ? 0u : scaled_threshold(c, T);
             // first entry whose running sum exceeds the smallest value that a word of cell i gives
             const uint32_t i = (uint32_t)((uint64_t)e - lo);
@@ -260,7 +261,7 @@ int validate_and_build(Graph* g, const float* w_dev, uint32_t* flags_dev, hipStr
     }
     if (g->links && !flags) {
         hipLaunchKernelGGL(build_links_kernel<OffT>, dim3((unsigned)((g->E + kLinkTile - 1) / kLinkTile)), dim3(256), 0,
-                           stream, (const OffT*)g->off, g->col, g->wq, g->cumq, g->V, g->E, g->links, flags_dev);
+                           stream, (const OffT*)g->off, g->col, g->wq, g->cumq, g->maxwq, g->V, g->E, g->links, flags_dev);
         ND_HIP_CHECK(hipGetLastError());
     }
     ND_HIP_CHECK(hipMemcpyAsync(&flags, flags_dev, sizeof(flags), hipMemcpyDeviceToHost, stream));

@@ -69,11 +69,14 @@ int walk_windows(const Graph& gr, int draw, bool multirw, const DrawArgs& d, int
                  int32_t* const* step_out, uint32_t* status, StepCtl* ctl, int32_t* mrw_state, uint32_t R,
                  hipStream_t stream);
 
-// Random walks over the graph's links (nd_walk_free.hip): DeepWalk and PPR.  The call's header, one flag
-// per workgroup (o_flags) and the live walks per workgroup and step (o_parts) go to the workspace.
-int64_t walk_free_groups(int64_t S);
+// Random walks over the graph's links (nd_walk_free.hip): DeepWalk, PPR, node2vec and (mrw_R > 0) the
+// multi-dimensional walk, whose roots pass through mrw_state where the call takes several launches.  The
+// call's header, one flag per workgroup (o_flags) and the live walks per workgroup and step (o_parts)
+// go to the workspace.
+int64_t walk_free_groups(int64_t S, uint32_t mrw_R);
 int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t num_steps, const int32_t* roots,
-              int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, hipStream_t stream);
+              int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, uint32_t mrw_R, int32_t* mrw_state,
+              hipStream_t stream);
 
 // All hops of a k-hop call in one launch (nd_khop.hip).  fits: the graph has links, the rows of a
 // sample's widest hop with children fit LDS, and grouping by transit would not be faster; groups: workgroups, hence flags and rows of live counts.

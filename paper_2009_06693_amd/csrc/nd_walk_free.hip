@@ -27,7 +27,13 @@ struct FreeArgs {
     uint32_t S;
     uint32_t first_step, n_steps;
     int32_t V;
-    const int32_t* src;        // the roots, or the output of step first_step - 1
+    const int32_t* src;        // the roots, or the output of step first_step - 1 (multi-dimensional walk: its roots)
+    const int32_t* prev_src;   // node2vec, first_step > 0: the output of step first_step - 2
+    const int32_t* rowset;     // node2vec: membership tables, may be null
+    uint32_t b_ret, b_com, b_far, b_max;
+    int32_t max_attempts, use_weights;
+    uint32_t R;                // multi-dimensional walk: roots per sample
+    int32_t* state;            // ... and where they go when more steps follow, else null
     WsHeader* hdr;
     uint32_t* flags;           // per workgroup: a root was outside [0, V) (first launch)
     uint32_t* parts;           // [workgroup][step of the call]: live walks
@@ -110,11 +116,11 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
                     const WeightLink w0 = reinterpret_cast<const WeightLink*>(row)[2u * j + 1u];
                     const WeightLink w1 = reinterpret_cast<const WeightLink*>(row)[2u * j1 + 1u];
                     const Link l0 = row[2u * j], l1 = row[2u * j1];
-                    if (R < w0.thr || w0.always || j == j1) {
+                    if (R < w0.thr || w0.always() || j == j1) {
                         l = l0;
                         break;
                     }
-                    if (R < w1.thr || w1.always || j1 + 1u == deg) {
+                    if (R < w1.thr || w1.always() || j1 + 1u == deg) {
                         l = l1;
                         break;
                     }
@@ -132,10 +138,253 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
     publish_live<THREADS>(lived, a.n_steps, s_hist, a.parts + (uint64_t)blockIdx.x * a.total_steps + a.first_step);
 }
 
+// ---------------------------------------------------------------- node2vec
+// Is u in the row of t?  (rs, deg: where that row lies.)  One 16-byte fetch of the row's table as a rule.
+template <typename OffT>
+__device__ __forceinline__ bool row_has(const GraphView<OffT>& g, const int32_t* rowset, int32_t t, uint32_t rs,
+                                        uint32_t deg, int32_t u) {
+    if (rowset == nullptr) return row_contains(g, rs, deg, u);
+    const int4* set = reinterpret_cast<const int4*>(rowset) + RowSet::first_group(t, rs);
+    const uint32_t ng = RowSet::groups(rs, deg);
+    uint32_t grp = mulhi32(RowSet::hash(u), ng);
+    bool found = false, on = true;
+    for (uint32_t probe = 0; on && probe < ng; ++probe) {
+        const int4 x = set[grp];
+        found = x.x == u || x.y == u || x.z == u || x.w == u;
+        on = !found && x.w >= 0;  // a group fills from the front: if its last place is free, that was all
+        grp = grp + 1u < ng ? grp + 1u : 0u;
+    }
+    return found;
+}
+
+// The exact draw after the last rejected attempt: inverse transform over the row's biased weights;
+// returns the entry's place in the row.  Rare, so out of line; what it needs travels in registers.
+template <int STRIDE, typename OffT>
+__device__ __noinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, const uint32_t* wq, const int32_t* rowset,
+                                           uint64_t R, uint32_t b_ret, uint32_t b_com, uint32_t b_far, int32_t t,
+                                           uint32_t rs_t, uint32_t deg_t, uint32_t rs, uint32_t deg) {
+    const GraphView<OffT> g{off, col, nullptr, nullptr, nullptr, 0};
+    uint64_t Z = 0, x = 0, run = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (uint32_t e = 0; e < deg; ++e) {
+            const int32_t u = col[(uint64_t)rs + e];
+            const uint64_t w = wq != nullptr ? wq[(uint64_t)rs + e] : kOneQ16;
+            uint64_t b = kOneQ16;
+            if (t >= 0) b = u == t ? b_ret : row_has(g, rowset, t, rs_t, deg_t, u) ? b_com : b_far;
+            if (pass == 0) {
+                Z += w * b;
+            } else {
+                run += w * b;
+                if (run > x) return e;
+            }
+        }
+        x = mulhi64(R, Z);
+    }
+    return deg - 1u;  // not reached: x < Z
+}
+
+// Every lane goes through its walk's attempts at its own pace: a wavefront whose lanes wait for each
+// other at every step pays for the slowest of 64 geometrically distributed attempt counts (7 rounds
+// per step where the mean is 1.9).  An attempt is one fetch of the candidate's link, and one of the
+// previous vertex's table when the two biases differ in their verdict; meanwhile the generator makes
+// the words of both possible next attempts.
+template <int STRIDE, typename OffT, int THREADS>
+__global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> g, FreeArgs a) {
+    __shared__ uint32_t s_hist[kFreeChunk + 1];
+    const uint32_t s = blockIdx.x * (uint32_t)THREADS + threadIdx.x;
+    int32_t v = first_transit<THREADS>(a, s);
+    uint32_t rs = 0, deg = 0, maxw = kOneQ16;
+    int32_t t = ND_NULL_VERTEX;        // the transit before v: none at the first step
+    uint32_t rs_t = 0, deg_t = 0;
+    if (v >= 0) {
+        const uint64_t r = (uint64_t)g.off[v];
+        rs = (uint32_t)r;
+        deg = row_length(g, v, r);
+        if (a.use_weights) maxw = g.maxwq[v];
+        if (a.first_step > 0) {
+            t = a.prev_src[s];
+            const uint64_t rt = (uint64_t)g.off[t];
+            rs_t = (uint32_t)rt;
+            deg_t = row_length(g, t, rt);
+        }
+    }
+    const uint32_t sid = a.sample_base + s;
+    const uint32_t b_lo = a.b_com < a.b_far ? a.b_com : a.b_far, b_hi = a.b_com < a.b_far ? a.b_far : a.b_com;
+    uint32_t si = 0;
+    int32_t att = 0;
+    Rand4 r = draw4(a.seed, sid, 0u, a.first_step, 0u);
+    while (si < a.n_steps && deg > 0u) {  // deg is 0 for a walk that has ended
+        uint32_t e;
+        const bool exact = att >= a.max_attempts;
+        if (exact)
+            e = n2v_exact<STRIDE, OffT>(g.off, g.col, a.use_weights ? g.wq : nullptr, a.rowset, cat64(r.r0, r.r1), a.b_ret,
+                                        a.b_com, a.b_far, t, rs_t, deg_t, rs, deg);
+        else
+            e = mulhi32(r.r0, deg);
+        const Link* at = a.links + (uint64_t)(rs + e) * STRIDE;
+        const Link l = *at;
+        uint32_t top = kOneQ16;
+        if (STRIDE == 2 && a.use_weights) top = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
+        const Rand4 again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + 1u);
+        const Rand4 onward = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
+        // The verdict and the move to the next vertex are selections, not branches: of the nest of
+        // branches that says the same, the compiler (ROCm 7.2) made code that lost the link's row on
+        // the way to the move.
+        const bool start = t < 0, back = l.v == t;
+        const uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
+        const uint64_t w = a.use_weights ? l.wq : kOneQ16;
+        bool take = exact || y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
+        const bool ask = !take && !start && !back && y < w * b_hi;
+        bool common = false;
+        if (ask) common = row_has(g, a.rowset, t, rs_t, deg_t, l.v);
+        take = take || (ask && y < w * (common ? a.b_com : a.b_far));
+        if (take) a.out[si][s] = l.v;
+        t = take ? v : t;
+        rs_t = take ? rs : rs_t;
+        deg_t = take ? deg : deg_t;
+        v = take ? l.v : v;
+        rs = take ? l.rs : rs;
+        deg = take ? l.deg : deg;
+        maxw = take ? top : maxw;
+        si += take ? 1u : 0u;
+        att = take ? 0 : att + 1;
+        r.r0 = take ? onward.r0 : again.r0;
+        r.r1 = take ? onward.r1 : again.r1;
+        r.r2 = take ? onward.r2 : again.r2;
+    }
+    // a walk that stands on a vertex without out-edges had a transit at this step still
+    const uint32_t lived = si + (si < a.n_steps && v >= 0 ? 1u : 0u);
+    if (s < a.S)
+        for (; si < a.n_steps; ++si) a.out[si][s] = ND_NULL_VERTEX;
+    publish_live<THREADS>(lived, a.n_steps, s_hist, a.parts + (uint64_t)blockIdx.x * a.total_steps + a.first_step);
+}
+
+// ---------------------------------------------------------------- multi-dimensional walk
+// A sample's steps depend on each other only through the root they pick, and which root a step picks
+// comes from the generator alone.  So a wavefront takes a sample and 64 of its steps at a time, one per
+// lane: a step that picks a root no earlier one of the 64 picked reads it from the sample's roots
+// in LDS, the others wait for the last earlier step with the same root - two to four rounds for 64 steps
+// and 100 roots, where step after step is 64 chains of three dependent fetches.
+template <int STRIDE, typename OffT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g, FreeArgs a) {
+    extern __shared__ uint32_t s_dyn[];
+    constexpr uint32_t T = WAVES * 64;
+    __shared__ int32_t s_tile[64][WAVES + 1];
+    __shared__ uint32_t s_live[kFreeChunk];
+    const uint32_t R = a.R;
+    const uint32_t wave = wave_uniform((uint32_t)wave_id());
+    const int lane = lane_id();
+    int32_t* state = (int32_t*)s_dyn + wave * R * 3u;  // the roots of my sample
+    uint32_t* picked = (uint32_t*)state + R;           // per root: which of the 64 steps pick it (two words)
+    const uint32_t s0 = blockIdx.x * WAVES, s = s0 + wave;
+    const bool mine = s < a.S;
+    bool bad = false;
+    for (uint32_t i = (uint32_t)lane; i < R; i += 64u) {
+        int32_t v = ND_NULL_VERTEX;
+        if (mine) {
+            v = a.src[(uint64_t)s * R + i];
+            if (v >= a.V || v < ND_NULL_VERTEX) {
+                bad = true;
+                v = ND_NULL_VERTEX;
+            }
+        }
+        state[i] = v;
+        picked[2u * i] = 0u;
+        picked[2u * i + 1u] = 0u;
+    }
+    for (uint32_t i = threadIdx.x; i < (uint32_t)kFreeChunk; i += T) s_live[i] = 0;
+    const int any_bad = __syncthreads_or(bad ? 1 : 0);
+    if (threadIdx.x == 0 && a.first_step == 0) {
+        a.flags[blockIdx.x] = any_bad ? 1u : 0u;
+        if (blockIdx.x == 0) write_header(a.hdr, a.total_steps, gridDim.x, a.o_flags, a.o_parts);
+    }
+    for (uint32_t base = 0; base < a.n_steps; base += 64u) {
+        const uint32_t si = base + (uint32_t)lane;
+        const bool step = mine && si < a.n_steps;
+        const Rand4 r = draw4(a.seed, a.sample_base + s, 0u, a.first_step + si, 0u);
+        const uint32_t pick = mulhi32(r.r2, R);
+        if (step) atomicOr(&picked[2u * pick + ((uint32_t)lane >> 5)], 1u << (lane & 31));
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint64_t same = step ? cat64(picked[2u * pick + 1u], picked[2u * pick]) : 0ull;
+        const uint64_t before = same & lanes_below(lane);
+        const int pred = before ? 63 - __clzll((long long)before) : -1;
+        // the root as I leave it (vertex, row); the first step of a root starts from the sample's
+        int32_t av = ND_NULL_VERTEX, added = ND_NULL_VERTEX;
+        uint32_t ars = 0, adeg = 0;
+        if (step && pred < 0) {
+            av = state[pick];
+            if (av >= 0) {
+                const uint64_t rs = (uint64_t)g.off[av];
+                ars = (uint32_t)rs;
+                adeg = row_length(g, av, rs);
+            }
+        }
+        bool had = false;
+        bool done = !step;
+        for (uint64_t all_done = __ballot(done); all_done != ~0ull; all_done = __ballot(done)) {
+            const bool go = !done && (pred < 0 || ((all_done >> (pred & 63)) & 1ull) != 0ull);
+            const int from = pred < 0 ? lane : pred;
+            const int32_t pv = __shfl(av, from, 64);
+            const uint32_t prs = (uint32_t)__shfl((int)ars, from, 64), pdeg = (uint32_t)__shfl((int)adeg, from, 64);
+            if (go) {
+                had = pv >= 0;
+                av = pv;
+                ars = prs;
+                adeg = pdeg;
+                if (adeg > 0u) {
+                    const Link l = a.links[(uint64_t)(ars + mulhi32(r.r0, adeg)) * STRIDE];
+                    added = av = l.v;
+                    ars = l.rs;
+                    adeg = l.deg;
+                }
+                done = true;
+            }
+        }
+        if (step) {
+            if ((same >> lane) == 1ull) state[pick] = av;  // the last of the 64 steps that picked this root
+            picked[2u * pick] = 0u;
+            picked[2u * pick + 1u] = 0u;
+            if (had) atomicAdd(&s_live[si], 1u);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        s_tile[lane][wave] = added;
+        __syncthreads();
+        // the samples of the workgroup are neighbours in every step's output
+        for (uint32_t i = threadIdx.x; i < 64u * WAVES; i += T) {
+            const uint32_t row = i / WAVES, w = i % WAVES;
+            if (base + row < a.n_steps && s0 + w < a.S) a.out[base + row][s0 + w] = s_tile[row][w];
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = threadIdx.x; i < a.n_steps; i += T)
+        a.parts[(uint64_t)blockIdx.x * a.total_steps + a.first_step + i] = s_live[i];
+    if (a.state != nullptr && mine)  // more steps follow in another launch
+        for (uint32_t i = (uint32_t)lane; i < R; i += 64u) a.state[(uint64_t)s * R + i] = state[i];
+}
+
+template <int WAVES, typename OffT>
+void launch_mrw(const Graph& gr, const FreeArgs& a, hipStream_t stream) {
+    const dim3 grid((a.S + WAVES - 1u) / WAVES), block(WAVES * 64);
+    const size_t lds = (size_t)WAVES * a.R * 12;  // at most 48 KB
+    if (gr.wq) hipLaunchKernelGGL((mrw_free_kernel<2, OffT, WAVES>), grid, block, lds, stream, view_of<OffT>(gr), a);
+    else hipLaunchKernelGGL((mrw_free_kernel<1, OffT, WAVES>), grid, block, lds, stream, view_of<OffT>(gr), a);
+}
+
+// Samples (wavefronts) per workgroup: sixteen, whose outputs then leave in runs of 64 bytes, as long as
+// their roots fit 48 KB of LDS (two workgroups per compute unit and room for a third).
+int mrw_waves(uint32_t R) { return R <= 256u ? 16 : R <= 1024u ? 4 : 1; }
+
 template <int THREADS, typename OffT>
 void launch_free(const Graph& gr, int draw, const FreeArgs& a, hipStream_t stream) {
     const dim3 grid((a.S + THREADS - 1u) / THREADS), block(THREADS);
     const GraphView<OffT> g = view_of<OffT>(gr);
+    if (draw == kDrawNode2vec) {
+        if (gr.wq) hipLaunchKernelGGL((walk_free_n2v_kernel<2, OffT, THREADS>), grid, block, 0, stream, g, a);
+        else hipLaunchKernelGGL((walk_free_n2v_kernel<1, OffT, THREADS>), grid, block, 0, stream, g, a);
+        return;
+    }
     if (draw == kDrawWeighted)
         hipLaunchKernelGGL((walk_free_kernel<kDrawWeighted, 2, OffT, THREADS>), grid, block, 0, stream, g, a);
     else if (gr.wq)
@@ -151,10 +400,14 @@ void launch_free(const Graph& gr, int draw, const FreeArgs& a, hipStream_t strea
 // have fewer headers and counters to write.
 static int free_threads(int64_t S) { return S <= 65536 ? 64 : 256; }
 
-int64_t walk_free_groups(int64_t S) { return (S + free_threads(S) - 1) / free_threads(S); }
+int64_t walk_free_groups(int64_t S, uint32_t mrw_R) {
+    const int64_t per = mrw_R > 0 ? mrw_waves(mrw_R) : free_threads(S);
+    return (S + per - 1) / per;
+}
 
 int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t num_steps, const int32_t* roots,
-              int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, hipStream_t stream) {
+              int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, uint32_t mrw_R, int32_t* mrw_state,
+              hipStream_t stream) {
     FreeArgs a{};
     a.links = gr.links;
     a.seed = d.seed;
@@ -162,6 +415,14 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.sample_base = d.sample_base;
     a.S = (uint32_t)S;
     a.V = (int32_t)gr.V;
+    a.rowset = gr.rowset.load(std::memory_order_acquire);
+    a.b_ret = d.b_ret;
+    a.b_com = d.b_com;
+    a.b_far = d.b_far;
+    a.b_max = d.b_max;
+    a.max_attempts = d.max_attempts;
+    a.use_weights = d.use_weights;
+    a.R = mrw_R;
     a.hdr = (WsHeader*)ws;
     a.flags = (uint32_t*)(ws + o_flags);
     a.parts = (uint32_t*)(ws + o_parts);
@@ -173,9 +434,23 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
         a.first_step = (uint32_t)first;
         a.n_steps = (uint32_t)n;
         a.src = first > 0 ? step_out[first - 1] : roots;
+        a.prev_src = first > 0 ? step_out[first - 2] : nullptr;  // kFreeChunk is at least two
         for (int32_t i = 0; i < kFreeChunk; ++i) a.out[i] = i < n ? step_out[first + i] : nullptr;
         mark_phase(ND_PHASE_WALK_WINDOW, stream);
-        if (gr.off64) {
+        if (mrw_R > 0) {
+            a.src = first > 0 ? mrw_state : roots;
+            a.state = first + n < num_steps ? mrw_state : nullptr;
+            const int waves = mrw_waves(mrw_R);
+            if (gr.off64) {
+                if (waves == 16) launch_mrw<16, int64_t>(gr, a, stream);
+                else if (waves == 4) launch_mrw<4, int64_t>(gr, a, stream);
+                else launch_mrw<1, int64_t>(gr, a, stream);
+            } else {
+                if (waves == 16) launch_mrw<16, int32_t>(gr, a, stream);
+                else if (waves == 4) launch_mrw<4, int32_t>(gr, a, stream);
+                else launch_mrw<1, int32_t>(gr, a, stream);
+            }
+        } else if (gr.off64) {
             if (free_threads(S) == 64) launch_free<64, int64_t>(gr, draw, a, stream);
             else launch_free<256, int64_t>(gr, draw, a, stream);
         } else {
