@@ -227,7 +227,8 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
         if (hb > pl->hist_bytes) pl->hist_bytes = hb;
     }
     pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
-                p->unique_rounds == 0 && khop_fused_fits(g, p->fanout, p->num_steps, pl->S);
+                (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
+                                      : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
     return ND_OK;
 }
 
@@ -269,7 +270,8 @@ void layout(Plan* pl, const Graph& g, const nd_params* p) {
         pl->o_bits = o; o = align_up(o + (size_t)pl->bit_words * 4);
     }
     if (pl->fused) {  // inside what the call may use when it groups
-        const size_t groups = (size_t)khop_fused_groups(g, p->fanout, pl->k, pl->S);
+        const size_t groups = (size_t)(p->unique_rounds > 0 ? khop_unique_groups(g, p->fanout, pl->k, pl->S)
+                                                            : khop_fused_groups(g, p->fanout, pl->k, pl->S));
         size_t f = pl->o_ctl;
         pl->o_flags = f; f = align_up(f + groups * 4);
         pl->o_parts = f; f = align_up(f + groups * (size_t)pl->k * 4);
@@ -442,7 +444,7 @@ int nd_graph_create(nd_graph** out, int64_t V, int64_t E, const void* row_offset
     const int rc = graph_create(&g, V, E, row_offsets, offsets_are_int64 ? 1 : 0, col_indices,
                                 weights_or_null, src_is_device, (hipStream_t)hip_stream);
     if (rc != ND_OK) return rc;
-    if (layer_prepare() != ND_OK || edges_prepare() != ND_OK) {
+    if (layer_prepare() != ND_OK || edges_prepare() != ND_OK || khop_prepare() != ND_OK) {
         graph_destroy(g);
         return ND_ERR_HIP;
     }
@@ -594,6 +596,13 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     int32_t* mrw_transits = (int32_t*)(ws + pl.o_transits);
     const uint32_t mrw_R = (uint32_t)params->roots_per_sample;
     if (pl.fused) {
+        if (params->unique_rounds > 0) {
+            rc = khop_unique(g, a, params->fanout, pl.k, params->unique_rounds, pl.S, roots_dev, step_out_dev, ws,
+                             pl.o_flags, pl.o_parts, stream);
+            if (rc != ND_OK) return rc;
+            mark_phase(ND_PHASE_NONE, stream);
+            return ND_OK;
+        }
         const bool few = num_roots <= kKhopStatusRoots;
         rc = khop_fused(g, a, params->fanout, pl.k, pl.S, roots_dev, step_out_dev, ws, pl.o_flags, pl.o_parts,
                         few ? status_dev : nullptr, stream);

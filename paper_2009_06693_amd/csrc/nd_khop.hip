@@ -8,6 +8,7 @@
 #include "nd_wave.h"
 #include "nd_sample.h"
 #include "nd_draw.h"
+#include "nd_group.h"
 
 namespace nd {
 
@@ -154,6 +155,346 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
     }
 }
 
+// ---------------------------------------------------------------- unique neighbours (Section 6.3)
+// All hops of a sample whose slots must hold different vertices, by one group of lanes.  The rules are
+// those of unique_kernel (nd_sample.hip): among the slots of a hop that propose the same vertex the
+// lowest keeps it, a slot that lost draws again with the next attempt, up to `rounds` draws, and a slot
+// whose parent's slots hold as many distinct vertices as the parent's row has entries ends empty.  Here
+// the first draws come straight from the parents' rows in LDS into the hash table, the later rounds find
+// the rows there too, and the outputs are written once, in order.
+//
+// Bound by instruction issue (vector and scalar alike), then by the fabric's lines; measured on the scale-22
+// R-MAT graph, every vertex, [25,10], 4 draws: 7.26 ms with the ordinary kernels first, all slots read back
+// and patched; 6.1 ms with one pass of the generator per round; 5.35 ms when lanes without a slot draw the
+// next attempts AND the registers are held to 64, so that a SIMD keeps 8 wavefronts (5.8 ms at 7, 6.4 at 5);
+// 5.2 ms with workgroups of one wavefront, which leave when their own samples are done; 5.0 ms with the
+// narrow hops' first round treated as one of the later ones.
+struct UniqueFusedArgs {
+    const Link* links;
+    uint64_t seed;
+    uint32_t sample_base;
+    uint32_t S;
+    int32_t V;
+    int32_t k, rounds;
+    uint32_t W[ND_MAX_FANOUT_STEPS];
+    FastDiv div_m[ND_MAX_FANOUT_STEPS];
+    uint32_t slots;             // widest hop, rounded up to what the lanes take: entries per LDS array
+    uint32_t rows;              // rows of the widest hop with children (or the root's)
+    const int32_t* roots;
+    int32_t* out[ND_MAX_FANOUT_STEPS];
+    WsHeader* hdr;
+    uint32_t* flags;
+    uint32_t* parts;
+    uint64_t o_flags, o_parts;
+};
+
+// Bytes of LDS per group.
+__host__ __device__ inline uint32_t unique_group_bytes(uint32_t slots, uint32_t rows) {
+    return 2u * slots * 4u      // hash table: a slot per bucket, two buckets per slot
+           + slots * 4u         // the hop's vertices
+           + slots * 4u         // two queues of open slots, 16 bits per entry
+           + rows * 4u          // per parent: distinct vertices its slots hold
+           + 2u * rows * 8u;    // rows of this hop's parents and of the next hop's
+}
+
+template <int STRIDE, typename OffT, int THREADS, int PER>
+__global__ __launch_bounds__(THREADS <= 64 ? 64 : 256, THREADS <= 64 ? 8 : 4)
+void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    constexpr uint32_t SUBS = THREADS <= 64 ? 64 / THREADS : 1;  // groups (samples in flight) per workgroup
+    __shared__ uint32_t s_live[ND_MAX_FANOUT_STEPS];
+    __shared__ uint32_t q_fill[2];            // queue lengths of a four-wavefront group
+    const uint32_t sub = threadIdx.x / (uint32_t)THREADS;
+    const uint32_t tix = threadIdx.x % (uint32_t)THREADS;  // my place in the group
+    const uint64_t group_lanes = THREADS == 32 ? 0xFFFFFFFFull << (threadIdx.x & 32u) : ~0ull;
+    unsigned char* mem = s_raw + (size_t)sub * unique_group_bytes(a.slots, a.rows);
+    uint2* rows_a = (uint2*)mem;
+    uint2* rows_b = rows_a + a.rows;
+    // A bucket names the slot whose vertex it stands for: j = slot j holds the vertex, kOpen + j = slot j
+    // is the lowest that proposes it so far.  (Keys and claims apart took twice the LDS, and with it a
+    // quarter of the wavefronts a compute unit can hold.)
+    constexpr uint32_t kOpen = 4096u, kFree = 0xFFFFFFFFu;
+    uint32_t* table = (uint32_t*)(rows_b + a.rows);
+    int32_t* s_res = (int32_t*)(table + 2u * a.slots);  // vertex that slot j holds or proposes
+    uint32_t* p_held = (uint32_t*)(s_res + a.slots);
+    uint16_t* queue[2] = {(uint16_t*)(p_held + a.rows), (uint16_t*)(p_held + a.rows) + a.slots};
+    if (threadIdx.x < ND_MAX_FANOUT_STEPS) s_live[threadIdx.x] = 0;
+    __syncthreads();
+    bool bad = false;
+    // live slots per hop of all my samples, counted where lane 0 of the group can add them up
+    for (uint32_t at = blockIdx.x * SUBS + sub; at < a.S; at += gridDim.x * SUBS) {  // the same in the whole group
+        // a wavefront's sample is a scalar, and with it the generator's first rounds (sample and step only)
+        const uint32_t s = THREADS >= 64 ? wave_uniform(at) : at;
+        int32_t root = a.roots[s];
+        if (root >= a.V || root < ND_NULL_VERTEX) {
+            bad = true;
+            root = ND_NULL_VERTEX;
+        }
+        uint2 first = make_uint2(0u, 0u);
+        if (root >= 0) {
+            const uint64_t rs = (uint64_t)g.off[root];
+            first = make_uint2((uint32_t)rs, row_length(g, root, rs));
+            if (tix == 0) atomicAdd(&s_live[0], 1u);
+        }
+        if (tix == 0) rows_a[0] = first;
+        bool any = first.y > 0u;   // some parent of this hop has a row
+        group_sync<THREADS>();
+        for (int hop = 0; hop < a.k; ++hop) {
+            const uint32_t W = a.W[hop], parents = hop > 0 ? a.W[hop - 1] : 1u;
+            const bool last = hop == a.k - 1;
+            const uint2* rows = (hop & 1) ? rows_b : rows_a;
+            uint2* next = (hop & 1) ? rows_a : rows_b;
+            int32_t* out_row = a.out[hop] + (uint64_t)s * W;
+            if (!any) {  // uniform: nothing to draw in this hop and those after it
+                for (uint32_t j = tix; j < W; j += (uint32_t)THREADS) out_row[j] = ND_NULL_VERTEX;
+                continue;
+            }
+            uint32_t buckets = 64;                  // power of two, at least 2 W
+            while (buckets < 2u * W) buckets <<= 1;
+            const uint32_t mask = buckets - 1u;
+            // proposes vertex c for slot j (s_res[j] is c already, for every proposer); returns the bucket of
+            // c.  The table never holds more than W distinct vertices in at least 2 W buckets, so a free or
+            // matching bucket is found long before the probe bound.
+            auto propose = [&](int32_t c, uint32_t j) -> uint32_t {
+                uint32_t b = ((uint32_t)c * 2654435761u >> 15) & mask;
+                for (uint32_t probe = 0; probe < buckets; ++probe) {
+                    const uint32_t old = atomicCAS(&table[b], kFree, kOpen + j);
+                    if (old == kFree) break;
+                    if (s_res[old & (kOpen - 1u)] == c) {
+                        atomicMin(&table[b], kOpen + j);
+                        break;
+                    }
+                    b = (b + 1u) & mask;
+                }
+                return b;
+            };
+            for (uint32_t b = tix; b < buckets / 4u; b += (uint32_t)THREADS)  // four free buckets per store
+                reinterpret_cast<int4*>(table)[b] = make_int4(-1, -1, -1, -1);
+            for (uint32_t pj = tix; pj < parents; pj += (uint32_t)THREADS) p_held[pj] = 0;
+            if (THREADS > 64 && tix == 0) q_fill[0] = 0;
+            // what a slot draws: an entry of the parent's row (its link where the hop has children)
+            auto fetch = [&](uint2 row, uint32_t j, uint32_t attempt, uint2* row_out) -> int32_t {
+                const Rand4 r = draw4(a.seed, a.sample_base + s, j, (uint32_t)hop, attempt);
+                const uint64_t e = (uint64_t)row.x + mulhi32(r.r0, row.y);
+                *row_out = make_uint2(0u, 0u);
+                if (last) return g.col[e];
+                const Link l = a.links[e * STRIDE];
+                *row_out = make_uint2(l.rs, l.deg);
+                return l.v;
+            };
+            int32_t cand[PER];
+            uint32_t where[PER];                // bucket, and from bit 16 the parent
+            bool won[PER];
+            uint32_t cur = 0;                   // the queue being read
+            uint32_t fill = 0;                  // entries in the queue being written (group inside one wavefront)
+            int32_t r = 0;
+            if (THREADS <= 64 && 2u * W <= (uint32_t)THREADS) {
+                // every slot is open, and the first round is one of those below
+                if (tix < W) {
+                    s_res[tix] = ND_NULL_VERTEX;
+                    if (!last) next[tix] = make_uint2(0u, 0u);
+                    queue[0][tix] = (uint16_t)tix;
+                }
+                fill = W;
+            } else {
+                r = 1;
+                // The kernel pays for vector instructions first, so the unrolled loops end where the hop or the
+                // queue does: a test of scalars (W, L), the same in the whole group.
+#pragma unroll
+                for (int t = 0; t < PER; ++t) {   // all fetches are on their way before the first is looked at
+                    const uint32_t j = tix + (uint32_t)t * (uint32_t)THREADS;
+                    cand[t] = ND_NULL_VERTEX;
+                    where[t] = 0;
+                    if ((uint32_t)t * (uint32_t)THREADS < W && j < W) {
+                        const uint32_t pj = fastdiv(j, a.div_m[hop]);
+                        const uint2 row = rows[pj];
+                        where[t] = pj << 16;
+                        uint2 crow = make_uint2(0u, 0u);
+                        if (row.y > 0u) cand[t] = fetch(row, j, 0u, &crow);
+                        if (!last) next[j] = crow;
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < PER; ++t) {
+                    const uint32_t j = tix + (uint32_t)t * (uint32_t)THREADS;
+                    if ((uint32_t)t * (uint32_t)THREADS < W && j < W) s_res[j] = cand[t];
+                }
+                group_sync<THREADS>();
+#pragma unroll
+                for (int t = 0; t < PER; ++t) {
+                    if ((uint32_t)t * (uint32_t)THREADS >= W) break;
+                    if (cand[t] >= 0) where[t] |= propose(cand[t], tix + (uint32_t)t * (uint32_t)THREADS);
+                }
+                group_sync<THREADS>();
+#pragma unroll
+                for (int t = 0; t < PER; ++t) {
+                    won[t] = false;
+                    if ((uint32_t)t * (uint32_t)THREADS >= W) continue;
+                    won[t] = cand[t] >= 0 && table[where[t] & 0xFFFFu] == kOpen + tix + (uint32_t)t * (uint32_t)THREADS;
+                }
+                group_sync<THREADS>();              // every claim has been read
+                // a winner marks its bucket as held: whoever proposes that vertex later loses; a loser queues
+#pragma unroll
+                for (int t = 0; t < PER; ++t) {
+                    if ((uint32_t)t * (uint32_t)THREADS >= W) break;
+                    const uint32_t j = tix + (uint32_t)t * (uint32_t)THREADS;
+                    if (won[t]) {
+                        table[where[t] & 0xFFFFu] = j;
+                        atomicAdd(&p_held[where[t] >> 16], 1u);
+                    } else if (j < W) {
+                        s_res[j] = ND_NULL_VERTEX;
+                        if (!last) next[j] = make_uint2(0u, 0u);
+                    }
+                    const bool open = cand[t] >= 0 && !won[t];
+                    const uint32_t at = group_reserve<THREADS>(open, group_lanes, &fill, &q_fill[0]);
+                    if (open) queue[0][at] = (uint16_t)j;
+                }
+            }
+            if (THREADS > 64 && tix == 0) q_fill[1] = 0;
+            group_sync<THREADS>();
+            uint32_t L = THREADS > 64 ? q_fill[0] : fill;  // slots still open (uniform in the group)
+            if (THREADS >= 64) L = wave_uniform(L);
+
+            // ---- rounds.  The generator's quarter-rate multiplies are what a round pays for most, and it costs
+            // a wavefront the same for one open slot as for 64.  So when at most half the lanes have a slot, the
+            // others draw the same slots' next attempts: one pass of the generator and one fetch serve two, four
+            // or eight rounds, which then only take their candidates from the lanes that hold them.
+            while (r < a.rounds && L > 0) {
+                if (THREADS <= 64 && L <= (uint32_t)THREADS / 2u && r + 1 < a.rounds) {
+                    const uint32_t lg = L <= (uint32_t)THREADS / 8u ? 3u : L <= (uint32_t)THREADS / 4u ? 2u : 1u;
+                    const uint32_t span = (uint32_t)THREADS >> lg;  // lanes per attempt
+                    const uint32_t e = tix & (span - 1u);
+                    const int32_t mine = r + (int32_t)(tix / span);
+                    uint32_t j = 0, pj = 0;
+                    uint2 row = make_uint2(0u, 0u), vrow = make_uint2(0u, 0u);
+                    int32_t v = ND_NULL_VERTEX;
+                    if (e < L && mine < a.rounds) {
+                        j = queue[cur][e];
+                        pj = fastdiv(j, a.div_m[hop]);
+                        row = rows[pj];
+                        if (p_held[pj] < row.y) v = fetch(row, j, (uint32_t)mine, &vrow);
+                    }
+                    bool open = tix < span && v >= 0;  // lane e speaks for slot e
+                    for (uint32_t i = 0; i < (1u << lg) && r < a.rounds; ++i, ++r) {
+                        const int from = (int)((threadIdx.x & 63u) - tix + i * span + e);
+                        const int32_t c = __shfl(v, from, 64);
+                        const uint2 cr = make_uint2((uint32_t)__shfl((int)vrow.x, from, 64),
+                                                    (uint32_t)__shfl((int)vrow.y, from, 64));
+                        // as many distinct vertices as the parent's row has entries: nothing left to draw
+                        open = open && p_held[pj] < row.y;
+                        if (!group_any<THREADS>(open, group_lanes)) {
+                            r = a.rounds;
+                            break;
+                        }
+                        if (open) s_res[j] = c;
+                        group_sync<THREADS>();
+                        uint32_t at = 0;
+                        if (open) at = propose(c, j);
+                        group_sync<THREADS>();
+                        const bool win = open && table[at] == kOpen + j;
+                        group_sync<THREADS>();          // every claim has been read
+                        if (win) {
+                            table[at] = j;
+                            if (!last) next[j] = cr;
+                            atomicAdd(&p_held[pj], 1u);
+                        } else if (open) {
+                            s_res[j] = ND_NULL_VERTEX;
+                        }
+                        open = open && !win;
+                        group_sync<THREADS>();
+                    }
+                    fill = 0;
+                    const uint32_t at = group_reserve<THREADS>(open, group_lanes, &fill, nullptr);
+                    if (open) queue[cur ^ 1u][at] = (uint16_t)j;
+                    group_sync<THREADS>();
+                    cur ^= 1u;
+                    L = fill;
+                    if (THREADS == 64) L = wave_uniform(L);
+                    continue;
+                }
+                uint32_t jq[PER];
+#pragma unroll
+                for (int p = 0; p < PER; ++p) {
+                    const uint32_t e = tix + (uint32_t)p * (uint32_t)THREADS;
+                    cand[p] = ND_NULL_VERTEX;
+                    where[p] = 0;
+                    jq[p] = 0;
+                    if ((uint32_t)p * (uint32_t)THREADS >= L || e >= L) continue;
+                    const uint32_t j = queue[cur][e];
+                    const uint32_t pj = fastdiv(j, a.div_m[hop]);
+                    const uint2 row = rows[pj];
+                    // the parent's slots already hold as many distinct vertices as its row has entries:
+                    // whatever this slot draws is held, now and in every later round
+                    if (p_held[pj] >= row.y) continue;
+                    uint2 crow;
+                    cand[p] = fetch(row, j, (uint32_t)r, &crow);
+                    jq[p] = j;
+                    where[p] = pj << 16;
+                    s_res[j] = cand[p];
+                    if (!last) next[j] = crow;
+                }
+                group_sync<THREADS>();
+#pragma unroll
+                for (int p = 0; p < PER; ++p) {
+                    if ((uint32_t)p * (uint32_t)THREADS >= L) break;
+                    if (cand[p] >= 0) where[p] |= propose(cand[p], jq[p]);
+                }
+                group_sync<THREADS>();
+#pragma unroll
+                for (int p = 0; p < PER; ++p) {
+                    won[p] = false;
+                    if ((uint32_t)p * (uint32_t)THREADS >= L) continue;
+                    won[p] = cand[p] >= 0 && table[where[p] & 0xFFFFu] == kOpen + jq[p];
+                }
+                group_sync<THREADS>();          // every claim has been read
+                fill = 0;
+#pragma unroll
+                for (int p = 0; p < PER; ++p) {
+                    if ((uint32_t)p * (uint32_t)THREADS >= L) break;
+                    if (won[p]) {
+                        table[where[p] & 0xFFFFu] = jq[p];
+                        atomicAdd(&p_held[where[p] >> 16], 1u);
+                    }
+                    const bool open = cand[p] >= 0 && !won[p];
+                    if (open) {
+                        s_res[jq[p]] = ND_NULL_VERTEX;
+                        if (!last) next[jq[p]] = make_uint2(0u, 0u);
+                    }
+                    const uint32_t at = group_reserve<THREADS>(open, group_lanes, &fill, &q_fill[cur ^ 1u]);
+                    if (open) queue[cur ^ 1u][at] = (uint16_t)jq[p];
+                }
+                if (THREADS > 64 && tix == 0) q_fill[cur] = 0;  // everybody read it two barriers ago
+                group_sync<THREADS>();
+                cur ^= 1u;
+                L = THREADS > 64 ? q_fill[cur] : fill;
+                if (THREADS >= 64) L = wave_uniform(L);
+                ++r;
+            }
+            // ---- a slot that never won a vertex of its own stays empty; the hop leaves in order
+            int alive = 0;
+            uint32_t got = 0;
+            for (uint32_t j = tix; j < W; j += (uint32_t)THREADS) {
+                const int32_t v = s_res[j];
+                out_row[j] = v;
+                got += v >= 0 ? 1u : 0u;
+                if (!last) alive |= next[j].y > 0u ? 1 : 0;
+            }
+            if (!last) {
+                if (got) atomicAdd(&s_live[hop + 1], got);
+                any = group_or<THREADS>(alive, group_lanes) != 0;
+            }
+            group_sync<THREADS>();  // table, queues and rows are rebuilt for the next hop or sample
+        }
+    }
+    const int any_bad = __syncthreads_or(bad ? 1 : 0);
+    if (threadIdx.x < (uint32_t)a.k)
+        a.parts[(uint64_t)blockIdx.x * (uint32_t)a.k + threadIdx.x] = s_live[threadIdx.x];
+    if (threadIdx.x == 0) {
+        a.flags[blockIdx.x] = any_bad ? 1u : 0u;
+        if (blockIdx.x == 0) write_header(a.hdr, (uint32_t)a.k, gridDim.x, a.o_flags, a.o_parts);
+    }
+}
+
 constexpr int64_t kFusedRows = 4096;  // rows per workgroup (32 KB of LDS) of the widest hop that has children
 
 struct FusedShape {
@@ -280,6 +621,111 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     }
 #undef ND_FUSED_LAUNCH
     ND_HIP_CHECK(hipGetLastError());
+    return ND_OK;
+}
+
+// ---------------------------------------------------------------- unique neighbours
+namespace {
+struct UniqueShape {
+    uint32_t slots, rows, threads;
+    int64_t groups;   // workgroups
+    size_t lds;
+};
+UniqueShape unique_shape(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
+    int64_t W[ND_MAX_FANOUT_STEPS];
+    slots_per_sample(fanout, k, W);
+    int64_t widest = 1, rows = 1;
+    for (int32_t i = 0; i < k; ++i) {
+        if (W[i] > widest) widest = W[i];
+        if (i + 1 < k && W[i] > rows) rows = W[i];
+    }
+    UniqueShape u;
+    // half a wavefront per sample up to 32 slots, a whole one up to 256, four above
+    u.threads = widest <= 32 ? 32 : widest <= 256 ? 64 : 256;
+    u.slots = 32;
+    while (u.slots < widest) u.slots <<= 1;
+    u.rows = (uint32_t)(rows + 1) / 2 * 2;
+    const int64_t subs = u.threads <= 64 ? 64 / u.threads : 1;
+    u.lds = (size_t)subs * unique_group_bytes(u.slots, u.rows);
+    u.groups = (S + subs - 1) / subs;
+    if (u.groups > (int64_t)gr.num_cus * 128) u.groups = (int64_t)gr.num_cus * 128;  // groups walk over samples with a stride
+    if (u.groups < 1) u.groups = 1;
+    return u;
+}
+constexpr size_t kUniqueLdsMost = 128 << 10;
+}  // namespace
+
+bool khop_unique_fits(const Graph& gr, const int32_t* fanout, int32_t k) {
+    return gr.links && unique_shape(gr, fanout, k, 1).lds <= kUniqueLdsMost;
+}
+
+int64_t khop_unique_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
+    return unique_shape(gr, fanout, k, S).groups;
+}
+
+int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_t k, int32_t rounds, int64_t S,
+                const int32_t* roots, int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts,
+                hipStream_t stream) {
+    int64_t W[ND_MAX_FANOUT_STEPS];
+    slots_per_sample(fanout, k, W);
+    const UniqueShape u = unique_shape(gr, fanout, k, S);
+    UniqueFusedArgs a{};
+    a.links = gr.links;
+    a.seed = d.seed;
+    a.sample_base = d.sample_base;
+    a.S = (uint32_t)S;
+    a.V = (int32_t)gr.V;
+    a.k = k;
+    a.rounds = rounds;
+    for (int32_t i = 0; i < k; ++i) {
+        a.W[i] = (uint32_t)W[i];
+        a.div_m[i] = make_fastdiv((uint32_t)fanout[i]);
+        a.out[i] = step_out[i];
+    }
+    a.slots = u.slots;
+    a.rows = u.rows;
+    a.roots = roots;
+    a.hdr = (WsHeader*)ws;
+    a.flags = (uint32_t*)(ws + o_flags);
+    a.parts = (uint32_t*)(ws + o_parts);
+    a.o_flags = o_flags;
+    a.o_parts = o_parts;
+    mark_phase(ND_PHASE_UNIQUE, stream);
+#define ND_UNIQUE_GO(STRIDE, OFFT, THREADS, PER)                                                                   \
+    hipLaunchKernelGGL((khop_unique_kernel<STRIDE, OFFT, THREADS, PER>), dim3((unsigned)u.groups), dim3(THREADS <= 64 ? 64 : 256), u.lds, \
+                       stream, view_of<OFFT>(gr), a)
+#define ND_UNIQUE_SIZE(STRIDE, OFFT)                                    \
+    do {                                                                \
+        if (u.slots <= 32) ND_UNIQUE_GO(STRIDE, OFFT, 32, 1);           \
+        else if (u.slots <= 64) ND_UNIQUE_GO(STRIDE, OFFT, 64, 1);      \
+        else if (u.slots <= 128) ND_UNIQUE_GO(STRIDE, OFFT, 64, 2);     \
+        else if (u.slots <= 256) ND_UNIQUE_GO(STRIDE, OFFT, 64, 4);     \
+        else if (u.slots <= 512) ND_UNIQUE_GO(STRIDE, OFFT, 256, 2);    \
+        else if (u.slots <= 1024) ND_UNIQUE_GO(STRIDE, OFFT, 256, 4);   \
+        else ND_UNIQUE_GO(STRIDE, OFFT, 256, 8);                        \
+    } while (0)
+    if (gr.off64) {
+        if (gr.wq) ND_UNIQUE_SIZE(2, int64_t);
+        else ND_UNIQUE_SIZE(1, int64_t);
+    } else {
+        if (gr.wq) ND_UNIQUE_SIZE(2, int32_t);
+        else ND_UNIQUE_SIZE(1, int32_t);
+    }
+    ND_HIP_CHECK(hipGetLastError());
+    return ND_OK;
+}
+
+// Dynamic LDS above the 64 KB default has to be allowed once per kernel (samples of 1,025 to 2,048 slots
+// use more); done when a graph is created, so that the call itself only launches.
+int khop_prepare() {
+#define ND_UNIQUE_ALLOW(STRIDE, OFFT)                                                                             \
+    ND_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&khop_unique_kernel<STRIDE, OFFT, 256, 8>),    \
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUniqueLdsMost))
+    ND_UNIQUE_ALLOW(1, int64_t);
+    ND_UNIQUE_ALLOW(2, int64_t);
+    ND_UNIQUE_ALLOW(1, int32_t);
+    ND_UNIQUE_ALLOW(2, int32_t);
+#undef ND_UNIQUE_ALLOW
     return ND_OK;
 }
 

@@ -89,6 +89,15 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
                int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, uint32_t* status_out,
                hipStream_t stream);
 
+// The same with unique neighbours (Section 6.3), one group of lanes per sample.
+bool khop_unique_fits(const Graph& gr, const int32_t* fanout, int32_t k);
+int64_t khop_unique_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S);
+int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_t k, int32_t rounds, int64_t S,
+                const int32_t* roots, int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts,
+                hipStream_t stream);
+// Once per device before the first call (nd_graph_create does it).
+int khop_prepare();
+
 // Unique neighbours (Section 6.3) for one k-hop step whose first draw round has already been
 // written to `out`: per sample, duplicates are removed (the lowest slot keeps the vertex) and
 // the slots that lost draw again, sample-parallel, for rounds - 1 further attempts.

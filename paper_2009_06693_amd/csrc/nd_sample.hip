@@ -29,6 +29,7 @@
 #include "nd_wave.h"
 #include "nd_sample.h"
 #include "nd_draw.h"
+#include "nd_group.h"
 
 namespace nd {
 
@@ -389,44 +390,6 @@ int launch_sp(const Graph& gr, const DrawArgs& a, const int32_t* src, int64_t n_
 //    keyed by the slot the entry names;
 //  * groups of a wavefront or less share a 256-lane workgroup, each with its own table and queues,
 //    and every group walks over samples with a stride.
-template <int THREADS>
-__device__ __forceinline__ void group_sync() {
-    if (THREADS > 64) {
-        __syncthreads();
-    } else {  // part of one wavefront: its LDS operations complete in order; keep the compiler from moving them
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-// true when x is non-zero in any lane of the group; group_lanes: the group's lanes within its wavefront
-template <int THREADS>
-__device__ __forceinline__ int group_or(int x, uint64_t group_lanes) {
-    if (THREADS > 64) return __syncthreads_or(x);
-    group_sync<THREADS>();
-    const int r = (__ballot(x != 0) & group_lanes) != 0ull;
-    group_sync<THREADS>();
-    return r;
-}
-// A queue place for every lane with flag set (any order).  A group inside one wavefront counts in a
-// register (*fill, the same in all its lanes); a four-wavefront group counts in LDS (*fill_lds).
-// Every lane of the group calls it, in converged code.
-template <int THREADS>
-__device__ __forceinline__ uint32_t group_reserve(bool flag, uint64_t group_lanes, uint32_t* fill, uint32_t* fill_lds) {
-    const uint64_t votes = __ballot(flag) & group_lanes;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t before = (uint32_t)__popcll(votes & ((1ull << lane) - 1ull));
-    const uint32_t n = (uint32_t)__popcll(votes);
-    if (THREADS > 64) {
-        uint32_t base = 0;
-        if (lane == 0 && n > 0) base = atomicAdd(fill_lds, n);
-        base = (uint32_t)__shfl((int)base, 0, 64);
-        return base + before;
-    }
-    const uint32_t base = *fill;
-    *fill = base + n;
-    return base + before;
-}
-
 template <typename OffT, int THREADS, int kPerThread>
 __global__ __launch_bounds__(256) void unique_kernel(GraphView<OffT> g, UniqueArgs a, uint32_t num_samples) {
     static_assert(THREADS == 32 || THREADS == 64 || THREADS == 256, "a group is half a wavefront, one, or four");
