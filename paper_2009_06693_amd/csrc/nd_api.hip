@@ -48,6 +48,7 @@ struct Plan {
     uint32_t heavy_min = 64;   // pairs of one transit in a window from which the workgroup class serves it
     bool free_walk = false;    // walks over the graph's links, one lane per walk (nd_walk_free.hip)
     bool fused = false;        // k-hop: all hops in one launch (nd_khop.hip)
+    bool layer_fused = false;  // layer sampling: all steps of a sample by one workgroup
     size_t o_flags = 0, o_parts = 0;  // per workgroup: flag, live pairs per step
 };
 
@@ -226,6 +227,7 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
         const size_t hb = sort_hist_bytes(make_sort_plan(ns, g.V, p->sched_group_bits));
         if (hb > pl->hist_bytes) pl->hist_bytes = hb;
     }
+    pl->layer_fused = app == ND_LAYER && g.links != nullptr;
     pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
                 (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
                                       : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
@@ -241,7 +243,9 @@ void layout(Plan* pl, const Graph& g, const nd_params* p) {
         pl->o_state = o; o = align_up(o + (size_t)(pl->state_len > 0 ? pl->state_len : 1) * 4);
         pl->o_transits = o; o = align_up(o + (size_t)(pl->S > 0 ? pl->S : 1) * 4);
     }
-    if (pl->free_walk) {
+    if (pl->layer_fused) {
+        pl->o_flags = o; o = align_up(o + (size_t)layer_fused_groups(g, pl->S) * 4);
+    } else if (pl->free_walk) {
         const size_t groups = (size_t)walk_free_groups(pl->S, pl->app == ND_MULTIRW ? (uint32_t)p->roots_per_sample : 0u);
         pl->o_flags = o; o = align_up(o + groups * 4);
         pl->o_parts = o; o = align_up(o + groups * (size_t)pl->k * 4);
@@ -528,7 +532,7 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     char* ws = (char*)workspace_dev;
     WsHeader* hdr = (WsHeader*)ws;
     StepCtl* ctl = (StepCtl*)(ws + pl.o_ctl);
-    const bool own_header = (pl.free_walk || pl.fused) && pl.S > 0;  // its first kernel writes the header
+    const bool own_header = (pl.free_walk || pl.fused || pl.layer_fused) && pl.S > 0;  // its first kernel writes the header
     if (!own_header) {
         mark_phase(ND_PHASE_INIT, stream);
         const int64_t n_init = pl.bit_words > pl.k ? pl.bit_words : pl.k;
@@ -541,6 +545,13 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
         return ND_OK;
     }
 
+    if (pl.layer_fused) {
+        rc = layer_fused(g, seed, (uint32_t)params->sample_id_base, params->use_weights != 0, params->roots_per_sample,
+                         params->fanout, pl.k, pl.S, roots_dev, step_out_dev, ws, pl.o_flags, stream);
+        if (rc != ND_OK) return rc;
+        mark_phase(ND_PHASE_NONE, stream);
+        return ND_OK;
+    }
     if (app == ND_LAYER) {
         for (int i = 0; i < pl.k; ++i) {
             LayerArgs a{};
@@ -853,7 +864,9 @@ int nd_sample_stats(const void* workspace_dev, void* hip_stream, int32_t max_ste
     int n = (int)hdr.num_steps < max_steps ? (int)hdr.num_steps : max_steps;
     if (n > ND_MAX_WALK_STEPS) n = ND_MAX_WALK_STEPS;
     static thread_local StepCtl host_ctl[ND_MAX_WALK_STEPS];
-    if (n > 0 && hdr.n_groups > 0) {  // only the live pairs are counted on these routes
+    if (hdr.n_groups > 0 && hdr.o_parts == 0) {  // layer sampling has no pairs to count
+        n = 0;
+    } else if (n > 0 && hdr.n_groups > 0) {  // only the live pairs are counted on these routes
         std::vector<uint32_t> parts((size_t)hdr.n_groups * hdr.num_steps);
         ND_HIP_CHECK(hipMemcpyAsync(parts.data(), (const char*)workspace_dev + hdr.o_parts, parts.size() * 4,
                                     hipMemcpyDeviceToHost, stream));

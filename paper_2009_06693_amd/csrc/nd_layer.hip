@@ -127,6 +127,150 @@ __global__ __launch_bounds__(kLayerThreads) void layer_kernel(GraphView<OffT> g,
     }
 }
 
+// ---------------------------------------------------------------- all steps of a sample in one launch
+// A sample's steps depend on nothing but the sample, so its workgroup does them one after the other: the
+// rows of a step's transits come with the links of the entries that were drawn (off, then off + 1, are
+// only looked up for the roots) and stay in LDS.  One scattered line per draw is what a large call is bound
+// by; a call with a few samples is a chain of dependent fetches, and what counts there is their number.
+// Inside a weighted row the guide table (WeightLink) starts the search, where a binary search over the
+// running sums is one fetch per level: 257 samples of [512, 512] over 2.9 M vertices, symmetric weights,
+// took 31 us with a launch per step and the binary search.
+struct LayerFusedArgs {
+    const Link* links;
+    uint64_t seed;
+    uint32_t sample_base;
+    uint32_t S;
+    int32_t k;
+    uint32_t n[ND_MAX_FANOUT_STEPS];    // transits of a step (roots_per_sample, then the fanouts)
+    uint32_t m[ND_MAX_FANOUT_STEPS];    // draws of a step
+    uint32_t o_rows_b, o_incl;          // in LDS, in bytes: the second rows buffer, the running sums
+    const int32_t* roots;
+    int32_t* out[ND_MAX_FANOUT_STEPS];
+    WsHeader* hdr;
+    uint32_t* flags;
+    uint64_t o_flags;
+};
+
+// c(v) = floor(2^48 / deg^2).  In double precision: deg^2 < 2^48 is exact, and the quotient lies at least
+// 2^-48 of its value below the next whole number, which rounding to 2^-53 does not bridge.
+__device__ __forceinline__ uint64_t column_weight(uint32_t deg) {
+    return (uint64_t)(281474976710656.0 / ((double)deg * (double)deg));
+}
+
+// First entry of a row (links from `row`, running sums from `cum`) whose running sum exceeds rest < total.
+// The guide of a cell at or below the one that rest lies in names an entry at or before it; the estimate
+// of the cell is lowered by more than its rounding error.  Two looks at four entries find nearly every
+// entry; a cell with more of them (many light entries beside heavy ones) is searched by halves.
+__device__ __forceinline__ uint32_t guided_search(const Link* row, const uint64_t* cum, uint32_t deg, uint64_t rest,
+                                                  uint64_t total) {
+    if (deg < 2u) return 0u;
+    const double f = (double)rest / (double)total * (1.0 - 0x1p-48);
+    const uint32_t cell = mulhi32((uint32_t)(f * 4294967296.0), deg);
+    uint32_t j = reinterpret_cast<const WeightLink*>(row)[2ull * cell + 1u].guide;
+    const uint32_t last = deg - 1u;
+    for (int look = 0; look < 2; ++look) {
+        uint64_t c[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) c[i] = cum[j + i < last ? j + i : last];
+        uint32_t skip = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) skip += c[i] <= rest ? 1u : 0u;  // running sums do not fall
+        if (j + skip > last) return last;
+        j += skip;
+        if (skip < 4u) return j;
+    }
+    uint32_t lo = j, hi = last;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (cum[mid] > rest) hi = mid;
+        else lo = mid + 1u;
+    }
+    return lo;
+}
+
+template <typename OffT, bool WEIGHTED, int STRIDE, int THREADS>
+__global__ __launch_bounds__(THREADS) void layer_fused_kernel(GraphView<OffT> g, LayerFusedArgs a) {
+    extern __shared__ uint64_t lds[];
+    char* mem = (char*)lds;
+    uint2* buf_a = (uint2*)mem;
+    uint2* buf_b = (uint2*)(mem + a.o_rows_b);
+    uint64_t* s_incl = (uint64_t*)(mem + a.o_incl);
+    __shared__ uint64_t scan_tmp[THREADS / 64 + 1];
+    bool bad = false;
+    for (uint32_t b = blockIdx.x; b < a.S; b += gridDim.x) {
+        for (uint32_t t = threadIdx.x; t < a.n[0]; t += THREADS) {
+            const int32_t v = a.roots[(uint64_t)b * a.n[0] + t];
+            uint2 row = make_uint2(0u, 0u);
+            if (v >= g.V || v < ND_NULL_VERTEX) bad = true;
+            else if (v >= 0) {
+                const uint64_t rs = (uint64_t)g.off[v];
+                row = make_uint2((uint32_t)rs, row_length(g, v, rs));
+            }
+            buf_a[t] = row;
+        }
+        __syncthreads();
+        for (int step = 0; step < a.k; ++step) {
+            const uint2* rows = (step & 1) ? buf_b : buf_a;
+            uint2* next = (step & 1) ? buf_a : buf_b;
+            const uint32_t n = a.n[step], m = a.m[step];
+            const bool last = step == a.k - 1;
+            // running sums of the transits' masses: every thread a stretch of its own, one scan
+            const uint32_t per = (n + THREADS - 1) / THREADS;
+            const uint32_t t0 = threadIdx.x * per, t1 = t0 + per < n ? t0 + per : n;
+            uint64_t sum = 0;
+            for (uint32_t t = t0; t < t1; ++t) {
+                const uint2 row = rows[t];
+                if (row.y > 0u) {
+                    if (WEIGHTED) sum += g.cumq[(uint64_t)row.x + row.y - 1u];
+                    else sum += row.y * column_weight(row.y);
+                }
+                s_incl[t] = sum;
+            }
+            uint64_t total;
+            const uint64_t before_me = block_exclusive_scan<uint64_t, THREADS>(sum, scan_tmp, &total);
+            for (uint32_t t = t0; t < t1; ++t) s_incl[t] += before_me;
+            __syncthreads();
+            int32_t* out = a.out[step] + (uint64_t)b * m;
+            for (uint32_t j = threadIdx.x; j < m; j += THREADS) {
+                int32_t res = ND_NULL_VERTEX;
+                uint2 row_out = make_uint2(0u, 0u);
+                if (total > 0) {
+                    const Rand4 r = draw4(a.seed, a.sample_base + b, j, (uint32_t)step, 0u);
+                    const uint64_t x = mulhi64(cat64(r.r0, r.r1), total);
+                    uint32_t lo = 0, hi = n - 1u;
+                    while (lo < hi) {  // first transit whose running sum exceeds x
+                        const uint32_t mid = (lo + hi) >> 1;
+                        if (s_incl[mid] > x) hi = mid;
+                        else lo = mid + 1u;
+                    }
+                    const uint64_t before = lo ? s_incl[lo - 1u] : 0ull;
+                    const uint2 row = rows[lo];
+                    uint64_t e = row.x;
+                    if (WEIGHTED)
+                        e += guided_search(a.links + 2ull * row.x, g.cumq + row.x, row.y, x - before, s_incl[lo] - before);
+                    else
+                        e += div_small_quotient(x - before, column_weight(row.y));
+                    if (last) {
+                        res = g.col[e];
+                    } else {
+                        const Link l = a.links[e * STRIDE];
+                        res = l.v;
+                        row_out = make_uint2(l.rs, l.deg);
+                    }
+                }
+                out[j] = res;
+                if (!last) next[j] = row_out;
+            }
+            __syncthreads();  // the next step reads the rows and rewrites the sums
+        }
+    }
+    const int any = __syncthreads_or(bad ? 1 : 0);
+    if (threadIdx.x == 0) {
+        a.flags[blockIdx.x] = any ? 1u : 0u;
+        if (blockIdx.x == 0) write_header(a.hdr, (uint32_t)a.k, gridDim.x, a.o_flags, 0);
+    }
+}
+
 }  // namespace
 
 // Dynamic LDS above the 64 KB default has to be allowed once per kernel; done when a graph is
@@ -141,9 +285,82 @@ int layer_prepare() {
     ND_LAYER_ALLOW(int32_t, true);
     ND_LAYER_ALLOW(int32_t, false);
 #undef ND_LAYER_ALLOW
+#define ND_LAYER_ALLOW_T(OFFT, W, STRIDE, T)                                                               \
+    ND_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_fused_kernel<OFFT, W, STRIDE, T>), \
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,                           \
+                                     ND_MAX_LAYER_TRANSITS * 24))
+#define ND_LAYER_ALLOW(OFFT, W, STRIDE)       \
+    ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 512);   \
+    ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 1024)
+    ND_LAYER_ALLOW(int64_t, true, 2);
+    ND_LAYER_ALLOW(int64_t, false, 2);
+    ND_LAYER_ALLOW(int64_t, false, 1);
+    ND_LAYER_ALLOW(int32_t, true, 2);
+    ND_LAYER_ALLOW(int32_t, false, 2);
+    ND_LAYER_ALLOW(int32_t, false, 1);
+#undef ND_LAYER_ALLOW_T
+#undef ND_LAYER_ALLOW
     return ND_OK;
 }
 
+int64_t layer_fused_groups(const Graph& gr, int64_t S) {
+    const int64_t most = (int64_t)gr.num_cus * 64;  // bounds the flags; the workgroups stride over the samples
+    return S < most ? S : most;
+}
+
+int layer_fused(const Graph& gr, uint64_t seed, uint32_t sample_base, bool weighted, int32_t roots_per_sample,
+                const int32_t* fanout, int32_t k, int64_t S, const int32_t* roots, int32_t* const* step_out, char* ws,
+                uint64_t o_flags, hipStream_t stream) {
+    LayerFusedArgs a{};
+    a.links = gr.links;
+    a.seed = seed;
+    a.sample_base = sample_base;
+    a.S = (uint32_t)S;
+    a.k = k;
+    uint32_t rows[2] = {0, 0}, widest = 0, most_draws = 0;
+    for (int32_t i = 0; i < k; ++i) {
+        a.n[i] = (uint32_t)(i == 0 ? roots_per_sample : fanout[i - 1]);
+        a.m[i] = (uint32_t)fanout[i];
+        a.out[i] = step_out[i];
+        if (a.m[i] > most_draws) most_draws = a.m[i];
+        if (a.n[i] > rows[i & 1]) rows[i & 1] = a.n[i];
+        if (a.n[i] > widest) widest = a.n[i];
+    }
+    a.o_rows_b = rows[0] * 8u;
+    a.o_incl = a.o_rows_b + rows[1] * 8u;
+    const size_t lds_bytes = (size_t)a.o_incl + (size_t)widest * 8u;  // at most 24 bytes per transit
+    a.roots = roots;
+    a.hdr = (WsHeader*)ws;
+    a.flags = (uint32_t*)(ws + o_flags);
+    a.o_flags = o_flags;
+    mark_phase(ND_PHASE_LAYER, stream);
+    // Twice the lanes where the samples leave compute units idle and the draws are more than one per lane
+    // (48 samples of [2048, 2048] over 4.2 M vertices: 17.2 us with 512 lanes, 14.6 with 1,024)
+    const bool wide = most_draws > kLayerThreads && S <= 2 * (int64_t)gr.num_cus;
+#define ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, T)                                                               \
+    hipLaunchKernelGGL((layer_fused_kernel<OFFT, W, STRIDE, T>), dim3((unsigned)layer_fused_groups(gr, S)), \
+                       dim3(T), lds_bytes, stream, view_of<OFFT>(gr), a)
+#define ND_LAYER_LAUNCH(OFFT, W, STRIDE)                       \
+    do {                                                       \
+        if (wide) ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 1024);    \
+        else ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 512);          \
+    } while (0)
+    if (gr.off64) {
+        if (weighted) ND_LAYER_LAUNCH(int64_t, true, 2);
+        else if (gr.wq) ND_LAYER_LAUNCH(int64_t, false, 2);
+        else ND_LAYER_LAUNCH(int64_t, false, 1);
+    } else {
+        if (weighted) ND_LAYER_LAUNCH(int32_t, true, 2);
+        else if (gr.wq) ND_LAYER_LAUNCH(int32_t, false, 2);
+        else ND_LAYER_LAUNCH(int32_t, false, 1);
+    }
+#undef ND_LAYER_LAUNCH_T
+#undef ND_LAYER_LAUNCH
+    ND_HIP_CHECK(hipGetLastError());
+    return ND_OK;
+}
+
+// One step with the rows looked up per transit: graphs without links.
 int layer_step(const Graph& gr, const LayerArgs& a, int64_t num_samples, hipStream_t stream) {
     if (num_samples == 0) return ND_OK;
     const size_t lds_bytes = (size_t)a.n_prev * 24;  // at most 96 KB of the 160 KB per CU

@@ -127,6 +127,11 @@ struct LayerArgs {
     int32_t use_weights;          // entries weigh w_q(v,u) instead of c(v)
     uint32_t* status;
 };
+// All steps of a call in one launch (graphs with links): workgroups, for the flags, and the launch.
+int64_t layer_fused_groups(const Graph& gr, int64_t S);
+int layer_fused(const Graph& gr, uint64_t seed, uint32_t sample_base, bool weighted, int32_t roots_per_sample,
+                const int32_t* fanout, int32_t k, int64_t S, const int32_t* roots, int32_t* const* step_out, char* ws,
+                uint64_t o_flags, hipStream_t stream);
 int layer_step(const Graph& gr, const LayerArgs& a, int64_t num_samples, hipStream_t stream);
 // Once per device before the first layer_step (nd_graph_create does it): lifts the kernels' LDS limit.
 int layer_prepare();
