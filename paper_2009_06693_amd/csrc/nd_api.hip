@@ -239,14 +239,17 @@ void layout(Plan* pl, const Graph& g, const nd_params* p) {
     size_t o = sizeof(WsHeader);
     pl->o_ctl = o;
     o = align_up(o + sizeof(StepCtl) * (size_t)pl->k);
-    if (pl->app == ND_MULTIRW) {
+    if (pl->app == ND_MULTIRW && !pl->free_walk) {
         pl->o_state = o; o = align_up(o + (size_t)(pl->state_len > 0 ? pl->state_len : 1) * 4);
         pl->o_transits = o; o = align_up(o + (size_t)(pl->S > 0 ? pl->S : 1) * 4);
     }
     if (pl->layer_fused) {
         pl->o_flags = o; o = align_up(o + (size_t)layer_fused_groups(g, pl->S) * 4);
     } else if (pl->free_walk) {
-        const size_t groups = (size_t)walk_free_groups(pl->S, pl->app == ND_MULTIRW ? (uint32_t)p->roots_per_sample : 0u);
+        const uint32_t R = pl->app == ND_MULTIRW ? (uint32_t)p->roots_per_sample : 0u;
+        const size_t groups = (size_t)walk_free_groups(pl->S, pl->k, R);
+        if (pl->S > 0) o = pl->o_ctl;  // a call that launches this route has no control blocks
+        pl->o_state = o; o = align_up(o + (size_t)walk_free_state_bytes(pl->S, pl->k, R));
         pl->o_flags = o; o = align_up(o + groups * 4);
         pl->o_parts = o; o = align_up(o + groups * (size_t)pl->k * 4);
     } else if (pl->mode == ND_MODE_TRANSIT_PARALLEL && !pl->collective && pl->window == 0) {

@@ -25,6 +25,7 @@ struct FreeArgs {
     uint64_t ppr_thr;
     uint32_t sample_base;
     uint32_t S;
+    uint32_t s_first;          // the launch's first sample: a call of very many samples takes several launches
     uint32_t first_step, n_steps;
     int32_t V;
     const int32_t* src;        // the roots, or the output of step first_step - 1 (multi-dimensional walk: its roots)
@@ -35,8 +36,9 @@ struct FreeArgs {
     uint32_t R;                // multi-dimensional walk: roots per sample
     int32_t* state;            // ... and where they go when more steps follow, else null
     WsHeader* hdr;
-    uint32_t* flags;           // per workgroup: a root was outside [0, V) (first launch)
+    uint32_t* flags;           // per workgroup: a root was outside [0, V) (launches of the first steps)
     uint32_t* parts;           // [workgroup][step of the call]: live walks
+                               // launches after the call's first samples add to both
     uint32_t total_steps;
     uint64_t o_flags, o_parts;
     int32_t* out[kFreeChunk];
@@ -45,7 +47,9 @@ struct FreeArgs {
 // Live pairs of every step, from what each lane knows at the end: its walk had a transit at the first
 // `lived` steps of this launch.  One histogram entry per lane, then sums from the top.
 template <int THREADS>
-__device__ __forceinline__ void publish_live(uint32_t lived, uint32_t n_steps, uint32_t* hist, uint32_t* parts) {
+__device__ __forceinline__ void publish_live(uint32_t lived, const FreeArgs& a, uint32_t* hist) {
+    const uint32_t n_steps = a.n_steps;
+    uint32_t* parts = a.parts + (uint64_t)blockIdx.x * a.total_steps + a.first_step;
     for (uint32_t i = threadIdx.x; i <= (uint32_t)kFreeChunk; i += THREADS) hist[i] = 0;
     __syncthreads();
     if (lived > 0) atomicAdd(&hist[lived], 1u);
@@ -57,10 +61,16 @@ __device__ __forceinline__ void publish_live(uint32_t lived, uint32_t n_steps, u
             const uint32_t step = (uint32_t)(half * 64 + 63 - lane);  // a live length above `step` counts
             const uint32_t mine = step < n_steps ? hist[step + 1u] : 0u;
             const uint32_t incl = wave_inclusive_scan(mine, lane);
-            if (step < n_steps) parts[step] = carry + incl;
+            if (step < n_steps) parts[step] = (a.s_first > 0 ? parts[step] : 0u) + carry + incl;
             carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         }
     }
+}
+
+// One lane per workgroup: what its roots looked like, and the header.
+__device__ __forceinline__ void publish_root_check(const FreeArgs& a, int any_bad) {
+    a.flags[blockIdx.x] = (a.s_first > 0 ? a.flags[blockIdx.x] : 0u) | (any_bad ? 1u : 0u);
+    if (blockIdx.x == 0 && a.s_first == 0) write_header(a.hdr, a.total_steps, gridDim.x, a.o_flags, a.o_parts);
 }
 
 // The walk's first transit and, in the first launch, what the host may ask for afterwards.
@@ -71,10 +81,7 @@ __device__ __forceinline__ int32_t first_transit(const FreeArgs& a, uint32_t s) 
         const bool bad = v >= a.V || v < ND_NULL_VERTEX;
         if (bad) v = ND_NULL_VERTEX;
         const int any = __syncthreads_or(bad ? 1 : 0);
-        if (threadIdx.x == 0) {
-            a.flags[blockIdx.x] = any ? 1u : 0u;
-            if (blockIdx.x == 0) write_header(a.hdr, a.total_steps, gridDim.x, a.o_flags, a.o_parts);
-        }
+        if (threadIdx.x == 0) publish_root_check(a, any);
     }
     return v;
 }
@@ -85,7 +92,7 @@ __device__ __forceinline__ int32_t first_transit(const FreeArgs& a, uint32_t s) 
 template <int DRAW, int STRIDE, typename OffT, int THREADS>
 __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
-    const uint32_t s = blockIdx.x * (uint32_t)THREADS + threadIdx.x;
+    const uint32_t s = a.s_first + blockIdx.x * (uint32_t)THREADS + threadIdx.x;
     int32_t v = first_transit<THREADS>(a, s);
     uint32_t rs = 0, deg = 0;
     if (v >= 0) {
@@ -135,7 +142,7 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
         deg = l.deg;
         if (s < a.S) a.out[si][s] = v;
     }
-    publish_live<THREADS>(lived, a.n_steps, s_hist, a.parts + (uint64_t)blockIdx.x * a.total_steps + a.first_step);
+    publish_live<THREADS>(lived, a, s_hist);
 }
 
 // ---------------------------------------------------------------- node2vec
@@ -191,7 +198,7 @@ __device__ __noinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, 
 template <int STRIDE, typename OffT, int THREADS>
 __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
-    const uint32_t s = blockIdx.x * (uint32_t)THREADS + threadIdx.x;
+    const uint32_t s = a.s_first + blockIdx.x * (uint32_t)THREADS + threadIdx.x;
     int32_t v = first_transit<THREADS>(a, s);
     uint32_t rs = 0, deg = 0, maxw = kOneQ16;
     int32_t t = ND_NULL_VERTEX;        // the transit before v: none at the first step
@@ -256,7 +263,7 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
     const uint32_t lived = si + (si < a.n_steps && v >= 0 ? 1u : 0u);
     if (s < a.S)
         for (; si < a.n_steps; ++si) a.out[si][s] = ND_NULL_VERTEX;
-    publish_live<THREADS>(lived, a.n_steps, s_hist, a.parts + (uint64_t)blockIdx.x * a.total_steps + a.first_step);
+    publish_live<THREADS>(lived, a, s_hist);
 }
 
 // ---------------------------------------------------------------- multi-dimensional walk
@@ -276,7 +283,7 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
     const int lane = lane_id();
     int32_t* state = (int32_t*)s_dyn + wave * R * 3u;  // the roots of my sample
     uint32_t* picked = (uint32_t*)state + R;           // per root: which of the 64 steps pick it (two words)
-    const uint32_t s0 = blockIdx.x * WAVES, s = s0 + wave;
+    const uint32_t s0 = a.s_first + blockIdx.x * WAVES, s = s0 + wave;
     const bool mine = s < a.S;
     bool bad = false;
     for (uint32_t i = (uint32_t)lane; i < R; i += 64u) {
@@ -294,10 +301,7 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
     }
     for (uint32_t i = threadIdx.x; i < (uint32_t)kFreeChunk; i += T) s_live[i] = 0;
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
-    if (threadIdx.x == 0 && a.first_step == 0) {
-        a.flags[blockIdx.x] = any_bad ? 1u : 0u;
-        if (blockIdx.x == 0) write_header(a.hdr, a.total_steps, gridDim.x, a.o_flags, a.o_parts);
-    }
+    if (threadIdx.x == 0 && a.first_step == 0) publish_root_check(a, any_bad);
     for (uint32_t base = 0; base < a.n_steps; base += 64u) {
         const uint32_t si = base + (uint32_t)lane;
         const bool step = mine && si < a.n_steps;
@@ -358,15 +362,15 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
         }
         __syncthreads();
     }
-    for (uint32_t i = threadIdx.x; i < a.n_steps; i += T)
-        a.parts[(uint64_t)blockIdx.x * a.total_steps + a.first_step + i] = s_live[i];
+    uint32_t* parts = a.parts + (uint64_t)blockIdx.x * a.total_steps + a.first_step;
+    for (uint32_t i = threadIdx.x; i < a.n_steps; i += T) parts[i] = (a.s_first > 0 ? parts[i] : 0u) + s_live[i];
     if (a.state != nullptr && mine)  // more steps follow in another launch
         for (uint32_t i = (uint32_t)lane; i < R; i += 64u) a.state[(uint64_t)s * R + i] = state[i];
 }
 
 template <int WAVES, typename OffT>
-void launch_mrw(const Graph& gr, const FreeArgs& a, hipStream_t stream) {
-    const dim3 grid((a.S + WAVES - 1u) / WAVES), block(WAVES * 64);
+void launch_mrw(const Graph& gr, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
+    const dim3 grid(groups), block(WAVES * 64);
     const size_t lds = (size_t)WAVES * a.R * 12;  // at most 48 KB
     if (gr.wq) hipLaunchKernelGGL((mrw_free_kernel<2, OffT, WAVES>), grid, block, lds, stream, view_of<OffT>(gr), a);
     else hipLaunchKernelGGL((mrw_free_kernel<1, OffT, WAVES>), grid, block, lds, stream, view_of<OffT>(gr), a);
@@ -377,8 +381,8 @@ void launch_mrw(const Graph& gr, const FreeArgs& a, hipStream_t stream) {
 int mrw_waves(uint32_t R) { return R <= 256u ? 16 : R <= 1024u ? 4 : 1; }
 
 template <int THREADS, typename OffT>
-void launch_free(const Graph& gr, int draw, const FreeArgs& a, hipStream_t stream) {
-    const dim3 grid((a.S + THREADS - 1u) / THREADS), block(THREADS);
+void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
+    const dim3 grid(groups), block(THREADS);
     const GraphView<OffT> g = view_of<OffT>(gr);
     if (draw == kDrawNode2vec) {
         if (gr.wq) hipLaunchKernelGGL((walk_free_n2v_kernel<2, OffT, THREADS>), grid, block, 0, stream, g, a);
@@ -400,9 +404,26 @@ void launch_free(const Graph& gr, int draw, const FreeArgs& a, hipStream_t strea
 // have fewer headers and counters to write.
 static int free_threads(int64_t S) { return S <= 65536 ? 64 : 256; }
 
-int64_t walk_free_groups(int64_t S, uint32_t mrw_R) {
-    const int64_t per = mrw_R > 0 ? mrw_waves(mrw_R) : free_threads(S);
-    return (S + per - 1) / per;
+static int64_t samples_per_group(int64_t S, uint32_t mrw_R) { return mrw_R > 0 ? mrw_waves(mrw_R) : free_threads(S); }
+
+// Bytes of the workspace that hold a multi-dimensional walk's roots between two launches.
+int64_t walk_free_state_bytes(int64_t S, int32_t num_steps, uint32_t mrw_R) {
+    return num_steps > kFreeChunk ? S * (int64_t)mrw_R * 4 : 0;
+}
+
+// Workgroups per launch.  Each owns a flag and a counter per step of the call in the workspace; samples
+// beyond what these workgroups take go to further launches.  24 MB of counters are 62,000 workgroups (15.9 M
+// walks) of 100 steps, or 1,535 of the 4,096 steps that a call may have.  No call may need more of the
+// static scratch array than walks whose scratch is a control block (64 bytes) per step, the roots and a
+// transit per sample of the multi-dimensional walk, so beside many roots the counters take what those took.
+int64_t walk_free_groups(int64_t S, int32_t num_steps, uint32_t mrw_R) {
+    const int64_t per = samples_per_group(S, mrw_R), k = num_steps;
+    int64_t room = (24ll << 20) - walk_free_state_bytes(S, num_steps, mrw_R);
+    const int64_t least = 64 * k + (mrw_R > 0 ? 4 * S : 0);
+    if (room < least) room = least;
+    const int64_t most = room / (4 + 4 * k);  // at least 8 (one step)
+    const int64_t groups = (S + per - 1) / per;
+    return groups < most ? groups : most;
 }
 
 int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t num_steps, const int32_t* roots,
@@ -429,35 +450,41 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.total_steps = (uint32_t)num_steps;
     a.o_flags = o_flags;
     a.o_parts = o_parts;
-    for (int32_t first = 0; first < num_steps; first += kFreeChunk) {
-        const int32_t n = num_steps - first < kFreeChunk ? num_steps - first : kFreeChunk;
-        a.first_step = (uint32_t)first;
-        a.n_steps = (uint32_t)n;
-        a.src = first > 0 ? step_out[first - 1] : roots;
-        a.prev_src = first > 0 ? step_out[first - 2] : nullptr;  // kFreeChunk is at least two
-        for (int32_t i = 0; i < kFreeChunk; ++i) a.out[i] = i < n ? step_out[first + i] : nullptr;
-        mark_phase(ND_PHASE_WALK_WINDOW, stream);
-        if (mrw_R > 0) {
-            a.src = first > 0 ? mrw_state : roots;
-            a.state = first + n < num_steps ? mrw_state : nullptr;
-            const int waves = mrw_waves(mrw_R);
-            if (gr.off64) {
-                if (waves == 16) launch_mrw<16, int64_t>(gr, a, stream);
-                else if (waves == 4) launch_mrw<4, int64_t>(gr, a, stream);
-                else launch_mrw<1, int64_t>(gr, a, stream);
+    const int64_t per = samples_per_group(S, mrw_R), most = walk_free_groups(S, num_steps, mrw_R);  // S >= 1
+    for (int64_t s = 0; s < S; s += most * per) {
+        const int64_t left = (S - s + per - 1) / per;
+        const uint32_t groups = (uint32_t)(left < most ? left : most);
+        a.s_first = (uint32_t)s;
+        for (int32_t first = 0; first < num_steps; first += kFreeChunk) {
+            const int32_t n = num_steps - first < kFreeChunk ? num_steps - first : kFreeChunk;
+            a.first_step = (uint32_t)first;
+            a.n_steps = (uint32_t)n;
+            a.src = first > 0 ? step_out[first - 1] : roots;
+            a.prev_src = first > 0 ? step_out[first - 2] : nullptr;  // kFreeChunk is at least two
+            for (int32_t i = 0; i < kFreeChunk; ++i) a.out[i] = i < n ? step_out[first + i] : nullptr;
+            mark_phase(ND_PHASE_WALK_WINDOW, stream);
+            if (mrw_R > 0) {
+                a.src = first > 0 ? mrw_state : roots;
+                a.state = first + n < num_steps ? mrw_state : nullptr;
+                const int waves = mrw_waves(mrw_R);
+                if (gr.off64) {
+                    if (waves == 16) launch_mrw<16, int64_t>(gr, a, groups, stream);
+                    else if (waves == 4) launch_mrw<4, int64_t>(gr, a, groups, stream);
+                    else launch_mrw<1, int64_t>(gr, a, groups, stream);
+                } else {
+                    if (waves == 16) launch_mrw<16, int32_t>(gr, a, groups, stream);
+                    else if (waves == 4) launch_mrw<4, int32_t>(gr, a, groups, stream);
+                    else launch_mrw<1, int32_t>(gr, a, groups, stream);
+                }
+            } else if (gr.off64) {
+                if (free_threads(S) == 64) launch_free<64, int64_t>(gr, draw, a, groups, stream);
+                else launch_free<256, int64_t>(gr, draw, a, groups, stream);
             } else {
-                if (waves == 16) launch_mrw<16, int32_t>(gr, a, stream);
-                else if (waves == 4) launch_mrw<4, int32_t>(gr, a, stream);
-                else launch_mrw<1, int32_t>(gr, a, stream);
+                if (free_threads(S) == 64) launch_free<64, int32_t>(gr, draw, a, groups, stream);
+                else launch_free<256, int32_t>(gr, draw, a, groups, stream);
             }
-        } else if (gr.off64) {
-            if (free_threads(S) == 64) launch_free<64, int64_t>(gr, draw, a, stream);
-            else launch_free<256, int64_t>(gr, draw, a, stream);
-        } else {
-            if (free_threads(S) == 64) launch_free<64, int32_t>(gr, draw, a, stream);
-            else launch_free<256, int32_t>(gr, draw, a, stream);
+            ND_HIP_CHECK(hipGetLastError());
         }
-        ND_HIP_CHECK(hipGetLastError());
     }
     return ND_OK;
 }

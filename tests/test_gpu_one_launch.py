@@ -1,0 +1,185 @@
+"""The routes that run all steps of a sample in one launch (k-hop, unique neighbours, walks, layer
+samples), at the sizes where their kernels change shape, against the oracle: one draw or two per
+lane, several samples per workgroup or several workgroups per sample, rows in LDS up to the last
+that fit, launches of 128 steps, 64 or 256 walks and 4 or 16 samples per workgroup, weighted links,
+rows whose weights all quantise to zero, calls of more walks than one launch has counters for."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2009_06693_amd import binding as B
+from paper_2009_06693_amd import inputs
+
+from gpu_util import assert_steps_equal, gpu_sample
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(weighted, int64_offsets, zeros=True):
+    """Skewed, with dead ends, one row that holds nearly every vertex, and (weighted) rows and
+    entries whose weights quantise to zero."""
+    rng = np.random.default_rng(7)
+    V = 700
+    pairs = set(zip(rng.integers(0, V, 6000).tolist(), (rng.random(6000) ** 2 * V).astype(int).tolist()))
+    pairs |= {(3, v) for v in range(0, V, 2)} | {(v, 3) for v in range(0, V, 3)}
+    pairs = sorted((a, b) for a, b in pairs if a % 11 != 5)    # rows 5, 16, ... are empty
+    w = None
+    if weighted:
+        w = (1.0 + 4.0 * rng.random(len(pairs))).astype(np.float32)
+        if zeros:
+            w[rng.random(len(pairs)) < 0.1] = 1e-6
+            w[[a % 13 == 1 for a, _ in pairs]] = 1e-6
+    g = inputs.from_edges(V, pairs, weights=w, int64_offsets=int64_offsets)
+    return g, B.nd_graph_create(g.row_offsets, g.col_indices, g.weights), \
+        oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+
+
+@pytest.fixture(scope="module", params=[(False, False), (True, False), (False, True), (True, True)],
+                ids=["plain32", "weighted32", "plain64", "weighted64"])
+def graph(request):
+    return _graph(*request.param)
+
+
+def _roots(V, n, seed):
+    r = np.random.default_rng(seed).integers(0, V, size=n, dtype=np.int32)
+    r[::17] = -1
+    return r
+
+
+@pytest.mark.parametrize("fanout,S", [([1], 1), ([7], 9000), ([2], 9000), ([2, 3], 9000), ([3, 2, 1, 2], 3000),
+                                      ([15, 10, 5], 37), ([25, 10], 2049), ([4096, 2], 3), ([63, 64, 2], 2),
+                                      ([64, 64, 2], 2), ([300000], 2)])
+def test_khop(graph, fanout, S):
+    g, dg, og = graph
+    roots = _roots(g.V, S, 1)
+    want = oracle.khop(og, roots, fanout, seed=5, sample_id_base=9)
+    got, stats = gpu_sample(dg, B.ND_KHOP, roots, 5, num_steps=len(fanout), fanout=fanout, sample_id_base=9)
+    assert_steps_equal(got, want, f"khop {fanout} S={S}")
+    live = [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
+    assert stats[:, 0].tolist() == live
+
+
+def test_khop_into_outputs_of_any_alignment(graph):
+    g, dg, og = graph
+    roots = _roots(g.V, 333, 2)
+    want = oracle.khop(og, roots, [3, 4], seed=6)
+    p = B.nd_params_init(num_steps=2, fanout=[3, 4])
+    lens, ws = B.nd_sample_query(dg, B.ND_KHOP, p, 333)
+    for skip in (0, 1, 2, 3):
+        flat = [torch.full((n + 8,), -7, dtype=torch.int32, device="cuda:0") for n in lens]
+        out = [f[skip:skip + n] for f, n in zip(flat, lens)]
+        B.nd_sample(dg, B.ND_KHOP, p, torch.as_tensor(roots, device="cuda:0"), 6, out,
+                    torch.empty(ws, dtype=torch.uint8, device="cuda:0"))
+        torch.cuda.synchronize()
+        assert_steps_equal([o.cpu().numpy() for o in out], want, f"skip={skip}")
+        for f, n in zip(flat, lens):
+            assert (f[:skip] == -7).all() and (f[skip + n:] == -7).all()
+
+
+@pytest.mark.parametrize("fanout,rounds", [([1], 1), ([32], 64), ([33], 3), ([16, 2], 4), ([5, 7, 3], 5), ([255, 1], 2),
+                                           ([2, 1024], 2), ([1024, 2], 3)])
+def test_unique_neighbours(graph, fanout, rounds):
+    g, dg, og = graph
+    roots = _roots(g.V, 257, 3)
+    want = oracle.khop(og, roots, fanout, seed=8, unique_rounds=rounds)
+    got, _ = gpu_sample(dg, B.ND_KHOP, roots, 8, num_steps=len(fanout), fanout=fanout, unique_rounds=rounds)
+    assert_steps_equal(got, want, f"unique {fanout} rounds={rounds}")
+
+
+@pytest.mark.parametrize("steps,S", [(1, 1), (127, 63), (128, 64), (129, 65), (257, 130), (3, 65536), (3, 65537)])
+def test_walks(graph, steps, S):
+    g, dg, og = graph
+    roots = _roots(g.V, S, 4)
+    for weighted in ((0, 1) if g.weights is not None else (0,)):
+        kw = dict(num_steps=steps, use_weights=weighted)
+        want = oracle.deepwalk(og, roots, steps, seed=9, use_weights=bool(weighted))
+        got, stats = gpu_sample(dg, B.ND_DEEPWALK, roots, 9, **kw)
+        assert_steps_equal(got, list(want), "deepwalk")
+        assert stats[:, 0].tolist() == [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
+        want = oracle.ppr(og, roots, steps, 0.02, seed=10, use_weights=bool(weighted))
+        got, _ = gpu_sample(dg, B.ND_PPR, roots, 10, term_prob=0.02, **kw)
+        assert_steps_equal(got, list(want), "ppr")
+
+
+@pytest.mark.parametrize("int64_offsets", [False, True])
+@pytest.mark.parametrize("steps,S", [(1, 1), (127, 63), (129, 65), (257, 130), (3, 65537)])
+def test_node2vec(int64_offsets, steps, S):
+    g, dg, og = _graph(True, int64_offsets, zeros=False)
+    roots = _roots(g.V, S, 4)
+    for weighted in (0, 1):
+        for attempts in (0, 1, 64):
+            want = oracle.node2vec(og, roots, steps, 2.0, 0.5, seed=11, use_weights=bool(weighted),
+                                   max_attempts=attempts)
+            got, stats = gpu_sample(dg, B.ND_NODE2VEC, roots, 11, num_steps=steps, p=2.0, q=0.5,
+                                    n2v_max_attempts=attempts, use_weights=weighted)
+            assert_steps_equal(got, list(want), f"node2vec attempts={attempts} weighted={weighted}")
+            assert stats[:, 0].tolist() == [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
+
+
+def test_node2vec_without_membership_tables():
+    """The tables are made when the scratch of a node2vec call is asked for; without them rows are searched."""
+    g, dg, og = _graph(True, False, zeros=False)
+    roots = _roots(g.V, 500, 5)
+    want = oracle.node2vec(og, roots, 20, 0.5, 4.0, seed=12, use_weights=True)
+    lens, ws = B.nd_sample_query(dg, B.ND_DEEPWALK, B.nd_params_init(num_steps=20), 500)  # the same scratch
+    out = [torch.empty(n, dtype=torch.int32, device="cuda:0") for n in lens]
+    B.nd_sample(dg, B.ND_NODE2VEC, B.nd_params_init(num_steps=20, p=0.5, q=4.0, use_weights=1),
+                torch.as_tensor(roots, device="cuda:0"), 12, out, torch.empty(ws, dtype=torch.uint8, device="cuda:0"))
+    torch.cuda.synchronize()
+    assert_steps_equal([o.cpu().numpy() for o in out], list(want), "node2vec")
+
+
+@pytest.mark.parametrize("R,steps,S", [(1, 64, 15), (2, 129, 17), (100, 65, 16), (256, 70, 33), (257, 130, 5),
+                                       (1024, 300, 4), (1025, 300, 3), (4096, 64, 1)])
+def test_multi_dimensional_walk(graph, R, steps, S):
+    g, dg, og = graph
+    roots = _roots(g.V, R * S, 6)
+    want = oracle.multirw(og, roots, R, steps, seed=13)
+    got, _ = gpu_sample(dg, B.ND_MULTIRW, roots, 13, num_steps=steps, roots_per_sample=R)
+    assert_steps_equal(got, list(want), f"multirw R={R}")
+
+
+@pytest.mark.parametrize("app,steps,S,R", [(B.ND_DEEPWALK, 2100, 800_000, 1), (B.ND_MULTIRW, 2100, 60_000, 3)])
+def test_more_walks_than_one_launch_counts_for_fit_the_static_scratch(app, steps, S, R):
+    """Counters for every workgroup of these calls would take 26 and 32 MB; samples beyond what the scratch
+    has room for go to further launches.  The bad roots are the first launch's and the last launch's."""
+    g, dg, og = _graph(False, False)
+    roots = np.random.default_rng(8).integers(0, g.V, size=S * R, dtype=np.int32)
+    roots[[5, S * R - 2]] = g.V
+    p = B.nd_params_init(num_steps=steps, roots_per_sample=R) if R > 1 else B.nd_params_init(num_steps=steps)
+    lens, ws = B.nd_sample_query(dg, app, p, S * R)
+    assert ws <= B.ND_STATIC_SCRATCH_BYTES
+    flat = torch.empty((steps, S), dtype=torch.int32, device="cuda:0")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    out = [flat[i] for i in range(steps)]
+    r = torch.as_tensor(roots, device="cuda:0")
+    B.nd_sample_static(dg, app, p, r, 21, out, status)
+    torch.cuda.synchronize()
+    assert int(status) == 1
+    clean = roots.copy()
+    clean[[5, S * R - 2]] = -1
+    for a, n in ((0, 200), (S // 2, 200), (S - 200, 200)):
+        part = clean[a * R:(a + n) * R]
+        want = (oracle.multirw(og, part, R, steps, seed=21, sample_id_base=a) if R > 1
+                else oracle.deepwalk(og, part, steps, seed=21, sample_id_base=a))
+        assert np.array_equal(flat[:, a:a + n].cpu().numpy(), np.stack(list(want)))
+    if R == 1:
+        workspace = torch.empty(ws, dtype=torch.uint8, device="cuda:0")
+        B.nd_sample(dg, app, p, r, 21, out, workspace)
+        live = B.nd_sample_stats(workspace, steps)[:, 0]
+        assert live[0] == S - 2 and live[1:].tolist() == (flat[:-1] >= 0).sum(dim=1).tolist()
+        with pytest.raises(B.NdError):
+            B.nd_sample_status(workspace)
+
+
+@pytest.mark.parametrize("per,fanout,S", [(1, [1], 1), (64, [512], 513), (64, [513, 7], 512), (3, [513, 600], 513),
+                                          (512, [4096, 512], 2), (4096, [9, 4096], 2), (2, [3], 16_500)])
+def test_layer(graph, per, fanout, S):
+    g, dg, og = graph
+    roots = _roots(g.V, per * S, 7)
+    for weighted in ((0, 1) if g.weights is not None else (0,)):
+        want = oracle.layer(og, roots, per, fanout, seed=14, use_weights=bool(weighted))
+        got, _ = gpu_sample(dg, B.ND_LAYER, roots, 14, num_steps=len(fanout), fanout=fanout, roots_per_sample=per,
+                            use_weights=weighted)
+        assert_steps_equal(got, want, f"layer per={per} {fanout} weighted={weighted}")
