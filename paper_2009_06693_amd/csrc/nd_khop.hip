@@ -188,13 +188,15 @@ struct UniqueFusedArgs {
     uint64_t o_flags, o_parts;
 };
 
-// Bytes of LDS per group.
+// Bytes of LDS per group: a multiple of 16, so that the hash table of a workgroup's second group lies as the
+// first one's does (it is cleared 16 bytes at a time; an even number of rows lies before it).
 __host__ __device__ inline uint32_t unique_group_bytes(uint32_t slots, uint32_t rows) {
-    return 2u * slots * 4u      // hash table: a slot per bucket, two buckets per slot
-           + slots * 4u         // the hop's vertices
-           + slots * 4u         // two queues of open slots, 16 bits per entry
-           + rows * 4u          // per parent: distinct vertices its slots hold
-           + 2u * rows * 8u;    // rows of this hop's parents and of the next hop's
+    const uint32_t bytes = 2u * slots * 4u      // hash table: a slot per bucket, two buckets per slot
+                           + slots * 4u         // the hop's vertices
+                           + slots * 4u         // two queues of open slots, 16 bits per entry
+                           + rows * 4u          // per parent: distinct vertices its slots hold
+                           + 2u * rows * 8u;    // rows of this hop's parents and of the next hop's
+    return (bytes + 15u) & ~15u;
 }
 
 template <int STRIDE, typename OffT, int THREADS, int PER>
