@@ -100,14 +100,6 @@ __global__ __launch_bounds__(256) void check_rows_kernel(const OffT* __restrict_
     if (bad) atomicOr(flags, bad);
 }
 
-// ceil(c * 2^64 / T) for 0 <= c < T < 2^39: long division, 24 + 24 + 16 bits at a time.
-__device__ __forceinline__ uint64_t scaled_threshold(uint64_t c, uint64_t T) {
-    const uint64_t n1 = c << 24, q1 = n1 / T, r1 = n1 - q1 * T;
-    const uint64_t n2 = r1 << 24, q2 = n2 / T, r2 = n2 - q2 * T;
-    const uint64_t n3 = r2 << 16, q3 = n3 / T, r3 = n3 - q3 * T;
-    return (q1 << 40) + (q2 << 16) + q3 + (r3 != 0 ? 1u : 0u);  // below 2^64: c < T
-}
-
 // The row that holds entry e: the last one that starts at or before it, among rows [lo, hi].
 template <typename OffT>
 __device__ __forceinline__ int64_t row_of(const OffT* __restrict__ off, int64_t e, int64_t lo, int64_t hi) {

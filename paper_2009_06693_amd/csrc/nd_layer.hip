@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kLayerThreads) void layer_kernel(GraphView<OffT> g,
 // by; a call with a few samples is a chain of dependent fetches, and what counts there is their number.
 // Inside a weighted row the guide table (WeightLink) starts the search, where a binary search over the
 // running sums is one fetch per level: 257 samples of [512, 512] over 2.9 M vertices, symmetric weights,
-// took 31 us with a launch per step and the binary search.
+// took 37 us with a launch per step and the binary search, 30.9 us like this.
 struct LayerFusedArgs {
     const Link* links;
     uint64_t seed;
@@ -157,35 +157,34 @@ __device__ __forceinline__ uint64_t column_weight(uint32_t deg) {
     return (uint64_t)(281474976710656.0 / ((double)deg * (double)deg));
 }
 
-// First entry of a row (links from `row`, running sums from `cum`) whose running sum exceeds rest < total.
-// The guide of a cell at or below the one that rest lies in names an entry at or before it; the estimate
-// of the cell is lowered by more than its rounding error.  Two looks at four entries find nearly every
-// entry; a cell with more of them (many light entries beside heavy ones) is searched by halves.
-__device__ __forceinline__ uint32_t guided_search(const Link* row, const uint64_t* cum, uint32_t deg, uint64_t rest,
-                                                  uint64_t total) {
-    if (deg < 2u) return 0u;
-    const double f = (double)rest / (double)total * (1.0 - 0x1p-48);
-    const uint32_t cell = mulhi32((uint32_t)(f * 4294967296.0), deg);
-    uint32_t j = reinterpret_cast<const WeightLink*>(row)[2ull * cell + 1u].guide;
-    const uint32_t last = deg - 1u;
-    for (int look = 0; look < 2; ++look) {
-        uint64_t c[4];
-#pragma unroll
-        for (uint32_t i = 0; i < 4u; ++i) c[i] = cum[j + i < last ? j + i : last];
-        uint32_t skip = 0;
-#pragma unroll
-        for (uint32_t i = 0; i < 4u; ++i) skip += c[i] <= rest ? 1u : 0u;  // running sums do not fall
-        if (j + skip > last) return last;
-        j += skip;
-        if (skip < 4u) return j;
+// The link of the first entry of a row whose running sum exceeds rest < total.  ceil(rest * 2^64 / total) is a
+// word that a draw over this row alone would turn into `rest`, so the row's own thresholds answer in its place:
+// thr rises with the running sum (2^64 / total exceeds 2^25, so different sums have different thresholds), and
+// the guide of the word's cell names an entry at or before the one looked for.  The links come with the
+// thresholds, two entries at a time; a cell with more than a few entries (many light ones beside heavy ones) is
+// searched by halves.  It looks at nothing but the row's links: over the running sums, four at a time, and the
+// link or column after them, a draw was three dependent fetches and a third array: 257 samples of [512, 512] over
+// 2.9 M vertices took 31.4 us, 97 on a graph not looked at before; now 30.9 and 76.
+__device__ __forceinline__ Link guided_search(const Link* row, uint32_t deg, uint64_t rest, uint64_t total) {
+    const uint64_t word = scaled_threshold(rest, total);
+    const WeightLink* weights = reinterpret_cast<const WeightLink*>(row);
+    uint32_t j = deg > 1u ? weights[2ull * mulhi32((uint32_t)(word >> 32), deg) + 1u].guide : 0u;
+    for (int look = 0; look < 4; ++look) {
+        const uint32_t j1 = j + 1u < deg ? j + 1u : j;
+        const WeightLink w0 = weights[2ull * j + 1u], w1 = weights[2ull * j1 + 1u];
+        const Link l0 = row[2ull * j], l1 = row[2ull * j1];
+        if (word < w0.thr || w0.always() || j1 == j) return l0;
+        if (word < w1.thr || w1.always() || j1 + 1u == deg) return l1;
+        j = j1 + 1u;
     }
-    uint32_t lo = j, hi = last;
+    uint32_t lo = j, hi = deg - 1u;
     while (lo < hi) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (cum[mid] > rest) hi = mid;
+        const WeightLink w = weights[2ull * mid + 1u];
+        if (word < w.thr || w.always()) hi = mid;
         else lo = mid + 1u;
     }
-    return lo;
+    return row[2ull * lo];
 }
 
 template <typename OffT, bool WEIGHTED, int STRIDE, int THREADS>
@@ -245,17 +244,19 @@ __global__ __launch_bounds__(THREADS) void layer_fused_kernel(GraphView<OffT> g,
                     }
                     const uint64_t before = lo ? s_incl[lo - 1u] : 0ull;
                     const uint2 row = rows[lo];
-                    uint64_t e = row.x;
-                    if (WEIGHTED)
-                        e += guided_search(a.links + 2ull * row.x, g.cumq + row.x, row.y, x - before, s_incl[lo] - before);
-                    else
-                        e += div_small_quotient(x - before, column_weight(row.y));
-                    if (last) {
-                        res = g.col[e];
-                    } else {
-                        const Link l = a.links[e * STRIDE];
+                    if (WEIGHTED) {
+                        const Link l = guided_search(a.links + 2ull * row.x, row.y, x - before, s_incl[lo] - before);
                         res = l.v;
                         row_out = make_uint2(l.rs, l.deg);
+                    } else {
+                        const uint64_t e = row.x + div_small_quotient(x - before, column_weight(row.y));
+                        if (last) {
+                            res = g.col[e];
+                        } else {
+                            const Link l = a.links[e * STRIDE];
+                            res = l.v;
+                            row_out = make_uint2(l.rs, l.deg);
+                        }
                     }
                 }
                 out[j] = res;

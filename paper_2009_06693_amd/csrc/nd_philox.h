@@ -45,6 +45,31 @@ __device__ __forceinline__ uint32_t mulhi32(uint32_t a, uint32_t b) { return __u
 __device__ __forceinline__ uint64_t mulhi64(uint64_t a, uint64_t b) { return __umul64hi(a, b); }
 __device__ __forceinline__ uint64_t cat64(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
 
+// n / T and the remainder for n < 2^24 T, n < 2^63, T < 2^39, inv = 1 / T rounded: the product is within
+// 2^-27 of the quotient, so its whole part is off by at most one.
+__device__ __forceinline__ uint32_t divide_step(uint64_t n, uint64_t T, double inv, uint64_t* rest) {
+    uint32_t q = (uint32_t)((double)n * inv);
+    int64_t r = (int64_t)(n - (uint64_t)q * T);
+    if (r < 0) {
+        --q;
+        r += (int64_t)T;
+    } else if (r >= (int64_t)T) {
+        ++q;
+        r -= (int64_t)T;
+    }
+    *rest = (uint64_t)r;
+    return q;
+}
+// ceil(c * 2^64 / T) for 0 <= c < T < 2^39: long division, 24 + 24 + 16 bits at a time.
+__device__ __forceinline__ uint64_t scaled_threshold(uint64_t c, uint64_t T) {
+    const double inv = 1.0 / (double)T;
+    uint64_t r;
+    const uint64_t q1 = divide_step(c << 24, T, inv, &r);
+    const uint64_t q2 = divide_step(r << 24, T, inv, &r);
+    const uint64_t q3 = divide_step(r << 16, T, inv, &r);
+    return (q1 << 40) + (q2 << 16) + q3 + (r != 0 ? 1u : 0u);  // below 2^64: c < T
+}
+
 __device__ __forceinline__ uint32_t fastdiv(uint32_t n, const FastDiv& f) {
     return f.d == 1 ? n : (__umulhi(n, f.magic) >> f.shift);
 }

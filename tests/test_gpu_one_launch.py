@@ -183,3 +183,22 @@ def test_layer(graph, per, fanout, S):
         got, _ = gpu_sample(dg, B.ND_LAYER, roots, 14, num_steps=len(fanout), fanout=fanout, roots_per_sample=per,
                             use_weights=weighted)
         assert_steps_equal(got, want, f"layer per={per} {fanout} weighted={weighted}")
+
+
+@pytest.mark.parametrize("heavy_first", [False, True])
+def test_layer_rows_whose_guide_cells_hold_many_entries(heavy_first):
+    """A few heavy entries beside hundreds of light ones: all light ones of a stretch fall into one or two cells
+    of the row's guide table, so the search inside the row goes on by halves."""
+    V = 900
+    pairs = [(a, b) for a in range(V) for b in range(0, V, 1 if a < 8 else 90)]
+    w = np.full(len(pairs), 0.5, np.float32)
+    w[np.arange(len(pairs)) % 450 == (0 if heavy_first else 449)] = 3000.0
+    g = inputs.from_edges(V, pairs, weights=w, int64_offsets=heavy_first)
+    dg, og = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights), \
+        oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    roots = np.arange(40, dtype=np.int32) % 8
+    want = oracle.layer(og, roots, 4, [2000, 700], seed=3, use_weights=True)
+    light = np.asarray(want[0]) % 450 != (0 if heavy_first else 449)
+    assert light.sum() > 100   # some draws do end among the light entries
+    got, _ = gpu_sample(dg, B.ND_LAYER, roots, 3, num_steps=2, fanout=[2000, 700], roots_per_sample=4, use_weights=1)
+    assert_steps_equal(got, want, f"heavy_first={heavy_first}")
