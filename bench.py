@@ -27,11 +27,8 @@ HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per launch of the dominant kernel from two rocprofv3 --pmc runs of this file
 # (FETCH_SIZE, then WRITE_SIZE; scaled by the factors the copy kernel of `--workload copy_calib`
-# gives: x2.0 and x1.0), averaged over the launches of one call.  Sources: the counter tables in
-# profiles/c5_khop_tp_rocprofv3.md and profiles/c5_deepwalk_tp_rocprofv3.md.  None where not profiled.
+# gives: x2.0 and x1.0), averaged over the launches of one call.  None where not profiled.
 MEASURED_TRAFFIC_BYTES = {
-    ("c5_khop", "tp", "sample_sub"): 3162426811,        # 1,337.6 MiB fetched + 1,678.4 MiB written per launch
-    ("c5_deepwalk", "tp", "walk_window"): 52888034690,  # 48,813.0 MiB fetched + 1,625.0 MiB written per launch
 }
 
 WORKLOADS = {
@@ -260,7 +257,8 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
     stats = s.stats() if (mode == B.ND_MODE_TRANSIT_PARALLEL and app != B.ND_LAYER) else None
     phase_ms = {k: v[0] / args.steps for k, v in phases.items() if v[1] > 0}
     launches = {k: v[1] / args.steps for k, v in phases.items() if v[1] > 0}
-    kernel_phases = [k for k in ("sample_sub", "walk_window", "sample_sp", "layer", "sample_wg") if k in phase_ms]
+    kernel_phases = [k for k in ("sample_sub", "walk_window", "sample_sp", "layer", "sample_wg", "unique")
+                     if k in phase_ms and (k != "unique" or "sample_sub" not in phase_ms)]
     dom = max(kernel_phases, key=lambda k: phase_ms[k])
     avg_launch_ms = phase_ms[dom] / launches[dom]
     off_bytes = 16.0 if g.row_offsets.dtype.itemsize == 8 else 8.0        # the two row offsets of a transit
@@ -278,7 +276,21 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
     #     sums (log2 of the mean degree probes), node2vec 4 + 4 log2(mean degree) per membership test.
     #   sample-parallel: per output entry 4, per non-NULL one 4, per parent slot 4 + (if live) two offsets.
     #   layer: per sample and transit slot 4 + two row offsets, per draw 4 + 4.
-    if dom in ("sample_sub", "sample_wg") and stats is not None:
+    #   one launch over the graph's links (walks, k-hop, layer; nothing is grouped, so no distinct
+    #     transits are counted): per root 4 + two row offsets, per output entry 4, per non-NULL draw a
+    #     16-byte link, or 4 (adjacency entry) in the last hop of k-hop and layer; a weighted draw reads
+    #     16 more of its row's guide and thresholds, a node2vec draw 16 of a membership table.
+    links = "init" not in phase_ms  # its kernel writes the header itself
+    if links:
+        draws = live
+        per_draw = [16.0] * n_steps
+        if app in (B.ND_KHOP, B.ND_LAYER):
+            per_draw[-1] = 4.0
+        if pkw.get("use_weights", 0) or app == B.ND_NODE2VEC:
+            per_draw = [x + 16.0 for x in per_draw]
+        total_bytes = (4.0 + off_bytes) * int(roots.numel()) + sum(
+            4.0 * s.step_len[i] + per_draw[i] * live_per_step[i] for i in range(n_steps))
+    elif dom in ("sample_sub", "sample_wg") and stats is not None:
         draws = sum(int(stats[i, 0]) * m_per_step[i] for i in range(n_steps))
         total_bytes = sum(8.0 * int(stats[i, 0]) + off_bytes * int(stats[i, 1]) + 4.0 * live_per_step[i]
                           + 4.0 * int(stats[i, 0]) * m_per_step[i] for i in range(n_steps))
@@ -306,10 +318,16 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
         total_bytes = n_samples * sum(n * (4.0 + off_bytes) for n in n_prev) + 8.0 * live
     alg_per_launch = total_bytes / launches[dom]
     hbm_gbs = alg_per_launch / (avg_launch_ms * 1e-3) / 1e9
-    traffic = MEASURED_TRAFFIC_BYTES.get((name, args.mode, dom))
+    if links:
+        kernel = {"sample_sub": "khop_fused_kernel", "unique": "khop_unique_kernel", "layer": "layer_fused_kernel",
+                  "walk_window": {B.ND_NODE2VEC: "walk_free_n2v_kernel",
+                                  B.ND_MULTIRW: "mrw_free_kernel"}.get(app, "walk_free_kernel")}[dom]
+    else:
+        kernel = {"sample_sub": "sample_tp_kernel", "sample_sp": "sample_sp_kernel", "layer": "layer_kernel",
+                  "sample_wg": "sample_tp_kernel", "walk_window": "walk_window_kernel"}[dom]
+    traffic = MEASURED_TRAFFIC_BYTES.get((name, kernel))
     roofline = {
-        "kernel": {"sample_sub": "sample_tp_kernel", "sample_sp": "sample_sp_kernel", "layer": "layer_kernel",
-                   "sample_wg": "sample_tp_kernel", "walk_window": "walk_window_kernel"}[dom],
+        "kernel": kernel,
         "bound": "hbm", "achieved": round(hbm_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(hbm_gbs / HBM_PEAK_GBS, 4),
         "traffic": traffic,
