@@ -27,8 +27,11 @@ HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per launch of the dominant kernel from two rocprofv3 --pmc runs of this file
 # (FETCH_SIZE, then WRITE_SIZE; scaled by the factors the copy kernel of `--workload copy_calib`
-# gives: x2.0 and x1.0), averaged over the launches of one call.  None where not profiled.
+# gives: x2.0 and x1.0), averaged over the launches of one call.  Source: the counter table in
+# profiles/one_launch_routes_rocprofv3.md.  None where not profiled.
 MEASURED_TRAFFIC_BYTES = {
+    ("c5_khop", "khop_fused_kernel"): 22265146368,     # 17,194,038 KiB fetched + 4,549,269 KiB written
+    ("c5_deepwalk", "walk_free_kernel"): 29931946240,  # 27,583,722 KiB fetched + 1,645,913 KiB written
 }
 
 WORKLOADS = {
