@@ -31,7 +31,7 @@ HBM_PEAK_GBS = 8000.0
 # profiles/one_launch_routes_rocprofv3.md.  None where not profiled.
 MEASURED_TRAFFIC_BYTES = {
     ("c5_khop", "khop_fused_kernel"): 22265146368,     # 17,194,038 KiB fetched + 4,549,269 KiB written
-    ("c5_deepwalk", "walk_free_kernel"): 29931946240,  # 27,583,722 KiB fetched + 1,645,913 KiB written
+    ("c5_deepwalk", "walk_free_kernel"): 29931146240,  # 27,583,722 KiB fetched + 1,645,913 KiB written
 }
 
 WORKLOADS = {
