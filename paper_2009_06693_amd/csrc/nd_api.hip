@@ -228,7 +228,9 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
         if (hb > pl->hist_bytes) pl->hist_bytes = hb;
     }
     pl->layer_fused = app == ND_LAYER && g.links != nullptr;
+    // a call without samples draws nothing, and its fanouts have no bound that a shape could be made from
     pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
+                pl->S > 0 &&
                 (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
                                       : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
     return ND_OK;

@@ -657,6 +657,7 @@ UniqueShape unique_shape(const Graph& gr, const int32_t* fanout, int32_t k, int6
 constexpr size_t kUniqueLdsMost = 128 << 10;
 }  // namespace
 
+// At most ND_MAX_UNIQUE_SLOTS slots per sample and hop (the call's plan has checked).
 bool khop_unique_fits(const Graph& gr, const int32_t* fanout, int32_t k) {
     return gr.links && unique_shape(gr, fanout, k, 1).lds <= kUniqueLdsMost;
 }

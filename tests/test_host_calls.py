@@ -1,0 +1,42 @@
+"""What calls do on the host - argument checks, plans, sizes, the kernels they launch - without a GPU:
+the library runs against stand-ins for the HIP functions (host_calls.c) and no kernel executes."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2009_06693_amd import binding as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host") / "host_calls")
+    lib = os.path.abspath(B.LIB_PATH)
+    subprocess.run(["gcc", "-O1", "-Wall", "-rdynamic", os.path.join(HERE, "host_calls.c"), lib, "-o", exe,
+                    f"-Wl,-rpath,{os.path.dirname(lib)}", "-Wl,--allow-shlib-undefined"], check=True)
+
+    def run(app, num_roots, V=1000, E=4000, weighted=0, free_bytes=0, **params):
+        args = [str(x) for x in (V, E, weighted, free_bytes, app, num_roots)]
+        args += [f"{k}={','.join(map(str, v)) if isinstance(v, (list, tuple)) else v}" for k, v in params.items()]
+        r = subprocess.run([exe, *args], capture_output=True, text=True)
+        assert r.returncode == 0, (args, r.returncode, r.stdout, r.stderr)
+        got = {"launches": []}
+        for line in r.stdout.splitlines():
+            what, *rest = line.split()
+            if what == "launch":
+                got["launches"].append(rest[0])
+            else:
+                got[what] = [int(x) for x in rest]
+        return got
+    return run
+
+
+@pytest.mark.parametrize("fanout", [[65536, 65536], [1 << 14, 1 << 14], [1 << 20] * 3])
+def test_a_call_without_roots_returns_whatever_the_fanouts(program, fanout):
+    """No samples, hence no limit on the slots of one: the calls return, launch no sampling and ask for little."""
+    got = program(B.ND_KHOP, 0, fanout=fanout, unique_rounds=2)
+    assert got["query"][0] == 0 and got["query"][1] < 1 << 20 and got["query"][2] == len(fanout)
+    assert got["static"] == [0]
+    assert not any("khop" in k or "sample" in k for k in got["launches"])
