@@ -18,6 +18,7 @@
 #include "nd_common.h"
 #include "nd_philox.h"
 #include "nd_sample.h"
+#include "nd_draw.h"
 #include "nd_wave.h"
 
 namespace nd {
@@ -159,32 +160,12 @@ __device__ __forceinline__ uint64_t column_weight(uint32_t deg) {
 
 // The link of the first entry of a row whose running sum exceeds rest < total.  ceil(rest * 2^64 / total) is a
 // word that a draw over this row alone would turn into `rest`, so the row's own thresholds answer in its place:
-// thr rises with the running sum (2^64 / total exceeds 2^25, so different sums have different thresholds), and
-// the guide of the word's cell names an entry at or before the one looked for.  The links come with the
-// thresholds, two entries at a time; a cell with more than a few entries (many light ones beside heavy ones) is
-// searched by halves.  It looks at nothing but the row's links: over the running sums, four at a time, and the
-// link or column after them, a draw was three dependent fetches and a third array: 257 samples of [512, 512] over
-// 2.9 M vertices took 31.4 us, 97 on a graph not looked at before; now 30.9 and 76.
+// thr rises with the running sum (2^64 / total exceeds 2^25, so different sums have different thresholds).  It
+// looks at nothing but the row's links: over the running sums, four at a time, and the link or column after
+// them, a draw was three dependent fetches and a third array: 257 samples of [512, 512] over 2.9 M vertices took
+// 31.4 us, 97 on a graph not looked at before; now 30.9 and 76.
 __device__ __forceinline__ Link guided_search(const Link* row, uint32_t deg, uint64_t rest, uint64_t total) {
-    const uint64_t word = scaled_threshold(rest, total);
-    const WeightLink* weights = reinterpret_cast<const WeightLink*>(row);
-    uint32_t j = deg > 1u ? weights[2ull * mulhi32((uint32_t)(word >> 32), deg) + 1u].guide : 0u;
-    for (int look = 0; look < 4; ++look) {
-        const uint32_t j1 = j + 1u < deg ? j + 1u : j;
-        const WeightLink w0 = weights[2ull * j + 1u], w1 = weights[2ull * j1 + 1u];
-        const Link l0 = row[2ull * j], l1 = row[2ull * j1];
-        if (word < w0.thr || w0.always() || j1 == j) return l0;
-        if (word < w1.thr || w1.always() || j1 + 1u == deg) return l1;
-        j = j1 + 1u;
-    }
-    uint32_t lo = j, hi = deg - 1u;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        const WeightLink w = weights[2ull * mid + 1u];
-        if (word < w.thr || w.always()) hi = mid;
-        else lo = mid + 1u;
-    }
-    return row[2ull * lo];
+    return drawn_link(row, deg, scaled_threshold(rest, total));
 }
 
 template <typename OffT, bool WEIGHTED, int STRIDE, int THREADS>

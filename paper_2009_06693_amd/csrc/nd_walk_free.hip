@@ -111,29 +111,8 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
         l.rs = 0;
         l.deg = 0;
         if (draws) {
-            const uint32_t i = mulhi32(r.r0, deg);
-            if (DRAW == kDrawUniform) {
-                l = a.links[(uint64_t)(rs + i) * STRIDE];
-            } else {
-                const Link* row = a.links + (uint64_t)rs * 2u;
-                const uint64_t R = cat64(r.r0, r.r1);
-                uint32_t j = reinterpret_cast<const WeightLink*>(row)[2u * i + 1u].guide;
-                for (;; ++j) {  // ends at the row's last entry; two entries are on their way at a time
-                    const uint32_t j1 = j + 1u < deg ? j + 1u : j;
-                    const WeightLink w0 = reinterpret_cast<const WeightLink*>(row)[2u * j + 1u];
-                    const WeightLink w1 = reinterpret_cast<const WeightLink*>(row)[2u * j1 + 1u];
-                    const Link l0 = row[2u * j], l1 = row[2u * j1];
-                    if (R < w0.thr || w0.always() || j == j1) {
-                        l = l0;
-                        break;
-                    }
-                    if (R < w1.thr || w1.always() || j1 + 1u == deg) {
-                        l = l1;
-                        break;
-                    }
-                    j = j1;
-                }
-            }
+            if (DRAW == kDrawUniform) l = a.links[(uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE];
+            else l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r.r0, r.r1));
         }
         // the next step's word does not wait for the link
         r = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);

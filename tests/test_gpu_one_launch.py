@@ -202,3 +202,38 @@ def test_layer_rows_whose_guide_cells_hold_many_entries(heavy_first):
     assert light.sum() > 100   # some draws do end among the light entries
     got, _ = gpu_sample(dg, B.ND_LAYER, roots, 3, num_steps=2, fanout=[2000, 700], roots_per_sample=4, use_weights=1)
     assert_steps_equal(got, want, f"heavy_first={heavy_first}")
+
+
+@pytest.mark.parametrize("heavy_first", [False, True])
+def test_weighted_walks_where_one_entry_outweighs_a_long_row(heavy_first):
+    """A hub whose light entries all fall into two cells of its row's guide table: a draw that ends among them takes
+    the looks of a search by halves, not one look per light entry (14,000 of them: milliseconds, where the whole
+    call takes a tenth of one), so the call takes about as long as with equal weights."""
+    V, S, steps = 20_001, 65_536, 8
+    pairs = [(0, b) for b in range(1, V)] + [(a, 0) for a in range(1, V)]
+    heavy = 0 if heavy_first else V - 2
+    w = np.ones(len(pairs), np.float32)
+    w[:V - 1] = 1e-4
+    w[heavy] = 30_000.0
+    g = inputs.from_edges(V, pairs, weights=w)
+    og = oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    roots = np.zeros(S, np.int32)
+    want = oracle.deepwalk(og, roots, steps, seed=19, use_weights=True)
+    assert sum((np.asarray(want[i]) != heavy + 1).sum() for i in range(0, steps, 2)) > 5  # light entries are drawn
+    times = []
+    for weights in (np.ones_like(w), g.weights):
+        dg = B.nd_graph_create(g.row_offsets, g.col_indices, weights)
+        s = B.Sampler(dg, B.ND_DEEPWALK, B.nd_params_init(num_steps=steps, use_weights=1), S)
+        r = torch.as_tensor(roots, device="cuda:0")
+        s.run(r, 19)
+        marks = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+        for m in marks:
+            m.record()
+            out = s.run(r, 19)
+        torch.cuda.synchronize()
+        times.append(min(a.elapsed_time(b) for a, b in zip(marks, marks[1:])))
+    assert_steps_equal([o.cpu().numpy() for o in out], list(want), f"heavy_first={heavy_first}")
+    got, _ = gpu_sample(dg, B.ND_PPR, roots, 20, num_steps=steps, use_weights=1, term_prob=0.02)
+    assert_steps_equal(got, list(oracle.ppr(og, roots, steps, 0.02, seed=20, use_weights=True)), "ppr")
+    print(f"[times] equal weights {times[0]:.4f} ms, one heavy entry {times[1]:.4f} ms", flush=True)
+    assert times[1] < 8.0 * times[0] + 0.05  # 0.0129 and 0.0154 ms; entry by entry 2.4 ms
