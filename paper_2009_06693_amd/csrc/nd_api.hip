@@ -360,6 +360,22 @@ void set_error(const char* fmt, ...) {
     va_end(ap);
 }
 
+// What the workgroups of a call left in its workspace, read in pieces (a walk's counters are up to 24 MB) and
+// without allocating: use(word) for each of the n words at byte `at`, in order.  Waits for the stream.
+template <typename F>
+static int read_back(const void* workspace_dev, uint64_t at, uint64_t n, hipStream_t stream, F use) {
+    constexpr uint64_t kPiece = 65536;
+    static thread_local uint32_t piece[kPiece];
+    for (uint64_t first = 0; first < n; first += kPiece) {
+        const uint64_t m = n - first < kPiece ? n - first : kPiece;
+        ND_HIP_CHECK(hipMemcpyAsync(piece, (const char*)workspace_dev + at + first * 4, m * 4, hipMemcpyDeviceToHost,
+                                    stream));
+        ND_HIP_CHECK(hipStreamSynchronize(stream));
+        for (uint64_t i = 0; i < m; ++i) use(piece[i]);
+    }
+    return ND_OK;
+}
+
 }  // namespace nd
 
 using namespace nd;
@@ -839,12 +855,10 @@ int nd_sample_status(const void* workspace_dev, void* hip_stream) {
     ND_HIP_CHECK(hipMemcpyAsync(&hdr, workspace_dev, sizeof(hdr), hipMemcpyDeviceToHost, (hipStream_t)hip_stream));
     ND_HIP_CHECK(hipStreamSynchronize((hipStream_t)hip_stream));
     uint32_t status = hdr.status;
-    if (hdr.n_groups > 0) {
-        std::vector<uint32_t> flags(hdr.n_groups);
-        ND_HIP_CHECK(hipMemcpyAsync(flags.data(), (const char*)workspace_dev + hdr.o_flags, flags.size() * 4,
-                                    hipMemcpyDeviceToHost, (hipStream_t)hip_stream));
-        ND_HIP_CHECK(hipStreamSynchronize((hipStream_t)hip_stream));
-        for (uint32_t f : flags) status |= f;
+    if (hdr.n_groups > 0 && hdr.mark == kGroupsMark) {
+        const int rc = read_back(workspace_dev, hdr.o_flags, hdr.n_groups, (hipStream_t)hip_stream,
+                                 [&](uint32_t flag) { status |= flag; });
+        if (rc != ND_OK) return rc;
     }
     if (status & 1u) {
         set_error("a root was outside [0, V); it was treated as NULL");
@@ -869,17 +883,18 @@ int nd_sample_stats(const void* workspace_dev, void* hip_stream, int32_t max_ste
     int n = (int)hdr.num_steps < max_steps ? (int)hdr.num_steps : max_steps;
     if (n > ND_MAX_WALK_STEPS) n = ND_MAX_WALK_STEPS;
     static thread_local StepCtl host_ctl[ND_MAX_WALK_STEPS];
-    if (hdr.n_groups > 0 && hdr.o_parts == 0) {  // layer sampling has no pairs to count
+    const bool groups = hdr.n_groups > 0 && hdr.mark == kGroupsMark;
+    if (groups && hdr.o_parts == 0) {  // layer sampling has no pairs to count
         n = 0;
-    } else if (n > 0 && hdr.n_groups > 0) {  // only the live pairs are counted on these routes
-        std::vector<uint32_t> parts((size_t)hdr.n_groups * hdr.num_steps);
-        ND_HIP_CHECK(hipMemcpyAsync(parts.data(), (const char*)workspace_dev + hdr.o_parts, parts.size() * 4,
-                                    hipMemcpyDeviceToHost, stream));
-        ND_HIP_CHECK(hipStreamSynchronize(stream));
-        for (int i = 0; i < n; ++i) {
-            host_ctl[i] = StepCtl{};
-            for (uint32_t b = 0; b < hdr.n_groups; ++b) host_ctl[i].P += parts[(size_t)b * hdr.num_steps + (size_t)i];
-        }
+    } else if (n > 0 && groups) {  // only the live pairs are counted on these routes
+        for (int i = 0; i < n; ++i) host_ctl[i] = StepCtl{};
+        uint32_t step = 0;
+        const int rc = read_back(workspace_dev, hdr.o_parts, (uint64_t)hdr.n_groups * hdr.num_steps, stream,
+                                 [&](uint32_t pairs) {
+                                     if (step < (uint32_t)n) host_ctl[step].P += pairs;
+                                     step = step + 1u < hdr.num_steps ? step + 1u : 0u;
+                                 });
+        if (rc != ND_OK) return rc;
     } else if (n > 0) {
         ND_HIP_CHECK(hipMemcpyAsync(host_ctl, (const char*)workspace_dev + sizeof(WsHeader),
                                     sizeof(StepCtl) * (size_t)n, hipMemcpyDeviceToHost, stream));

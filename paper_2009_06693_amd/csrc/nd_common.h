@@ -167,17 +167,20 @@ struct WsHeader {
     // Routes that need no kernel to clear counters: every workgroup writes what it found to places of
     // its own, and whoever asks (nd_sample_status, nd_sample_stats) adds up.  0 groups: not that route.
     uint32_t n_groups;
-    uint32_t pad0;
+    uint32_t mark;          // kGroupsMark where the four fields beside it are this library's: a workspace that no
+                            // call has written to holds whatever it held
     uint64_t o_flags;       // n_groups words: a root was out of range
     uint64_t o_parts;       // [n_groups][num_steps] words: live pairs
     uint32_t pad[56];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
+constexpr uint32_t kGroupsMark = 0x6E645753u;
 __device__ __forceinline__ void write_header(WsHeader* h, uint32_t num_steps, uint32_t n_groups, uint64_t o_flags,
                                              uint64_t o_parts) {
     h->status = 0;
     h->num_steps = num_steps;
     h->n_groups = n_groups;
+    h->mark = kGroupsMark;
     h->o_flags = o_flags;
     h->o_parts = o_parts;
 }

@@ -12,8 +12,9 @@
  *   static RC
  *   launch KERNEL          (one line per launch, of the sampling call only)
  *   allocated BYTES        (live when the program ends, before the graph is destroyed)
- * Names: the fields of nd_params, fanout as a,b,c; and fail_malloc=N (the first N allocations of the
- * query fail).  A call that does not return within 20 seconds ends the program with SIGALRM. */
+ * Names: the fields of nd_params, fanout as a,b,c; fail_malloc=N (the first N allocations of the query
+ * fail); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
+ * and prints "unused STATS_RC STATUS_RC").  A call that does not return within 20 seconds ends the program with SIGALRM. */
 #define _GNU_SOURCE
 #include <stdio.h>
 #include <stdlib.h>
@@ -113,7 +114,7 @@ int main(int argc, char** argv) {
     free_limit = (size_t)atoll(argv[4]);
     nd_params p;
     nd_params_init(&p);
-    int fail = 0;
+    int fail = 0, unused = -1;
     for (int i = 7; i < argc; ++i) {
         char* eq = strchr(argv[i], '=');
         if (!eq) return 2;
@@ -129,6 +130,7 @@ int main(int argc, char** argv) {
         else if (!strcmp(n, "sched_window")) p.sched_window = atoi(v);
         else if (!strcmp(n, "mode")) p.mode = atoi(v);
         else if (!strcmp(n, "use_weights")) p.use_weights = atoi(v);
+        else if (!strcmp(n, "unused")) unused = atoi(v);
         else if (!strcmp(n, "fail_malloc")) fail = atoi(v);
         else return 2;
     }
@@ -149,6 +151,14 @@ int main(int argc, char** argv) {
     trace = 1;
     printf("static %d\n", nd_sample_static(g, app, &p, any, roots, 1, out, any, NULL));
     trace = 0;
+    if (unused >= 0) {
+        const size_t n = 1 << 20;
+        char* bytes = reserve(n);
+        int64_t stats[4 * 8];
+        memset(bytes, unused, n);
+        const int stats_rc = nd_sample_stats(bytes, NULL, 4, stats);
+        printf("unused %d %d\n", stats_rc, nd_sample_status(bytes, NULL));
+    }
     printf("allocated %zu\n", live_bytes);
     nd_graph_destroy(g);
     return live_bytes == 0 ? 0 : 3;

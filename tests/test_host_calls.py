@@ -40,3 +40,9 @@ def test_a_call_without_roots_returns_whatever_the_fanouts(program, fanout):
     assert got["query"][0] == 0 and got["query"][1] < 1 << 20 and got["query"][2] == len(fanout)
     assert got["static"] == [0]
     assert not any("khop" in k or "sample" in k for k in got["launches"])
+
+
+@pytest.mark.parametrize("byte", [0, 0x7E, 0xFE])
+def test_status_and_statistics_of_a_workspace_that_no_call_has_used(program, byte):
+    """What lies there is not taken for places and numbers of words to fetch (no status bit is set in these bytes)."""
+    assert program(B.ND_KHOP, 10, fanout=[3], unused=byte)["unused"] == [0, 0]
