@@ -162,9 +162,10 @@ void nd_params_init(nd_params* p);
  * Copies a CSR graph into device memory owned by the library (Section 5.1:
  * the graph lives in GPU global memory) and, when weights are given, builds
  * what the paper's Vertex class offers (Section 4.1): per vertex the largest
- * edge weight and the running sums of its edge weights.  Where the device has
- * room (16 bytes per entry, 32 with weights; E < 2^31) every entry also gets a
- * link: its vertex together with the place of that vertex's row.  Weights are
+ * edge weight and the running sums of its edge weights.  Where they fit in a
+ * quarter of the device's free memory (16 bytes per entry, 32 with weights;
+ * E < 2^31) every entry also gets a link: its vertex together with the place of
+ * that vertex's row.  Weights are
  * quantised once to integers, w_q = floor(w * 2^16 + 0.5), and all later
  * arithmetic on them is integer.
  *

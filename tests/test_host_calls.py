@@ -46,3 +46,16 @@ def test_a_call_without_roots_returns_whatever_the_fanouts(program, fanout):
 def test_status_and_statistics_of_a_workspace_that_no_call_has_used(program, byte):
     """What lies there is not taken for places and numbers of words to fetch (no status bit is set in these bytes)."""
     assert program(B.ND_KHOP, 10, fanout=[3], unused=byte)["unused"] == [0, 0]
+
+
+@pytest.mark.parametrize("weighted", [0, 1])
+def test_links_are_taken_from_a_quarter_of_the_free_memory(program, weighted):
+    """The rest is left to the caller, who may have had room for a call's outputs and nothing else."""
+    V, E = 1000, 8_000_000
+    graph = (V + 1) * 8 + E * 4 + (E * 12 + V * 4 if weighted else 0)
+    links = E * (32 if weighted else 16)
+    during = graph + 256 + (E * 4 if weighted else 0)      # flags, and the weights as given
+    got = program(B.ND_DEEPWALK, 10, V=V, E=E, weighted=weighted, free_bytes=during + 4 * links, num_steps=2)
+    assert got["allocated"] == [graph + links] and any("walk_free" in k for k in got["launches"])
+    got = program(B.ND_DEEPWALK, 10, V=V, E=E, weighted=weighted, free_bytes=during + 4 * links - 1, num_steps=2)
+    assert got["allocated"] == [graph] and any("walk_window" in k for k in got["launches"])
