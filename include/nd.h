@@ -188,8 +188,8 @@ int nd_graph_create(nd_graph** out, int64_t V, int64_t E, const void* row_offset
 /*
  * Ends the life of the graph's device copy (Section 5.1: the graph stays in GPU
  * global memory for as long as samples are drawn from it; Section 6.4: one copy
- * per GPU).  Frees everything nd_graph_create allocated.  Accepts NULL.  No
- * nd_sample call on this graph may still be running.
+ * per GPU).  Frees everything nd_graph_create and nd_sample_query allocated for
+ * it.  Accepts NULL.  No nd_sample call on this graph may still be running.
  */
 int nd_graph_destroy(nd_graph* g);
 
@@ -211,6 +211,15 @@ int nd_graph_info(const nd_graph* g, int64_t* V, int64_t* E, int* has_weights,
  *                    Walks: S.  k-hop: S * fanout[0] * ... * fanout[i].
  *                    Layer: num_samples * fanout[i].
  *   workspace_bytes  out: device scratch nd_sample needs for these arguments
+ *
+ * Asked for node2vec on a graph with links for the first time, the call also
+ * builds what tells neighbours of the previous vertex from others: a membership
+ * table of every row (8 bytes per entry and 16 per vertex, where a quarter of
+ * the free device memory holds them), on the graph's device, and waits for it.
+ * The tables belong to the graph and serve every later node2vec call on it,
+ * nd_sample_static included.  Where nobody asked for sizes, or there was no
+ * room, node2vec searches the rows instead: same output, longer calls.  No
+ * other call of this function touches the device.
  */
 int nd_sample_query(const nd_graph* g, int app, const nd_params* params, int64_t num_roots,
                     int32_t* num_steps, int64_t* step_len, size_t* workspace_bytes);

@@ -70,10 +70,9 @@ struct Graph {
     // E links, each followed by its WeightLink on a weighted graph; null when E >= 2^31 or when the
     // device had no room for them (walks then take the window kernel)
     Link* links = nullptr;
-    // Membership table of every row (see RowSet): built when node2vec is first asked for
+    // Membership table of every row (see RowSet): built when the sizes of a node2vec call are first asked for
     mutable std::atomic<int32_t*> rowset{nullptr};
     mutable std::mutex rowset_mutex;
-    mutable bool rowset_failed = false;
 };
 void graph_need_rowset(const Graph& g);
 

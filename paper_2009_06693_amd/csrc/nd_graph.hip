@@ -337,42 +337,43 @@ int graph_create(Graph** out, int64_t V, int64_t E, const void* off, int off64, 
 
 void graph_destroy(Graph* g) { free_graph(g); }
 
-// Builds the rows' membership tables when they are not there yet: 8 bytes per entry, on a stream of
-// its own, so that it neither waits for the caller's work nor joins a stream capture.  Without room
-// for them node2vec searches the rows.
+// Builds the rows' membership tables when they are not there yet: 8 bytes per entry and 16 per vertex, on the
+// graph's device and a stream of its own, so that it neither waits for the caller's work nor joins a stream
+// capture.  Without room for them node2vec searches the rows; whoever asks next tries again.
 void graph_need_rowset(const Graph& g) {
     if (!g.links || g.rowset.load(std::memory_order_acquire)) return;
     std::lock_guard<std::mutex> lock(g.rowset_mutex);
-    if (g.rowset.load(std::memory_order_acquire) || g.rowset_failed) return;
-    int here = -1;
-    if (hipGetDevice(&here) != hipSuccess || here != g.device) return;  // not this graph's device: another time
+    if (g.rowset.load(std::memory_order_acquire)) return;
     hipStreamCaptureMode capture = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&capture);
-    int32_t* set = nullptr;
-    hipStream_t stream = nullptr;
-    const int64_t n = g.E / 2 + g.V + 1;
-    const dim3 grid((unsigned)((g.E + kLinkTile - 1) / kLinkTile));
-    bool ok = hipMalloc((void**)&set, (size_t)n * 16) == hipSuccess &&
-              hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess;
-    if (ok) {
-        hipLaunchKernelGGL(fill_empty_kernel, dim3((unsigned)g.num_cus * 32u), dim3(256), 0, stream, (int4*)set, n);
-        if (g.off64)
-            hipLaunchKernelGGL(build_rowset_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off, g.col,
-                               g.V, g.E, set);
-        else
-            hipLaunchKernelGGL(build_rowset_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.col,
-                               g.V, g.E, set);
-        ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(stream) == hipSuccess;
+    int here = -1;
+    if (hipGetDevice(&here) == hipSuccess && (here == g.device || hipSetDevice(g.device) == hipSuccess)) {
+        int32_t* set = nullptr;
+        hipStream_t stream = nullptr;
+        const int64_t n = g.E / 2 + g.V + 1;
+        const dim3 grid((unsigned)((g.E + kLinkTile - 1) / kLinkTile));
+        bool ok = spare_room((size_t)n * 16) && hipMalloc((void**)&set, (size_t)n * 16) == hipSuccess &&
+                  hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess;
+        if (ok) {
+            hipLaunchKernelGGL(fill_empty_kernel, dim3((unsigned)g.num_cus * 32u), dim3(256), 0, stream, (int4*)set, n);
+            if (g.off64)
+                hipLaunchKernelGGL(build_rowset_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off,
+                                   g.col, g.V, g.E, set);
+            else
+                hipLaunchKernelGGL(build_rowset_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off,
+                                   g.col, g.V, g.E, set);
+            ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(stream) == hipSuccess;
+        }
+        if (stream) (void)hipStreamDestroy(stream);
+        if (ok) {
+            g.rowset.store(set, std::memory_order_release);
+        } else {
+            (void)hipGetLastError();
+            (void)hipFree(set);
+        }
+        if (here != g.device) (void)hipSetDevice(here);
     }
-    if (stream) (void)hipStreamDestroy(stream);
     (void)hipThreadExchangeStreamCaptureMode(&capture);
-    if (ok) {
-        g.rowset.store(set, std::memory_order_release);
-    } else {
-        (void)hipGetLastError();
-        (void)hipFree(set);
-        g.rowset_failed = true;
-    }
 }
 
 }  // namespace nd

@@ -11,9 +11,12 @@
  *   query RC WORKSPACE_BYTES STEPS
  *   static RC
  *   launch KERNEL          (one line per launch, of the sampling call only)
+ *   device D               (current when the queries have returned)
  *   allocated BYTES        (live when the program ends, before the graph is destroyed)
- * Names: the fields of nd_params, fanout as a,b,c; fail_malloc=N (the first N allocations of the query
- * fail); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
+ * Names: the fields of nd_params, fanout as a,b,c; queries=N (asks N times); fail_malloc=N (the first N
+ * allocations of the queries fail); left=B (of the device's memory, B bytes are free when the first query
+ * is made); device=D (current during the queries; the graph lies on device 0, and memory taken on another
+ * is counted as elsewhere and ends the program with status 4); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
  * and prints "unused STATS_RC STATUS_RC").  A call that does not return within 20 seconds ends the program with SIGALRM. */
 #define _GNU_SOURCE
 #include <stdio.h>
@@ -28,7 +31,7 @@ typedef struct { unsigned x, y, z; } dim3_t;
 typedef struct { void* p; size_t n; } Block;
 
 static Block blocks[256];
-static int n_blocks, fail_malloc, trace;
+static int n_blocks, fail_malloc, trace, device, elsewhere;
 static size_t live_bytes, free_limit;
 static struct { const void* f; const char* name; } kernels[1024];
 static int n_kernels;
@@ -45,6 +48,7 @@ int hipMalloc(void** p, size_t n) {
     blocks[n_blocks].p = *p;
     blocks[n_blocks++].n = n;
     live_bytes += n;
+    elsewhere |= device != 0;
     return 0;
 }
 int hipFree(void* p) {
@@ -67,8 +71,8 @@ int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* stream) {
     return 0;
 }
 int hipMemsetAsync(void* d, int v, size_t n, void* s) { (void)d; (void)v; (void)n; (void)s; return 0; }
-int hipGetDevice(int* d) { *d = 0; return 0; }
-int hipSetDevice(int d) { (void)d; return 0; }
+int hipGetDevice(int* d) { *d = device; return 0; }
+int hipSetDevice(int d) { device = d; return 0; }
 int hipDeviceGetAttribute(int* v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
 int hipFuncSetAttribute(const void* f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
 int hipGetLastError(void) { return 0; }
@@ -114,7 +118,8 @@ int main(int argc, char** argv) {
     free_limit = (size_t)atoll(argv[4]);
     nd_params p;
     nd_params_init(&p);
-    int fail = 0, unused = -1;
+    int fail = 0, unused = -1, queries = 1, query_device = 0;
+    long long left = -1;
     for (int i = 7; i < argc; ++i) {
         char* eq = strchr(argv[i], '=');
         if (!eq) return 2;
@@ -132,6 +137,9 @@ int main(int argc, char** argv) {
         else if (!strcmp(n, "use_weights")) p.use_weights = atoi(v);
         else if (!strcmp(n, "unused")) unused = atoi(v);
         else if (!strcmp(n, "fail_malloc")) fail = atoi(v);
+        else if (!strcmp(n, "queries")) queries = atoi(v);
+        else if (!strcmp(n, "left")) left = atoll(v);
+        else if (!strcmp(n, "device")) query_device = atoi(v);
         else return 2;
     }
     nd_graph* g = NULL;
@@ -143,9 +151,13 @@ int main(int argc, char** argv) {
     static int64_t lens[ND_MAX_WALK_STEPS];
     size_t ws = 0;
     fail_malloc = fail;
-    rc = nd_sample_query(g, app, &p, roots, &steps, lens, &ws);
+    if (left >= 0) free_limit = live_bytes + (size_t)left;
+    device = query_device;
+    for (int i = 0; i < queries; ++i) rc = nd_sample_query(g, app, &p, roots, &steps, lens, &ws);
     fail_malloc = 0;
     printf("query %d %zu %d\n", rc, ws, steps);
+    printf("device %d\n", device);
+    device = 0;
     static int32_t* out[ND_MAX_WALK_STEPS];
     for (int i = 0; i < ND_MAX_WALK_STEPS; ++i) out[i] = any;
     trace = 1;
@@ -161,5 +173,5 @@ int main(int argc, char** argv) {
     }
     printf("allocated %zu\n", live_bytes);
     nd_graph_destroy(g);
-    return live_bytes == 0 ? 0 : 3;
+    return live_bytes != 0 ? 3 : elsewhere ? 4 : 0;
 }

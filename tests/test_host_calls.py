@@ -59,3 +59,32 @@ def test_links_are_taken_from_a_quarter_of_the_free_memory(program, weighted):
     assert got["allocated"] == [graph + links] and any("walk_free" in k for k in got["launches"])
     got = program(B.ND_DEEPWALK, 10, V=V, E=E, weighted=weighted, free_bytes=during + 4 * links - 1, num_steps=2)
     assert got["allocated"] == [graph] and any("walk_window" in k for k in got["launches"])
+
+
+def _tables(V, E):
+    return (E // 2 + V + 1) * 16
+
+
+def test_membership_tables_that_could_not_be_made_are_made_when_there_is_room(program):
+    """One refused allocation does not decide for the rest of the graph's life."""
+    V, E = 1000, 80_000
+    graph = (V + 1) * 8 + E * 4 + E * 16
+    for queries, tables in ((1, 0), (2, _tables(V, E)), (3, _tables(V, E))):
+        got = program(B.ND_NODE2VEC, 10, V=V, E=E, num_steps=2, fail_malloc=1, queries=queries)
+        assert got["query"][0] == 0 and got["allocated"] == [graph + tables]
+
+
+def test_membership_tables_are_taken_from_a_quarter_of_the_free_memory(program):
+    V, E = 1000, 80_000
+    graph = (V + 1) * 8 + E * 4 + E * 16
+    for left, tables in ((4 * _tables(V, E), _tables(V, E)), (4 * _tables(V, E) - 1, 0)):
+        got = program(B.ND_NODE2VEC, 10, V=V, E=E, num_steps=2, left=left)
+        assert got["query"][0] == 0 and got["allocated"] == [graph + tables]
+
+
+def test_membership_tables_are_made_on_the_device_of_the_graph(program):
+    """Whatever device is current when sizes are asked for, and that one stays current."""
+    V, E = 1000, 80_000
+    graph = (V + 1) * 8 + E * 4 + E * 16
+    got = program(B.ND_NODE2VEC, 10, V=V, E=E, num_steps=2, device=1)
+    assert got["allocated"] == [graph + _tables(V, E)] and got["device"] == [1]
