@@ -54,7 +54,8 @@ __device__ __forceinline__ int32_t draw_weighted(const DrawArgs& a, uint32_t deg
 
 // The same draw over the row's WeightLinks (deg >= 1): the link of the first entry whose threshold exceeds the
 // draw's 64-bit word.  The guide of the word's cell names an entry at or before it, about one entry before on
-// average; links come with the thresholds, two entries to a look.  A cell holds as many entries as are light
+// average; a look is at two entries and their links (as compiled one entry after the other, the last word of
+// each after its threshold).  A cell holds as many entries as are light
 // beside the row's heavy ones, up to nearly the whole row, so after four looks the rest of the row is searched
 // by halves: 65,536 walks of 8 steps between a hub of 20,000 entries, one of which outweighs the others
 // together, and its leaves took 2.4 ms where the walk went on entry by entry, 0.015 like this.

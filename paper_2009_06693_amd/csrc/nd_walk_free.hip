@@ -87,8 +87,9 @@ __device__ __forceinline__ int32_t first_transit(const FreeArgs& a, uint32_t s) 
 }
 
 // DeepWalk and PPR.  Many walks: bound by the scattered 128-byte fetches of the links (one per draw;
-// the chip serves 5.5e10 of them per second whatever the array's size).  Few walks: by one fetch per
-// step, the generator runs while it is under way.
+// the chip serves 5.5e10 of them per second whatever the array's size).  Few walks: by the chain of a
+// step, 0.65 us.  The generator needs nothing of the link, but as compiled (ROCm 7.2) its ten rounds for
+// the next step come after the wait for the link and the store of its vertex, so the chain is their sum.
 template <int DRAW, int STRIDE, typename OffT, int THREADS>
 __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
@@ -114,7 +115,6 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
             if (DRAW == kDrawUniform) l = a.links[(uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE];
             else l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r.r0, r.r1));
         }
-        // the next step's word does not wait for the link
         r = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
         v = l.v;
         rs = l.rs;
@@ -172,8 +172,8 @@ __device__ __noinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, 
 // Every lane goes through its walk's attempts at its own pace: a wavefront whose lanes wait for each
 // other at every step pays for the slowest of 64 geometrically distributed attempt counts (7 rounds
 // per step where the mean is 1.9).  An attempt is one fetch of the candidate's link, and one of the
-// previous vertex's table when the two biases differ in their verdict; meanwhile the generator makes
-// the words of both possible next attempts.
+// previous vertex's table when the two biases differ in their verdict.  The generator makes the words of
+// both possible next attempts; as compiled (ROCm 7.2) after the verdict, the second only where a walk moves on.
 template <int STRIDE, typename OffT, int THREADS>
 __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
@@ -213,9 +213,10 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
         if (STRIDE == 2 && a.use_weights) top = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
         const Rand4 again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + 1u);
         const Rand4 onward = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
-        // The verdict and the move to the next vertex are selections, not branches: of the nest of
-        // branches that says the same, the compiler (ROCm 7.2) made code that lost the link's row on
-        // the way to the move.
+        // The verdict and the move to the next vertex are selections, not branches.  From the nest of branches
+        // that says the same, the compiler (ROCm 7.2, -O3) makes code in which the registers of the link's row
+        // and length take the weight and the envelope, and a walk that accepts its candidate moves on with the
+        // row it stood on; compiled for the CPU, under sanitizers, both forms give the oracle's walks.
         const bool start = t < 0, back = l.v == t;
         const uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
         const uint64_t w = a.use_weights ? l.wq : kOneQ16;
