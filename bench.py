@@ -409,8 +409,11 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
     }
     if stats is not None:
         res["scheduling"] = {"live_pairs": [int(x) for x in stats[:2, 0]] + ([int(stats[-1, 0])] if len(stats) > 2 else []),
-                             "distinct_transits": [int(x) for x in stats[:2, 1]],
-                             "sub_wg_grid": [[int(x) for x in stats[i, 2:5]] for i in range(min(2, len(stats)))]}
+                             "distinct_transits": None, "sub_wg_grid": None}
+        if not links:  # nothing is grouped over links, so neither is counted
+            res["scheduling"].update(
+                distinct_transits=[int(x) for x in stats[:2, 1]],
+                sub_wg_grid=[[int(x) for x in stats[i, 2:5]] for i in range(min(2, len(stats)))])
     del s, out, dg
     torch.cuda.empty_cache()
     return res

@@ -147,7 +147,8 @@ typedef struct nd_params {
                                /* the graph's links, ungrouped (windows where the device has   */
                                /* no room for links); k-hop runs all hops in one launch where  */
                                /* draws seldom meet in a line of the graph, and groups GPU-    */
-                               /* wide on dense graphs with many pairs per vertex.             */
+                               /* wide on dense graphs with many pairs per vertex.  Where      */
+                               /* nothing is grouped lds_stage_policy has nothing to stage.    */
                                /* Same output.                                                 */
     int32_t reserved[2];
 } nd_params;
@@ -297,7 +298,9 @@ int nd_sample_status(const void* workspace_dev, void* hip_stream);
  * first max_steps steps, 8 int64 values: live pairs, distinct transits,
  * transits in the sub-wavefront / workgroup / grid class, grid chunks,
  * work items staged in LDS, draws made by the workgroup and grid classes.  Evidence
- * for Section 6.1.2's partition.
+ * for Section 6.1.2's partition, so the values after the first are 0 where a call
+ * did not group: sched_window = 0 over links, one launch per call (walks; k-hop
+ * unless its graph is dense).  Layer sampling has no pairs; all its values are 0.
  */
 int nd_sample_stats(const void* workspace_dev, void* hip_stream, int32_t max_steps,
                     int64_t* stats);
@@ -393,20 +396,24 @@ int nd_samples_pack(const int32_t* const* step_out_dev, int32_t num_steps, const
  * ms[ND_PHASE_COUNT] and intervals[ND_PHASE_COUNT] (the caller zeroes them),
  * and resets the recording.  At most 16384 events are kept between reads;
  * later marks are dropped and nd_profile_read then returns ND_ERR_BAD_ARGUMENT.
- * The sampling phases contain exactly one kernel launch per interval.
+ * The sampling phases contain exactly one kernel launch per interval; a call over
+ * links has one phase and no others.
  */
 typedef enum nd_phase {
     ND_PHASE_NONE = -1,
     ND_PHASE_INIT = 0,        /* workspace header / bitmap reset                    */
     ND_PHASE_SORT = 1,        /* transit enumeration, NULL fill + radix sort        */
     ND_PHASE_GROUP = 2,       /* segmented scan + classification                    */
-    ND_PHASE_SAMPLE_SUB = 3,  /* the step's sampling kernel (all three classes)     */
+    ND_PHASE_SAMPLE_SUB = 3,  /* the step's sampling kernel (all three classes), or */
+                              /* k-hop's one launch for all hops                    */
     ND_PHASE_SAMPLE_WG = 4,   /* the same kernel when a heavy class is forced       */
     ND_PHASE_SAMPLE_SP = 5,   /* sample-parallel kernel (ablation mode)             */
-    ND_PHASE_LAYER = 6,       /* collective (layer) kernel                          */
-    ND_PHASE_UNIQUE = 7,      /* duplicate removal and refill (unique neighbours)   */
-    ND_PHASE_WALK_WINDOW = 8, /* walk kernel with per-window grouping in LDS (one   */
-                              /* launch per 128 steps)                              */
+    ND_PHASE_LAYER = 6,       /* collective (layer) kernel: one launch per call, or */
+                              /* per step without links                             */
+    ND_PHASE_UNIQUE = 7,      /* unique neighbours: one launch for all hops, or a   */
+                              /* step's duplicate removal and refill                */
+    ND_PHASE_WALK_WINDOW = 8, /* walk kernel, over links or with per-window         */
+                              /* grouping in LDS (one launch per 128 steps)         */
     ND_PHASE_COUNT = 9
 } nd_phase;
 int nd_profile_enable(int on);

@@ -269,7 +269,8 @@ def nd_sample_status(workspace: torch.Tensor, stream=None):
 
 def nd_sample_stats(workspace: torch.Tensor, num_steps: int, stream=None) -> np.ndarray:
     """int64 [num_steps, 8]: live pairs, distinct transits, sub-wavefront / workgroup / grid
-    transits, grid chunks, work items staged in LDS, reserved."""
+    transits, grid chunks, work items staged in LDS, draws of the workgroup and grid classes;
+    only the first is counted where a call does not group (walks and k-hop over links)."""
     out = (ctypes.c_int64 * (8 * num_steps))()
     _check(lib().nd_sample_stats(workspace.data_ptr(), _stream_ptr(stream), num_steps, out))
     return np.array(out, dtype=np.int64).reshape(num_steps, 8)
