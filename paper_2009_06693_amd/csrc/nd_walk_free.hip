@@ -143,30 +143,80 @@ __device__ __forceinline__ bool row_has(const GraphView<OffT>& g, const int32_t*
     return found;
 }
 
-// The exact draw after the last rejected attempt: inverse transform over the row's biased weights;
-// returns the entry's place in the row.  Rare, so out of line; what it needs travels in registers.
+// The exact draw after the last rejected attempt: inverse transform over the row's biased weights.  `exact`:
+// this lane's walk needs one; returns the entry's place in the row.  All lanes of the wavefront call it.
+// Rare where the biases are alike, so out of line; where they are far apart (p = 0.05, q = 20) it is most of
+// the time.  Lanes at their own pace come here one or two at a time, and a lane that goes through its row by
+// itself keeps 63 others waiting, so the wavefront goes through one lane's row after the other, 64 entries at a
+// time: 57 K weighted walks of 20 steps over 57 K vertices took 92 ms with a row per lane (43 in windows,
+// whose lanes come together), 6.3 like this.  Where many lanes come at once and the longest of their rows
+// has fewer entries than all have pieces of 64, each lane does its own.  The sums are whole numbers: their
+// order does not matter.
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, int lane) {
+    return cat64((uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane),
+                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane));
+}
 template <int STRIDE, typename OffT>
 __device__ __noinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, const uint32_t* wq, const int32_t* rowset,
-                                           uint64_t R, uint32_t b_ret, uint32_t b_com, uint32_t b_far, int32_t t,
-                                           uint32_t rs_t, uint32_t deg_t, uint32_t rs, uint32_t deg) {
+                                           bool exact, uint64_t R, uint32_t b_ret, uint32_t b_com, uint32_t b_far,
+                                           int32_t t, uint32_t rs_t, uint32_t deg_t, uint32_t rs, uint32_t deg) {
+    uint32_t e = 0;
     const GraphView<OffT> g{off, col, nullptr, nullptr, nullptr, 0};
-    uint64_t Z = 0, x = 0, run = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (uint32_t e = 0; e < deg; ++e) {
-            const int32_t u = col[(uint64_t)rs + e];
-            const uint64_t w = wq != nullptr ? wq[(uint64_t)rs + e] : kOneQ16;
-            uint64_t b = kOneQ16;
-            if (t >= 0) b = u == t ? b_ret : row_has(g, rowset, t, rs_t, deg_t, u) ? b_com : b_far;
-            if (pass == 0) {
-                Z += w * b;
-            } else {
-                run += w * b;
-                if (run > x) return e;
+    auto biased = [&](uint64_t at, int32_t prev, uint32_t prev_rs, uint32_t prev_deg) -> uint64_t {
+        const int32_t u = col[at];
+        const uint64_t w = wq != nullptr ? wq[at] : kOneQ16;
+        uint64_t b = kOneQ16;
+        if (prev >= 0) b = u == prev ? b_ret : row_has(g, rowset, prev, prev_rs, prev_deg, u) ? b_com : b_far;
+        return w * b;
+    };
+    const int lane = lane_id();
+    uint32_t longest = exact ? deg : 0u;
+    uint64_t pieces = exact ? (deg + 63u) >> 6 : 0u;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)longest, d, 64);
+        longest = o > longest ? o : longest;
+        pieces += __shfl_xor(pieces, d, 64);
+    }
+    if (pieces > longest) {
+        if (exact) {
+            uint64_t Z = 0, run = 0;
+            for (uint32_t i = 0; i < deg; ++i) Z += biased((uint64_t)rs + i, t, rs_t, deg_t);
+            const uint64_t x = mulhi64(R, Z);
+            for (e = 0; e + 1u < deg; ++e) {
+                run += biased((uint64_t)rs + e, t, rs_t, deg_t);
+                if (run > x) break;
             }
         }
-        x = mulhi64(R, Z);
+        return e;
     }
-    return deg - 1u;  // not reached: x < Z
+    for (uint64_t need = __ballot(exact); need != 0ull; need &= need - 1ull) {
+        const int who = __builtin_ctzll(need);
+        const int32_t p_t = __builtin_amdgcn_readlane(t, who);
+        const uint32_t p_rs_t = (uint32_t)__builtin_amdgcn_readlane((int)rs_t, who);
+        const uint32_t p_deg_t = (uint32_t)__builtin_amdgcn_readlane((int)deg_t, who);
+        const uint32_t p_rs = (uint32_t)__builtin_amdgcn_readlane((int)rs, who);
+        const uint32_t p_deg = (uint32_t)__builtin_amdgcn_readlane((int)deg, who);
+        uint64_t Z = 0, run = 0;
+        for (uint32_t i = (uint32_t)lane; i < p_deg; i += 64u) Z += biased((uint64_t)p_rs + i, p_t, p_rs_t, p_deg_t);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) Z += __shfl_xor(Z, d, 64);
+        const uint64_t x = mulhi64(lane_value(R, who), Z);
+        uint32_t found = p_deg - 1u;  // where no weight is left, as for a row that a lane goes through
+        for (uint32_t base = 0; base < p_deg; base += 64u) {
+            const uint32_t i = base + (uint32_t)lane;
+            const uint64_t w = i < p_deg ? biased((uint64_t)p_rs + i, p_t, p_rs_t, p_deg_t) : 0ull;
+            const uint64_t incl = run + wave_inclusive_scan(w, lane);
+            const uint64_t hit = __ballot(incl > x);
+            if (hit != 0ull) {
+                found = base + (uint32_t)__builtin_ctzll(hit);
+                break;
+            }
+            run = lane_value(incl, 63);
+        }
+        if (lane == who) e = found;
+    }
+    return e;
 }
 
 // Every lane goes through its walk's attempts at its own pace: a wavefront whose lanes wait for each
@@ -199,45 +249,61 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
     uint32_t si = 0;
     int32_t att = 0;
     Rand4 r = draw4(a.seed, sid, 0u, a.first_step, 0u);
-    while (si < a.n_steps && deg > 0u) {  // deg is 0 for a walk that has ended
-        uint32_t e;
-        const bool exact = att >= a.max_attempts;
-        if (exact)
-            e = n2v_exact<STRIDE, OffT>(g.off, g.col, a.use_weights ? g.wq : nullptr, a.rowset, cat64(r.r0, r.r1), a.b_ret,
-                                        a.b_com, a.b_far, t, rs_t, deg_t, rs, deg);
-        else
-            e = mulhi32(r.r0, deg);
-        const Link* at = a.links + (uint64_t)(rs + e) * STRIDE;
-        const Link l = *at;
-        uint32_t top = kOneQ16;
-        if (STRIDE == 2 && a.use_weights) top = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
-        const Rand4 again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + 1u);
-        const Rand4 onward = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
-        // The verdict and the move to the next vertex are selections, not branches.  From the nest of branches
-        // that says the same, the compiler (ROCm 7.2, -O3) makes code in which the registers of the link's row
-        // and length take the weight and the envelope, and a walk that accepts its candidate moves on with the
-        // row it stood on; compiled for the CPU, under sanitizers, both forms give the oracle's walks.
-        const bool start = t < 0, back = l.v == t;
-        const uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
-        const uint64_t w = a.use_weights ? l.wq : kOneQ16;
-        bool take = exact || y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
-        const bool ask = !take && !start && !back && y < w * b_hi;
-        bool common = false;
-        if (ask) common = row_has(g, a.rowset, t, rs_t, deg_t, l.v);
-        take = take || (ask && y < w * (common ? a.b_com : a.b_far));
-        if (take) a.out[si][s] = l.v;
-        t = take ? v : t;
-        rs_t = take ? rs : rs_t;
-        deg_t = take ? deg : deg_t;
-        v = take ? l.v : v;
-        rs = take ? l.rs : rs;
-        deg = take ? l.deg : deg;
-        maxw = take ? top : maxw;
-        si += take ? 1u : 0u;
-        att = take ? 0 : att + 1;
-        r.r0 = take ? onward.r0 : again.r0;
-        r.r1 = take ? onward.r1 : again.r1;
-        r.r2 = take ? onward.r2 : again.r2;
+    for (;;) {
+        while (si < a.n_steps && deg > 0u) {  // deg is 0 for a walk that has ended
+            if (__ballot(att >= a.max_attempts) != 0ull) break;  // the wavefront leaves: a lane's attempts are used up
+            const Link* at = a.links + (uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE;
+            const Link l = *at;
+            uint32_t top = kOneQ16;
+            if (STRIDE == 2 && a.use_weights) top = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
+            const Rand4 again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + 1u);
+            const Rand4 onward = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
+            // The verdict and the move to the next vertex are selections, not branches.  From the nest of branches
+            // that says the same, the compiler (ROCm 7.2, -O3) makes code in which the registers of the link's row
+            // and length take the weight and the envelope, and a walk that accepts its candidate moves on with the
+            // row it stood on; compiled for the CPU, under sanitizers, both forms give the oracle's walks.
+            const bool start = t < 0, back = l.v == t;
+            const uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
+            const uint64_t w = a.use_weights ? l.wq : kOneQ16;
+            bool take = y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
+            const bool ask = !take && !start && !back && y < w * b_hi;
+            bool common = false;
+            if (ask) common = row_has(g, a.rowset, t, rs_t, deg_t, l.v);
+            take = take || (ask && y < w * (common ? a.b_com : a.b_far));
+            if (take) a.out[si][s] = l.v;
+            t = take ? v : t;
+            rs_t = take ? rs : rs_t;
+            deg_t = take ? deg : deg_t;
+            v = take ? l.v : v;
+            rs = take ? l.rs : rs;
+            deg = take ? l.deg : deg;
+            maxw = take ? top : maxw;
+            si += take ? 1u : 0u;
+            att = take ? 0 : att + 1;
+            r.r0 = take ? onward.r0 : again.r0;
+            r.r1 = take ? onward.r1 : again.r1;
+            r.r2 = take ? onward.r2 : again.r2;
+        }
+        const bool exact = si < a.n_steps && deg > 0u && att >= a.max_attempts;
+        if (__ballot(exact) == 0ull) break;  // every walk of the wavefront is done
+        const uint32_t e = n2v_exact<STRIDE, OffT>(g.off, g.col, a.use_weights ? g.wq : nullptr, a.rowset, exact,
+                                                   cat64(r.r0, r.r1), a.b_ret, a.b_com, a.b_far, t, rs_t, deg_t, rs,
+                                                   deg);
+        if (exact) {
+            const Link* at = a.links + (uint64_t)(rs + e) * STRIDE;
+            const Link l = *at;
+            if (STRIDE == 2 && a.use_weights) maxw = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
+            a.out[si][s] = l.v;
+            t = v;
+            rs_t = rs;
+            deg_t = deg;
+            v = l.v;
+            rs = l.rs;
+            deg = l.deg;
+            ++si;
+            att = 0;
+            r = draw4(a.seed, sid, 0u, a.first_step + si, 0u);
+        }
     }
     // a walk that stands on a vertex without out-edges had a transit at this step still
     const uint32_t lived = si + (si < a.n_steps && v >= 0 ? 1u : 0u);

@@ -237,3 +237,46 @@ def test_weighted_walks_where_one_entry_outweighs_a_long_row(heavy_first):
     assert_steps_equal(got, list(oracle.ppr(og, roots, steps, 0.02, seed=20, use_weights=True)), "ppr")
     print(f"[times] equal weights {times[0]:.4f} ms, one heavy entry {times[1]:.4f} ms", flush=True)
     assert times[1] < 8.0 * times[0] + 0.05  # 0.0129 and 0.0154 ms; entry by entry 2.4 ms
+
+
+@pytest.mark.parametrize("weighted,int64_offsets", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("p,q,attempts", [(0.05, 20.0, 64), (0.05, 20.0, 2), (2.0, 0.5, 0), (20.0, 0.05, 1)])
+def test_node2vec_draws_that_end_in_the_exact_one(weighted, int64_offsets, p, q, attempts):
+    """Few lanes of a wavefront at a time (its lanes share a row then) and all of them; rows around one and two
+    wavefronts long; samples in workgroups of 64 and 256."""
+    V = 701
+    pairs = [(a, (31 * a + 7 * j) % V) for a in range(V) for j in range((1, 63, 64, 65, 3, 0, 129, 500)[a % 8])]
+    pairs = sorted(pairs)
+    w = 1.0 + 4.0 * np.random.default_rng(5).random(len(pairs), dtype=np.float32) if weighted else None
+    g = inputs.from_edges(V, pairs, weights=w, int64_offsets=int64_offsets)
+    dg, og = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights), \
+        oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    for steps, S in ((9, 700), (2, 65_600)):
+        roots = _roots(g.V, S, 9)
+        for use in ((0, 1) if weighted else (0,)):
+            want = oracle.node2vec(og, roots, steps, p, q, seed=22, use_weights=bool(use), max_attempts=attempts)
+            got, _ = gpu_sample(dg, B.ND_NODE2VEC, roots, 22, num_steps=steps, p=p, q=q, n2v_max_attempts=attempts,
+                                use_weights=use)
+            assert_steps_equal(got, list(want), f"node2vec p={p} q={q} attempts={attempts} weighted={use}")
+
+
+def test_node2vec_with_biases_far_apart_takes_no_longer_than_in_windows():
+    """Most candidates are rejected 64 times and a row is gone through for the draw: by one lane each where the lanes
+    come together (windows), by the wavefront where they come one by one."""
+    g = inputs.config2_graph()
+    dg = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights)
+    r = torch.as_tensor(inputs.all_vertices_roots(g)[:20_000], device="cuda:0")
+    times, outs = [], []
+    for window in (0, 256):
+        s = B.Sampler(dg, B.ND_NODE2VEC, B.nd_params_init(num_steps=10, p=0.05, q=20.0, use_weights=1,
+                                                          sched_window=window), r.numel())
+        outs.append([o.clone() for o in s.run(r, 19)])
+        marks = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+        for m in marks:
+            m.record()
+            s.run(r, 19)
+        torch.cuda.synchronize()
+        times.append(min(a.elapsed_time(b) for a, b in zip(marks, marks[1:])))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    print(f"[times] over links {times[0]:.2f} ms, in windows {times[1]:.2f} ms", flush=True)
+    assert times[0] < 1.1 * times[1]
