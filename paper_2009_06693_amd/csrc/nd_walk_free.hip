@@ -145,46 +145,58 @@ __device__ __forceinline__ bool row_has(const GraphView<OffT>& g, const int32_t*
 
 // The exact draw after the last rejected attempt: inverse transform over the row's biased weights.  `exact`:
 // this lane's walk needs one; returns the entry's place in the row.  All lanes of the wavefront call it.
-// Rare where the biases are alike, so out of line; where they are far apart (p = 0.05, q = 20) it is most of
-// the time.  Lanes at their own pace come here one or two at a time, and a lane that goes through its row by
-// itself keeps 63 others waiting, so the wavefront goes through one lane's row after the other, 64 entries at a
-// time: 57 K weighted walks of 20 steps over 57 K vertices took 92 ms with a row per lane (43 in windows,
-// whose lanes come together), 6.3 like this.  Where many lanes come at once and the longest of their rows
-// has fewer entries than all have pieces of 64, each lane does its own.  The sums are whole numbers: their
-// order does not matter.
+// Rare where the biases are alike; where they are far apart (p = 0.05, q = 20) it is most of the time.  Lanes at their own pace come here one or two at a time, and a lane that goes through its row by
+// itself keeps 63 others waiting, so the wavefront goes through one lane's row after the other, 256 entries
+// at a time; what it has added up tells the stretch in which the draw ends, so only that is gone through
+// again.  Where many lanes come at once and the longest of their rows has fewer entries than that takes
+// steps, each lane does its own, and so does it in rows of up to four entries.  The sums are whole numbers: their
+// order does not matter.  A row per lane, in windows, and like this: 57 K weighted walks of 20 steps, p = 0.05,
+// q = 20, 87, 42 and 5.7 ms; 4 M walks of 5 steps, p = 0.25, q = 4, over the scale-22 R-MAT graph 101, 310 and
+// 6.7 ms; 64 walks of 4 steps through a hub of a million entries one of which outweighs the rest 7.2, 1.0, 0.78 s.
 __device__ __forceinline__ uint64_t lane_value(uint64_t x, int lane) {
     return cat64((uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane),
                  (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane));
 }
-template <int STRIDE, typename OffT>
-__device__ __noinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, const uint32_t* wq, const int32_t* rowset,
+__device__ __forceinline__ uint64_t wave_sum(uint64_t x) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+    return x;
+}
+template <typename OffT>
+__device__ __forceinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, const uint32_t* wq, const int32_t* rowset,
                                            bool exact, uint64_t R, uint32_t b_ret, uint32_t b_com, uint32_t b_far,
                                            int32_t t, uint32_t rs_t, uint32_t deg_t, uint32_t rs, uint32_t deg) {
+    constexpr uint32_t kPieces = 4u, kBlock = kPieces * 64u;  // entries per lane and step, entries per step
     uint32_t e = 0;
     const GraphView<OffT> g{off, col, nullptr, nullptr, nullptr, 0};
-    auto biased = [&](uint64_t at, int32_t prev, uint32_t prev_rs, uint32_t prev_deg) -> uint64_t {
-        const int32_t u = col[at];
-        const uint64_t w = wq != nullptr ? wq[at] : kOneQ16;
-        uint64_t b = kOneQ16;
-        if (prev >= 0) b = u == prev ? b_ret : row_has(g, rowset, prev, prev_rs, prev_deg, u) ? b_com : b_far;
-        return w * b;
+    auto bias = [&](int32_t u, int32_t prev, uint32_t prev_rs, uint32_t prev_deg) -> uint64_t {
+        if (prev < 0) return kOneQ16;
+        return u == prev ? b_ret : row_has(g, rowset, prev, prev_rs, prev_deg, u) ? b_com : b_far;
     };
     const int lane = lane_id();
-    uint32_t longest = exact ? deg : 0u;
-    uint64_t pieces = exact ? (deg + 63u) >> 6 : 0u;
+    bool alone = __ballot(exact && deg > 4u) == 0ull;
+    if (!alone) {
+        uint32_t longest = exact ? deg : 0u;
+        uint32_t steps = exact ? (deg >> 8) + 2u : 0u;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)longest, d, 64);
-        longest = o > longest ? o : longest;
-        pieces += __shfl_xor(pieces, d, 64);
+        for (int d = 32; d >= 1; d >>= 1) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)longest, d, 64);
+            longest = o > longest ? o : longest;
+            steps += (uint32_t)__shfl_xor((int)steps, d, 64);
+        }
+        alone = steps > longest;
     }
-    if (pieces > longest) {
+    if (alone) {
         if (exact) {
+            auto biased = [&](uint32_t i) {
+                const uint64_t at = (uint64_t)rs + i;
+                return (wq != nullptr ? wq[at] : (uint64_t)kOneQ16) * bias(col[at], t, rs_t, deg_t);
+            };
             uint64_t Z = 0, run = 0;
-            for (uint32_t i = 0; i < deg; ++i) Z += biased((uint64_t)rs + i, t, rs_t, deg_t);
+            for (uint32_t i = 0; i < deg; ++i) Z += biased(i);
             const uint64_t x = mulhi64(R, Z);
             for (e = 0; e + 1u < deg; ++e) {
-                run += biased((uint64_t)rs + e, t, rs_t, deg_t);
+                run += biased(e);
                 if (run > x) break;
             }
         }
@@ -197,26 +209,85 @@ __device__ __noinline__ uint32_t n2v_exact(const OffT* off, const int32_t* col, 
         const uint32_t p_deg_t = (uint32_t)__builtin_amdgcn_readlane((int)deg_t, who);
         const uint32_t p_rs = (uint32_t)__builtin_amdgcn_readlane((int)rs, who);
         const uint32_t p_deg = (uint32_t)__builtin_amdgcn_readlane((int)deg, who);
-        uint64_t Z = 0, run = 0;
-        for (uint32_t i = (uint32_t)lane; i < p_deg; i += 64u) Z += biased((uint64_t)p_rs + i, p_t, p_rs_t, p_deg_t);
+        uint64_t w[kPieces];
+        auto take_block = [&](uint32_t base) {  // my entries of a block: base + 64 p + lane
+            int32_t u[kPieces];
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) Z += __shfl_xor(Z, d, 64);
-        const uint64_t x = mulhi64(lane_value(R, who), Z);
-        uint32_t found = p_deg - 1u;  // where no weight is left, as for a row that a lane goes through
-        for (uint32_t base = 0; base < p_deg; base += 64u) {
-            const uint32_t i = base + (uint32_t)lane;
-            const uint64_t w = i < p_deg ? biased((uint64_t)p_rs + i, p_t, p_rs_t, p_deg_t) : 0ull;
-            const uint64_t incl = run + wave_inclusive_scan(w, lane);
-            const uint64_t hit = __ballot(incl > x);
-            if (hit != 0ull) {
-                found = base + (uint32_t)__builtin_ctzll(hit);
-                break;
+            for (uint32_t p = 0; p < kPieces; ++p) {
+                const uint32_t i = base + p * 64u + (uint32_t)lane;
+                u[p] = ND_NULL_VERTEX;
+                w[p] = 0;
+                if (i < p_deg) {
+                    const uint64_t at = (uint64_t)p_rs + i;
+                    u[p] = col[at];
+                    w[p] = wq != nullptr ? wq[at] : kOneQ16;
+                }
             }
-            run = lane_value(incl, 63);
+#pragma unroll
+            for (uint32_t p = 0; p < kPieces; ++p)
+                if (u[p] >= 0) w[p] *= bias(u[p], p_t, p_rs_t, p_deg_t);
+        };
+        // 64 stretches of whole blocks; lane k keeps the sum of stretch k
+        const uint32_t blocks = (p_deg + kBlock - 1u) / kBlock;
+        const uint32_t stretch = (blocks + 63u) / 64u * kBlock;
+        uint64_t mine = 0;
+        int k = 0;
+        for (uint32_t lo = 0; lo < p_deg; ++k) {
+            const uint32_t hi = p_deg - lo > stretch ? lo + stretch : p_deg;
+            uint64_t sum = 0;
+            for (; lo < hi; lo += kBlock) {
+                take_block(lo);
+                sum += w[0] + w[1] + w[2] + w[3];
+            }
+            sum = wave_sum(sum);
+            if (lane == k) mine = sum;
+        }
+        const uint64_t through = wave_inclusive_scan(mine, lane);
+        const uint64_t x = mulhi64(lane_value(R, who), lane_value(through, 63));
+        const uint64_t past = __ballot(through > x);
+        uint32_t found = p_deg - 1u;  // where no weight is left, as for a row that a lane goes through
+        if (past != 0ull) {
+            const int in = __builtin_ctzll(past);
+            uint64_t run = lane_value(through, in) - lane_value(mine, in);
+            bool more = true;
+            for (uint32_t lo = (uint32_t)in * stretch; more; lo += kBlock) {  // ends: the stretch's sum exceeds x
+                if (blocks > 1u) {  // one block: still in registers
+                    take_block(lo);
+                    const uint64_t all = wave_sum(w[0] + w[1] + w[2] + w[3]);
+                    if (run + all <= x) {
+                        run += all;
+                        continue;
+                    }
+                }
+                more = false;
+                bool open = true;
+#pragma unroll
+                for (uint32_t p = 0; p < kPieces; ++p) {
+                    const uint64_t incl = run + wave_inclusive_scan(w[p], lane);
+                    const uint64_t hit = __ballot(incl > x);
+                    if (open && hit != 0ull) {
+                        found = lo + p * 64u + (uint32_t)__builtin_ctzll(hit);
+                        open = false;
+                    }
+                    run = lane_value(incl, 63);
+                }
+            }
         }
         if (lane == who) e = found;
     }
     return e;
+}
+
+// Out of line for workgroups of one wavefront (at most 65,536 walks, one wavefront per SIMD: 88 registers do not
+// matter, and the attempts' loop is better without it: 57 K weighted walks of 100 steps 419 us, 435 inlined);
+// inlined for many walks (59 registers: 7 wavefronts per SIMD instead of 5; a million weighted walks of 10
+// steps 454 us, 470 out of line).
+template <typename OffT>
+__device__ __noinline__ uint32_t n2v_exact_call(const OffT* off, const int32_t* col, const uint32_t* wq,
+                                                const int32_t* rowset, bool exact, uint64_t R, uint32_t b_ret,
+                                                uint32_t b_com, uint32_t b_far, int32_t t, uint32_t rs_t, uint32_t deg_t,
+                                                uint32_t rs, uint32_t deg) {
+    return n2v_exact(off, col, wq, rowset, exact, R, b_ret, b_com, b_far, t, rs_t, deg_t, rs, deg);
 }
 
 // Every lane goes through its walk's attempts at its own pace: a wavefront whose lanes wait for each
@@ -265,7 +336,8 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
             const bool start = t < 0, back = l.v == t;
             const uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
             const uint64_t w = a.use_weights ? l.wq : kOneQ16;
-            bool take = y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
+            // a row of one entry has one outcome, whatever its attempts say
+            bool take = deg == 1u || y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
             const bool ask = !take && !start && !back && y < w * b_hi;
             bool common = false;
             if (ask) common = row_has(g, a.rowset, t, rs_t, deg_t, l.v);
@@ -286,9 +358,12 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
         }
         const bool exact = si < a.n_steps && deg > 0u && att >= a.max_attempts;
         if (__ballot(exact) == 0ull) break;  // every walk of the wavefront is done
-        const uint32_t e = n2v_exact<STRIDE, OffT>(g.off, g.col, a.use_weights ? g.wq : nullptr, a.rowset, exact,
-                                                   cat64(r.r0, r.r1), a.b_ret, a.b_com, a.b_far, t, rs_t, deg_t, rs,
-                                                   deg);
+        const uint32_t* wq = a.use_weights ? g.wq : nullptr;
+        const uint64_t word = cat64(r.r0, r.r1);
+        const uint32_t e = THREADS == 64 ? n2v_exact_call(g.off, g.col, wq, a.rowset, exact, word, a.b_ret, a.b_com,
+                                                          a.b_far, t, rs_t, deg_t, rs, deg)
+                                         : n2v_exact(g.off, g.col, wq, a.rowset, exact, word, a.b_ret, a.b_com, a.b_far,
+                                                     t, rs_t, deg_t, rs, deg);
         if (exact) {
             const Link* at = a.links + (uint64_t)(rs + e) * STRIDE;
             const Link l = *at;

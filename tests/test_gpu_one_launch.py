@@ -280,3 +280,62 @@ def test_node2vec_with_biases_far_apart_takes_no_longer_than_in_windows():
     assert all(torch.equal(a, b) for a, b in zip(*outs))
     print(f"[times] over links {times[0]:.2f} ms, in windows {times[1]:.2f} ms", flush=True)
     assert times[0] < 1.1 * times[1]
+
+
+@pytest.mark.parametrize("weighted,int64_offsets", [(False, True), (True, False)])
+@pytest.mark.parametrize("attempts", [0, 3])
+def test_node2vec_exact_draws_in_long_rows(weighted, int64_offsets, attempts):
+    """Rows whose entries one pass of the wavefront covers, just not, and those that are cut into stretches of one
+    and of several passes; rows of one entry, which need no draw; weights of zero beside others."""
+    lengths = [1, 2, 5, 255, 256, 257, 512, 16_383, 16_385, 33_000]
+    V = 33_100
+    pairs = sorted({(a, (17 + j) % V) for a, n in enumerate(lengths) for j in range(n)} |
+                   {(b, b % len(lengths)) for b in range(len(lengths), V)} | {(b, b // 3) for b in range(30, V, 7)})
+    w = None
+    if weighted:
+        w = 1.0 + 4.0 * np.random.default_rng(5).random(len(pairs), dtype=np.float32)
+        first = np.array([i == 0 or pairs[i - 1][0] != a for i, (a, _) in enumerate(pairs)])
+        w[(np.arange(len(pairs)) % 3 == 0) & ~first] = 1e-6  # quantises to zero; no row of nothing else
+    g = inputs.from_edges(V, pairs, weights=w, int64_offsets=int64_offsets)
+    dg, og = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights), \
+        oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    for S in (60, 65_700):   # workgroups of 64 and of 256; few walks live
+        roots = np.full(S, -1, np.int32)
+        roots[:60] = np.arange(60) % 23
+        if S > 60:
+            roots[-60:] = np.arange(60) % 12
+        for use in ((0, 1) if weighted else (0,)):
+            for p, q in ((20.0, 0.05), (0.05, 20.0)):
+                want = oracle.node2vec(og, roots, 6, p, q, seed=23, use_weights=bool(use), max_attempts=attempts)
+                got, _ = gpu_sample(dg, B.ND_NODE2VEC, roots, 23, num_steps=6, p=p, q=q, n2v_max_attempts=attempts,
+                                    use_weights=use)
+                assert_steps_equal(got, list(want), f"node2vec S={S} p={p} q={q} weighted={use}")
+
+
+def _least_time(dg, app, params, r, seed=19):
+    """Milliseconds of the fastest of a few calls, and the outputs."""
+    s = B.Sampler(dg, app, params, r.numel())
+    out = [o.clone() for o in s.run(r, seed)]
+    marks = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+    for m in marks:
+        m.record()
+        s.run(r, seed)
+    torch.cuda.synchronize()
+    return min(a.elapsed_time(b) for a, b in zip(marks, marks[1:])), out
+
+
+def test_node2vec_over_a_hub_takes_no_longer_than_in_windows():
+    """Every other step stands on a row of 200,000 entries one of which outweighs the rest, so every draw from it
+    is an exact one, of many walks at once."""
+    V = 200_001
+    pairs = [(0, b) for b in range(1, V)] + [(a, 0) for a in range(1, V)]
+    w = np.full(len(pairs), 0.01, np.float32)
+    w[V // 2] = 30_000.0
+    g = inputs.from_edges(V, pairs, weights=w)
+    dg = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights)
+    r = torch.arange(64, dtype=torch.int32, device="cuda:0") * 3000
+    (links, a), (windows, b) = (_least_time(dg, B.ND_NODE2VEC, B.nd_params_init(
+        num_steps=2, p=2.0, q=0.5, use_weights=1, sched_window=window), r) for window in (0, 256))
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    print(f"[times] over links {links:.2f} ms, in windows {windows:.2f} ms", flush=True)
+    assert links < 1.1 * windows
