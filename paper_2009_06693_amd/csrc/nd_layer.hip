@@ -272,6 +272,9 @@ int layer_prepare() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize,                           \
                                      ND_MAX_LAYER_TRANSITS * 24))
 #define ND_LAYER_ALLOW(OFFT, W, STRIDE)       \
+    ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 64);    \
+    ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 128);   \
+    ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 256);   \
     ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 512);   \
     ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 1024)
     ND_LAYER_ALLOW(int64_t, true, 2);
@@ -284,6 +287,8 @@ int layer_prepare() {
 #undef ND_LAYER_ALLOW
     return ND_OK;
 }
+
+constexpr size_t kLdsPerUnit = 160 << 10;
 
 int64_t layer_fused_groups(const Graph& gr, int64_t S) {
     const int64_t most = (int64_t)gr.num_cus * 64;  // bounds the flags; the workgroups stride over the samples
@@ -316,16 +321,26 @@ int layer_fused(const Graph& gr, uint64_t seed, uint32_t sample_base, bool weigh
     a.flags = (uint32_t*)(ws + o_flags);
     a.o_flags = o_flags;
     mark_phase(ND_PHASE_LAYER, stream);
-    // Twice the lanes where the samples leave compute units idle and the draws are more than one per lane
-    // (48 samples of [2048, 2048] over 4.2 M vertices: 17.2 us with 512 lanes, 14.6 with 1,024)
-    const bool wide = most_draws > kLayerThreads && S <= 2 * (int64_t)gr.num_cus;
+    // A lane per transit and draw up to 512, so that a compute unit holds as many small samples as it can: 50,000
+    // samples of 4 transits and 7 draws over 1.6 M entries take 31 us with 64 lanes, 55, 91 and 179 with 128, 256
+    // and 512; 3,000 of [100,100,100] 17 with 64 or 128, 42 with 512; 2,000 of [512,512] 25 with 128 or 256, 28
+    // with 512, but 257 of them 29 with 64 and 10.5 with 512.  1,024 lanes where a unit has one sample at a time,
+    // because there are no more (200 of [2048]: 9.5 us, 10.4 with 512; 300: 16.4 and 13.2) or because two
+    // do not fit its LDS (600 of [4096,4096]: 108 and 137).
+    const uint32_t lanes = widest > most_draws ? widest : most_draws;
+    const bool one_each = S <= (int64_t)gr.num_cus || lds_bytes > kLdsPerUnit / 2;
+    const int threads = lanes <= 64u ? 64 : lanes <= 128u ? 128 : lanes <= 256u ? 256
+                        : lanes > 512u && one_each ? 1024 : 512;
 #define ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, T)                                                               \
     hipLaunchKernelGGL((layer_fused_kernel<OFFT, W, STRIDE, T>), dim3((unsigned)layer_fused_groups(gr, S)), \
                        dim3(T), lds_bytes, stream, view_of<OFFT>(gr), a)
 #define ND_LAYER_LAUNCH(OFFT, W, STRIDE)                       \
     do {                                                       \
-        if (wide) ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 1024);    \
-        else ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 512);          \
+        if (threads == 64) ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 64);        \
+        else if (threads == 128) ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 128); \
+        else if (threads == 256) ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 256); \
+        else if (threads == 512) ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 512); \
+        else ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, 1024);                    \
     } while (0)
     if (gr.off64) {
         if (weighted) ND_LAYER_LAUNCH(int64_t, true, 2);

@@ -174,7 +174,9 @@ def test_more_walks_than_one_launch_counts_for_fit_the_static_scratch(app, steps
 
 
 @pytest.mark.parametrize("per,fanout,S", [(1, [1], 1), (64, [512], 513), (64, [513, 7], 512), (3, [513, 600], 513),
-                                          (512, [4096, 512], 2), (4096, [9, 4096], 2), (2, [3], 16_500)])
+                                          (512, [4096, 512], 2), (4096, [9, 4096], 2), (2, [3], 16_500),
+                                          (63, [64], 5), (65, [3, 64], 5), (128, [2, 1], 3), (4, [129], 3),
+                                          (256, [5], 3), (257, [256], 3), (1, [513, 512], 300), (4096, [514], 257)])
 def test_layer(graph, per, fanout, S):
     g, dg, og = graph
     roots = _roots(g.V, per * S, 7)

@@ -88,3 +88,15 @@ def test_membership_tables_are_made_on_the_device_of_the_graph(program):
     graph = (V + 1) * 8 + E * 4 + E * 16
     got = program(B.ND_NODE2VEC, 10, V=V, E=E, num_steps=2, device=1)
     assert got["allocated"] == [graph + _tables(V, E)] and got["device"] == [1]
+
+
+@pytest.mark.parametrize("per,fanout,samples,lanes", [
+    (4, [7], 50_000, 64), (64, [64, 64], 3, 64), (65, [1], 9, 128), (1, [128, 3], 300, 128), (2, [129], 1, 256),
+    (256, [256], 9000, 256), (64, [512, 512], 2000, 512), (512, [2048], 300, 512), (512, [2048], 256, 1024),
+    (4096, [4096, 512], 257, 1024), (4096, [512], 257, 512), (64, [4096], 257, 512)])
+def test_layer_samples_take_as_many_lanes_as_they_have_transits_and_draws(program, per, fanout, samples, lanes):
+    """A workgroup that is wider than its sample keeps others from the compute unit (50,000 samples of 4 transits and
+    7 draws took 210 us with 512 lanes each, 140 step by step); the widest where a unit has one sample at a time."""
+    got = program(B.ND_LAYER, samples * per, fanout=fanout, roots_per_sample=per)
+    assert got["static"] == [0] and len(got["launches"]) >= 1
+    assert f"Li{lanes}EE" in got["launches"][0] and "layer_fused" in got["launches"][0]
