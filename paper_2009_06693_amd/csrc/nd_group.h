@@ -1,4 +1,4 @@
-// Groups of lanes that work on one sample: half a wavefront, a wavefront, or a workgroup of four.
+// Groups of lanes that work on one sample: half a wavefront, a wavefront, or a workgroup of several.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,11 +27,11 @@ __device__ __forceinline__ int group_or(int x, uint64_t group_lanes) {
 // true when x is true in any lane of a group inside one wavefront; orders nothing
 template <int THREADS>
 __device__ __forceinline__ bool group_any(bool x, uint64_t group_lanes) {
-    static_assert(THREADS <= 64 || THREADS == 256, "groups of more than a wavefront do not call it");
+    static_assert(THREADS <= 64, "groups of more than a wavefront do not call it");
     return (__ballot(x) & group_lanes) != 0ull;
 }
 // A queue place for every lane with flag set (any order).  A group inside one wavefront counts in a
-// register (*fill, the same in all its lanes); a four-wavefront group counts in LDS (*fill_lds).
+// register (*fill, the same in all its lanes); a group of several wavefronts counts in LDS (*fill_lds).
 // Every lane of the group calls it, in converged code.
 template <int THREADS>
 __device__ __forceinline__ uint32_t group_reserve(bool flag, uint64_t group_lanes, uint32_t* fill, uint32_t* fill_lds) {

@@ -200,12 +200,13 @@ __host__ __device__ inline uint32_t unique_group_bytes(uint32_t slots, uint32_t 
 }
 
 template <int STRIDE, typename OffT, int THREADS, int PER>
-__global__ __launch_bounds__(THREADS <= 64 ? 64 : 256, THREADS <= 64 ? 8 : 4)
+__global__ __launch_bounds__(THREADS <= 64 ? 64 : THREADS, THREADS <= 64 ? 8 : 4)
 void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     constexpr uint32_t SUBS = THREADS <= 64 ? 64 / THREADS : 1;  // groups (samples in flight) per workgroup
+    constexpr int kLanes = THREADS <= 64 ? THREADS : 64;         // lanes of a group within one wavefront
     __shared__ uint32_t s_live[ND_MAX_FANOUT_STEPS];
-    __shared__ uint32_t q_fill[2];            // queue lengths of a four-wavefront group
+    __shared__ uint32_t q_fill[2];            // queue lengths of a group of several wavefronts
     const uint32_t sub = threadIdx.x / (uint32_t)THREADS;
     const uint32_t tix = threadIdx.x % (uint32_t)THREADS;  // my place in the group
     const uint64_t group_lanes = THREADS == 32 ? 0xFFFFFFFFull << (threadIdx.x & 32u) : ~0ull;
@@ -360,59 +361,72 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
             // ---- rounds.  The generator's quarter-rate multiplies are what a round pays for most, and it costs
             // a wavefront the same for one open slot as for 64.  So when at most half the lanes have a slot, the
             // others draw the same slots' next attempts: one pass of the generator and one fetch serve two, four
-            // or eight rounds, which then only take their candidates from the lanes that hold them.
+            // or eight rounds, which then only take their candidates from the lanes that hold them.  A group of
+            // several wavefronts leaves its last 64 open slots to the first one, whose rounds need no barriers: slots
+            // that cannot win (two neighbours, one held elsewhere) stay open for all rounds, and with four barriers
+            // of 256 lanes each, 64 rounds of [10,10,10] from 30,000 vertices of a ring took 3.5 ms, 2.3 in a kernel
+            // per hop whose narrow hops run in one wavefront, 1.9 like this (1.5 with 128 lanes).
             while (r < a.rounds && L > 0) {
-                if (THREADS <= 64 && L <= (uint32_t)THREADS / 2u && r + 1 < a.rounds) {
-                    const uint32_t lg = L <= (uint32_t)THREADS / 8u ? 3u : L <= (uint32_t)THREADS / 4u ? 2u : 1u;
-                    const uint32_t span = (uint32_t)THREADS >> lg;  // lanes per attempt
-                    const uint32_t e = tix & (span - 1u);
-                    const int32_t mine = r + (int32_t)(tix / span);
-                    uint32_t j = 0, pj = 0;
-                    uint2 row = make_uint2(0u, 0u), vrow = make_uint2(0u, 0u);
-                    int32_t v = ND_NULL_VERTEX;
-                    if (e < L && mine < a.rounds) {
-                        j = queue[cur][e];
-                        pj = fastdiv(j, a.div_m[hop]);
-                        row = rows[pj];
-                        if (p_held[pj] < row.y) v = fetch(row, j, (uint32_t)mine, &vrow);
+                if (THREADS > 64 ? L <= (uint32_t)kLanes : L <= (uint32_t)kLanes / 2u && r + 1 < a.rounds) {
+                    if (THREADS <= 64 || tix < (uint32_t)kLanes) {
+                        do {
+                            const uint32_t lg = L <= (uint32_t)kLanes / 8u   ? 3u
+                                                : L <= (uint32_t)kLanes / 4u ? 2u
+                                                : L <= (uint32_t)kLanes / 2u ? 1u
+                                                                             : 0u;
+                            const uint32_t span = (uint32_t)kLanes >> lg;  // lanes per attempt
+                            const uint32_t e = tix & (span - 1u);
+                            const int32_t mine = r + (int32_t)(tix / span);
+                            uint32_t j = 0, pj = 0;
+                            uint2 row = make_uint2(0u, 0u), vrow = make_uint2(0u, 0u);
+                            int32_t v = ND_NULL_VERTEX;
+                            if (e < L && mine < a.rounds) {
+                                j = queue[cur][e];
+                                pj = fastdiv(j, a.div_m[hop]);
+                                row = rows[pj];
+                                if (p_held[pj] < row.y) v = fetch(row, j, (uint32_t)mine, &vrow);
+                            }
+                            bool open = tix < span && v >= 0;  // lane e speaks for slot e
+                            for (uint32_t i = 0; i < (1u << lg) && r < a.rounds; ++i, ++r) {
+                                const int from = (int)((threadIdx.x & 63u) - tix + i * span + e);
+                                const int32_t c = __shfl(v, from, 64);
+                                const uint2 cr = make_uint2((uint32_t)__shfl((int)vrow.x, from, 64),
+                                                            (uint32_t)__shfl((int)vrow.y, from, 64));
+                                // as many distinct vertices as the parent's row has entries: nothing left to draw
+                                open = open && p_held[pj] < row.y;
+                                if (!group_any<kLanes>(open, group_lanes)) {
+                                    r = a.rounds;
+                                    break;
+                                }
+                                if (open) s_res[j] = c;
+                                group_sync<kLanes>();
+                                uint32_t at = 0;
+                                if (open) at = propose(c, j);
+                                group_sync<kLanes>();
+                                const bool win = open && table[at] == kOpen + j;
+                                group_sync<kLanes>();          // every claim has been read
+                                if (win) {
+                                    table[at] = j;
+                                    if (!last) next[j] = cr;
+                                    atomicAdd(&p_held[pj], 1u);
+                                } else if (open) {
+                                    s_res[j] = ND_NULL_VERTEX;
+                                }
+                                open = open && !win;
+                                group_sync<kLanes>();
+                            }
+                            fill = 0;
+                            const uint32_t at = group_reserve<kLanes>(open, group_lanes, &fill, nullptr);
+                            if (open) queue[cur ^ 1u][at] = (uint16_t)j;
+                            group_sync<kLanes>();
+                            cur ^= 1u;
+                            L = fill;
+                            if (THREADS >= 64) L = wave_uniform(L);
+                        } while (THREADS > 64 && r < a.rounds && L > 0);
                     }
-                    bool open = tix < span && v >= 0;  // lane e speaks for slot e
-                    for (uint32_t i = 0; i < (1u << lg) && r < a.rounds; ++i, ++r) {
-                        const int from = (int)((threadIdx.x & 63u) - tix + i * span + e);
-                        const int32_t c = __shfl(v, from, 64);
-                        const uint2 cr = make_uint2((uint32_t)__shfl((int)vrow.x, from, 64),
-                                                    (uint32_t)__shfl((int)vrow.y, from, 64));
-                        // as many distinct vertices as the parent's row has entries: nothing left to draw
-                        open = open && p_held[pj] < row.y;
-                        if (!group_any<THREADS>(open, group_lanes)) {
-                            r = a.rounds;
-                            break;
-                        }
-                        if (open) s_res[j] = c;
-                        group_sync<THREADS>();
-                        uint32_t at = 0;
-                        if (open) at = propose(c, j);
-                        group_sync<THREADS>();
-                        const bool win = open && table[at] == kOpen + j;
-                        group_sync<THREADS>();          // every claim has been read
-                        if (win) {
-                            table[at] = j;
-                            if (!last) next[j] = cr;
-                            atomicAdd(&p_held[pj], 1u);
-                        } else if (open) {
-                            s_res[j] = ND_NULL_VERTEX;
-                        }
-                        open = open && !win;
-                        group_sync<THREADS>();
-                    }
-                    fill = 0;
-                    const uint32_t at = group_reserve<THREADS>(open, group_lanes, &fill, nullptr);
-                    if (open) queue[cur ^ 1u][at] = (uint16_t)j;
+                    if (THREADS <= 64) continue;
                     group_sync<THREADS>();
-                    cur ^= 1u;
-                    L = fill;
-                    if (THREADS == 64) L = wave_uniform(L);
-                    continue;
+                    break;  // the other wavefronts' L and r are those of the first one's start
                 }
                 uint32_t jq[PER];
 #pragma unroll
@@ -642,8 +656,13 @@ UniqueShape unique_shape(const Graph& gr, const int32_t* fanout, int32_t k, int6
         if (i + 1 < k && W[i] > rows) rows = W[i];
     }
     UniqueShape u;
-    // half a wavefront per sample up to 32 slots, a whole one up to 256, four above
-    u.threads = widest <= 32 ? 32 : widest <= 256 ? 64 : 256;
+    // Half a wavefront per sample up to 32 slots, a whole one up to 256.  Above, four where samples are few and
+    // the time is that of one, two where they are many and what counts is how long lanes wait at barriers:
+    // [25,20] of 1,000 vertices of a 57 K-vertex graph take 21.7 us with four and 25.1 with two, 3,000 44 and 34,
+    // 20,000 220 and 150 (145 with one); [30,30] of 3,000 54 and 59, of 10,000 144 and 139, of 20,000 271 and 253.
+    // Above 1,024 slots two would keep 16 slots per lane in registers.
+    const bool many = S >= (int64_t)gr.num_cus * (widest <= 512 ? 8 : 32);
+    u.threads = widest <= 32 ? 32 : widest <= 256 ? 64 : widest <= 1024 && many ? 128 : 256;
     u.slots = 32;
     while (u.slots < widest) u.slots <<= 1;
     u.rows = (uint32_t)(rows + 1) / 2 * 2;
@@ -695,7 +714,7 @@ int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32
     a.o_parts = o_parts;
     mark_phase(ND_PHASE_UNIQUE, stream);
 #define ND_UNIQUE_GO(STRIDE, OFFT, THREADS, PER)                                                                   \
-    hipLaunchKernelGGL((khop_unique_kernel<STRIDE, OFFT, THREADS, PER>), dim3((unsigned)u.groups), dim3(THREADS <= 64 ? 64 : 256), u.lds, \
+    hipLaunchKernelGGL((khop_unique_kernel<STRIDE, OFFT, THREADS, PER>), dim3((unsigned)u.groups), dim3(THREADS <= 64 ? 64 : THREADS), u.lds, \
                        stream, view_of<OFFT>(gr), a)
 #define ND_UNIQUE_SIZE(STRIDE, OFFT)                                    \
     do {                                                                \
@@ -703,6 +722,8 @@ int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32
         else if (u.slots <= 64) ND_UNIQUE_GO(STRIDE, OFFT, 64, 1);      \
         else if (u.slots <= 128) ND_UNIQUE_GO(STRIDE, OFFT, 64, 2);     \
         else if (u.slots <= 256) ND_UNIQUE_GO(STRIDE, OFFT, 64, 4);     \
+        else if (u.threads == 128 && u.slots <= 512) ND_UNIQUE_GO(STRIDE, OFFT, 128, 4); \
+        else if (u.threads == 128) ND_UNIQUE_GO(STRIDE, OFFT, 128, 8);  \
         else if (u.slots <= 512) ND_UNIQUE_GO(STRIDE, OFFT, 256, 2);    \
         else if (u.slots <= 1024) ND_UNIQUE_GO(STRIDE, OFFT, 256, 4);   \
         else ND_UNIQUE_GO(STRIDE, OFFT, 256, 8);                        \

@@ -341,3 +341,31 @@ def test_node2vec_over_a_hub_takes_no_longer_than_in_windows():
     assert all(torch.equal(x, y) for x, y in zip(a, b))
     print(f"[times] over links {links:.2f} ms, in windows {windows:.2f} ms", flush=True)
     assert links < 1.1 * windows
+
+
+@pytest.mark.parametrize("fanout,S", [([257], 2048), ([512], 2047), ([32, 16], 2048), ([5, 171], 2048),
+                                      ([1024], 8191), ([10, 10, 10], 8192), ([1, 1025], 8192)])
+def test_unique_neighbours_of_many_samples(graph, fanout, S):
+    """Two wavefronts per sample up to 1,024 slots, four above and for few samples; rounds that one wavefront ends."""
+    g, dg, og = graph
+    roots = _roots(g.V, S, 3)
+    want = oracle.khop(og, roots, fanout, seed=8, unique_rounds=6)
+    got, _ = gpu_sample(dg, B.ND_KHOP, roots, 8, num_steps=len(fanout), fanout=fanout, unique_rounds=6)
+    assert_steps_equal(got, want, f"unique {fanout} S={S}")
+
+
+@pytest.mark.parametrize("fanout,rounds,S", [([10, 10, 10], 64, 30_000), ([25, 20], 4, 57_000)])
+def test_unique_neighbours_take_no_longer_than_hop_by_hop(fanout, rounds, S):
+    """On a ring most slots find nothing that is not held and stay open for all rounds."""
+    if rounds == 64:
+        V = 100_000
+        g = inputs.from_edges(V, sorted({(v, (v + d) % V) for v in range(V) for d in (1, V - 1)}))
+    else:
+        g = inputs.config2_graph()
+    dg = B.nd_graph_create(g.row_offsets, g.col_indices, None)
+    r = torch.as_tensor(inputs.all_vertices_roots(g)[:S], device="cuda:0")
+    (links, a), (hops, b) = (_least_time(dg, B.ND_KHOP, B.nd_params_init(
+        num_steps=len(fanout), fanout=fanout, unique_rounds=rounds, sched_window=window), r) for window in (0, -1))
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    print(f"[times] all hops {links:.3f} ms, hop by hop {hops:.3f} ms", flush=True)
+    assert links < 1.1 * hops
