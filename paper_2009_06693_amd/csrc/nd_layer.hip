@@ -165,6 +165,7 @@ __device__ __forceinline__ uint64_t column_weight(uint32_t deg) {
 // them, a draw was three dependent fetches and a third array: 257 samples of [512, 512] over 2.9 M vertices took
 // 31.4 us, 97 on a graph not looked at before; now 30.9 and 76.
 __device__ __forceinline__ Link guided_search(const Link* row, uint32_t deg, uint64_t rest, uint64_t total) {
+    if (deg == 1u) return row[0];
     return drawn_link(row, deg, scaled_threshold(rest, total));
 }
 

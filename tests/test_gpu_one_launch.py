@@ -369,3 +369,25 @@ def test_unique_neighbours_take_no_longer_than_hop_by_hop(fanout, rounds, S):
     assert all(torch.equal(x, y) for x, y in zip(a, b))
     print(f"[times] all hops {links:.3f} ms, hop by hop {hops:.3f} ms", flush=True)
     assert links < 1.1 * hops
+
+
+@pytest.mark.parametrize("int64_offsets", [False, True])
+def test_weighted_draws_from_rows_whose_weights_span_decades(int64_offsets):
+    """Guide cells of every length, first, last and only ones of a row among them: what two looks do not find is
+    searched for up to the next cell's guide."""
+    V = 2100
+    rng = np.random.default_rng(15)
+    pairs = [(a, (a + j) % V) for a in range(V) for j in range((1, 2, 3, 40, 700, 2000)[a % 6] if a < 60 else 5)]
+    pairs = sorted(pairs)
+    w = np.minimum(10.0 ** (6.5 * rng.random(len(pairs)) - 4.0), 30_000.0).astype(np.float32)
+    g = inputs.from_edges(V, pairs, weights=w, int64_offsets=int64_offsets)
+    dg, og = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights), \
+        oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    roots = (np.arange(6000) % 60).astype(np.int32)
+    got, _ = gpu_sample(dg, B.ND_DEEPWALK, roots, 24, num_steps=4, use_weights=1)
+    assert_steps_equal(got, list(oracle.deepwalk(og, roots, 4, seed=24, use_weights=True)), "deepwalk")
+    for per, fanout in ((1, [600, 30]), (60, [900])):
+        want = oracle.layer(og, roots[:600], per, fanout, seed=25, use_weights=True)
+        got, _ = gpu_sample(dg, B.ND_LAYER, roots[:600], 25, num_steps=len(fanout), fanout=fanout,
+                            roots_per_sample=per, use_weights=1)
+        assert_steps_equal(got, want, f"layer {per} {fanout}")
