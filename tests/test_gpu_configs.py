@@ -63,15 +63,19 @@ def _windows(n, width, count, seed):
     return [(a, min(n, a + width)) for a in starts]
 
 
+WALK_ROUTES = (dict(mode=TP), dict(mode=TP, sched_window=256), dict(mode=TP, sched_window=1024),
+               dict(mode=TP, sched_window=-1), dict(mode=SP))
+
+
 def test_config1_deepwalk_full():
     g = inputs.config1_graph()
     dg = B.nd_graph_create(g.row_offsets, g.col_indices)
     og = oracle.OracleGraph(g.row_offsets, g.col_indices)
     roots = inputs.all_vertices_roots(g)
     want = oracle.deepwalk(og, roots, 100, seed=1)
-    # transit-parallel with the grouping per window (the default for walks), with the GPU-wide
-    # grouping of Section 6.1.2, and sample-parallel
-    for kw in (dict(mode=TP), dict(mode=TP, sched_window=-1), dict(mode=SP)):
+    # over the graph's links (the default for walks), grouped per window, with the GPU-wide grouping
+    # of Section 6.1.2, and sample-parallel
+    for kw in WALK_ROUTES:
         _, out = _run(dg, B.ND_DEEPWALK, roots, 1, num_steps=100, **kw)
         assert_steps_equal([o.cpu().numpy() for o in out], list(want), f"config 1 {kw}")
 
@@ -82,11 +86,11 @@ def test_config2_node2vec_and_ppr_full():
     og = oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
     roots = inputs.all_vertices_roots(g)
     want = oracle.node2vec(og, roots, 100, 2.0, 0.5, seed=2, use_weights=True)
-    for kw in (dict(mode=TP), dict(mode=TP, sched_window=-1), dict(mode=SP)):
+    for kw in WALK_ROUTES:
         _, out = _run(dg, B.ND_NODE2VEC, roots, 2, num_steps=100, p=2.0, q=0.5, use_weights=1, **kw)
         assert_steps_equal([o.cpu().numpy() for o in out], list(want), f"config 2 node2vec {kw}")
     want = oracle.ppr(og, roots, 100, 0.01, seed=2, use_weights=True)
-    for kw in (dict(mode=TP), dict(mode=TP, sched_window=-1), dict(mode=SP)):
+    for kw in WALK_ROUTES:
         s, out = _run(dg, B.ND_PPR, roots, 2, num_steps=100, term_prob=0.01, use_weights=1, **kw)
         assert_steps_equal([o.cpu().numpy() for o in out], list(want), f"config 2 ppr {kw}")
     # mean walk length under termination probability 0.01 with cap 100 is about 63
