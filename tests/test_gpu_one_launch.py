@@ -391,3 +391,22 @@ def test_weighted_draws_from_rows_whose_weights_span_decades(int64_offsets):
         got, _ = gpu_sample(dg, B.ND_LAYER, roots[:600], 25, num_steps=len(fanout), fanout=fanout,
                             roots_per_sample=per, use_weights=1)
         assert_steps_equal(got, want, f"layer {per} {fanout}")
+
+
+@pytest.mark.parametrize("degree,fanout,grouped", [(120, [10, 100], True), (119, [10, 100], False), (120, [7, 143], False),
+                                                   (130, [10, 99], False), (80, [16, 44], True), (79, [16, 44], False),
+                                                   (80, [16, 43], False)])
+def test_khop_groups_where_the_graph_is_dense_and_pairs_are_many(degree, fanout, grouped):
+    """Both sides of the rule's lines (20 and 14 M draws, 8 and 16 pairs per vertex); the routes agree."""
+    V = 20_000
+    v = torch.arange(V, device="cuda:0")
+    col = ((v[:, None] + 3 * torch.arange(1, degree + 1, device="cuda:0")) % V).sort(dim=1).values
+    dg = B.nd_graph_create(torch.arange(V + 1, device="cuda:0") * degree, col.reshape(-1).to(torch.int32))
+    r = torch.randperm(V, device="cuda:0").to(torch.int32)
+    outs = []
+    for window in (0, -1):
+        s = B.Sampler(dg, B.ND_KHOP, B.nd_params_init(num_steps=2, fanout=fanout, sched_window=window), V)
+        outs.append(s.run(r, 26))
+        torch.cuda.synchronize()
+        assert (s.stats()[1, 1] > 0) == (grouped or window == -1)
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
