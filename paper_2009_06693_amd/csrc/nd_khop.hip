@@ -564,7 +564,7 @@ void slots_per_sample(const int32_t* fanout, int32_t k, int64_t* W) {
 // scattered fetch per line a pair's draws touch, whatever other pairs touch; grouping by transit fetches a
 // line once for all its draws and pays for it with the sort and with scattered stores.  Measured from
 // all, a tenth and a fiftieth of the vertices of ten graphs with fanouts [25,10], [10,10], [10,25], [20] and
-// [15,10,5] (profiles/dispatch_rules.md): grouping wins, by up to 1.4x, on dense graphs (rows that ten draws
+// [15,10,5]: grouping wins, by up to 1.4x, on dense graphs (rows that ten draws
 // rarely share a line of) with many pairs per vertex and enough draws to pay for its 26 launches; elsewhere it
 // loses, by up to 9x.  At the lines, over links and grouped: mean degree 145, 10 pairs per vertex, 23 M draws 325
 // and 286 us, 58 M 565 and 426; degree 93, 26 M 262 and 275; degree 204, 25 pairs, 14 M 172 and 160; degree 869, 25
