@@ -249,7 +249,7 @@ void layout(Plan* pl, const Graph& g, const nd_params* p) {
         pl->o_flags = o; o = align_up(o + (size_t)layer_fused_groups(g, pl->S) * 4);
     } else if (pl->free_walk) {
         const uint32_t R = pl->app == ND_MULTIRW ? (uint32_t)p->roots_per_sample : 0u;
-        const size_t groups = (size_t)walk_free_groups(pl->S, pl->k, R);
+        const size_t groups = (size_t)walk_free_groups(pl->S, pl->k, pl->app == ND_NODE2VEC, R);
         if (pl->S > 0) o = pl->o_ctl;  // a call that launches this route has no control blocks
         pl->o_state = o; o = align_up(o + (size_t)walk_free_state_bytes(pl->S, pl->k, R));
         pl->o_flags = o; o = align_up(o + groups * 4);

@@ -208,7 +208,8 @@ bool spare_room(size_t bytes) {
 // Room for the links.  Optional: without them walks and k-hop take longer.
 void allocate_links(Graph* g, bool weighted) {
     if (g->E < 1 || g->E >= (1ll << 31)) return;
-    const size_t bytes = (size_t)g->E * sizeof(Link) * (weighted ? 2 : 1);
+    // one entry more, never written: where a walk looks that stands on an empty row behind all others
+    const size_t bytes = (size_t)(g->E + 1) * sizeof(Link) * (weighted ? 2 : 1);
     if (spare_room(bytes) && hipMalloc((void**)&g->links, bytes) != hipSuccess) {
         (void)hipGetLastError();
         g->links = nullptr;

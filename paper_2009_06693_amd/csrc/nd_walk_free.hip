@@ -7,6 +7,8 @@
 // or the rate of scattered fetches (many).  Both are cut by the graph's Links: the edge that is drawn
 // carries the row of its end vertex, so a step is one fetch instead of two dependent ones, and a lane
 // keeps its walk in registers from the first step to the last, with no barrier in between.
+#include <utility>
+
 #include "nd_common.h"
 #include "nd_philox.h"
 #include "nd_wave.h"
@@ -18,6 +20,7 @@ namespace nd {
 namespace {
 
 constexpr int kFreeChunk = 128;  // steps per launch: their output pointers are kernel arguments
+constexpr int kFewThreads = 256, kFewLanes = 16;  // few walks: threads per workgroup, lanes per walk
 
 struct FreeArgs {
     const Link* links;
@@ -87,13 +90,16 @@ __device__ __forceinline__ int32_t first_transit(const FreeArgs& a, uint32_t s) 
 }
 
 // DeepWalk and PPR.  Many walks: bound by the scattered 128-byte fetches of the links (one per draw;
-// the chip serves 5.5e10 of them per second whatever the array's size).  Few walks: by the chain of a
-// step, 0.41 us.  The generator needs nothing of the link, but as compiled (ROCm 7.2) its ten rounds for
-// the next step come after the wait for the link and the store of its vertex, so the chain is their sum.
+// the chip serves 5.5e10 of them per second whatever the array's size, once it exceeds L2).  Fewer: by the chain of a
+// step, 0.27 us from L2.  While a link is on its way, the vertex of the step before is stored and the words of the
+// next step are made; the assembler statement keeps the compiler (ROCm 7.2) from moving their making behind the wait for
+// the link, where it and the acknowledged store were part of the chain (32,768 walks of 100 steps over 1.5 MB of
+// links 37 us, like this 29; over 1.1 GB 72 and 60).
 template <int DRAW, int STRIDE, typename OffT, int THREADS>
 __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
-    const uint32_t s = a.s_first + blockIdx.x * (uint32_t)THREADS + threadIdx.x;
+    const uint32_t at = a.s_first + blockIdx.x * (uint32_t)THREADS + threadIdx.x;
+    const uint32_t s = at < a.S ? at : a.S - 1u;  // lanes past the last sample walk and write with it
     int32_t v = first_transit<THREADS>(a, s);
     uint32_t rs = 0, deg = 0;
     if (v >= 0) {
@@ -115,13 +121,92 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
             if (DRAW == kDrawUniform) l = a.links[(uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE];
             else l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r.r0, r.r1));
         }
+        if (si > 0) a.out[si - 1u][s] = v;  // after the load, which the next wait is for
         r = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
+        asm volatile("" : "+v"(r.r0), "+v"(r.r1), "+v"(r.r3));
         v = l.v;
         rs = l.rs;
         deg = l.deg;
-        if (s < a.S) a.out[si][s] = v;
     }
-    publish_live<THREADS>(lived, a, s_hist);
+    a.out[a.n_steps - 1u][s] = v;
+    publish_live<THREADS>(at < a.S ? lived : 0u, a, s_hist);
+}
+
+// The value that lane I of every row of 16 lanes holds, in all of them.
+template <int I>
+__device__ __forceinline__ uint32_t from_lane(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + I, 0xf, 0xf, true);  // row_newbcast
+}
+
+template <int... I, typename F>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F& f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// DeepWalk and PPR where walks are few, so that the time is that of one walk: 16 lanes per walk.  The words of a
+// step depend on nothing that the walk does, so each lane makes those of one step in 16, and all 16 lanes
+// take the walk's step with them (same link, one fetch); what is left of a step's chain is the multiplication, the
+// link's fetch (110 ns from L2, 350 from the last-level cache) and three selections.  The words of the next 16 steps and
+// the vertices of the last 16 leave while a link is on its way.  4,096 walks of 100 steps over 1.5 MB of links: 36.5 us
+// with a lane per walk that made its words between two links, 18.6 like this.
+template <int DRAW, int STRIDE, typename OffT>
+__global__ __launch_bounds__(kFewThreads) void walk_few_kernel(GraphView<OffT> g, FreeArgs a) {
+    __shared__ uint32_t s_hist[kFreeChunk + 1];
+    constexpr int L = kFewLanes;
+    static_assert(L == 16, "from_lane");
+    const uint32_t k = threadIdx.x & (uint32_t)(L - 1);
+    const uint32_t at = a.s_first + blockIdx.x * (uint32_t)(kFewThreads / L) + threadIdx.x / (uint32_t)L;
+    const uint32_t s = at < a.S ? at : a.S - 1u;  // lanes past the last sample walk and write with it
+    int32_t v = first_transit<kFewThreads>(a, s);
+    uint32_t rs = 0, deg = 0;
+    if (v >= 0) {
+        const uint64_t r = (uint64_t)g.off[v];
+        rs = (uint32_t)r;
+        deg = row_length(g, v, r);
+    }
+    const uint32_t sid = a.sample_base + s;
+    uint32_t lived = 0;
+    int32_t mine = ND_NULL_VERTEX;                              // the vertex of step base + k
+    Rand4 next = draw4(a.seed, sid, 0u, a.first_step + k, 0u);  // the words of step base + k
+    uint32_t base = 0;
+    for (;; base += (uint32_t)L) {
+        const Rand4 r = next;
+        uint32_t last = (uint32_t)L;                            // the walk stops before step base + last
+        if (a.ppr_thr != 0) {
+            const uint64_t stops = __ballot((uint64_t)r.r3 < a.ppr_thr) >> (threadIdx.x & 63u & ~(uint32_t)(L - 1));
+            last = (uint32_t)__builtin_ctz((uint32_t)stops | (1u << L));
+        }
+        int32_t* const before = base > 0 ? a.out[base - (uint32_t)L + k] : nullptr;
+        auto step = [&](auto index) {
+            constexpr int I = decltype(index)::value;
+            if (base + (uint32_t)I >= a.n_steps) return;  // the same for the whole launch
+            lived += v >= 0 ? 1u : 0u;
+            const bool draws = deg > 0u && (uint32_t)I < last;
+            const uint32_t r0 = from_lane<I>(r.r0);
+            Link l;
+            if (DRAW == kDrawUniform) {
+                // a walk that has ended looks again where it stood: no branch on the way to the load
+                l = a.links[(uint64_t)(rs + mulhi32(r0, deg)) * STRIDE];
+            } else {
+                l.v = ND_NULL_VERTEX;
+                l.rs = l.deg = 0;
+                if (draws) l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r0, from_lane<I>(r.r1)));
+            }
+            if (I == 0) {
+                if (base > 0) before[s] = mine;
+                next = draw4(a.seed, sid, 0u, a.first_step + base + (uint32_t)L + k, 0u);
+                asm volatile("" : "+v"(next.r0), "+v"(next.r1), "+v"(next.r3));
+            }
+            v = draws ? l.v : ND_NULL_VERTEX;
+            rs = draws ? l.rs : rs;
+            deg = draws ? l.deg : 0u;
+            mine = k == (uint32_t)I ? v : mine;
+        };
+        unrolled(std::make_integer_sequence<int, L>{}, step);
+        if (base + (uint32_t)L >= a.n_steps) break;
+    }
+    if (base + k < a.n_steps) a.out[base + k][s] = mine;
+    publish_live<kFewThreads>(k == 0 && at < a.S ? lived : 0u, a, s_hist);
 }
 
 // ---------------------------------------------------------------- node2vec
@@ -503,6 +588,18 @@ void launch_mrw(const Graph& gr, const FreeArgs& a, uint32_t groups, hipStream_t
 // they are alike.
 int mrw_waves(uint32_t R) { return R <= 256u ? 16 : R <= 1024u ? 4 : 1; }
 
+template <typename OffT>
+void launch_few(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
+    const dim3 grid(groups), block(kFewThreads);
+    const GraphView<OffT> g = view_of<OffT>(gr);
+    if (draw == kDrawWeighted)
+        hipLaunchKernelGGL((walk_few_kernel<kDrawWeighted, 2, OffT>), grid, block, 0, stream, g, a);
+    else if (gr.wq)
+        hipLaunchKernelGGL((walk_few_kernel<kDrawUniform, 2, OffT>), grid, block, 0, stream, g, a);
+    else
+        hipLaunchKernelGGL((walk_few_kernel<kDrawUniform, 1, OffT>), grid, block, 0, stream, g, a);
+}
+
 template <int THREADS, typename OffT>
 void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
     const dim3 grid(groups), block(THREADS);
@@ -529,7 +626,17 @@ void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, 
 // us, 539 with one).
 static int free_threads(int64_t S) { return S <= 65536 ? 64 : 256; }
 
-static int64_t samples_per_group(int64_t S, uint32_t mrw_R) { return mrw_R > 0 ? mrw_waves(mrw_R) : free_threads(S); }
+// DeepWalk and PPR up to this many walks: sixteen lanes per walk (walk_few_kernel).  100 steps, sixteen lanes and
+// one, us: over links that L2 holds (1.5 MB) 18.6 and 28.1 for 4,096 walks, 20.8 and 28.4 for 8,192, 25.6 and 28.9 for
+// 16,384, 39 and 29 for 32,768; over 1.1 GB 18.3 and 27.4 for 1,024, 34 and 39 for 4,096, 38.1 and 39.5 for 8,192,
+// 42.6 and 40.8 for 16,384.
+constexpr int64_t kFewWalks = 8192;
+static bool few_walks(int64_t S, bool node2vec) { return !node2vec && S <= kFewWalks; }
+
+static int64_t samples_per_group(int64_t S, bool node2vec, uint32_t mrw_R) {
+    if (mrw_R > 0) return mrw_waves(mrw_R);
+    return few_walks(S, node2vec) ? kFewThreads / kFewLanes : free_threads(S);
+}
 
 // Bytes of the workspace that hold a multi-dimensional walk's roots between two launches.
 int64_t walk_free_state_bytes(int64_t S, int32_t num_steps, uint32_t mrw_R) {
@@ -541,8 +648,8 @@ int64_t walk_free_state_bytes(int64_t S, int32_t num_steps, uint32_t mrw_R) {
 // walks) of 100 steps, or 1,535 of the 4,096 steps that a call may have.  No call may need more of the
 // static scratch array than walks whose scratch is a control block (64 bytes) per step, the roots and a
 // transit per sample of the multi-dimensional walk, so beside many roots the counters take what those took.
-int64_t walk_free_groups(int64_t S, int32_t num_steps, uint32_t mrw_R) {
-    const int64_t per = samples_per_group(S, mrw_R), k = num_steps;
+int64_t walk_free_groups(int64_t S, int32_t num_steps, bool node2vec, uint32_t mrw_R) {
+    const int64_t per = samples_per_group(S, node2vec, mrw_R), k = num_steps;
     int64_t room = (24ll << 20) - walk_free_state_bytes(S, num_steps, mrw_R);
     const int64_t least = 64 * k + (mrw_R > 0 ? 4 * S : 0);
     if (room < least) room = least;
@@ -575,7 +682,9 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.total_steps = (uint32_t)num_steps;
     a.o_flags = o_flags;
     a.o_parts = o_parts;
-    const int64_t per = samples_per_group(S, mrw_R), most = walk_free_groups(S, num_steps, mrw_R);  // S >= 1
+    const bool node2vec = draw == kDrawNode2vec;
+    const int64_t per = samples_per_group(S, node2vec, mrw_R);
+    const int64_t most = walk_free_groups(S, num_steps, node2vec, mrw_R);  // S >= 1
     for (int64_t s = 0; s < S; s += most * per) {
         const int64_t left = (S - s + per - 1) / per;
         const uint32_t groups = (uint32_t)(left < most ? left : most);
@@ -601,6 +710,9 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
                     else if (waves == 4) launch_mrw<4, int32_t>(gr, a, groups, stream);
                     else launch_mrw<1, int32_t>(gr, a, groups, stream);
                 }
+            } else if (few_walks(S, node2vec)) {
+                if (gr.off64) launch_few<int64_t>(gr, draw, a, groups, stream);
+                else launch_few<int32_t>(gr, draw, a, groups, stream);
             } else if (gr.off64) {
                 if (free_threads(S) == 64) launch_free<64, int64_t>(gr, draw, a, groups, stream);
                 else launch_free<256, int64_t>(gr, draw, a, groups, stream);

@@ -102,6 +102,26 @@ def test_walks(graph, steps, S):
         assert_steps_equal(got, list(want), "ppr")
 
 
+@pytest.mark.parametrize("steps,S", [(1, 15), (15, 16), (16, 17), (17, 255), (33, 257), (144, 1000), (31, 8192),
+                                     (31, 8193)])
+def test_walks_of_sixteen_lanes(graph, steps, S):
+    """Up to 8,192 walks: blocks of 16 steps, walks that end at any place inside one, empty rows at the graph's end."""
+    g, dg, og = graph
+    roots = _roots(g.V, S, 14)
+    roots[-1] = g.V - 1
+    for weighted in ((0, 1) if g.weights is not None else (0,)):
+        kw = dict(num_steps=steps, use_weights=weighted, sample_id_base=77)
+        want = oracle.deepwalk(og, roots, steps, seed=15, use_weights=bool(weighted), sample_id_base=77)
+        got, stats = gpu_sample(dg, B.ND_DEEPWALK, roots, 15, **kw)
+        assert_steps_equal(got, list(want), "deepwalk")
+        assert stats[:, 0].tolist() == [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
+        for p in (0.0, 0.1, 1.0):
+            want = oracle.ppr(og, roots, steps, p, seed=16, use_weights=bool(weighted), sample_id_base=77)
+            got, stats = gpu_sample(dg, B.ND_PPR, roots, 16, term_prob=p, **kw)
+            assert_steps_equal(got, list(want), f"ppr {p}")
+            assert stats[:, 0].tolist() == [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
+
+
 @pytest.mark.parametrize("int64_offsets", [False, True])
 @pytest.mark.parametrize("steps,S", [(1, 1), (127, 63), (129, 65), (257, 130), (3, 65537)])
 def test_node2vec(int64_offsets, steps, S):
