@@ -1,5 +1,5 @@
-"""Thin ctypes binding of libnd.so: same names as include/nd.h, argument
-marshalling only.  PyTorch supplies device memory and the current stream;
+"""Thin binding of libnd.so: same names as include/nd.h, argument marshalling only
+(ctypes; the sampling and gathering calls through the compiled module _nd_call).  PyTorch supplies device memory and the current stream;
 every step of the sampling path runs inside the library's HIP kernels.
 
 There is no CPU fallback: if the shared library is missing, loading fails.
@@ -69,11 +69,12 @@ class NdError(RuntimeError):
 
 
 _lib = None
+_call = None
 
 
 def lib() -> ctypes.CDLL:
-    """Loads libnd.so (built in-tree by paper_2009_06693_amd.build)."""
-    global _lib
+    """Loads libnd.so and _nd_call.so (built in-tree by paper_2009_06693_amd.build)."""
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -129,6 +130,14 @@ def lib() -> ctypes.CDLL:
         L.nd_last_error.argtypes = []
         L.nd_version.restype = ctypes.c_int
         L.nd_version.argtypes = []
+        try:
+            from . import _nd_call
+        except ModuleNotFoundError as e:
+            raise FileNotFoundError(f"_nd_call.so is missing beside {__file__}: run "
+                                    "`python -m paper_2009_06693_amd.build`") from e
+        _nd_call.init(*(ctypes.cast(f, vp).value for f in (L.nd_sample, L.nd_sample_static, L.nd_samples_pack)),
+                      ctypes.sizeof(nd_params))
+        _call = _nd_call
         _lib = L
     return _lib
 
@@ -159,8 +168,10 @@ def nd_params_init(**overrides) -> nd_params:
 
 
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle without an object around it (1 us less)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class Graph:
@@ -234,15 +245,11 @@ def nd_sample_query(g: Graph, app: int, params: nd_params, num_roots: int):
 def nd_sample(g: Graph, app: int, params: nd_params, roots: torch.Tensor, seed: int,
               step_out: Sequence[torch.Tensor], workspace: torch.Tensor, stream=None):
     """Asynchronous on the stream; step_out[i] are caller-allocated int32 CUDA tensors."""
-    if roots.dtype != torch.int32 or not roots.is_cuda or not roots.is_contiguous():
-        raise TypeError("roots must be a contiguous int32 CUDA tensor")
-    for t in step_out:
-        if t.dtype != torch.int32 or not t.is_cuda or not t.is_contiguous():
-            raise TypeError("outputs must be contiguous int32 CUDA tensors")
-    arr = (ctypes.c_void_p * len(step_out))(*[t.data_ptr() for t in step_out])
-    _check(lib().nd_sample(g._h, app, ctypes.byref(params), roots.data_ptr(), roots.numel(), seed, arr,
-                           workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                           _stream_ptr(stream)))
+    if _call is None:
+        lib()
+    rc = _call.sample(g._h, app, params, roots, seed, step_out, workspace, _stream_ptr(stream))
+    if rc != ND_OK:
+        _check(rc)
 
 
 ND_STATIC_SCRATCH_BYTES = 32 << 20
@@ -252,15 +259,11 @@ def nd_sample_static(g: Graph, app: int, params: nd_params, roots: torch.Tensor,
                      step_out: Sequence[torch.Tensor], status: Optional[torch.Tensor] = None, stream=None):
     """nd_sample on the library's own scratch array (no workspace, nothing allocated);
     status: optional int32/uint32 CUDA tensor of one element that receives the status word."""
-    if roots.dtype != torch.int32 or not roots.is_cuda or not roots.is_contiguous():
-        raise TypeError("roots must be a contiguous int32 CUDA tensor")
-    for t in step_out:
-        if t.dtype != torch.int32 or not t.is_cuda or not t.is_contiguous():
-            raise TypeError("outputs must be contiguous int32 CUDA tensors")
-    arr = (ctypes.c_void_p * len(step_out))(*[t.data_ptr() for t in step_out])
-    _check(lib().nd_sample_static(g._h, app, ctypes.byref(params), roots.data_ptr(), roots.numel(), seed,
-                                  arr, None if status is None else status.data_ptr(),
-                                  _stream_ptr(stream)))
+    if _call is None:
+        lib()
+    rc = _call.sample_static(g._h, app, params, roots, seed, step_out, status, _stream_ptr(stream))
+    if rc != ND_OK:
+        _check(rc)
 
 
 def nd_sample_status(workspace: torch.Tensor, stream=None):
@@ -314,19 +317,14 @@ def nd_samples_pack(step_out: Sequence[torch.Tensor], num_samples: int, samples:
                     stream=None) -> torch.Tensor:
     """Gathers the per-step arrays of an nd_sample call into one record per sample
     (int32 [num_samples, record])."""
-    k = len(step_out)
-    for o in step_out:
-        if o.dtype != torch.int32 or not o.is_cuda or not o.is_contiguous():
-            raise TypeError("step arrays must be contiguous int32 CUDA tensors")
-    lens = (ctypes.c_int64 * k)(*[int(o.numel()) for o in step_out])
-    ptrs = (ctypes.c_void_p * k)(*[o.data_ptr() for o in step_out])
-    record = sum(int(o.numel()) // num_samples for o in step_out) if num_samples else 0
+    if _call is None:
+        lib()
     if samples is None:
+        record = _call.record_length(step_out, num_samples)
         samples = torch.empty((num_samples, record), dtype=torch.int32, device=step_out[0].device)
-    elif samples.dtype != torch.int32 or samples.numel() < num_samples * record or not samples.is_contiguous():
-        raise TypeError("samples must be a contiguous int32 tensor of num_samples * record entries")
-    _check(lib().nd_samples_pack(ptrs, k, lens, num_samples, samples.data_ptr() if samples.numel() else None,
-                                 _stream_ptr(stream)))
+    rc = _call.pack(step_out, num_samples, samples, _stream_ptr(stream))
+    if rc != ND_OK:
+        _check(rc)
     return samples
 
 

@@ -63,6 +63,10 @@ void step_shape(const Plan& pl, const nd_params* p, int i, int64_t* n_slots, int
         *n_out = pl.S * (int64_t)p->fanout[i];
         return;
     }
+    if (pl.app != ND_KHOP) {  // walks: a slot per sample at every step, of which there may be thousands
+        *n_slots = *n_out = pl.S;
+        return;
+    }
     int64_t w = 1;
     for (int l = 0; l < i; ++l) w *= step_fanout(pl.app, p, l);
     *n_slots = pl.S * w;
@@ -204,6 +208,7 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     }
     pl->max_slots = 0;
     pl->max_out = 0;
+    int64_t planned = -1;  // slots that the last sort plan was made for
     double guard = 1.0;
     for (int i = 0; i < pl->k; ++i) {
         guard = (app == ND_KHOP) ? guard * p->fanout[i] : 1.0;
@@ -224,8 +229,11 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
                       ND_MAX_UNIQUE_SLOTS, i, (long long)(no / pl->S));
             return ND_ERR_BAD_ARGUMENT;
         }
-        const size_t hb = sort_hist_bytes(make_sort_plan(ns, g.V, p->sched_group_bits));
-        if (hb > pl->hist_bytes) pl->hist_bytes = hb;
+        if (ns != planned) {
+            const size_t hb = sort_hist_bytes(make_sort_plan(ns, g.V, p->sched_group_bits));
+            if (hb > pl->hist_bytes) pl->hist_bytes = hb;
+            planned = ns;
+        }
     }
     pl->layer_fused = app == ND_LAYER && g.links != nullptr;
     // a call without samples draws nothing, and its fanouts have no bound that a shape could be made from

@@ -4,6 +4,9 @@ import ctypes
 import os
 import re
 
+import pytest
+import torch
+
 from paper_2009_06693_amd import binding as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -42,3 +45,20 @@ def test_null_arguments_are_errors_not_crashes():
     assert L.nd_graph_create(ctypes.byref(h), 4, 0, None, 0, None, None, 0, None) == B.ND_ERR_NULL_POINTER
     assert L.nd_graph_create(None, 4, 0, None, 0, None, None, 0, None) == B.ND_ERR_NULL_POINTER
     assert L.nd_group_workspace_bytes(1000, 50) > 0
+
+
+@pytest.mark.parametrize("call,complaint", [
+    (lambda p, t: B._call.sample(None, 0, p, t, 1, [t], t, 0), "roots must be"),
+    (lambda p, t: B._call.sample(None, 0, p, 3, 1, [t], t, 0), "roots must be"),
+    (lambda p, t: B._call.sample(None, 0, None, t, 1, [t], t, 0), ""),
+    (lambda p, t: B._call.sample(None, 0, b"x", t, 1, [t], t, 0), "nd_params"),
+    (lambda p, t: B._call.sample_static(None, 0, p, t, 1.5, [t], None, 0), "integers"),
+    (lambda p, t: B._call.sample(None, 0, p, t, 1, [t], t), "expected 8"),
+    (lambda p, t: B._call.pack([t], 3, t, 0), "step arrays must be"),
+    (lambda p, t: B._call.pack(t, "3", t, 0), ""),
+    (lambda p, t: B._call.record_length([t, 1], 3), "step arrays must be"),
+])
+def test_marshalling_refuses_what_is_no_gpu_array(call, complaint):
+    B.lib()
+    with pytest.raises(TypeError, match=complaint):
+        call(B.nd_params_init(), torch.zeros(3, dtype=torch.int32))
