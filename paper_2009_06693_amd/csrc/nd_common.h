@@ -37,7 +37,7 @@ void mark_phase(int phase, hipStream_t stream);
 // (row offsets, then the entry).  The quantised weight sits in the fourth word.
 struct Link {
     int32_t v;
-    uint32_t rs, deg;   // the row of v: first entry and length
+    uint32_t rs, deg;   // the row of v: first entry (0 for an empty row) and length
     uint32_t wq;        // quantised weight of this edge (0 on an unweighted graph)
 };
 static_assert(sizeof(Link) == 16, "one 16-byte load");

@@ -142,6 +142,7 @@ __global__ __launch_bounds__(256) void build_links_kernel(const OffT* __restrict
         l.v = u;
         l.rs = (uint32_t)off[u];
         l.deg = (uint32_t)off[u + 1] - l.rs;
+        l.rs = l.deg > 0u ? l.rs : 0u;  // a place inside the links whatever the row
         l.wq = wq != nullptr ? wq[e] : 0u;
         if (wq == nullptr) {
             links[e] = l;
@@ -208,8 +209,7 @@ bool spare_room(size_t bytes) {
 // Room for the links.  Optional: without them walks and k-hop take longer.
 void allocate_links(Graph* g, bool weighted) {
     if (g->E < 1 || g->E >= (1ll << 31)) return;
-    // one entry more, never written: where a walk looks that stands on an empty row behind all others
-    const size_t bytes = (size_t)(g->E + 1) * sizeof(Link) * (weighted ? 2 : 1);
+    const size_t bytes = (size_t)g->E * sizeof(Link) * (weighted ? 2 : 1);
     if (spare_room(bytes) && hipMalloc((void**)&g->links, bytes) != hipSuccess) {
         (void)hipGetLastError();
         g->links = nullptr;

@@ -150,7 +150,7 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F& f)
 // the vertices of the last 16 leave while a link is on its way.  4,096 walks of 100 steps over 1.5 MB of links: 36.5 us
 // with a lane per walk that made its words between two links, 18.6 like this.
 template <int DRAW, int STRIDE, typename OffT>
-__global__ __launch_bounds__(kFewThreads) void walk_few_kernel(GraphView<OffT> g, FreeArgs a) {
+__global__ __launch_bounds__(kFewThreads) void walk_free_few_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
     constexpr int L = kFewLanes;
     static_assert(L == 16, "from_lane");
@@ -161,8 +161,8 @@ __global__ __launch_bounds__(kFewThreads) void walk_few_kernel(GraphView<OffT> g
     uint32_t rs = 0, deg = 0;
     if (v >= 0) {
         const uint64_t r = (uint64_t)g.off[v];
-        rs = (uint32_t)r;
         deg = row_length(g, v, r);
+        rs = deg > 0u ? (uint32_t)r : 0u;  // a place inside the links, as a link has it
     }
     const uint32_t sid = a.sample_base + s;
     uint32_t lived = 0;
@@ -593,11 +593,11 @@ void launch_few(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, h
     const dim3 grid(groups), block(kFewThreads);
     const GraphView<OffT> g = view_of<OffT>(gr);
     if (draw == kDrawWeighted)
-        hipLaunchKernelGGL((walk_few_kernel<kDrawWeighted, 2, OffT>), grid, block, 0, stream, g, a);
+        hipLaunchKernelGGL((walk_free_few_kernel<kDrawWeighted, 2, OffT>), grid, block, 0, stream, g, a);
     else if (gr.wq)
-        hipLaunchKernelGGL((walk_few_kernel<kDrawUniform, 2, OffT>), grid, block, 0, stream, g, a);
+        hipLaunchKernelGGL((walk_free_few_kernel<kDrawUniform, 2, OffT>), grid, block, 0, stream, g, a);
     else
-        hipLaunchKernelGGL((walk_few_kernel<kDrawUniform, 1, OffT>), grid, block, 0, stream, g, a);
+        hipLaunchKernelGGL((walk_free_few_kernel<kDrawUniform, 1, OffT>), grid, block, 0, stream, g, a);
 }
 
 template <int THREADS, typename OffT>
@@ -626,7 +626,7 @@ void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, 
 // us, 539 with one).
 static int free_threads(int64_t S) { return S <= 65536 ? 64 : 256; }
 
-// DeepWalk and PPR up to this many walks: sixteen lanes per walk (walk_few_kernel).  100 steps, sixteen lanes and
+// DeepWalk and PPR up to this many walks: sixteen lanes per walk (walk_free_few_kernel).  100 steps, sixteen lanes and
 // one, us: over links that L2 holds (1.5 MB) 18.6 and 28.1 for 4,096 walks, 20.8 and 28.4 for 8,192, 25.6 and 28.9 for
 // 16,384, 39 and 29 for 32,768; over 1.1 GB 18.3 and 27.4 for 1,024, 34 and 39 for 4,096, 38.1 and 39.5 for 8,192,
 // 42.6 and 40.8 for 16,384.
