@@ -56,6 +56,17 @@ struct WeightLink {
 };
 static_assert(sizeof(WeightLink) == 16, "one 16-byte load");
 
+// What a step of a weighted walk looks up, in one aligned 64-byte piece (half a line: the scattered fetch of a line is
+// what a draw costs, whatever is read of it).  Cell i of a row belongs to the words whose guide-table cell is i,
+// and holds the four entries from the guide on: the high words of their thresholds, all ones where the threshold would
+// be 2^64, and their links without the weight.  A draw that ends behind them, or whose high word equals a threshold's,
+// is made from the WeightLinks.
+struct WeightCell {
+    uint32_t thr[4];
+    uint32_t link[4][3];  // v, rs, deg
+};
+static_assert(sizeof(WeightCell) == 64, "four 16-byte loads");
+
 struct Graph {
     int64_t V = 0, E = 0;
     int off64 = 0;              // width of row offsets as stored
@@ -72,9 +83,12 @@ struct Graph {
     Link* links = nullptr;
     // Membership table of every row (see RowSet): built when the sizes of a node2vec call are first asked for
     mutable std::atomic<int32_t*> rowset{nullptr};
-    mutable std::mutex rowset_mutex;
+    // E cells: built when the sizes of another call over edge weights are first asked for
+    mutable std::atomic<WeightCell*> cells{nullptr};
+    mutable std::mutex extra_mutex;
 };
 void graph_need_rowset(const Graph& g);
+void graph_need_cells(const Graph& g);
 
 // Is u in the row of v?  Every row owns a hash table of at least 2 deg + 1 places in groups of four
 // (16 bytes), open addressing by groups, empty places -1: one fetch answers most questions where a

@@ -83,6 +83,43 @@ __device__ __forceinline__ Link drawn_link(const Link* row, uint32_t deg, uint64
     return row[2ull * lo];
 }
 
+// The same draw through the row's WeightCells: one scattered fetch, where the guide and then the entries are two or
+// three.  100 steps of PPR at 0.01, weights in [1, 5): 57 K walks on 1.6 M entries 174 us by the links and 85 by the
+// cells, 64 walks (16 lanes each) 54 and 31, 600 K walks on 39 M entries 1,465 and 1,001; symmetric weights 2^14 / (deg
+// deg), where a draw ends behind its cell's four entries more often, 216 and 146 for the 57 K.  Not used by layer
+// sampling: over the 115 M entries of 2.9 M vertices, 7 GB of cells, 257 samples of [512, 512] took 42.8 us, 30.5 by
+// the links.  In two halves so that other work can go between them: the cell's fetch,
+// and the choice.  The assembler statement keeps the four loads whole and together: the compiler otherwise leaves loads of
+// the words that are selected until it knows which, a second and a third wait.
+typedef uint32_t Words4 __attribute__((ext_vector_type(4)));
+struct CellWords {
+    Words4 thr, a, b, c;
+};
+__device__ __forceinline__ void fetch_cell(CellWords& x, const WeightCell* cells, uint32_t rs, uint32_t deg, uint32_t hi) {
+    const Words4* piece = reinterpret_cast<const Words4*>(cells + (uint64_t)(rs + mulhi32(hi, deg)));
+    x.thr = piece[0];
+    x.a = piece[1];
+    x.b = piece[2];
+    x.c = piece[3];
+}
+__device__ __forceinline__ uint32_t either(bool which, uint32_t x, uint32_t y) { return which ? x : y; }
+// draws: this lane has fetched a cell (others' answers mean nothing).
+__device__ __forceinline__ Link pick_link(CellWords& x, const Link* links, uint32_t rs, uint32_t deg, uint64_t word,
+                                          bool draws) {
+    asm volatile("" : "+v"(x.thr), "+v"(x.a), "+v"(x.b), "+v"(x.c));
+    const uint32_t hi = (uint32_t)(word >> 32);
+    const bool b0 = hi >= x.thr.x, b1 = hi >= x.thr.y, b2 = hi >= x.thr.z;
+    Link l;
+    // one selection after the other (nested, they become branches)
+    l.v = (int32_t)either(b2, x.c.y, either(b1, x.b.z, either(b0, x.a.w, x.a.x)));
+    l.rs = either(b2, x.c.z, either(b1, x.b.w, either(b0, x.b.x, x.a.y)));
+    l.deg = either(b2, x.c.w, either(b1, x.c.x, either(b0, x.b.y, x.a.z)));
+    l.wq = 0;
+    const bool unsure = hi >= x.thr.w || hi == x.thr.x || hi == x.thr.y || hi == x.thr.z;
+    if (draws && unsure) l = drawn_link(links + (uint64_t)rs * 2u, deg, word);
+    return l;
+}
+
 // node2vec (Section 4.2): rejection sampling under the envelope
 // maxEdgeWeight(v) * largest bias; the bias of candidate u depends on its
 // relation to t, the transit of the previous step.  The membership search in

@@ -191,6 +191,34 @@ __global__ __launch_bounds__(256) void build_rowset_kernel(const OffT* __restric
     }
 }
 
+// The WeightCells, one entry per thread: bound by their 64 bytes of stores.
+template <typename OffT>
+__global__ __launch_bounds__(256) void build_cells_kernel(const OffT* __restrict__ off, const Link* __restrict__ links,
+                                                          int64_t V, int64_t E, WeightCell* __restrict__ cells) {
+    const int64_t first = (int64_t)blockIdx.x * kLinkTile;
+    const int64_t last = first + kLinkTile < E ? first + kLinkTile - 1 : E - 1;
+    const int64_t row_lo = row_of(off, first, 0, V - 1), row_hi = row_of(off, last, row_lo, V - 1);
+    const int64_t e = first + threadIdx.x;
+    if (e > last) return;
+    const WeightLink* weights = reinterpret_cast<const WeightLink*>(links);
+    const int64_t v = row_of(off, e, row_lo, row_hi);
+    const uint64_t lo = (uint64_t)off[v];
+    const uint32_t deg = (uint32_t)((uint64_t)off[v + 1] - lo);
+    const uint32_t guide = weights[2 * e + 1].guide;
+    WeightCell c;
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) {
+        const uint32_t j = guide + k < deg ? guide + k : deg - 1u;
+        const WeightLink w = weights[2ull * (lo + j) + 1u];
+        const Link l = links[2ull * (lo + j)];
+        c.thr[k] = w.always() ? 0xFFFFFFFFu : (uint32_t)(w.thr >> 32);
+        c.link[k][0] = (uint32_t)l.v;
+        c.link[k][1] = l.rs;
+        c.link[k][2] = l.deg;
+    }
+    cells[e] = c;
+}
+
 __global__ __launch_bounds__(256) void fill_empty_kernel(int4* p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         p[i] = make_int4(-1, -1, -1, -1);
@@ -225,6 +253,7 @@ void free_graph(Graph* g) {
     (void)hipFree(g->maxwq);
     (void)hipFree(g->links);
     (void)hipFree(g->rowset.load());
+    (void)hipFree(g->cells.load());
     delete g;
 }
 
@@ -338,43 +367,65 @@ int graph_create(Graph** out, int64_t V, int64_t E, const void* off, int off64, 
 
 void graph_destroy(Graph* g) { free_graph(g); }
 
-// Builds the rows' membership tables when they are not there yet: 8 bytes per entry and 16 per vertex, on the
-// graph's device and a stream of its own, so that it neither waits for the caller's work nor joins a stream
-// capture.  Without room for them node2vec searches the rows; whoever asks next tries again.
-void graph_need_rowset(const Graph& g) {
-    if (!g.links || g.rowset.load(std::memory_order_acquire)) return;
-    std::lock_guard<std::mutex> lock(g.rowset_mutex);
-    if (g.rowset.load(std::memory_order_acquire)) return;
+// What is built on a graph after its creation: on the graph's device and a stream of its own, so that it neither waits
+// for the caller's work nor joins a stream capture, and from a quarter of the free memory.  Without it calls are
+// slower; whoever asks next tries again.  launch(memory, stream) enqueues the kernels that fill the memory.
+template <typename T, typename F>
+static void need_extra(const Graph& g, std::atomic<T*>& extra, size_t bytes, F launch) {
+    if (!g.links || extra.load(std::memory_order_acquire)) return;
+    std::lock_guard<std::mutex> lock(g.extra_mutex);
+    if (extra.load(std::memory_order_acquire)) return;
     hipStreamCaptureMode capture = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&capture);
     int here = -1;
     if (hipGetDevice(&here) == hipSuccess && (here == g.device || hipSetDevice(g.device) == hipSuccess)) {
-        int32_t* set = nullptr;
+        T* memory = nullptr;
         hipStream_t stream = nullptr;
-        const int64_t n = g.E / 2 + g.V + 1;
-        const dim3 grid((unsigned)((g.E + kLinkTile - 1) / kLinkTile));
-        bool ok = spare_room((size_t)n * 16) && hipMalloc((void**)&set, (size_t)n * 16) == hipSuccess &&
+        bool ok = spare_room(bytes) && hipMalloc((void**)&memory, bytes) == hipSuccess &&
                   hipStreamCreateWithFlags(&stream, hipStreamNonBlocking) == hipSuccess;
         if (ok) {
-            hipLaunchKernelGGL(fill_empty_kernel, dim3((unsigned)g.num_cus * 32u), dim3(256), 0, stream, (int4*)set, n);
-            if (g.off64)
-                hipLaunchKernelGGL(build_rowset_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off,
-                                   g.col, g.V, g.E, set);
-            else
-                hipLaunchKernelGGL(build_rowset_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off,
-                                   g.col, g.V, g.E, set);
+            launch(memory, stream);
             ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(stream) == hipSuccess;
         }
         if (stream) (void)hipStreamDestroy(stream);
         if (ok) {
-            g.rowset.store(set, std::memory_order_release);
+            extra.store(memory, std::memory_order_release);
         } else {
             (void)hipGetLastError();
-            (void)hipFree(set);
+            (void)hipFree(memory);
         }
         if (here != g.device) (void)hipSetDevice(here);
     }
     (void)hipThreadExchangeStreamCaptureMode(&capture);
+}
+
+// The rows' membership tables: 8 bytes per entry and 16 per vertex.  Without them node2vec searches the rows.
+void graph_need_rowset(const Graph& g) {
+    const int64_t n = g.E / 2 + g.V + 1;
+    const dim3 grid((unsigned)((g.E + kLinkTile - 1) / kLinkTile));
+    need_extra(g, g.rowset, (size_t)n * 16, [&](int32_t* set, hipStream_t stream) {
+        hipLaunchKernelGGL(fill_empty_kernel, dim3((unsigned)g.num_cus * 32u), dim3(256), 0, stream, (int4*)set, n);
+        if (g.off64)
+            hipLaunchKernelGGL(build_rowset_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off, g.col,
+                               g.V, g.E, set);
+        else
+            hipLaunchKernelGGL(build_rowset_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.col,
+                               g.V, g.E, set);
+    });
+}
+
+// The cells of weighted draws: 64 bytes per entry.  Without them a draw looks its guide up first.
+void graph_need_cells(const Graph& g) {
+    if (!g.wq) return;
+    const dim3 grid((unsigned)((g.E + kLinkTile - 1) / kLinkTile));
+    need_extra(g, g.cells, (size_t)g.E * sizeof(WeightCell), [&](WeightCell* cells, hipStream_t stream) {
+        if (g.off64)
+            hipLaunchKernelGGL(build_cells_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off, g.links,
+                               g.V, g.E, cells);
+        else
+            hipLaunchKernelGGL(build_cells_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.links,
+                               g.V, g.E, cells);
+    });
 }
 
 }  // namespace nd

@@ -20,6 +20,7 @@ namespace nd {
 namespace {
 
 constexpr int kFreeChunk = 128;  // steps per launch: their output pointers are kernel arguments
+constexpr int kDrawCells = 3;    // kDrawWeighted through the WeightCells
 constexpr int kFewThreads = 256, kFewLanes = 16;  // few walks: threads per workgroup, lanes per walk
 
 struct FreeArgs {
@@ -34,6 +35,7 @@ struct FreeArgs {
     const int32_t* src;        // the roots, or the output of step first_step - 1 (multi-dimensional walk: its roots)
     const int32_t* prev_src;   // node2vec, first_step > 0: the output of step first_step - 2
     const int32_t* rowset;     // node2vec: membership tables, may be null
+    const WeightCell* cells;   // weighted draws: may be null
     uint32_t b_ret, b_com, b_far, b_max;
     int32_t max_attempts, use_weights;
     uint32_t R;                // multi-dimensional walk: roots per sample
@@ -110,6 +112,7 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
     const uint32_t sid = a.sample_base + s;
     uint32_t lived = 0;
     Rand4 r = draw4(a.seed, sid, 0u, a.first_step, 0u);
+    CellWords cell{};
     for (uint32_t si = 0; si < a.n_steps; ++si) {
         lived += v >= 0 ? 1u : 0u;
         const bool draws = deg > 0u && !(a.ppr_thr != 0 && (uint64_t)r.r3 < a.ppr_thr);
@@ -119,11 +122,19 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
         l.deg = 0;
         if (draws) {
             if (DRAW == kDrawUniform) l = a.links[(uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE];
+            else if (DRAW == kDrawCells) fetch_cell(cell, a.cells, rs, deg, r.r0);
             else l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r.r0, r.r1));
         }
+        const uint64_t word = cat64(r.r0, r.r1);
         if (si > 0) a.out[si - 1u][s] = v;  // after the load, which the next wait is for
         r = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
         asm volatile("" : "+v"(r.r0), "+v"(r.r1), "+v"(r.r3));
+        if (DRAW == kDrawCells) {
+            const Link c = pick_link(cell, a.links, rs, deg, word, draws);
+            l.v = draws ? c.v : ND_NULL_VERTEX;
+            l.rs = c.rs;
+            l.deg = draws ? c.deg : 0u;
+        }
         v = l.v;
         rs = l.rs;
         deg = l.deg;
@@ -168,6 +179,7 @@ __global__ __launch_bounds__(kFewThreads) void walk_free_few_kernel(GraphView<Of
     uint32_t lived = 0;
     int32_t mine = ND_NULL_VERTEX;                              // the vertex of step base + k
     Rand4 next = draw4(a.seed, sid, 0u, a.first_step + k, 0u);  // the words of step base + k
+    CellWords cell{};
     uint32_t base = 0;
     for (;; base += (uint32_t)L) {
         const Rand4 r = next;
@@ -182,21 +194,24 @@ __global__ __launch_bounds__(kFewThreads) void walk_free_few_kernel(GraphView<Of
             if (base + (uint32_t)I >= a.n_steps) return;  // the same for the whole launch
             lived += v >= 0 ? 1u : 0u;
             const bool draws = deg > 0u && (uint32_t)I < last;
-            const uint32_t r0 = from_lane<I>(r.r0);
+            const uint32_t r0 = from_lane<I>(r.r0), r1 = DRAW == kDrawUniform ? 0u : from_lane<I>(r.r1);
             Link l;
             if (DRAW == kDrawUniform) {
                 // a walk that has ended looks again where it stood: no branch on the way to the load
                 l = a.links[(uint64_t)(rs + mulhi32(r0, deg)) * STRIDE];
+            } else if (DRAW == kDrawCells) {
+                if (draws) fetch_cell(cell, a.cells, rs, deg, r0);
             } else {
                 l.v = ND_NULL_VERTEX;
                 l.rs = l.deg = 0;
-                if (draws) l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r0, from_lane<I>(r.r1)));
+                if (draws) l = drawn_link(a.links + (uint64_t)rs * 2u, deg, cat64(r0, r1));
             }
             if (I == 0) {
                 if (base > 0) before[s] = mine;
                 next = draw4(a.seed, sid, 0u, a.first_step + base + (uint32_t)L + k, 0u);
                 asm volatile("" : "+v"(next.r0), "+v"(next.r1), "+v"(next.r3));
             }
+            if (DRAW == kDrawCells) l = pick_link(cell, a.links, rs, deg, cat64(r0, r1), draws);
             v = draws ? l.v : ND_NULL_VERTEX;
             rs = draws ? l.rs : rs;
             deg = draws ? l.deg : 0u;
@@ -592,7 +607,9 @@ template <typename OffT>
 void launch_few(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
     const dim3 grid(groups), block(kFewThreads);
     const GraphView<OffT> g = view_of<OffT>(gr);
-    if (draw == kDrawWeighted)
+    if (draw == kDrawWeighted && a.cells)
+        hipLaunchKernelGGL((walk_free_few_kernel<kDrawCells, 2, OffT>), grid, block, 0, stream, g, a);
+    else if (draw == kDrawWeighted)
         hipLaunchKernelGGL((walk_free_few_kernel<kDrawWeighted, 2, OffT>), grid, block, 0, stream, g, a);
     else if (gr.wq)
         hipLaunchKernelGGL((walk_free_few_kernel<kDrawUniform, 2, OffT>), grid, block, 0, stream, g, a);
@@ -609,7 +626,9 @@ void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, 
         else hipLaunchKernelGGL((walk_free_n2v_kernel<1, OffT, THREADS>), grid, block, 0, stream, g, a);
         return;
     }
-    if (draw == kDrawWeighted)
+    if (draw == kDrawWeighted && a.cells)
+        hipLaunchKernelGGL((walk_free_kernel<kDrawCells, 2, OffT, THREADS>), grid, block, 0, stream, g, a);
+    else if (draw == kDrawWeighted)
         hipLaunchKernelGGL((walk_free_kernel<kDrawWeighted, 2, OffT, THREADS>), grid, block, 0, stream, g, a);
     else if (gr.wq)
         hipLaunchKernelGGL((walk_free_kernel<kDrawUniform, 2, OffT, THREADS>), grid, block, 0, stream, g, a);
@@ -669,6 +688,7 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.S = (uint32_t)S;
     a.V = (int32_t)gr.V;
     a.rowset = gr.rowset.load(std::memory_order_acquire);
+    a.cells = gr.cells.load(std::memory_order_acquire);
     a.b_ret = d.b_ret;
     a.b_com = d.b_com;
     a.b_far = d.b_far;

@@ -413,6 +413,70 @@ def test_weighted_draws_from_rows_whose_weights_span_decades(int64_offsets):
         assert_steps_equal(got, want, f"layer {per} {fanout}")
 
 
+@pytest.mark.parametrize("S", [40, 8192, 8193])
+@pytest.mark.parametrize("int64_offsets", [False, True])
+def test_weighted_walks_with_and_without_cells(int64_offsets, S):
+    """The cells are made when the sizes of a weighted walk are asked for; rows of one to 400 entries whose cells
+    hold none, four and hundreds of them, rows and ends of rows without weight."""
+    rng = np.random.default_rng(31)
+    V, pairs, w = 500, [], []
+    for v in range(V):
+        deg = (1, 2, 3, 4, 5, 9, 64, 400, 0)[v % 9]
+        row = np.sort(rng.choice(V, size=deg, replace=False)).tolist()
+        pairs += [(v, u) for u in row]
+        kind = v % 5
+        x = np.ones(deg) if kind == 0 else 1.0 + 4.0 * rng.random(deg) if kind == 1 else 10.0 ** rng.uniform(-4, 4, deg)
+        if kind == 3 and deg > 2:
+            x[deg // 2:] = 1e-6
+        if kind == 4 and v % 3 == 0:
+            x[:] = 1e-6
+        w += x.tolist()
+    g = inputs.from_edges(V, pairs, weights=np.array(w, dtype=np.float32), int64_offsets=int64_offsets)
+    roots = _roots(V, S, 32)
+    og = oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    want = oracle.ppr(og, roots, 40, 0.01, seed=33, use_weights=True)
+    for asked in (False, True):
+        dg = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights)
+        p = B.nd_params_init(num_steps=40, term_prob=0.01, use_weights=1)
+        lens, ws = B.nd_sample_query(dg, B.ND_PPR, p if asked else B.nd_params_init(num_steps=40), S)  # the same scratch
+        out = [torch.empty(n, dtype=torch.int32, device="cuda:0") for n in lens]
+        B.nd_sample(dg, B.ND_PPR, p, torch.as_tensor(roots, device="cuda:0"), 33, out,
+                    torch.empty(ws, dtype=torch.uint8, device="cuda:0"))
+        torch.cuda.synchronize()
+        assert_steps_equal([o.cpu().numpy() for o in out], list(want), f"asked={asked}")
+
+
+@pytest.mark.parametrize("below", [False, True])
+@pytest.mark.parametrize("S", [1, 8193])
+def test_weighted_draw_whose_high_word_is_that_of_a_threshold(S, below):
+    """The cells hold the thresholds' high words: where the draw's is the same, the low words decide."""
+    seed = 5
+    r0, r1, *_ = (int(x) for x in oracle.philox4x32_10([0, 0, 0, 0], [seed, 0]))
+    word = (r0 << 32) + r1
+    # a threshold ceil(c 2^64 / total) beside the word, on the side that is asked for
+    total, c = next((t, c) for t in range(2**32 - 2**16, 2**32 - 2**20, -256)
+                    for c in range(word * t // 2**64 - 1, word * t // 2**64 + 3)
+                    if -(-c * 2**64 // t) >> 32 == r0 and (word < -(-c * 2**64 // t)) == below)
+
+    def parts(x):  # x as weights that float32 holds exactly
+        half = x // 2 // 256 * 256
+        return [y for y in (half, (x - half) // 256 * 256, (x - half) % 256) if y > 0]
+    first, second = parts(c), parts(total - c)
+    q = first + second
+    assert sum(q) == total and all(float(np.float32(y)) == y and y < 2**31 for y in q)
+    V = len(q) + 1
+    pairs = [(0, 1 + i) for i in range(len(q))] + [(1 + i, 0) for i in range(len(q))]
+    w = np.array([x / 65536.0 for x in q] + [1.0] * len(q), dtype=np.float32)
+    g = inputs.from_edges(V, pairs, weights=w)
+    dg = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights)
+    og = oracle.OracleGraph(g.row_offsets, g.col_indices, g.weights)
+    roots = np.zeros(S, dtype=np.int32)
+    want = oracle.deepwalk(og, roots, 2, seed=seed, use_weights=True)
+    assert (want[0][0] <= len(first)) == below
+    got, _ = gpu_sample(dg, B.ND_DEEPWALK, roots, seed, num_steps=2, use_weights=1)
+    assert_steps_equal(got, list(want), "deepwalk")
+
+
 @pytest.mark.parametrize("degree,fanout,grouped", [(120, [10, 100], True), (119, [10, 100], False), (120, [7, 143], False),
                                                    (130, [10, 99], False), (80, [16, 44], True), (79, [16, 44], False),
                                                    (80, [16, 43], False)])
