@@ -21,6 +21,7 @@ namespace {
 
 constexpr int kFreeChunk = 128;  // steps per launch: their output pointers are kernel arguments
 constexpr int kDrawCells = 3;    // kDrawWeighted through the WeightCells
+constexpr int kAttemptLanes = 4;  // few walks of node2vec: attempts at once
 constexpr int kFewThreads = 256, kFewLanes = 16;  // few walks: threads per workgroup, lanes per walk
 
 struct FreeArgs {
@@ -379,7 +380,7 @@ __device__ __forceinline__ uint32_t n2v_exact(const OffT* off, const int32_t* co
 }
 
 // Out of line for workgroups of one wavefront (at most 65,536 walks, one wavefront per SIMD: 88 registers do not
-// matter, and the attempts' loop is better without it: 57 K weighted walks of 100 steps 419 us, 435 inlined);
+// matter, and the attempts' loop was better without it: 57 K weighted walks of 100 steps 419 us, 435 inlined);
 // inlined for many walks (59 registers: 7 wavefronts per SIMD instead of 5; a million weighted walks of 10
 // steps 454 us, 470 out of line).
 template <typename OffT>
@@ -390,16 +391,30 @@ __device__ __noinline__ uint32_t n2v_exact_call(const OffT* off, const int32_t* 
     return n2v_exact(off, col, wq, rowset, exact, R, b_ret, b_com, b_far, t, rs_t, deg_t, rs, deg);
 }
 
-// Every lane goes through its walk's attempts at its own pace: a wavefront whose lanes wait for each
-// other at every step pays for the slowest of 64 geometrically distributed attempt counts (7 rounds
-// per step where the mean is 1.9).  An attempt is one fetch of the candidate's link, and one of the
-// previous vertex's table when the two biases differ in their verdict.  The generator makes the words of
-// both possible next attempts; as compiled (ROCm 7.2) after the verdict, the second only where a walk moves on.
-template <int STRIDE, typename OffT, int THREADS>
+// Every walk goes through its attempts at its own pace: a wavefront whose lanes wait for each other at every step
+// pays for the slowest of 64 geometrically distributed attempt counts (7 rounds per step where the mean is 1.9).
+// A round is one fetch: of the candidate's link or, where the two biases differ in their verdict on the candidate before,
+// of a group of the previous vertex's table; both are 16 bytes, and a lane that looks into a table does not keep the
+// others from their links.  While it is on its way, the generator makes the words of both possible next attempts and the
+// vertex that was taken last is stored; the assembler statements keep the compiler (ROCm 7.2) from making the words
+// after the wait.  100 steps, p = 2, q = 0.5, weights in [1, 5): 57 K walks on 1.6 M entries 417 us with the table asked in
+// the attempt's own round and everything after the wait, 327 with rounds of one fetch, 264 with the words made
+// meanwhile (rounds of about 1.1 us, one wavefront per SIMD; 13 M fetches would take 0.2 ms at the rate of
+// scattered fetches); 57 K walks on 39 M entries 644 and 347.
+// LANES lanes per walk make as many attempts at once, of which the first that is not refused counts (walks are few, and a
+// step is as long as its attempts; the rule stands at attempt_lanes).
+typedef __attribute__((address_space(1))) int32_t GlobalInt;  // what lies behind a pointer that was read from LDS
+template <int STRIDE, typename OffT, int THREADS, int LANES>
 __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
-    const uint32_t s = a.s_first + blockIdx.x * (uint32_t)THREADS + threadIdx.x;
+    __shared__ int32_t* s_out[kFreeChunk];
+    constexpr uint32_t kWalks = (uint32_t)(THREADS / LANES);
+    const uint32_t k = threadIdx.x % (uint32_t)LANES;
+    const int walk = (int)(threadIdx.x & 63u) - (int)k;  // the wavefront's lane that is my walk's first
+    const uint32_t s = a.s_first + blockIdx.x * kWalks + threadIdx.x / (uint32_t)LANES;
+    for (uint32_t i = threadIdx.x; i < a.n_steps; i += THREADS) s_out[i] = a.out[i];
     int32_t v = first_transit<THREADS>(a, s);
+    __syncthreads();
     uint32_t rs = 0, deg = 0, maxw = kOneQ16;
     int32_t t = ND_NULL_VERTEX;        // the transit before v: none at the first step
     uint32_t rs_t = 0, deg_t = 0;
@@ -417,58 +432,110 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
     }
     const uint32_t sid = a.sample_base + s;
     const uint32_t b_lo = a.b_com < a.b_far ? a.b_com : a.b_far, b_hi = a.b_com < a.b_far ? a.b_far : a.b_com;
+    const bool common_high = a.b_com > a.b_far;
     uint32_t si = 0;
-    int32_t att = 0;
-    Rand4 r = draw4(a.seed, sid, 0u, a.first_step, 0u);
+    int32_t att = 0;                   // the attempt of my walk's first lane
+    Rand4 r = draw4(a.seed, sid, 0u, a.first_step, k);
+    enum : uint32_t { kTry, kAsk, kTake, kNo };
+    uint32_t what = kTry;              // my attempt: to be made; its verdict needs the table; accepted; refused
+    Link cand{};
+    uint32_t cand_top = kOneQ16, grp = 0, probe = 0;
+    uint32_t stores = 0;               // a vertex taken, not stored yet
+    GlobalInt* store_at = nullptr;
+    int32_t store_v = 0;
     for (;;) {
         while (si < a.n_steps && deg > 0u) {  // deg is 0 for a walk that has ended
-            if (__ballot(att >= a.max_attempts) != 0ull) break;  // the wavefront leaves: a lane's attempts are used up
-            const Link* at = a.links + (uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE;
-            const Link l = *at;
-            uint32_t top = kOneQ16;
-            if (STRIDE == 2 && a.use_weights) top = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
-            const Rand4 again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + 1u);
-            const Rand4 onward = draw4(a.seed, sid, 0u, a.first_step + si + 1u, 0u);
-            // The verdict and the move to the next vertex are selections, not branches.  From the nest of branches
-            // that says the same, the compiler (ROCm 7.2, -O3) makes code in which the registers of the link's row
-            // and length take the weight and the envelope, and a walk that accepts its candidate moves on with the
-            // row it stood on; compiled for the CPU, under sanitizers, both forms give the oracle's walks.
-            const bool start = t < 0, back = l.v == t;
-            const uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
-            const uint64_t w = a.use_weights ? l.wq : kOneQ16;
+            if (__ballot(att >= a.max_attempts) != 0ull) break;  // the wavefront leaves: a walk's attempts are used up
+            const uint32_t ng = RowSet::groups(rs_t, deg_t);
+            const Words4* link_at = reinterpret_cast<const Words4*>(a.links + (uint64_t)(rs + mulhi32(r.r0, deg)) * STRIDE);
+            const Words4* set_at = reinterpret_cast<const Words4*>(a.rowset) + (RowSet::first_group(t, rs_t) + grp);
+            const Words4* at = what == kAsk ? set_at : link_at;
+            Words4 got = *at;
+            uint32_t top = 0;
+            if (STRIDE == 2) top = reinterpret_cast<const uint32_t*>(at)[what == kAsk ? 0 : 7];
+            if (stores != 0u) *store_at = store_v;
+            Rand4 onward = draw4(a.seed, sid, 0u, a.first_step + si + 1u, k);
+            Rand4 again = r;
+            if (LANES == 1) again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + 1u);
+            const bool start = t < 0;
+            uint64_t y = mulhi64(cat64(r.r1, r.r2), (uint64_t)maxw * (start ? kOneQ16 : a.b_max));
+            store_at = (GlobalInt*)s_out[si] + s;
+            asm volatile("" : "+v"(onward.r0), "+v"(onward.r1), "+v"(onward.r2), "+v"(y));
+            if (LANES == 1) asm volatile("" : "+v"(again.r0), "+v"(again.r1), "+v"(again.r2));
+            asm volatile("" : "+v"(got), "+v"(top));
+            const int4 x = make_int4((int)got.x, (int)got.y, (int)got.z, (int)got.w);
+            // The verdict and the move to the next vertex are selections, not branches.  From a nest of branches that
+            // said the same, the compiler (ROCm 7.2, -O3) made code in which the registers of the link's row and length
+            // took the weight and the envelope; compiled for the CPU, under sanitizers, both forms gave the oracle's walks.
+            const bool back = x.x == t;
+            const uint64_t w = a.use_weights ? (uint32_t)x.w : kOneQ16;
             // a row of one entry has one outcome, whatever its attempts say
-            bool take = deg == 1u || y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
-            const bool ask = !take && !start && !back && y < w * b_hi;
-            bool common = false;
-            if (ask) common = row_has(g, a.rowset, t, rs_t, deg_t, l.v);
-            take = take || (ask && y < w * (common ? a.b_com : a.b_far));
-            if (take) a.out[si][s] = l.v;
-            t = take ? v : t;
-            rs_t = take ? rs : rs_t;
-            deg_t = take ? deg : deg_t;
-            v = take ? l.v : v;
-            rs = take ? l.rs : rs;
-            deg = take ? l.deg : deg;
-            maxw = take ? top : maxw;
-            si += take ? 1u : 0u;
-            att = take ? 0 : att + 1;
-            r.r0 = take ? onward.r0 : again.r0;
-            r.r1 = take ? onward.r1 : again.r1;
-            r.r2 = take ? onward.r2 : again.r2;
+            const bool low = deg == 1u || y < w * (start ? kOneQ16 : back ? a.b_ret : b_lo);
+            const bool high = !start && !back && y < w * b_hi;  // between the biases: accepted if it has the higher one
+            // a table's group: found, or not to be found, or in the next group (a group fills from the front)
+            const bool found = x.x == cand.v || x.y == cand.v || x.z == cand.v || x.w == cand.v;
+            const bool more = !found && x.w >= 0 && probe + 1u < ng;
+            const bool tries = what == kTry;
+            cand.v = tries ? x.x : cand.v;
+            cand.rs = tries ? (uint32_t)x.y : cand.rs;
+            cand.deg = tries ? (uint32_t)x.z : cand.deg;
+            if (STRIDE == 2) cand_top = tries ? (a.use_weights ? top & 0x7FFFFFFFu : kOneQ16) : cand_top;
+            const uint32_t first = LANES > 1 && att + (int32_t)k >= a.max_attempts ? kNo : low ? kTake : high ? kAsk : kNo;
+            const uint32_t then = more ? kAsk : found == common_high ? kTake : kNo;
+            grp = tries ? mulhi32(RowSet::hash(cand.v), ng) : grp + 1u < ng ? grp + 1u : 0u;
+            probe = tries ? 0u : probe + 1u;
+            what = tries ? first : what == kAsk ? then : what;
+            if (a.rowset == nullptr && what == kAsk)
+                what = row_contains(g, rs_t, deg_t, cand.v) == common_high ? kTake : kNo;
+            bool moves = what == kTake, refused = what == kNo;
+            Link to = cand;
+            uint32_t to_top = cand_top;
+            if (LANES > 1) {  // the first lane that has not been refused speaks for the walk, once it knows
+                constexpr uint32_t kAll = (1u << LANES) - 1u;
+                const uint32_t open = (uint32_t)(__ballot(what != kNo) >> walk) & kAll;
+                const uint32_t taken = (uint32_t)(__ballot(what == kTake) >> walk) & kAll;
+                const int from = walk + (int)__builtin_ctz(open | (1u << LANES));  // none: not used
+                refused = open == 0u;
+                moves = (open & (0u - open) & taken) != 0u;
+                to.v = __shfl(cand.v, from, 64);
+                to.rs = (uint32_t)__shfl((int)cand.rs, from, 64);
+                to.deg = (uint32_t)__shfl((int)cand.deg, from, 64);
+                if (STRIDE == 2) to_top = (uint32_t)__shfl((int)cand_top, from, 64);
+                if (refused) again = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)att + (uint32_t)LANES + k);
+            }
+            store_v = to.v;
+            stores = moves && k == 0u ? 1u : 0u;
+            t = moves ? v : t;
+            rs_t = moves ? rs : rs_t;
+            deg_t = moves ? deg : deg_t;
+            v = moves ? to.v : v;
+            rs = moves ? to.rs : rs;
+            deg = moves ? to.deg : deg;
+            maxw = moves ? to_top : maxw;
+            si += moves ? 1u : 0u;
+            att = moves ? 0 : refused ? att + LANES : att;
+            r.r0 = moves ? onward.r0 : refused ? again.r0 : r.r0;
+            r.r1 = moves ? onward.r1 : refused ? again.r1 : r.r1;
+            r.r2 = moves ? onward.r2 : refused ? again.r2 : r.r2;
+            what = moves || refused ? (uint32_t)kTry : what;
         }
-        const bool exact = si < a.n_steps && deg > 0u && att >= a.max_attempts;
-        if (__ballot(exact) == 0ull) break;  // every walk of the wavefront is done
+        if (stores != 0u) *store_at = store_v;
+        stores = 0;
+        const bool ends = si < a.n_steps && deg > 0u && att >= a.max_attempts, exact = ends && k == 0u;
+        if (__ballot(ends) == 0ull) break;  // every walk of the wavefront is done
+        if (LANES > 1 && ends) r = draw4(a.seed, sid, 0u, a.first_step + si, (uint32_t)a.max_attempts);
         const uint32_t* wq = a.use_weights ? g.wq : nullptr;
         const uint64_t word = cat64(r.r0, r.r1);
-        const uint32_t e = THREADS == 64 ? n2v_exact_call(g.off, g.col, wq, a.rowset, exact, word, a.b_ret, a.b_com,
+        uint32_t e = THREADS == 64 ? n2v_exact_call(g.off, g.col, wq, a.rowset, exact, word, a.b_ret, a.b_com,
                                                           a.b_far, t, rs_t, deg_t, rs, deg)
                                          : n2v_exact(g.off, g.col, wq, a.rowset, exact, word, a.b_ret, a.b_com, a.b_far,
                                                      t, rs_t, deg_t, rs, deg);
-        if (exact) {
+        if (LANES > 1) e = (uint32_t)__shfl((int)e, walk, 64);
+        if (ends) {
             const Link* at = a.links + (uint64_t)(rs + e) * STRIDE;
             const Link l = *at;
             if (STRIDE == 2 && a.use_weights) maxw = reinterpret_cast<const WeightLink*>(at)[1].top & 0x7FFFFFFFu;
-            a.out[si][s] = l.v;
+            if (k == 0u) s_out[si][s] = l.v;
             t = v;
             rs_t = rs;
             deg_t = deg;
@@ -477,14 +544,14 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
             deg = l.deg;
             ++si;
             att = 0;
-            r = draw4(a.seed, sid, 0u, a.first_step + si, 0u);
+            r = draw4(a.seed, sid, 0u, a.first_step + si, k);
         }
     }
     // a walk that stands on a vertex without out-edges had a transit at this step still
     const uint32_t lived = si + (si < a.n_steps && v >= 0 ? 1u : 0u);
     if (s < a.S)
-        for (; si < a.n_steps; ++si) a.out[si][s] = ND_NULL_VERTEX;
-    publish_live<THREADS>(lived, a, s_hist);
+        for (si += k; si < a.n_steps; si += (uint32_t)LANES) s_out[si][s] = ND_NULL_VERTEX;
+    publish_live<THREADS>(k == 0u ? lived : 0u, a, s_hist);
 }
 
 // ---------------------------------------------------------------- multi-dimensional walk
@@ -617,15 +684,25 @@ void launch_few(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, h
         hipLaunchKernelGGL((walk_free_few_kernel<kDrawUniform, 1, OffT>), grid, block, 0, stream, g, a);
 }
 
+template <int THREADS, int LANES, typename OffT>
+void launch_n2v_shape(const Graph& gr, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
+    const dim3 grid(groups), block(THREADS);
+    const GraphView<OffT> g = view_of<OffT>(gr);
+    if (gr.wq) hipLaunchKernelGGL((walk_free_n2v_kernel<2, OffT, THREADS, LANES>), grid, block, 0, stream, g, a);
+    else hipLaunchKernelGGL((walk_free_n2v_kernel<1, OffT, THREADS, LANES>), grid, block, 0, stream, g, a);
+}
+template <typename OffT>
+void launch_n2v(const Graph& gr, const FreeArgs& a, int lanes, int64_t walks_per_group, uint32_t groups,
+                hipStream_t stream) {
+    if (lanes > 1) launch_n2v_shape<64, kAttemptLanes, OffT>(gr, a, groups, stream);
+    else if (walks_per_group == 64) launch_n2v_shape<64, 1, OffT>(gr, a, groups, stream);
+    else launch_n2v_shape<256, 1, OffT>(gr, a, groups, stream);
+}
+
 template <int THREADS, typename OffT>
 void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
     const dim3 grid(groups), block(THREADS);
     const GraphView<OffT> g = view_of<OffT>(gr);
-    if (draw == kDrawNode2vec) {
-        if (gr.wq) hipLaunchKernelGGL((walk_free_n2v_kernel<2, OffT, THREADS>), grid, block, 0, stream, g, a);
-        else hipLaunchKernelGGL((walk_free_n2v_kernel<1, OffT, THREADS>), grid, block, 0, stream, g, a);
-        return;
-    }
     if (draw == kDrawWeighted && a.cells)
         hipLaunchKernelGGL((walk_free_kernel<kDrawCells, 2, OffT, THREADS>), grid, block, 0, stream, g, a);
     else if (draw == kDrawWeighted)
@@ -650,11 +727,24 @@ static int free_threads(int64_t S) { return S <= 65536 ? 64 : 256; }
 // 16,384, 39 and 29 for 32,768; over 1.1 GB 18.3 and 27.4 for 1,024, 34 and 39 for 4,096, 38.1 and 39.5 for 8,192,
 // 42.6 and 40.8 for 16,384.
 constexpr int64_t kFewWalks = 8192;
-static bool few_walks(int64_t S, bool node2vec) { return !node2vec && S <= kFewWalks; }
 
-static int64_t samples_per_group(int64_t S, bool node2vec, uint32_t mrw_R) {
+// Attempts at once (lanes per walk) of a node2vec call: several where walks are few and an attempt is refused more often
+// than one time in four, estimated as if every neighbour were far and weighed 0.6 of its row's heaviest.  100 steps,
+// four lanes and one, us, weights in [1, 5), p = 2, q = 0.5: 57 K vertices 110 and 154 for 64 walks, 154 and 184 for
+// 8,192, 160 and 187 for 16,384, 261 and 206 for 32,768; 1 M vertices 195 and 220 for 8,192, 222 and 244 for 16,384, 346
+// and 280 for 32,768.  Without weights (one refused in fifty) 134 and 115 for 1,024, 149 and 127 for 16,384.
+// Eight lanes: 150 for 8,192 walks, 201 for 16,384.
+constexpr int64_t kFewAttemptWalks = 16384;
+static int attempt_lanes(int64_t S, const DrawArgs& d) {
+    const double accepted = (double)d.b_far / (double)d.b_max * (d.use_weights ? 0.6 : 1.0);
+    return S <= kFewAttemptWalks && accepted < 0.75 ? kAttemptLanes : 1;
+}
+
+// Walks per workgroup; lanes: attempts at once of a node2vec call, 0 for the others.
+static int64_t samples_per_group(int64_t S, int lanes, uint32_t mrw_R) {
     if (mrw_R > 0) return mrw_waves(mrw_R);
-    return few_walks(S, node2vec) ? kFewThreads / kFewLanes : free_threads(S);
+    if (lanes > 1) return 64 / lanes;
+    return lanes == 0 && S <= kFewWalks ? kFewThreads / kFewLanes : free_threads(S);
 }
 
 // Bytes of the workspace that hold a multi-dimensional walk's roots between two launches.
@@ -662,13 +752,15 @@ int64_t walk_free_state_bytes(int64_t S, int32_t num_steps, uint32_t mrw_R) {
     return num_steps > kFreeChunk ? S * (int64_t)mrw_R * 4 : 0;
 }
 
-// Workgroups per launch.  Each owns a flag and a counter per step of the call in the workspace; samples
+// Workgroups per launch, at most (node2vec may take fewer: its scratch does not depend on its biases).  Each owns a
+// flag and a counter per step of the call in the workspace; samples
 // beyond what these workgroups take go to further launches.  24 MB of counters are 62,000 workgroups (15.9 M
 // walks) of 100 steps, or 1,535 of the 4,096 steps that a call may have.  No call may need more of the
 // static scratch array than walks whose scratch is a control block (64 bytes) per step, the roots and a
 // transit per sample of the multi-dimensional walk, so beside many roots the counters take what those took.
 int64_t walk_free_groups(int64_t S, int32_t num_steps, bool node2vec, uint32_t mrw_R) {
-    const int64_t per = samples_per_group(S, node2vec, mrw_R), k = num_steps;
+    const int lanes = !node2vec ? 0 : S <= kFewAttemptWalks ? kAttemptLanes : 1;
+    const int64_t per = samples_per_group(S, lanes, mrw_R), k = num_steps;
     int64_t room = (24ll << 20) - walk_free_state_bytes(S, num_steps, mrw_R);
     const int64_t least = 64 * k + (mrw_R > 0 ? 4 * S : 0);
     if (room < least) room = least;
@@ -703,7 +795,8 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.o_flags = o_flags;
     a.o_parts = o_parts;
     const bool node2vec = draw == kDrawNode2vec;
-    const int64_t per = samples_per_group(S, node2vec, mrw_R);
+    const int lanes = node2vec ? attempt_lanes(S, d) : 0;
+    const int64_t per = samples_per_group(S, lanes, mrw_R);
     const int64_t most = walk_free_groups(S, num_steps, node2vec, mrw_R);  // S >= 1
     for (int64_t s = 0; s < S; s += most * per) {
         const int64_t left = (S - s + per - 1) / per;
@@ -730,7 +823,10 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
                     else if (waves == 4) launch_mrw<4, int32_t>(gr, a, groups, stream);
                     else launch_mrw<1, int32_t>(gr, a, groups, stream);
                 }
-            } else if (few_walks(S, node2vec)) {
+            } else if (node2vec) {
+                if (gr.off64) launch_n2v<int64_t>(gr, a, lanes, per, groups, stream);
+                else launch_n2v<int32_t>(gr, a, lanes, per, groups, stream);
+            } else if (S <= kFewWalks) {
                 if (gr.off64) launch_few<int64_t>(gr, draw, a, groups, stream);
                 else launch_few<int32_t>(gr, draw, a, groups, stream);
             } else if (gr.off64) {

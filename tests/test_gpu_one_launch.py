@@ -137,6 +137,23 @@ def test_node2vec(int64_offsets, steps, S):
             assert stats[:, 0].tolist() == [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
 
 
+@pytest.mark.parametrize("int64_offsets", [False, True])
+@pytest.mark.parametrize("steps,S", [(1, 15), (40, 17), (130, 33), (5, 16384), (5, 16385)])
+def test_node2vec_with_several_attempts_at_once(int64_offsets, steps, S):
+    """Four attempts per round up to 16,384 walks where most are refused; budgets that end inside a round or at its
+    end, whichever bias is the highest."""
+    g, dg, og = _graph(True, int64_offsets, zeros=False)
+    roots = _roots(g.V, S, 41)
+    for p, q, weighted in ((2.0, 0.5, 1), (0.25, 4.0, 0), (4.0, 4.0, 1), (1.0, 1.0, 0), (8.0, 0.125, 0)):
+        for attempts in (1, 4, 5, 64) if S < 1000 else (6,):
+            want = oracle.node2vec(og, roots, steps, p, q, seed=42, use_weights=bool(weighted), max_attempts=attempts,
+                                   sample_id_base=5)
+            got, stats = gpu_sample(dg, B.ND_NODE2VEC, roots, 42, num_steps=steps, p=p, q=q, sample_id_base=5,
+                                    n2v_max_attempts=attempts, use_weights=weighted)
+            assert_steps_equal(got, list(want), f"node2vec p={p} q={q} attempts={attempts} weighted={weighted}")
+            assert stats[:, 0].tolist() == [(roots >= 0).sum()] + [(w >= 0).sum() for w in want[:-1]]
+
+
 def test_node2vec_without_membership_tables():
     """The tables are made when the scratch of a node2vec call is asked for; without them rows are searched."""
     g, dg, og = _graph(True, False, zeros=False)
