@@ -28,6 +28,25 @@ def test_walk_records(L, S):
     assert np.array_equal(got.cpu().numpy(), oracle.pack_samples(steps))
 
 
+@pytest.mark.parametrize("L,S", [(5, 1), (5, 2), (3, 31), (4, 33), (128, 35), (129, 67), (130, 16384), (131, 16385),
+                                 (260, 66), (1, 16387)])
+@pytest.mark.parametrize("skip", [0, 1, 2, 3])
+def test_walk_records_wherever_the_arrays_start(L, S, skip):
+    """Samples and steps that are no multiples of four, step arrays and records that start anywhere, records of several
+    pieces; nothing is written beside them."""
+    rng = np.random.default_rng(L * 1000 + S)
+    steps = rng.integers(-1, 1 << 30, (L, S)).astype(np.int32)
+    flat = torch.empty(L * S + L + 8, dtype=torch.int32, device="cuda:0")
+    views = [flat[skip + i * (S + skip % 2):][:S] for i in range(L)]
+    for v, a in zip(views, steps):
+        v.copy_(torch.as_tensor(a, device="cuda:0"))
+    rec = torch.full((S * L + 8,), -7, dtype=torch.int32, device="cuda:0")
+    B.nd_samples_pack(views, S, rec[skip:skip + S * L])
+    torch.cuda.synchronize()
+    assert np.array_equal(rec[skip:skip + S * L].cpu().numpy(), oracle.pack_samples(steps).reshape(-1))
+    assert (rec[:skip] == -7).all() and (rec[skip + S * L:] == -7).all()
+
+
 @pytest.mark.parametrize("widths,S", [([25, 250], 777), ([2, 1, 1, 3, 1], 1001), ([64, 2048, 2048], 9),
                                       ([1] * 40 + [5] + [1] * 3, 130)])
 def test_records_of_mixed_widths(widths, S):
