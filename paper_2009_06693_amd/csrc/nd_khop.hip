@@ -70,12 +70,12 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
         if (v >= 0) {
             const uint64_t rs = (uint64_t)g.off[v];
             row = make_uint2((uint32_t)rs, row_length(g, v, rs));
-            ++live;
         }
+        live += (uint32_t)__popcll(__ballot(v >= 0));
         s_rows[i] = row;
     }
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
-    if (live) atomicAdd(&s_live[0], live);
+    if (lane_id() == 0 && live) atomicAdd(&s_live[0], live);
     for (int hop = 0; hop < a.k; ++hop) {
         const bool last = hop == a.k - 1;
         const uint2* rows = s_rows + ((hop & 1) ? a.lds_half : 0u);
@@ -94,12 +94,12 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
                 if (row.y > 0u) {
                     const Rand4 r = draw4(a.seed, a.sample_base + s0 + s, d - s * W, (uint32_t)hop, 0u);
                     l = a.links[(uint64_t)(row.x + mulhi32(r.r0, row.y)) * STRIDE];
-                    ++live;
                 }
+                live += (uint32_t)__popcll(__ballot(row.y > 0u));
                 next[d] = row_of_link(l);
                 if (part == 0) out[d] = l.v;
             }
-            if (live) atomicAdd(&s_live[hop + 1], live);
+            if (lane_id() == 0 && live) atomicAdd(&s_live[hop + 1], live);
         } else {
             // kInFlight independent pieces per lane and round, of R consecutive draws of one parent each
             constexpr uint32_t kInFlight = 4 / R;
@@ -492,11 +492,11 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
             for (uint32_t j = tix; j < W; j += (uint32_t)THREADS) {
                 const int32_t v = s_res[j];
                 out_row[j] = v;
-                got += v >= 0 ? 1u : 0u;
+                got += (uint32_t)__popcll(__ballot(v >= 0) & group_lanes);
                 if (!last) alive |= next[j].y > 0u ? 1 : 0;
             }
             if (!last) {
-                if (got) atomicAdd(&s_live[hop + 1], got);
+                if (tix % 64u == 0u && got) atomicAdd(&s_live[hop + 1], got);
                 any = group_or<THREADS>(alive, group_lanes) != 0;
             }
             group_sync<THREADS>();  // table, queues and rows are rebuilt for the next hop or sample
