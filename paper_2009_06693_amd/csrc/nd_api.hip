@@ -517,6 +517,7 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
     layout(&pl, *h->g, params);
     if (app == ND_NODE2VEC && pl.free_walk) graph_need_rowset(*h->g);
     else if (params->use_weights && pl.free_walk) graph_need_cells(*h->g);
+    else if (params->use_weights && pl.layer_fused) graph_need_totals(*h->g);
     if (num_steps) *num_steps = pl.k;
     if (step_len) {
         for (int i = 0; i < pl.k; ++i) {

@@ -85,9 +85,12 @@ struct Graph {
     mutable std::atomic<int32_t*> rowset{nullptr};
     // E cells: built when the sizes of another call over edge weights are first asked for
     mutable std::atomic<WeightCell*> cells{nullptr};
+    // V sums of the rows' weights: built when the sizes of a layer call over edge weights are first asked for
+    mutable std::atomic<uint64_t*> totals{nullptr};
     mutable std::mutex extra_mutex;
 };
 void graph_need_rowset(const Graph& g);
+void graph_need_totals(const Graph& g);
 void graph_need_cells(const Graph& g);
 
 // Is u in the row of v?  Every row owns a hash table of at least 2 deg + 1 places in groups of four

@@ -219,6 +219,15 @@ __global__ __launch_bounds__(256) void build_cells_kernel(const OffT* __restrict
     cells[e] = c;
 }
 
+template <typename OffT>
+__global__ __launch_bounds__(256) void build_totals_kernel(const OffT* __restrict__ off, const uint64_t* __restrict__ cumq,
+                                                           int64_t V, uint64_t* __restrict__ totals) {
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
+        const int64_t a = (int64_t)off[v], b = (int64_t)off[v + 1];
+        totals[v] = b > a ? cumq[b - 1] : 0ull;
+    }
+}
+
 __global__ __launch_bounds__(256) void fill_empty_kernel(int4* p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         p[i] = make_int4(-1, -1, -1, -1);
@@ -254,6 +263,7 @@ void free_graph(Graph* g) {
     (void)hipFree(g->links);
     (void)hipFree(g->rowset.load());
     (void)hipFree(g->cells.load());
+    (void)hipFree(g->totals.load());
     delete g;
 }
 
@@ -411,6 +421,20 @@ void graph_need_rowset(const Graph& g) {
         else
             hipLaunchKernelGGL(build_rowset_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.col,
                                g.V, g.E, set);
+    });
+}
+
+// The rows' sums of weights: 8 bytes per vertex.  Without them layer sampling reads the last running sum of a row.
+void graph_need_totals(const Graph& g) {
+    if (!g.wq) return;
+    const dim3 grid((unsigned)g.num_cus * 8u);
+    need_extra(g, g.totals, (size_t)g.V * 8, [&](uint64_t* totals, hipStream_t stream) {
+        if (g.off64)
+            hipLaunchKernelGGL(build_totals_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off, g.cumq,
+                               g.V, totals);
+        else
+            hipLaunchKernelGGL(build_totals_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.cumq,
+                               g.V, totals);
     });
 }
 

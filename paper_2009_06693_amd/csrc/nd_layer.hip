@@ -135,7 +135,9 @@ __global__ __launch_bounds__(kLayerThreads) void layer_kernel(GraphView<OffT> g,
 // by; a call with a few samples is a chain of dependent fetches, and what counts there is their number.
 // Inside a weighted row the guide table (WeightLink) starts the search, where a binary search over the
 // running sums is one fetch per level: 257 samples of [512, 512] over 2.9 M vertices, symmetric weights,
-// took 37 us with a launch per step and the binary search, 30.9 us like this.
+// took 37 us with a launch per step and the binary search, 30.9 us like this, and 29.6 with the rows' weight sums in an
+// array of their own: 24 MB of it instead of places all over 0.9 GB of running sums, and for a root known before its
+// row is (a draw's fetches take 5 of the 12 us of a step, over 4 GB of links).
 struct LayerFusedArgs {
     const Link* links;
     uint64_t seed;
@@ -145,6 +147,8 @@ struct LayerFusedArgs {
     uint32_t n[ND_MAX_FANOUT_STEPS];    // transits of a step (roots_per_sample, then the fanouts)
     uint32_t m[ND_MAX_FANOUT_STEPS];    // draws of a step
     uint32_t o_rows_b, o_incl;          // in LDS, in bytes: the second rows buffer, the running sums
+    uint32_t o_v;                       // ... and, where totals are, the rows' vertices
+    const uint64_t* totals;             // weighted: sum of every vertex's row, may be null
     const int32_t* roots;
     int32_t* out[ND_MAX_FANOUT_STEPS];
     WsHeader* hdr;
@@ -176,6 +180,7 @@ __global__ __launch_bounds__(THREADS) void layer_fused_kernel(GraphView<OffT> g,
     uint2* buf_a = (uint2*)mem;
     uint2* buf_b = (uint2*)(mem + a.o_rows_b);
     uint64_t* s_incl = (uint64_t*)(mem + a.o_incl);
+    int32_t* s_v = (int32_t*)(mem + a.o_v);
     __shared__ uint64_t scan_tmp[THREADS / 64 + 1];
     bool bad = false;
     for (uint32_t b = blockIdx.x; b < a.S; b += gridDim.x) {
@@ -186,6 +191,7 @@ __global__ __launch_bounds__(THREADS) void layer_fused_kernel(GraphView<OffT> g,
             else if (v >= 0) {
                 const uint64_t rs = (uint64_t)g.off[v];
                 row = make_uint2((uint32_t)rs, row_length(g, v, rs));
+                if (WEIGHTED && a.totals) s_v[t] = v;
             }
             buf_a[t] = row;
         }
@@ -202,7 +208,7 @@ __global__ __launch_bounds__(THREADS) void layer_fused_kernel(GraphView<OffT> g,
             for (uint32_t t = t0; t < t1; ++t) {
                 const uint2 row = rows[t];
                 if (row.y > 0u) {
-                    if (WEIGHTED) sum += g.cumq[(uint64_t)row.x + row.y - 1u];
+                    if (WEIGHTED) sum += a.totals ? a.totals[s_v[t]] : g.cumq[(uint64_t)row.x + row.y - 1u];
                     else sum += row.y * column_weight(row.y);
                 }
                 s_incl[t] = sum;
@@ -242,7 +248,10 @@ __global__ __launch_bounds__(THREADS) void layer_fused_kernel(GraphView<OffT> g,
                     }
                 }
                 out[j] = res;
-                if (!last) next[j] = row_out;
+                if (!last) {
+                    next[j] = row_out;
+                    if (WEIGHTED && a.totals) s_v[j] = res;  // this step's have been read
+                }
             }
             __syncthreads();  // the next step reads the rows and rewrites the sums
         }
@@ -271,7 +280,7 @@ int layer_prepare() {
 #define ND_LAYER_ALLOW_T(OFFT, W, STRIDE, T)                                                               \
     ND_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_fused_kernel<OFFT, W, STRIDE, T>), \
                                      hipFuncAttributeMaxDynamicSharedMemorySize,                           \
-                                     ND_MAX_LAYER_TRANSITS * 24))
+                                     ND_MAX_LAYER_TRANSITS * 28))
 #define ND_LAYER_ALLOW(OFFT, W, STRIDE)       \
     ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 64);    \
     ND_LAYER_ALLOW_T(OFFT, W, STRIDE, 128);   \
@@ -316,7 +325,10 @@ int layer_fused(const Graph& gr, uint64_t seed, uint32_t sample_base, bool weigh
     }
     a.o_rows_b = rows[0] * 8u;
     a.o_incl = a.o_rows_b + rows[1] * 8u;
-    const size_t lds_bytes = (size_t)a.o_incl + (size_t)widest * 8u;  // at most 24 bytes per transit
+    a.totals = weighted ? gr.totals.load(std::memory_order_acquire) : nullptr;
+    a.o_v = a.o_incl + widest * 8u;
+    // at most 24 bytes per transit, 28 with totals
+    const size_t lds_bytes = (size_t)a.o_v + (a.totals ? (size_t)widest * 4u : 0u);
     a.roots = roots;
     a.hdr = (WsHeader*)ws;
     a.flags = (uint32_t*)(ws + o_flags);

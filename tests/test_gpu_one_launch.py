@@ -224,6 +224,25 @@ def test_layer(graph, per, fanout, S):
         assert_steps_equal(got, want, f"layer per={per} {fanout} weighted={weighted}")
 
 
+@pytest.mark.parametrize("per,fanout", [(4096, [4096, 30]), (1, [700, 4096]), (65, [64, 63, 5])])
+def test_layer_over_weights_with_and_without_the_rows_totals(graph, per, fanout):
+    """They are made when the sizes of a weighted layer call are asked for."""
+    g, dg, og = graph
+    if g.weights is None:
+        pytest.skip("unweighted graph")
+    roots = _roots(g.V, per * 7, 51)
+    want = oracle.layer(og, roots, per, fanout, seed=52, use_weights=True)
+    kw = dict(num_steps=len(fanout), fanout=fanout, roots_per_sample=per)
+    fresh = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights)
+    for asked in (0, 1):
+        lens, ws = B.nd_sample_query(fresh, B.ND_LAYER, B.nd_params_init(use_weights=asked, **kw), roots.size)
+        out = [torch.empty(n, dtype=torch.int32, device="cuda:0") for n in lens]
+        B.nd_sample(fresh, B.ND_LAYER, B.nd_params_init(use_weights=1, **kw), torch.as_tensor(roots, device="cuda:0"), 52,
+                    out, torch.empty(ws, dtype=torch.uint8, device="cuda:0"))
+        torch.cuda.synchronize()
+        assert_steps_equal([o.cpu().numpy() for o in out], want, f"asked={asked}")
+
+
 @pytest.mark.parametrize("heavy_first", [False, True])
 def test_layer_rows_whose_guide_cells_hold_many_entries(heavy_first):
     """A few heavy entries beside hundreds of light ones: all light ones of a stretch fall into one or two cells
