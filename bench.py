@@ -295,7 +295,8 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
             4.0 * s.step_len[i] + per_draw[i] * live_per_step[i] for i in range(n_steps))
     elif dom in ("sample_sub", "sample_wg") and stats is not None:
         draws = sum(int(stats[i, 0]) * m_per_step[i] for i in range(n_steps))
-        total_bytes = sum(8.0 * int(stats[i, 0]) + off_bytes * int(stats[i, 1]) + 4.0 * live_per_step[i]
+        # a first step that is not grouped has no count of distinct transits: its roots differ
+        total_bytes = sum(8.0 * int(stats[i, 0]) + off_bytes * int(stats[i, 1] or stats[i, 0]) + 4.0 * live_per_step[i]
                           + 4.0 * int(stats[i, 0]) * m_per_step[i] for i in range(n_steps))
     elif dom == "walk_window" and stats is not None:
         draws = sum(int(stats[i, 0]) for i in range(n_steps))

@@ -304,7 +304,8 @@ int nd_sample_status(const void* workspace_dev, void* hip_stream);
  * work items staged in LDS, draws made by the workgroup and grid classes.  Evidence
  * for Section 6.1.2's partition, so the values after the first are 0 where a call
  * did not group: sched_window = 0 over links, one launch per call (walks; k-hop
- * unless its graph is dense).  Layer sampling has no pairs; all its values are 0.
+ * unless its graph is dense; the first step of dense k-hop with at most a root
+ * per vertex).  Layer sampling has no pairs; all its values are 0.
  */
 int nd_sample_stats(const void* workspace_dev, void* hip_stream, int32_t max_steps,
                     int64_t* stats);

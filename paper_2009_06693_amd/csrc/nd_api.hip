@@ -48,6 +48,7 @@ struct Plan {
     uint32_t heavy_min = 64;   // pairs of one transit in a window from which the workgroup class serves it
     bool free_walk = false;    // walks over the graph's links, one lane per walk (nd_walk_free.hip)
     bool fused = false;        // k-hop: all hops in one launch (nd_khop.hip)
+    bool first_free = false;   // k-hop that groups: its first hop does not
     bool layer_fused = false;  // layer sampling: all steps of a sample by one workgroup
     size_t o_flags = 0, o_parts = 0;  // per workgroup: flag, live pairs per step
 };
@@ -237,8 +238,9 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     }
     pl->layer_fused = app == ND_LAYER && g.links != nullptr;
     // a call without samples draws nothing, and its fanouts have no bound that a shape could be made from
-    pl->fused = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0 &&
-                pl->S > 0 &&
+    const bool khop_default = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0;
+    pl->first_free = khop_default && p->unique_rounds == 0 && g.links && pl->S <= g.V;
+    pl->fused = khop_default && pl->S > 0 &&
                 (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
                                       : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
     return ND_OK;
@@ -705,6 +707,11 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
                                     step_out_dev[i], stream);
                 if (rc != ND_OK) return rc;
             }
+            continue;
+        }
+        if (i == 0 && pl.first_free) {
+            rc = khop_first(g, a, m, pl.S, roots_dev, step_out_dev[0], ctl, &hdr->status, stream);
+            if (rc != ND_OK) return rc;
             continue;
         }
         SchedParams sp{m, pl.sub_max, pl.wg_max, params->sched_force_class};

@@ -90,7 +90,12 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
                int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, uint32_t* status_out,
                hipStream_t stream);
 
-// The same with unique neighbours (Section 6.3), one group of lanes per sample.
+// The first hop without grouping, for calls whose later hops are grouped: at most a root per vertex (ctl, status: the
+// step's live pairs and the call's bad roots are counted there).
+int khop_first(const Graph& gr, const DrawArgs& d, int32_t m, int64_t S, const int32_t* roots, int32_t* out, StepCtl* ctl,
+               uint32_t* status, hipStream_t stream);
+
+// All hops with unique neighbours (Section 6.3), one group of lanes per sample.
 bool khop_unique_fits(const Graph& gr, const int32_t* fanout, int32_t k);
 int64_t khop_unique_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S);
 int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_t k, int32_t rounds, int64_t S,

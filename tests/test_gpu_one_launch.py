@@ -530,3 +530,29 @@ def test_khop_groups_where_the_graph_is_dense_and_pairs_are_many(degree, fanout,
         torch.cuda.synchronize()
         assert (s.stats()[1, 1] > 0) == (grouped or window == -1)
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("int64_offsets", [False, True])
+@pytest.mark.parametrize("S", [20_000, 20_001])
+def test_dense_khop_whose_first_hop_is_not_grouped(int64_offsets, S):
+    """At most a root per vertex: the first hop is drawn in order; roots that are none, out of range or repeated."""
+    V, degree, fanout = 20_000, 130, [11, 95]
+    v = torch.arange(V, device="cuda:0")
+    col = ((v[:, None] + 3 * torch.arange(1, degree + 1, device="cuda:0")) % V).sort(dim=1).values
+    off = torch.arange(V + 1, device="cuda:0") * degree
+    col = col[:V - 1].reshape(-1)                              # the last row is empty
+    off[V] = off[V - 1]
+    dg = B.nd_graph_create(off if int64_offsets else off.to(torch.int32), col.to(torch.int32))
+    r = torch.arange(S, device="cuda:0").flip(0).to(torch.int32) % V
+    r[5], r[6], r[300], r[S - 1] = -1, r[7], V, -5
+    outs = []
+    for window in (0, -1):
+        s = B.Sampler(dg, B.ND_KHOP, B.nd_params_init(num_steps=2, fanout=fanout, sched_window=window, sample_id_base=9), S)
+        outs.append([o.clone() for o in s.run(r, 61)])
+        torch.cuda.synchronize()
+        with pytest.raises(B.NdError):
+            s.status()
+        stats = s.stats()
+        assert stats[0, 0] == S - 3 and stats[1, 0] == int((outs[-1][0] >= 0).sum()) and stats[1, 1] > 0
+        assert (stats[0, 1] == 0) == (window == 0 and S <= V)
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
