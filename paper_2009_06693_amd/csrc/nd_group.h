@@ -37,7 +37,8 @@ template <int THREADS>
 __device__ __forceinline__ uint32_t group_reserve(bool flag, uint64_t group_lanes, uint32_t* fill, uint32_t* fill_lds) {
     const uint64_t votes = __ballot(flag) & group_lanes;
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t before = (uint32_t)__popcll(votes & ((1ull << lane) - 1ull));
+    const uint32_t before =
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(votes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)votes, 0u));
     const uint32_t n = (uint32_t)__popcll(votes);
     if (THREADS > 64) {
         uint32_t base = 0;
