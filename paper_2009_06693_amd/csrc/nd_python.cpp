@@ -90,12 +90,10 @@ struct Call {
     }
     bool take(PyObject* const* a) {
         if (!as_address(a[0], &handle)) return false;
-        if (!PyLong_Check(a[1]) || !PyLong_Check(a[4])) {
-            PyErr_SetString(PyExc_TypeError, "app and seed must be integers");
-            return false;
-        }
-        app = (int)PyLong_AsUnsignedLongMask(a[1]);
+        app = (int)PyLong_AsUnsignedLongMask(a[1]);  // what has __index__ counts as an integer, NumPy's integers too
+        if (PyErr_Occurred()) return false;
         seed = PyLong_AsUnsignedLongLongMask(a[4]);
+        if (PyErr_Occurred()) return false;
         if (PyObject_GetBuffer(a[2], &params, PyBUF_SIMPLE) != 0) return false;  // the ctypes structure itself
         if (params.len != g_params_size) {
             PyErr_SetString(PyExc_TypeError, "params must be an nd_params");

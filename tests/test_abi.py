@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 import torch
 
@@ -52,7 +53,8 @@ def test_null_arguments_are_errors_not_crashes():
     (lambda p, t: B._call.sample(None, 0, p, 3, 1, [t], t, 0), "roots must be"),
     (lambda p, t: B._call.sample(None, 0, None, t, 1, [t], t, 0), ""),
     (lambda p, t: B._call.sample(None, 0, b"x", t, 1, [t], t, 0), "nd_params"),
-    (lambda p, t: B._call.sample_static(None, 0, p, t, 1.5, [t], None, 0), "integers"),
+    (lambda p, t: B._call.sample_static(None, 0, p, t, 1.5, [t], None, 0), "integer"),
+    (lambda p, t: B._call.sample(None, np.int32(0), p, t, np.int64(1), [t], t, 0), "roots must be"),
     (lambda p, t: B._call.sample(None, 0, p, t, 1, [t], t), "expected 8"),
     (lambda p, t: B._call.pack([t], 3, t, 0), "step arrays must be"),
     (lambda p, t: B._call.pack(t, "3", t, 0), ""),
