@@ -30,8 +30,8 @@ HBM_PEAK_GBS = 8000.0
 # gives: x2.0 and x1.0), averaged over the launches of one call.  Source: the counter table in
 # profiles/one_launch_routes_rocprofv3.md.  None where not profiled.
 MEASURED_TRAFFIC_BYTES = {
-    ("c5_khop", "khop_fused_kernel"): 22265146368,     # 17,194,038 KiB fetched + 4,549,269 KiB written
-    ("c5_deepwalk", "walk_free_kernel"): 29931146240,  # 27,583,722 KiB fetched + 1,645,913 KiB written
+    ("c5_khop", "khop_fused_kernel"): 22318600192,     # 17,135,604 KiB fetched + 4,659,904 KiB written
+    ("c5_deepwalk", "walk_free_kernel"): 29912658944,  # 27,565,350 KiB fetched + 1,646,231 KiB written
 }
 
 WORKLOADS = {
