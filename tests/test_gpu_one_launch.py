@@ -556,3 +556,19 @@ def test_dense_khop_whose_first_hop_is_not_grouped(int64_offsets, S):
         assert stats[0, 0] == S - 3 and stats[1, 0] == int((outs[-1][0] >= 0).sum()) and stats[1, 1] > 0
         assert (stats[0, 1] == 0) == (window == 0 and S <= V)
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("fanout", [[9, 3], [3, 6]])
+@pytest.mark.parametrize("rounds", [0, 3])
+def test_outputs_of_large_khop_calls_leave_past_the_caches(fanout, rounds):
+    """From 64 M draws of the last hop on: the first such call, against its two halves, which are below the line."""
+    g, dg, _ = _graph(False, False)
+    S = -(-(64 << 20) // (fanout[0] * fanout[1]))
+    r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
+
+    def call(first, last):
+        p = B.nd_params_init(num_steps=2, fanout=fanout, unique_rounds=rounds, sample_id_base=first)
+        return [o.reshape(-1) for o in B.Sampler(dg, B.ND_KHOP, p, last - first).run(r[first:last], 33)]
+
+    whole, halves = call(0, S), zip(call(0, S // 2), call(S // 2, S))
+    assert all(torch.equal(w, torch.cat(h)) for w, h in zip(whole, halves))
