@@ -9,8 +9,11 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <cstring>
 #include <exception>
 #include <vector>
+
+#include "../../include/nd.h"
 
 namespace {
 
@@ -22,7 +25,6 @@ using PackFn = int (*)(const int32_t* const*, int32_t, const int64_t*, int64_t, 
 SampleFn g_sample = nullptr;
 StaticFn g_static = nullptr;
 PackFn g_pack = nullptr;
-Py_ssize_t g_params_size = 0;
 
 // An address or handle given as an integer, None for null.
 bool as_address(PyObject* o, void** out) {
@@ -48,10 +50,15 @@ bool is_array(const at::Tensor& t) {
 struct Arrays {
     std::vector<int32_t*> ptr;
     std::vector<int64_t> len;
-    bool take(PyObject* seq, const char* complaint) {
+    bool take(PyObject* seq, const char* complaint, int64_t at_least = 0) {
         PyObject* fast = PySequence_Fast(seq, complaint);
         if (!fast) return false;
         const Py_ssize_t n = PySequence_Fast_GET_SIZE(fast);
+        if (n < at_least) {
+            PyErr_Format(PyExc_ValueError, "%zd arrays for %lld steps", n, (long long)at_least);
+            Py_DECREF(fast);
+            return false;
+        }
         ptr.reserve((size_t)n);
         len.reserve((size_t)n);
         bool ok = true;
@@ -95,7 +102,7 @@ struct Call {
         seed = PyLong_AsUnsignedLongLongMask(a[4]);
         if (PyErr_Occurred()) return false;
         if (PyObject_GetBuffer(a[2], &params, PyBUF_SIMPLE) != 0) return false;  // the ctypes structure itself
-        if (params.len != g_params_size) {
+        if (params.len != (Py_ssize_t)sizeof(nd_params)) {
             PyErr_SetString(PyExc_TypeError, "params must be an nd_params");
             return false;
         }
@@ -105,9 +112,14 @@ struct Call {
             PyErr_SetString(PyExc_TypeError, kRoots);
             return false;
         }
-        if (!out.take(a[5], kOutputs)) return false;
-        roots = (const int32_t*)r->data_ptr();
         num_roots = r->numel();
+        // the library reads an address per step and has no count of them
+        nd_params p;
+        std::memcpy(&p, params.buf, sizeof p);
+        const int64_t steps = p.num_steps <= ND_MAX_WALK_STEPS ? p.num_steps : 0;  // more than that it refuses
+        if (!out.take(a[5], kOutputs, num_roots > 0 ? steps : 0)) return false;
+        if ((int64_t)out.ptr.size() < steps) out.ptr.resize((size_t)steps, nullptr);
+        roots = (const int32_t*)r->data_ptr();
         return true;
     }
 };
@@ -121,8 +133,12 @@ bool expects(Py_ssize_t got, Py_ssize_t want) {
 PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void *s, *t, *p;
     if (!expects(n, 4) || !as_address(a[0], &s) || !as_address(a[1], &t) || !as_address(a[2], &p)) return nullptr;
-    g_params_size = PyLong_AsSsize_t(a[3]);
-    if (g_params_size < 0 && PyErr_Occurred()) return nullptr;
+    const Py_ssize_t params_size = PyLong_AsSsize_t(a[3]);
+    if (params_size < 0 && PyErr_Occurred()) return nullptr;
+    if (params_size != (Py_ssize_t)sizeof(nd_params)) {
+        PyErr_Format(PyExc_TypeError, "nd_params of %zd bytes, expected %zu", params_size, sizeof(nd_params));
+        return nullptr;
+    }
     g_sample = (SampleFn)s;
     g_static = (StaticFn)t;
     g_pack = (PackFn)p;

@@ -7,6 +7,7 @@ import re
 import numpy as np
 import pytest
 import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
 
 from paper_2009_06693_amd import binding as B
 
@@ -64,3 +65,26 @@ def test_marshalling_refuses_what_is_no_gpu_array(call, complaint):
     B.lib()
     with pytest.raises(TypeError, match=complaint):
         call(B.nd_params_init(), torch.zeros(3, dtype=torch.int32))
+
+
+def _on_gpu(n=3, dtype=torch.int32):
+    """What looks like an array on a GPU, without one (its address is null)."""
+    with FakeTensorMode():
+        return torch.empty(n, dtype=dtype, device="cuda:0")
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+def test_as_many_outputs_as_steps():
+    """The library reads an address per step: a shorter list is refused, not read past its end."""
+    B.lib()
+    t, none = _on_gpu(), _on_gpu(0)
+    for steps, call in ((3, lambda r, o: B._call.sample(None, B.ND_KHOP, p, r, 1, o, t, 0)),
+                        (4096, lambda r, o: B._call.sample_static(None, B.ND_PPR, p, r, 1, o, None, 0))):
+        p = B.nd_params_init(num_steps=steps)
+        for n in (0, 1, steps - 1):
+            with pytest.raises(ValueError, match=f"{n} arrays for {steps} steps"):
+                call(t, [t] * n)
+        for r, n in ((t, steps), (t, steps + 1), (none, 0)):  # no roots, nothing written
+            assert call(r, [t] * n) == B.ND_ERR_NULL_POINTER  # the library's answer: no graph
+    p = B.nd_params_init(num_steps=4097)
+    assert B._call.sample(None, B.ND_PPR, p, t, 1, [t], t, 0) == B.ND_ERR_NULL_POINTER
