@@ -46,6 +46,9 @@ bool is_array(const at::Tensor& t) {
     return t.scalar_type() == at::kInt && t.is_cuda() && t.is_contiguous();
 }
 
+// Memory that a kernel reaches at the tensor's address: the GPU's, or pinned on the host.
+bool is_reachable(const at::Tensor& t) { return t.is_cuda() || t.is_pinned(); }
+
 // The tensors of a sequence: contiguous int32 arrays on a GPU.
 struct Arrays {
     std::vector<int32_t*> ptr;
@@ -150,8 +153,13 @@ PyObject* sample(PyObject*, PyObject* const* a, Py_ssize_t n) try {
     Call c;
     void* stream;
     if (!expects(n, 8) || !c.take(a) || !as_address(a[7], &stream)) return nullptr;
-    const at::Tensor* w = as_tensor(a[6], "workspace must be a CUDA tensor");
+    constexpr const char* kWorkspace = "workspace must be a CUDA tensor without gaps";
+    const at::Tensor* w = as_tensor(a[6], kWorkspace);
     if (!w) return nullptr;
+    if (!is_reachable(*w) || !w->is_non_overlapping_and_dense()) {
+        PyErr_SetString(PyExc_TypeError, kWorkspace);
+        return nullptr;
+    }
     void* ws = w->data_ptr();
     const size_t bytes = (size_t)w->numel() * (size_t)w->element_size();
     int rc;
@@ -171,8 +179,14 @@ PyObject* sample_static(PyObject*, PyObject* const* a, Py_ssize_t n) try {
     if (!expects(n, 8) || !c.take(a) || !as_address(a[7], &stream)) return nullptr;
     uint32_t* status = nullptr;
     if (a[6] != Py_None) {
-        const at::Tensor* s = as_tensor(a[6], "status must be a CUDA tensor");
+        constexpr const char* kStatus = "status must be a CUDA tensor of one 32-bit element";
+        const at::Tensor* s = as_tensor(a[6], kStatus);
         if (!s) return nullptr;
+        const bool holds = s->numel() > 0 && (size_t)s->numel() * (size_t)s->element_size() >= sizeof(uint32_t);
+        if (!holds || !is_reachable(*s) || !s->is_non_overlapping_and_dense()) {
+            PyErr_SetString(PyExc_TypeError, kStatus);
+            return nullptr;
+        }
         status = (uint32_t*)s->data_ptr();
     }
     int rc;
@@ -200,10 +214,11 @@ PyObject* pack(PyObject*, PyObject* const* a, Py_ssize_t n) try {
     if (!expects(n, 4) || !steps.take(a[0], kSteps)) return nullptr;
     const int64_t num_samples = PyLong_AsLongLong(a[1]);
     if (PyErr_Occurred()) return nullptr;
-    constexpr const char* kRecords = "samples must be a contiguous int32 tensor of num_samples * record entries";
+    constexpr const char* kRecords = "samples must be a contiguous int32 CUDA tensor of num_samples * record entries";
     const at::Tensor* r = as_tensor(a[2], kRecords);
     if (!r || !as_address(a[3], &stream)) return nullptr;
-    if (r->scalar_type() != at::kInt || r->numel() < num_samples * record_of(steps, num_samples) || !r->is_contiguous()) {
+    if (r->scalar_type() != at::kInt || r->numel() < num_samples * record_of(steps, num_samples) || !r->is_contiguous() ||
+        (r->numel() > 0 && !is_reachable(*r))) {
         PyErr_SetString(PyExc_TypeError, kRecords);
         return nullptr;
     }

@@ -88,3 +88,32 @@ def test_as_many_outputs_as_steps():
             assert call(r, [t] * n) == B.ND_ERR_NULL_POINTER  # the library's answer: no graph
     p = B.nd_params_init(num_steps=4097)
     assert B._call.sample(None, B.ND_PPR, p, t, 1, [t], t, 0) == B.ND_ERR_NULL_POINTER
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+@pytest.mark.parametrize("bad", [torch.zeros(4096, dtype=torch.int32),                     # the host's own memory
+                                 _on_gpu(64)[::2], _on_gpu(1).expand(64), 7])
+def test_memory_that_a_kernel_cannot_use_is_refused(bad):
+    """Its address would be handed to a kernel, with more bytes behind it than the tensor has where it has gaps."""
+    B.lib()
+    p, t = B.nd_params_init(num_steps=1), _on_gpu()
+    with pytest.raises(TypeError, match="workspace must be"):
+        B._call.sample(None, 0, p, t, 1, [t], bad, 0)
+    with pytest.raises(TypeError, match="status must be"):
+        B._call.sample_static(None, 0, p, t, 1, [t], bad, 0)
+    with pytest.raises(TypeError, match="samples must be"):
+        B._call.pack([t], 3, bad, 0)
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+def test_memory_that_a_kernel_can_use_is_taken():
+    """Whatever the types and shapes of the scratch and the status word; no samples need no records."""
+    B.lib()
+    p, t = B.nd_params_init(num_steps=1), _on_gpu()
+    for ok in (_on_gpu(64, torch.uint8), _on_gpu(64, torch.float64).view(8, 8).t(), _on_gpu(1, torch.int64)):
+        assert B._call.sample(None, 0, p, t, 1, [t], ok, 0) == B.ND_ERR_NULL_POINTER
+        assert B._call.sample_static(None, 0, p, t, 1, [t], ok, 0) == B.ND_ERR_NULL_POINTER
+    assert B._call.pack([t], 0, torch.zeros(0, dtype=torch.int32), 0) == B.ND_OK
+    for short in (_on_gpu(0), _on_gpu(3, torch.uint8)):
+        with pytest.raises(TypeError, match="status must be"):
+            B._call.sample_static(None, 0, p, t, 1, [t], short, 0)
