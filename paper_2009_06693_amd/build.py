@@ -1,8 +1,11 @@
 """Builds in-tree: libnd.so (HIP, gfx950) with hipcc, no torch involved; _nd_call.so (the Python side's marshalling of
-tensors, csrc/nd_python.cpp) with the host compiler against torch's headers."""
+tensors, csrc/nd_python.cpp) with a host compiler against torch's headers, where there is a torch: callers of the C ABI
+need only the first."""
 from __future__ import annotations
 
+import importlib.util
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -31,10 +34,18 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _host_compiler() -> str:
+    """g++, or the clang++ that hipcc itself uses for host code."""
+    return os.environ.get("CXX") or shutil.which("g++") or os.path.join(os.path.dirname(HIPCC), "amdclang++")
+
+
 def _compile_marshalling() -> None:
+    if importlib.util.find_spec("torch") is None:
+        sys.stderr.write("torch is not installed: libnd.so is built without the Python binding's _nd_call.so\n")
+        return
     import torch
     root = os.path.dirname(torch.__file__)
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    cmd = [_host_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "nd_python.cpp"), "-o", CALL_LIB,
@@ -49,11 +60,11 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=6) as ex:
         marshalling = ex.submit(_compile_marshalling)
         objs = list(ex.map(_compile, SOURCES))
-        marshalling.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    marshalling.result()  # after the link: libnd.so does not depend on it
     if verbose:
         print("built", LIB)
     return LIB
