@@ -222,9 +222,13 @@ int nd_graph_info(const nd_graph* g, int64_t* V, int64_t* E, int* has_weights,
  * room, node2vec searches the rows instead: same output, longer calls.  Asked
  * for DeepWalk or PPR with use_weights for the first time, it builds in the same
  * way what their draws look up in one piece (64 bytes per entry); without it a
- * draw takes two dependent looks.  For layer sampling with use_weights it is
- * the sum of every row's weights (8 bytes per vertex).  No other call of this
- * function touches the device.
+ * draw takes two dependent looks.  It does so for up to 32,768 walks, and for any
+ * number on graphs of up to 58 M entries: more walks on larger graphs are faster
+ * without it, and do not use it where it is there.  For layer sampling with
+ * use_weights it is the sum of every row's weights (8 bytes per vertex).  A caller
+ * who wants the memory more than the speed asks for these sizes with
+ * use_weights = 0, which are the same.  No other call of this function touches
+ * the device.
  */
 int nd_sample_query(const nd_graph* g, int app, const nd_params* params, int64_t num_roots,
                     int32_t* num_steps, int64_t* step_len, size_t* workspace_bytes);

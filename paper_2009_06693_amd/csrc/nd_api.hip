@@ -518,7 +518,7 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
     if (rc != ND_OK) return rc;
     layout(&pl, *h->g, params);
     if (app == ND_NODE2VEC && pl.free_walk) graph_need_rowset(*h->g);
-    else if (params->use_weights && pl.free_walk) graph_need_cells(*h->g);
+    else if (params->use_weights && pl.free_walk && walk_uses_cells(*h->g, pl.S)) graph_need_cells(*h->g);
     else if (params->use_weights && pl.layer_fused) graph_need_totals(*h->g);
     if (num_steps) *num_steps = pl.k;
     if (step_len) {

@@ -83,7 +83,7 @@ struct Graph {
     Link* links = nullptr;
     // Membership table of every row (see RowSet): built when the sizes of a node2vec call are first asked for
     mutable std::atomic<int32_t*> rowset{nullptr};
-    // E cells: built when the sizes of another call over edge weights are first asked for
+    // E cells: built when the sizes of a call that draws from them (walk_uses_cells) are first asked for
     mutable std::atomic<WeightCell*> cells{nullptr};
     // V sums of the rows' weights: built when the sizes of a layer call over edge weights are first asked for
     mutable std::atomic<uint64_t*> totals{nullptr};

@@ -74,6 +74,7 @@ int walk_windows(const Graph& gr, int draw, bool multirw, const DrawArgs& d, int
 // call's header, one flag per workgroup (o_flags) and the live walks per workgroup and step (o_parts)
 // go to the workspace.
 int64_t walk_free_groups(int64_t S, int32_t num_steps, bool node2vec, uint32_t mrw_R);
+bool walk_uses_cells(const Graph& gr, int64_t S);  // DeepWalk and PPR over edge weights, where the cells are there
 int64_t walk_free_state_bytes(int64_t S, int32_t num_steps, uint32_t mrw_R);
 int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t num_steps, const int32_t* roots,
               int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, uint32_t mrw_R, int32_t* mrw_state,

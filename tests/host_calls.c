@@ -14,7 +14,7 @@
  *   device D               (current when the queries have returned)
  *   allocated BYTES        (live when the program ends, before the graph is destroyed)
  * Names: the fields of nd_params, fanout as a,b,c; queries=N (asks N times); fail_malloc=N (the first N
- * allocations of the queries fail); left=B (of the device's memory, B bytes are free when the first query
+ * allocations of the queries fail); query_roots=N (sizes are asked for N roots; the call keeps its own); left=B (of the device's memory, B bytes are free when the first query
  * is made); device=D (current during the queries; the graph lies on device 0, and memory taken on another
  * is counted as elsewhere and ends the program with status 4); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
  * and prints "unused STATS_RC STATUS_RC").  A call that does not return within 20 seconds ends the program with SIGALRM. */
@@ -119,7 +119,7 @@ int main(int argc, char** argv) {
     nd_params p;
     nd_params_init(&p);
     int fail = 0, unused = -1, queries = 1, query_device = 0;
-    long long left = -1;
+    long long left = -1, query_roots = roots;
     for (int i = 7; i < argc; ++i) {
         char* eq = strchr(argv[i], '=');
         if (!eq) return 2;
@@ -138,6 +138,7 @@ int main(int argc, char** argv) {
         else if (!strcmp(n, "unused")) unused = atoi(v);
         else if (!strcmp(n, "fail_malloc")) fail = atoi(v);
         else if (!strcmp(n, "queries")) queries = atoi(v);
+        else if (!strcmp(n, "query_roots")) query_roots = atoll(v);
         else if (!strcmp(n, "left")) left = atoll(v);
         else if (!strcmp(n, "device")) query_device = atoi(v);
         else return 2;
@@ -153,7 +154,7 @@ int main(int argc, char** argv) {
     fail_malloc = fail;
     if (left >= 0) free_limit = live_bytes + (size_t)left;
     device = query_device;
-    for (int i = 0; i < queries; ++i) rc = nd_sample_query(g, app, &p, roots, &steps, lens, &ws);
+    for (int i = 0; i < queries; ++i) rc = nd_sample_query(g, app, &p, query_roots, &steps, lens, &ws);
     fail_malloc = 0;
     printf("query %d %zu %d\n", rc, ws, steps);
     printf("device %d\n", device);

@@ -90,6 +90,24 @@ def test_membership_tables_are_made_on_the_device_of_the_graph(program):
     assert got["allocated"] == [graph + _tables(V, E)] and got["device"] == [1]
 
 
+_LIMIT = (7 << 29) // 64  # entries whose cells take 3.5 GB
+
+
+@pytest.mark.parametrize("app", [B.ND_DEEPWALK, B.ND_PPR])
+@pytest.mark.parametrize("E,walks,query_walks,built,used", [
+    (_LIMIT, 600_000, 600_000, True, True), (_LIMIT + 1, 600_000, 600_000, False, False),
+    (_LIMIT + 1, 32_768, 32_768, True, True), (_LIMIT + 1, 32_769, 32_769, False, False),
+    (2 * _LIMIT, 64, 64, True, True), (2 * _LIMIT, 600_000, 64, True, False)])
+def test_weighted_walks_draw_from_cells_where_they_are_the_faster(program, app, E, walks, query_walks, built, used):
+    """Many walks on graphs whose cells take 4 GB and more are slower by them (600 K walks of 20 steps on 117 M entries
+    590 us, 445 by the links): they use none, whoever had them built, and ask for none."""
+    V = 1000
+    graph = (V + 1) * 8 + E * 4 + E * 12 + V * 4 + E * 32
+    got = program(app, walks, V=V, E=E, weighted=1, num_steps=2, use_weights=1, query_roots=query_walks)
+    assert got["static"] == [0] and got["allocated"] == [graph + (E * 64 if built else 0)]
+    assert ("kernelILi3E" if used else "kernelILi1E") in got["launches"][0]
+
+
 @pytest.mark.parametrize("per,fanout,samples,lanes", [
     (4, [7], 50_000, 64), (64, [64, 64], 3, 64), (65, [1], 9, 128), (1, [128, 3], 300, 128), (2, [129], 1, 256),
     (256, [256], 9000, 256), (64, [512, 512], 2000, 512), (512, [2048], 300, 512), (512, [2048], 256, 1024),
