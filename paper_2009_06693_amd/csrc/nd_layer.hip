@@ -299,6 +299,15 @@ int layer_prepare() {
 }
 
 constexpr size_t kLdsPerUnit = 160 << 10;
+constexpr size_t kLdsPiece = 1280;                            // LDS is given out in pieces of this size
+constexpr size_t kLayerStaticLds = 256 + (512 / 64 + 1) * 8;  // the kernel's votes and its scan, with 512 lanes
+
+// Samples of 512 lanes that a compute unit has at a time: by their LDS, and by registers at most three.
+int64_t layer_samples_per_unit(size_t lds_bytes) {
+    const size_t each = (lds_bytes + kLayerStaticLds + kLdsPiece - 1) / kLdsPiece * kLdsPiece;
+    const int64_t n = (int64_t)(kLdsPerUnit / each);
+    return n < 3 ? n : 3;
+}
 
 int64_t layer_fused_groups(const Graph& gr, int64_t S) {
     const int64_t most = (int64_t)gr.num_cus * 64;  // bounds the flags; the workgroups stride over the samples
@@ -325,10 +334,16 @@ int layer_fused(const Graph& gr, uint64_t seed, uint32_t sample_base, bool weigh
     }
     a.o_rows_b = rows[0] * 8u;
     a.o_incl = a.o_rows_b + rows[1] * 8u;
-    a.totals = weighted ? gr.totals.load(std::memory_order_acquire) : nullptr;
     a.o_v = a.o_incl + widest * 8u;
-    // at most 24 bytes per transit, 28 with totals
-    const size_t lds_bytes = (size_t)a.o_v + (a.totals ? (size_t)widest * 4u : 0u);
+    // At most 24 bytes per transit, 28 with totals; without them where a call's samples then run at once and would not
+    // with them.  Without and with, us: 512 samples of [2920,2920] over 1.6 M entries 110 and 132 (two per unit and
+    // one), 700 of [2100,2100] 110 and 132 (three and two), 257 of [3200,3200] 93 and 108; more samples take more rounds
+    // either way, and the totals make up for it (4,096 of [3200,3200] 951 and 924; over 115 M entries 1,630 and 1,549).
+    const size_t with = (size_t)a.o_v + (size_t)widest * 4u;
+    const bool waits = S > (int64_t)gr.num_cus * layer_samples_per_unit(with) &&
+                       S <= (int64_t)gr.num_cus * layer_samples_per_unit(a.o_v);
+    a.totals = weighted && !waits ? gr.totals.load(std::memory_order_acquire) : nullptr;
+    const size_t lds_bytes = a.totals ? with : (size_t)a.o_v;
     a.roots = roots;
     a.hdr = (WsHeader*)ws;
     a.flags = (uint32_t*)(ws + o_flags);
@@ -341,7 +356,7 @@ int layer_fused(const Graph& gr, uint64_t seed, uint32_t sample_base, bool weigh
     // because there are no more (200 of [2048]: 9.5 us, 10.4 with 512; 300: 16.4 and 13.2) or because two
     // do not fit its LDS (600 of [4096,4096]: 108 and 137).
     const uint32_t lanes = widest > most_draws ? widest : most_draws;
-    const bool one_each = S <= (int64_t)gr.num_cus || lds_bytes > kLdsPerUnit / 2;
+    const bool one_each = S <= (int64_t)gr.num_cus || layer_samples_per_unit(lds_bytes) == 1;
     const int threads = lanes <= 64u ? 64 : lanes <= 128u ? 128 : lanes <= 256u ? 256
                         : lanes > 512u && one_each ? 1024 : 512;
 #define ND_LAYER_LAUNCH_T(OFFT, W, STRIDE, T)                                                               \

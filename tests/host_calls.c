@@ -10,7 +10,7 @@
  *   create RC
  *   query RC WORKSPACE_BYTES STEPS
  *   static RC
- *   launch KERNEL          (one line per launch, of the sampling call only)
+ *   launch KERNEL GRID LDS (one line per launch, of the sampling call only; LDS: the dynamic bytes)
  *   device D               (current when the queries have returned)
  *   allocated BYTES        (live when the program ends, before the graph is destroyed)
  * Names: the fields of nd_params, fanout as a,b,c; queries=N (asks N times); fail_malloc=N (the first N
@@ -103,9 +103,9 @@ int __hipPopCallConfiguration(dim3_t* g, dim3_t* b, size_t* lds, void** s) {
     return 0;
 }
 int hipLaunchKernel(const void* f, dim3_t g, dim3_t b, void** args, size_t lds, void* s) {
-    (void)b; (void)args; (void)lds; (void)s;
+    (void)b; (void)args; (void)s;
     for (int i = 0; trace && i < n_kernels; ++i)
-        if (kernels[i].f == f) printf("launch %s %u\n", kernels[i].name, g.x);
+        if (kernels[i].f == f) printf("launch %s %u %zu\n", kernels[i].name, g.x, lds);
     return 0;
 }
 

@@ -22,11 +22,12 @@ def program(tmp_path_factory):
         args += [f"{k}={','.join(map(str, v)) if isinstance(v, (list, tuple)) else v}" for k, v in params.items()]
         r = subprocess.run([exe, *args], capture_output=True, text=True)
         assert r.returncode == 0, (args, r.returncode, r.stdout, r.stderr)
-        got = {"launches": []}
+        got = {"launches": [], "lds": []}
         for line in r.stdout.splitlines():
             what, *rest = line.split()
             if what == "launch":
                 got["launches"].append(rest[0])
+                got["lds"].append(int(rest[2]))
             else:
                 got[what] = [int(x) for x in rest]
         return got
@@ -118,3 +119,24 @@ def test_layer_samples_take_as_many_lanes_as_they_have_transits_and_draws(progra
     got = program(B.ND_LAYER, samples * per, fanout=fanout, roots_per_sample=per)
     assert got["static"] == [0] and len(got["launches"]) >= 1
     assert f"Li{lanes}EE" in got["launches"][0] and "layer_fused" in got["launches"][0]
+
+
+@pytest.mark.parametrize("n,samples,totals,lanes", [
+    (3399, 256, True, 1024), (3399, 257, False, 512), (3399, 512, False, 512), (3399, 513, True, 1024),
+    (2914, 512, True, 512), (2915, 512, False, 512), (2915, 513, True, 1024), (3400, 257, True, 1024),
+    (1908, 513, True, 512), (1909, 513, False, 512), (2226, 513, False, 512), (2227, 513, True, 512),
+    (2100, 512, True, 512), (2100, 768, False, 512), (2100, 769, True, 512)])
+def test_weighted_layer_samples_that_ran_at_once_do_not_wait_for_the_rows_totals(program, n, samples, totals, lanes):
+    """Totals take 4 bytes of LDS per transit: not where fewer samples then fit a unit and a second round begins (512 of
+    [2920, 2920]: 132 us, 110 without); 1,024 lanes where one fits, its static LDS counted (3,400 transits)."""
+    got = program(B.ND_LAYER, samples * n, V=100_000, E=200_000, weighted=1, use_weights=1, fanout=[n, n],
+                  roots_per_sample=n)
+    assert got["static"] == [0] and "layer_fused" in got["launches"][0] and f"Li{lanes}EE" in got["launches"][0]
+    assert got["lds"][0] == n * (28 if totals else 24)
+
+
+def test_layer_samples_of_which_one_fits_a_unit_take_all_its_lanes(program):
+    """Two of 3,400 transits fit 160 KB only without the kernel's static LDS."""
+    for n, lanes in ((3399, 512), (3400, 1024)):
+        got = program(B.ND_LAYER, 300 * n, fanout=[n, n], roots_per_sample=n)
+        assert f"Li{lanes}EE" in got["launches"][0]
