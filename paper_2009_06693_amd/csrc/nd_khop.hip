@@ -649,14 +649,16 @@ bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t 
     return w * fanout[k - 1] < (1ll << 31);
 }
 
-// Draws of the last hop from which a call's outputs leave past the caches, which then hold more of the graph, where they
-// leave in pairs: every vertex of R-MAT 22, [25,10], 1.05 G draws, 3,220 us and 3,058 like this; 70 to 400 M draws of
-// [25,10] on R-MAT 18 979 and 891 (the largest), over weights on 57 K vertices 1,070 and 1,041, on 2 M alike.  A batch that
-// L2 holds (1,024 roots) is faster through it (8.6 and 8.8), and calls of 1 to 64 M draws are alike.  Outputs that leave
-// one by one stay in the caches' way: 400 M draws of [7,13] on R-MAT 22 1,520 us and 1,581 past them, of [5,5] 2,637 and
-// 2,719, on R-MAT 18 1,156 and 1,186; only where L2 holds most of the entries are they faster past it ([7,13] on 57 K
-// vertices 1,258 and 1,221).
+// Draws of the last hop from which a call's outputs leave past the caches, which then hold more of the graph: every
+// vertex of R-MAT 22, [25,10], 1.05 G draws, 3,220 us and 3,058 like this; 400 M draws of [25,10] on R-MAT 18 979 and 891,
+// over weights on 57 K vertices 1,070 and 1,041, on 2 M alike.  A batch that L2 holds (1,024 roots) is faster through it
+// (8.6 and 8.8), and calls of 1 to 64 M draws are alike.  Outputs that leave one by one (odd fanouts) go past the
+// caches only where the L2s, of 4 MB each, hold the entries between them: 400 M draws on 57 K vertices (6 MB of
+// entries) [7,13] 1,258 and 1,221, [15,10,5] 2,390 and 2,352, on R-MAT 18 (16 MB) 1,156 and 1,186, 2,114 and 2,096; not
+// on R-MAT 22 (275 MB) with 1,520 and 1,581 for [7,13], 2,637 and 2,719 for [5,5], 2,703 and 2,727 for [15,10,5], nor on 2 M
+// vertices (128 MB): 1,985 and 2,022, 3,883 and 3,983, 3,122 and 3,141.
 constexpr int64_t kPastCaches = 64 << 20;
+constexpr int64_t kPastCachesOneByOne = 8 << 20;  // entries: 32 MB
 
 int64_t khop_fused_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
     int64_t W[ND_MAX_FANOUT_STEPS];
@@ -697,14 +699,15 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     mark_phase(ND_PHASE_SAMPLE_SUB, stream);
     const dim3 grid((unsigned)f.groups), block(kFusedThreads);
     const bool pairs = khop_in_pairs(a.m[k - 1], step_out[k - 1]);
-    const bool past = pairs && S * W[k - 1] >= kPastCaches;
+    const bool past = S * W[k - 1] >= kPastCaches && (pairs || gr.E <= kPastCachesOneByOne);
 #define ND_FUSED_LAUNCH_R(STRIDE, R, PAST, OFFT)                                                                  \
     hipLaunchKernelGGL((khop_fused_kernel<STRIDE, R, PAST, OFFT>), grid, block, f.lds, stream, view_of<OFFT>(gr), a)
 #define ND_FUSED_LAUNCH(STRIDE, OFFT)                           \
     do {                                                        \
-        if (past) ND_FUSED_LAUNCH_R(STRIDE, 2, true, OFFT);     \
-        else if (pairs) ND_FUSED_LAUNCH_R(STRIDE, 2, false, OFFT); \
-        else ND_FUSED_LAUNCH_R(STRIDE, 1, false, OFFT);         \
+        if (pairs && past) ND_FUSED_LAUNCH_R(STRIDE, 2, true, OFFT);       \
+        else if (pairs) ND_FUSED_LAUNCH_R(STRIDE, 2, false, OFFT);         \
+        else if (past) ND_FUSED_LAUNCH_R(STRIDE, 1, true, OFFT);           \
+        else ND_FUSED_LAUNCH_R(STRIDE, 1, false, OFFT);                    \
     } while (0)
     if (gr.off64) {
         if (gr.wq) ND_FUSED_LAUNCH(2, int64_t);

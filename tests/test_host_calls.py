@@ -142,11 +142,13 @@ def test_layer_samples_of_which_one_fits_a_unit_take_all_its_lanes(program):
         assert f"Li{lanes}EE" in got["launches"][0]
 
 
-@pytest.mark.parametrize("fanout,samples,kernel", [(4096, 16_384, "Li2ELb1E"), (4096, 16_383, "Li2ELb0E"),
-                                                   (4097, 16_384, "Li1ELb0E"), (4097, 100_000, "Li1ELb0E")])
+@pytest.mark.parametrize("fanout,samples,E,kernel", [
+    (4096, 16_384, 4000, "Li2ELb1E"), (4096, 16_383, 4000, "Li2ELb0E"), (4096, 16_384, 20_000_000, "Li2ELb1E"),
+    (4097, 16_384, 8 << 20, "Li1ELb1E"), (4097, 16_384, (8 << 20) + 1, "Li1ELb0E"), (4097, 16_376, 4000, "Li1ELb0E")])
 @pytest.mark.parametrize("weighted", [0, 1])
-def test_khop_outputs_that_leave_one_by_one_do_not_pass_the_caches(program, fanout, samples, kernel, weighted):
-    """Past the caches from 64 M draws of the last hop on, in pairs (400 M draws of [7, 13] on R-MAT 22: 1,581 us one by
-    one past the caches, 1,520 through them)."""
-    got = program(B.ND_KHOP, samples, fanout=[fanout], weighted=weighted)
+def test_khop_outputs_that_leave_one_by_one_pass_the_caches_of_small_graphs_only(program, fanout, samples, E, kernel,
+                                                                                weighted):
+    """Past the caches from 64 M draws of the last hop on: in pairs, and one by one where L2 holds the entries (400 M draws
+    of [7, 13] on R-MAT 22: 1,581 us one by one past the caches, 1,520 through them)."""
+    got = program(B.ND_KHOP, samples, V=1_000_000, E=E, fanout=[fanout], weighted=weighted)
     assert got["static"] == [0] and f"khop_fused_kernelILi{1 + weighted}E{kernel}" in got["launches"][0]
