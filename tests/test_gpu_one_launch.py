@@ -224,12 +224,11 @@ def test_layer(graph, per, fanout, S):
         assert_steps_equal(got, want, f"layer per={per} {fanout} weighted={weighted}")
 
 
+@pytest.mark.parametrize("graph", [(True, False), (True, True)], ids=["weighted32", "weighted64"], indirect=True)
 @pytest.mark.parametrize("per,fanout", [(4096, [4096, 30]), (1, [700, 4096]), (65, [64, 63, 5])])
 def test_layer_over_weights_with_and_without_the_rows_totals(graph, per, fanout):
     """They are made when the sizes of a weighted layer call are asked for."""
     g, dg, og = graph
-    if g.weights is None:
-        pytest.skip("unweighted graph")
     roots = _roots(g.V, per * 7, 51)
     want = oracle.layer(og, roots, per, fanout, seed=52, use_weights=True)
     kw = dict(num_steps=len(fanout), fanout=fanout, roots_per_sample=per)
@@ -558,17 +557,53 @@ def test_dense_khop_whose_first_hop_is_not_grouped(int64_offsets, S):
     assert all(torch.equal(a, b) for a, b in zip(*outs))
 
 
+def _whole_and_halves(dg, app, S, roots, **kw):
+    """The outputs of a call, and of two calls for its halves, step by step."""
+    def call(first, last):
+        p = B.nd_params_init(sample_id_base=first, **kw)
+        return [o.reshape(-1) for o in B.Sampler(dg, app, p, last - first).run(roots[first:last], 33)]
+
+    return zip(call(0, S), zip(call(0, S // 2), call(S // 2, S)))
+
+
+@pytest.mark.parametrize("fanout", [[3, 6], [9, 4], [9, 3]])
+def test_outputs_of_large_khop_calls(graph, fanout):
+    """From 64 M draws of the last hop on outputs leave past the caches, in pairs or one by one: the first such call
+    against its two halves, which are below the line."""
+    g, dg, _ = graph
+    S = -(-(64 << 20) // (fanout[0] * fanout[1]))
+    r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
+    for whole, halves in _whole_and_halves(dg, B.ND_KHOP, S, r, num_steps=2, fanout=fanout):
+        assert torch.equal(whole, torch.cat(halves))
+
+
 @pytest.mark.parametrize("fanout", [[9, 3], [3, 6]])
-@pytest.mark.parametrize("rounds", [0, 3])
-def test_outputs_of_large_khop_calls_leave_past_the_caches(fanout, rounds):
-    """From 64 M draws of the last hop on: the first such call, against its two halves, which are below the line."""
+def test_large_khop_calls_with_unique_neighbours(fanout):
+    """64 M slots of the last hop against their two halves."""
     g, dg, _ = _graph(False, False)
     S = -(-(64 << 20) // (fanout[0] * fanout[1]))
     r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
+    for whole, halves in _whole_and_halves(dg, B.ND_KHOP, S, r, num_steps=2, fanout=fanout, unique_rounds=3):
+        assert torch.equal(whole, torch.cat(halves))
 
-    def call(first, last):
-        p = B.nd_params_init(num_steps=2, fanout=fanout, unique_rounds=rounds, sample_id_base=first)
-        return [o.reshape(-1) for o in B.Sampler(dg, B.ND_KHOP, p, last - first).run(r[first:last], 33)]
 
-    whole, halves = call(0, S), zip(call(0, S // 2), call(S // 2, S))
-    assert all(torch.equal(w, torch.cat(h)) for w, h in zip(whole, halves))
+@pytest.mark.parametrize("n", [2100, 2920, 3400])
+def test_layer_samples_over_weights_that_leave_the_totals(n):
+    """More samples than units hold with the rows' totals in LDS: against a graph that has none, and the oracle."""
+    g, dg, og = _graph(True, False)
+    S = 513 if n == 2100 else 257
+    roots = _roots(g.V, n * S, 61)
+    r = torch.as_tensor(roots, device="cuda:0")
+    kw = dict(num_steps=2, fanout=[n, n], roots_per_sample=n)
+    outs = []
+    for asked in (1, 0):
+        d = B.nd_graph_create(g.row_offsets, g.col_indices, g.weights)
+        lens, ws = B.nd_sample_query(d, B.ND_LAYER, B.nd_params_init(use_weights=asked, **kw), r.numel())
+        outs.append([torch.empty(k, dtype=torch.int32, device="cuda:0") for k in lens])
+        B.nd_sample(d, B.ND_LAYER, B.nd_params_init(use_weights=1, **kw), r, 62, outs[-1],
+                    torch.empty(ws, dtype=torch.uint8, device="cuda:0"))
+        torch.cuda.synchronize()
+    want = oracle.layer(og, roots[n * (S - 2):], n, [n, n], seed=62, use_weights=True, sample_id_base=S - 2)
+    for a, b, w in zip(*outs, want):
+        assert torch.equal(a, b)
+        assert np.array_equal(a[n * (S - 2):].cpu().numpy(), np.asarray(w).reshape(-1))
