@@ -25,10 +25,12 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM bytes per launch of the dominant kernel from two rocprofv3 --pmc runs of this file
-# (FETCH_SIZE, then WRITE_SIZE; scaled by the factors the copy kernel of `--workload copy_calib`
-# gives: x2.0 and x1.0), averaged over the launches of one call.  Source: the counter table in
-# profiles/one_launch_routes_rocprofv3.md.  None where not profiled.
+# Bytes per launch of the dominant kernel between L2 and what lies behind it, from two rocprofv3 --pmc
+# runs of this file (FETCH_SIZE, then WRITE_SIZE; scaled by the factors the copy kernel of `--workload
+# copy_calib` gives: x2.0 and x1.0), averaged over the launches of one call.  The last-level cache
+# serves a part of them, so `counter_frac`, their rate over the HBM peak, bounds the share of the peak
+# from above.  Source: the counter table in profiles/one_launch_routes_rocprofv3.md.  None where not
+# profiled.
 MEASURED_TRAFFIC_BYTES = {
     ("c5_khop", "khop_fused_kernel"): 22318600192,     # 17,135,604 KiB fetched + 4,659,904 KiB written
     ("c5_deepwalk", "walk_free_kernel"): 29912658944,  # 27,565,350 KiB fetched + 1,646,231 KiB written
@@ -281,23 +283,26 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
     #   layer: per sample and transit slot 4 + two row offsets, per draw 4 + 4.
     #   one launch over the graph's links (walks, k-hop, layer; nothing is grouped, so no distinct
     #     transits are counted): per root 4 + two row offsets, per output entry 4, per non-NULL draw a
-    #     16-byte link, or 4 (adjacency entry) in the last hop of k-hop and layer; a weighted draw reads
-    #     16 more of its row's guide and thresholds, a node2vec draw 16 of a membership table.
+    #     16-byte link, or 4 (adjacency entry) in the last hop of k-hop and layer; a weighted layer draw
+    #     reads 16 more of its row's guide and thresholds, a node2vec draw 16 of a membership table; a draw of
+    #     a weighted walk reads a cell of 64 (these graphs are all small enough for cells).
     links = "init" not in phase_ms  # its kernel writes the header itself
     if links:
         draws = live
         per_draw = [16.0] * n_steps
         if app in (B.ND_KHOP, B.ND_LAYER):
             per_draw[-1] = 4.0
-        if pkw.get("use_weights", 0) or app == B.ND_NODE2VEC:
+        if pkw.get("use_weights", 0) and app in (B.ND_DEEPWALK, B.ND_PPR):
+            per_draw = [64.0] * n_steps
+        elif pkw.get("use_weights", 0) or app == B.ND_NODE2VEC:
             per_draw = [x + 16.0 for x in per_draw]
         total_bytes = (4.0 + off_bytes) * int(roots.numel()) + sum(
             4.0 * s.step_len[i] + per_draw[i] * live_per_step[i] for i in range(n_steps))
     elif dom in ("sample_sub", "sample_wg") and stats is not None:
-        draws = sum(int(stats[i, 0]) * m_per_step[i] for i in range(n_steps))
-        # a first step that is not grouped has no count of distinct transits: its roots differ
-        total_bytes = sum(8.0 * int(stats[i, 0]) + off_bytes * int(stats[i, 1] or stats[i, 0]) + 4.0 * live_per_step[i]
-                          + 4.0 * int(stats[i, 0]) * m_per_step[i] for i in range(n_steps))
+        grouped = range(1 if "sample_sp" in phase_ms else 0, n_steps)  # khop_first_kernel draws the first hop of dense k-hop
+        draws = sum(int(stats[i, 0]) * m_per_step[i] for i in grouped)
+        total_bytes = sum(8.0 * int(stats[i, 0]) + off_bytes * int(stats[i, 1]) + 4.0 * live_per_step[i]
+                          + 4.0 * int(stats[i, 0]) * m_per_step[i] for i in grouped)
     elif dom == "walk_window" and stats is not None:
         draws = sum(int(stats[i, 0]) for i in range(n_steps))
         per_draw = 4.0
@@ -325,7 +330,8 @@ def run_workload(name, args, B, inputs, torch, np, cpu_baseline):
     if links:
         kernel = {"sample_sub": "khop_fused_kernel", "unique": "khop_unique_kernel", "layer": "layer_fused_kernel",
                   "walk_window": {B.ND_NODE2VEC: "walk_free_n2v_kernel",
-                                  B.ND_MULTIRW: "mrw_free_kernel"}.get(app, "walk_free_kernel")}[dom]
+                                  B.ND_MULTIRW: "mrw_free_kernel"}.get(
+                                      app, "walk_free_few_kernel" if roots.numel() <= 8192 else "walk_free_kernel")}[dom]
     else:
         kernel = {"sample_sub": "sample_tp_kernel", "sample_sp": "sample_sp_kernel", "layer": "layer_kernel",
                   "sample_wg": "sample_tp_kernel", "walk_window": "walk_window_kernel"}[dom]

@@ -416,7 +416,8 @@ typedef enum nd_phase {
     ND_PHASE_SAMPLE_SUB = 3,  /* the step's sampling kernel (all three classes), or */
                               /* k-hop's one launch for all hops                    */
     ND_PHASE_SAMPLE_WG = 4,   /* the same kernel when a heavy class is forced       */
-    ND_PHASE_SAMPLE_SP = 5,   /* sample-parallel kernel (ablation mode)             */
+    ND_PHASE_SAMPLE_SP = 5,   /* sample-parallel kernel: the ablation mode, and the */
+                              /* first hop of dense k-hop                           */
     ND_PHASE_LAYER = 6,       /* collective (layer) kernel: one launch per call, or */
                               /* per step without links                             */
     ND_PHASE_UNIQUE = 7,      /* unique neighbours: one launch for all hops, or a   */

@@ -729,7 +729,7 @@ int khop_first(const Graph& gr, const DrawArgs& d, int32_t m, int64_t S, const i
     int64_t groups = (n + per - 1) / per;
     if (groups > (int64_t)gr.num_cus * 16) groups = (int64_t)gr.num_cus * 16;
     const FastDiv div_m = make_fastdiv((uint32_t)m);
-    mark_phase(ND_PHASE_SAMPLE_SUB, stream);
+    mark_phase(ND_PHASE_SAMPLE_SP, stream);
     if (gr.off64)
         hipLaunchKernelGGL(khop_first_kernel<int64_t>, dim3((unsigned)groups), dim3(kFusedThreads), 0, stream,
                            view_of<int64_t>(gr), d.seed, d.sample_base, roots, n, div_m, out, ctl, status);
