@@ -191,7 +191,8 @@ __global__ __launch_bounds__(256) void build_rowset_kernel(const OffT* __restric
     }
 }
 
-// The WeightCells, one entry per thread: bound by their 64 bytes of stores.
+// The WeightCells, one entry per thread: 64 bytes stored for each at 1.5 to 1.9 TB/s (1.6 M entries 55 us, beside 0.28 ms
+// for the memory and the stream; 39 M 1.7 ms, 117 M 4.4, 412 M 14.5 with those), once per graph.
 template <typename OffT>
 __global__ __launch_bounds__(256) void build_cells_kernel(const OffT* __restrict__ off, const Link* __restrict__ links,
                                                           int64_t V, int64_t E, WeightCell* __restrict__ cells) {

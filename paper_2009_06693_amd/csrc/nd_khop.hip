@@ -626,12 +626,14 @@ void slots_per_sample(const int32_t* fanout, int32_t k, int64_t* W) {
 // Whether the fused kernel takes the call.  Its limits are the rows in LDS and the links.  Its cost is one
 // scattered fetch per line a pair's draws touch, whatever other pairs touch; grouping by transit fetches a
 // line once for all its draws and pays for it with the sort and with scattered stores.  Measured from
-// all, a tenth and a fiftieth of the vertices of ten graphs with fanouts [25,10], [10,10], [10,25], [20] and
-// [15,10,5]: grouping wins, by up to 1.4x, on dense graphs (rows that ten draws
-// rarely share a line of) with many pairs per vertex and enough draws to pay for its 26 launches; elsewhere it
-// loses, by up to 9x.  At the lines, over links and grouped: mean degree 145, 10 pairs per vertex, 23 M draws 325
-// and 286 us, 58 M 565 and 426; degree 93, 26 M 262 and 275; degree 204, 25 pairs, 14 M 172 and 160; degree 869, 25
-// pairs, 5 M 93 and 122; degree 487, 15 pairs, 17 M 368 and 449; degree 56, 25 pairs, 58 M 516 and 542.
+// all, a tenth and a fiftieth of the vertices of eleven graphs with fanouts [25,10], [10,10], [10,25], [20] and
+// [15,10,5]: grouping wins, by up to 1.6x, on dense graphs (rows that ten draws
+// rarely share a line of) with many pairs per vertex and enough draws to pay for its launches; elsewhere it
+// loses, by up to 11x.  Near the lines, over links and grouped: mean degree 149, 10 pairs per vertex, 23 M draws 279
+// and 239 us, 58 M 441 and 358; degree 203, 25 pairs, 14 M 161 and 131, 10 pairs, 14 M 113 and 110; degree 93, 10 pairs,
+// 26 M 251 and 248, 66 M 421 and 384, 25 pairs, 66 M 550 and 522; degree 82, 25 pairs, 66 M 481 and 500; degree 862, 25
+// pairs, 5 M 87 and 88; degree 487, 15 pairs, 17 M 357 and 400; degree 60, 25 pairs, 58 M 419 and 456.  The lines are where
+// they were before the first hop went ungrouped; what they leave on the slower side is at most 12 %.
 bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
     if (!gr.links) return false;
     int64_t pairs = S;

@@ -94,7 +94,7 @@ __device__ __forceinline__ int32_t first_transit(const FreeArgs& a, uint32_t s) 
 
 // DeepWalk and PPR.  Many walks: bound by the scattered 128-byte fetches of the links (one per draw;
 // the chip serves 5.5e10 of them per second whatever the array's size, once it exceeds L2).  Fewer: by the chain of a
-// step, 0.27 us from L2.  While a link is on its way, the vertex of the step before is stored and the words of the
+// step, 0.27 us from L2 (0.18 with 16 lanes per walk).  While a link is on its way, the vertex of the step before is stored and the words of the
 // next step are made; the assembler statement keeps the compiler (ROCm 7.2) from moving their making behind the wait for
 // the link, where it and the acknowledged store were part of the chain (32,768 walks of 100 steps over 1.5 MB of
 // links 37 us, like this 29; over 1.1 GB 72 and 60).
@@ -128,7 +128,11 @@ __global__ __launch_bounds__(THREADS) void walk_free_kernel(GraphView<OffT> g, F
         }
         const uint64_t word = cat64(r.r0, r.r1);
         if (si > 0) {  // after the load, which the next wait is for
-            // past the caches where walks are many: 4.2 M walks of 100 steps 4.79 ms, 4.72 like this
+            // Past the caches where walks are many.  Through them and past them, us: 4.2 M walks of 100 steps on R-MAT 22
+            // 4,921 and 4,855, 300 K of 40 143 and 140; on R-MAT 16 300 K of 100 355 and 353.  Records read the steps
+            // next, and find those of few outputs in the last-level cache: with them 600 K walks of 10 steps on R-MAT 16
+            // 83.5 and 86.5, of 100 steps 815 and 811, on R-MAT 22 93.8 and 95.4, 860 and 847.  (A line by the volume of
+            // the outputs gives up to 4 % to short walks with records and takes up to 2.5 % from walks without.)
             if (THREADS > 64) __builtin_nontemporal_store(v, &a.out[si - 1u][s]);
             else a.out[si - 1u][s] = v;
         }
@@ -162,9 +166,10 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F& f)
 // DeepWalk and PPR where walks are few, so that the time is that of one walk: 16 lanes per walk.  The words of a
 // step depend on nothing that the walk does, so each lane makes those of one step in 16, and all 16 lanes
 // take the walk's step with them (same link, one fetch); what is left of a step's chain is the multiplication, the
-// link's fetch (110 ns from L2, 350 from the last-level cache) and three selections.  The words of the next 16 steps and
+// link's fetch and three selections: 0.18 us a step where L2 holds the links, 0.36 where the last-level cache does (26 MB of
+// links), 0.51 over 1.1 GB (64 to 4,096 walks, another seed each call).  The words of the next 16 steps and
 // the vertices of the last 16 leave while a link is on its way.  4,096 walks of 100 steps over 1.5 MB of links: 36.5 us
-// with a lane per walk that made its words between two links, 18.6 like this.
+// with a lane per walk that made its words between two links, 18.3 like this.
 template <int DRAW, int STRIDE, typename OffT>
 __global__ __launch_bounds__(kFewThreads) void walk_free_few_kernel(GraphView<OffT> g, FreeArgs a) {
     __shared__ uint32_t s_hist[kFreeChunk + 1];
@@ -383,10 +388,11 @@ __device__ __forceinline__ uint32_t n2v_exact(const OffT* off, const int32_t* co
     return e;
 }
 
-// Out of line for workgroups of one wavefront (at most 65,536 walks, one wavefront per SIMD: 88 registers do not
-// matter, and the attempts' loop was better without it: 57 K weighted walks of 100 steps 419 us, 435 inlined);
-// inlined for many walks (59 registers: 7 wavefronts per SIMD instead of 5; a million weighted walks of 10
-// steps 454 us, 470 out of line).
+// Out of line for workgroups of one wavefront (at most 65,536 walks, of which a SIMD has one wavefront or two), inlined
+// for many walks (61 to 63 registers, 86 to 94 out of line: 7 wavefronts per SIMD instead of 5).  100 weighted steps,
+// out of line and inlined, us: p = 2, q = 0.5, 57 K walks on 1.6 M entries 262 and 262, on 38 M 338 and 337; p = 0.25, q = 4,
+// whose attempts are often used up, 4,439 and 4,361, 10,133 and 9,994.  Many walks, out of line
+// and inlined: a million of 10 steps on 38 M entries 549 and 554, of 20 steps without weights 511 and 515.
 template <typename OffT>
 __device__ __noinline__ uint32_t n2v_exact_call(const OffT* off, const int32_t* col, const uint32_t* wq,
                                                 const int32_t* rowset, bool exact, uint64_t R, uint32_t b_ret,
@@ -720,16 +726,18 @@ void launch_free(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, 
 }  // namespace
 
 // One walk per lane, and a workgroup of one wavefront as long as that gives every compute unit at
-// most a few of them: node2vec's walks end at their own pace, and a workgroup of four is held until the last
-// one has (16,384 walks of 20 steps 47 us, 59 with four; DeepWalk and PPR alike within a few percent).  More
-// walks take workgroups of four, which have fewer headers and counters to write (a million node2vec walks 522
-// us, 539 with one).
+// most a few of them: a workgroup of four starts and ends later than its wavefronts would.  20 steps on R-MAT 22, one
+// wavefront and four, us: 16,384 walks of DeepWalk 10.3 and 11.5, of node2vec 33.8 and 35.4; 65,536 17.3 and 17.1, 38.9 and
+// 38.4.  More walks take workgroups of four, which have fewer headers and counters to write: a million of DeepWalk 261 and
+// 254, of PPR 239 and 232 (node2vec 506 and 515).
 static int free_threads(int64_t S) { return S <= 65536 ? 64 : 256; }
 
 // DeepWalk and PPR up to this many walks: sixteen lanes per walk (walk_free_few_kernel).  100 steps, sixteen lanes and
 // one, us: over links that L2 holds (1.5 MB) 18.6 and 28.1 for 4,096 walks, 20.8 and 28.4 for 8,192, 25.6 and 28.9 for
 // 16,384, 39 and 29 for 32,768; over 1.1 GB 18.3 and 27.4 for 1,024, 34 and 39 for 4,096, 38.1 and 39.5 for 8,192,
-// 42.6 and 40.8 for 16,384.
+// 42.6 and 40.8 for 16,384 (calls repeated with one seed, whose links the caches then hold).  Over weights, PPR at 0.01 by the cells: 1.6 M entries, weights in [1, 5), 30.5 and 37.8 for
+// 1,024, 51.8 and 54.3 for 8,192, 57.0 and 55.2 for 16,384, 123 and 63 for 32,768; symmetric weights, whose draws search
+// more often, 64.6 and 86.2 for 8,192, 71 and 86 for 16,384, 139 and 103 for 32,768.
 constexpr int64_t kFewWalks = 8192;
 
 // Whether weighted walks draw from the cells.  One fetch of 64 bytes per entry stands against two of 32, so a graph's
