@@ -225,8 +225,10 @@ int nd_graph_info(const nd_graph* g, int64_t* V, int64_t* E, int* has_weights,
  * draw takes two dependent looks.  It does so for up to 32,768 walks, and for any
  * number on graphs of up to 58 M entries: more walks on larger graphs are faster
  * without it, and do not use it where it is there.  For layer sampling with
- * use_weights it is the sum of every row's weights (8 bytes per vertex).  A caller
- * who wants the memory more than the speed asks for these sizes with
+ * use_weights it is the sum of every row's weights (8 bytes per vertex).  For k-hop
+ * calls of 6 M draws and more (200 K on dense graphs) it is the columns in as many
+ * bits as a vertex takes, up to 25.  A caller
+ * who wants the memory more than the speed asks for the weighted calls' sizes with
  * use_weights = 0, which are the same.  No other call of this function touches
  * the device.
  */

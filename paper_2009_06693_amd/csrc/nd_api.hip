@@ -49,6 +49,7 @@ struct Plan {
     bool free_walk = false;    // walks over the graph's links, one lane per walk (nd_walk_free.hip)
     bool fused = false;        // k-hop: all hops in one launch (nd_khop.hip)
     bool first_free = false;   // k-hop that groups: its first hop does not
+    bool packed = false;       // k-hop: draws read the packed columns, where they are there
     bool layer_fused = false;  // layer sampling: all steps of a sample by one workgroup
     size_t o_flags = 0, o_parts = 0;  // per workgroup: flag, live pairs per step
 };
@@ -209,6 +210,7 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     }
     pl->max_slots = 0;
     pl->max_out = 0;
+    const bool khop_default = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0;
     int64_t planned = -1;  // slots that the last sort plan was made for
     double guard = 1.0;
     for (int i = 0; i < pl->k; ++i) {
@@ -238,11 +240,11 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     }
     pl->layer_fused = app == ND_LAYER && g.links != nullptr;
     // a call without samples draws nothing, and its fanouts have no bound that a shape could be made from
-    const bool khop_default = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0;
     pl->first_free = khop_default && p->unique_rounds == 0 && g.links && pl->S <= g.V;
     pl->fused = khop_default && pl->S > 0 &&
                 (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
                                       : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
+    pl->packed = khop_default && p->unique_rounds == 0 && khop_reads_packed(g, p->fanout, p->num_steps, pl->S);
     return ND_OK;
 }
 
@@ -520,6 +522,7 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
     if (app == ND_NODE2VEC && pl.free_walk) graph_need_rowset(*h->g);
     else if (params->use_weights && pl.free_walk && walk_uses_cells(*h->g, pl.S)) graph_need_cells(*h->g);
     else if (params->use_weights && pl.layer_fused) graph_need_totals(*h->g);
+    else if (pl.packed) graph_need_packed(*h->g);
     if (num_steps) *num_steps = pl.k;
     if (step_len) {
         for (int i = 0; i < pl.k; ++i) {
@@ -617,6 +620,8 @@ static int sample_impl(const nd_graph* h, int app, const nd_params* params, cons
     a.use_weights = params->use_weights ? 1 : 0;
     a.lds_policy = params->lds_stage_policy;
     a.max_attempts = params->n2v_max_attempts;
+    a.packed.bytes = pl.packed ? g.packed.load(std::memory_order_acquire) : nullptr;
+    a.packed.bits = packed_bits(g.V);
     if (app == ND_NODE2VEC) {
         if (params->bias_convention == 0) {
             a.b_ret = q16(1.0 / params->p);

@@ -67,6 +67,27 @@ struct WeightCell {
 };
 static_assert(sizeof(WeightCell) == 64, "four 16-byte loads");
 
+// The columns in as many bits as a vertex takes, one after the other, for the draws of k-hop, which are bound by the
+// lines they touch: a row has fewer of them.  Entry e starts at bit e * bits; the four bytes from that bit's byte on
+// hold the whole entry while bits <= 25, so that a draw stays one load, of any alignment.  Less than 4 GB, so that the
+// place is a 32-bit offset.
+struct PackedCols {
+    const uint8_t* bytes;   // null: not there
+    uint32_t bits;
+    static constexpr uint32_t kMostBits = 25;
+};
+__device__ __forceinline__ int32_t packed_entry(const PackedCols& p, uint32_t e) {
+    const uint64_t bit = (uint64_t)e * p.bits;
+    uint32_t word;
+    __builtin_memcpy(&word, p.bytes + (uint32_t)(bit >> 3), 4);
+    return (int32_t)__builtin_amdgcn_ubfe(word, (uint32_t)bit & 7u, p.bits);
+}
+inline uint32_t packed_bits(int64_t V) {
+    uint32_t bits = 1;
+    while ((1ll << bits) < V) ++bits;
+    return bits;
+}
+
 struct Graph {
     int64_t V = 0, E = 0;
     int off64 = 0;              // width of row offsets as stored
@@ -87,11 +108,14 @@ struct Graph {
     mutable std::atomic<WeightCell*> cells{nullptr};
     // V sums of the rows' weights: built when the sizes of a layer call over edge weights are first asked for
     mutable std::atomic<uint64_t*> totals{nullptr};
+    // E columns in packed_bits(V) bits: built when the sizes of a k-hop call that reads them are first asked for
+    mutable std::atomic<uint8_t*> packed{nullptr};
     mutable std::mutex extra_mutex;
 };
 void graph_need_rowset(const Graph& g);
 void graph_need_totals(const Graph& g);
 void graph_need_cells(const Graph& g);
+void graph_need_packed(const Graph& g);
 
 // Is u in the row of v?  Every row owns a hash table of at least 2 deg + 1 places in groups of four
 // (16 bytes), open addressing by groups, empty places -1: one fetch answers most questions where a

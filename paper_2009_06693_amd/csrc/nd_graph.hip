@@ -229,6 +229,24 @@ __global__ __launch_bounds__(256) void build_totals_kernel(const OffT* __restric
     }
 }
 
+// The packed columns, a 32-bit word per thread: the entries that have a bit in it, two to four where bits >= 11.  Reads
+// come from the caches, which neighbouring words share.
+__global__ __launch_bounds__(256) void build_packed_kernel(const int32_t* __restrict__ col, int64_t E, uint32_t bits,
+                                                           uint32_t words, uint32_t* __restrict__ packed) {
+    for (uint32_t w = blockIdx.x * 256u + threadIdx.x; w < words; w += gridDim.x * 256u) {  // words < 2^30
+        const uint32_t group = w / bits;                        // 32 entries fill `bits` whole words
+        const uint32_t first_bit = (w - group * bits) * 32u;
+        uint32_t k = first_bit / bits, word = 0;
+        int32_t at = (int32_t)(k * bits) - (int32_t)first_bit;  // where entry k starts in the word, from -(bits - 1) on
+        for (; at < 32; ++k, at += (int32_t)bits) {
+            const int64_t e = (int64_t)group * 32 + k;
+            const uint32_t v = e < E ? (uint32_t)col[e] : 0u;
+            word |= at < 0 ? v >> -at : v << at;
+        }
+        packed[w] = word;
+    }
+}
+
 __global__ __launch_bounds__(256) void fill_empty_kernel(int4* p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         p[i] = make_int4(-1, -1, -1, -1);
@@ -265,6 +283,7 @@ void free_graph(Graph* g) {
     (void)hipFree(g->rowset.load());
     (void)hipFree(g->cells.load());
     (void)hipFree(g->totals.load());
+    (void)hipFree(g->packed.load());
     delete g;
 }
 
@@ -436,6 +455,18 @@ void graph_need_totals(const Graph& g) {
         else
             hipLaunchKernelGGL(build_totals_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.cumq,
                                g.V, totals);
+    });
+}
+
+// The packed columns: packed_bits(V) bits per entry and up to three bytes that the last entry's load takes with it.
+void graph_need_packed(const Graph& g) {
+    const uint32_t bits = packed_bits(g.V);
+    if (bits > PackedCols::kMostBits) return;
+    const int64_t words = ((g.E + 31) / 32) * bits;
+    if (words * 4 + 4 >= (1ll << 32)) return;
+    need_extra(g, g.packed, (size_t)words * 4 + 4, [&](uint8_t* packed, hipStream_t stream) {
+        hipLaunchKernelGGL(build_packed_kernel, dim3((unsigned)g.num_cus * 16u), dim3(256), 0, stream, g.col, g.E, bits,
+                           (uint32_t)words, (uint32_t*)packed);
     });
 }
 

@@ -18,6 +18,7 @@ constexpr int kFusedThreads = 256;
 
 struct FusedArgs {
     const Link* links;
+    PackedCols packed;
     uint64_t seed;
     uint32_t sample_base;
     uint32_t S, G, splits;      // samples; per workgroup; workgroups that share the last hop of a group
@@ -53,8 +54,9 @@ __device__ __forceinline__ uint2 row_of_link(const Link& l) { return make_uint2(
 
 // Bound by latency (small calls: a hop is generator, link, row; 37 roots of three hops take one launch
 // instead of 26) or by the rate of scattered fetches (large ones).
-// R: draws per lane of the last hop, a divisor of its fanout.  PAST: outputs go past the caches.
-template <int STRIDE, int R, bool PAST, typename OffT>
+// R: draws per lane of the last hop, a divisor of its fanout.  PAST: outputs go past the caches.  PACKED: the last hop
+// reads the packed columns (R-MAT 22, every vertex, [25,10]: 22 bits instead of 32, 3,075 us and 2,860 like this).
+template <int STRIDE, int R, bool PAST, bool PACKED, typename OffT>
 __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<OffT> g, FusedArgs a) {
     extern __shared__ uint2 s_rows[];  // rows of the parents of this hop, of the next, in turn
     __shared__ uint32_t s_live[ND_MAX_FANOUT_STEPS];
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
 #pragma unroll
                     for (uint32_t i = 0; i < R; ++i) {
                         v[u][i] = ND_NULL_VERTEX;
-                        if (row[u].y > 0u) v[u][i] = g.col[e[u][i]];
+                        if (row[u].y > 0u) v[u][i] = PACKED ? packed_entry(a.packed, e[u][i]) : g.col[e[u][i]];
                     }
 #pragma unroll
                 for (uint32_t u = 0; u < kInFlight; ++u)
@@ -164,8 +166,8 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
 // The first hop of a call that groups its later ones: roots as a rule differ, so that grouping them by transit finds
 // nothing to share, and their draws leave in order.  Bound by the lines of the rows.  233 K roots of 25 draws, mean
 // degree 487: 85 us, 133 with the grouping (a sort, four kernels of groups and classes, 74 for the draws).
-template <typename OffT>
-__global__ __launch_bounds__(kFusedThreads) void khop_first_kernel(GraphView<OffT> g, uint64_t seed, uint32_t sample_base,
+template <bool PACKED, typename OffT>
+__global__ __launch_bounds__(kFusedThreads) void khop_first_kernel(GraphView<OffT> g, PackedCols packed, uint64_t seed, uint32_t sample_base,
                                                                    const int32_t* __restrict__ roots, uint32_t n,
                                                                    FastDiv div_m, int32_t* __restrict__ out, StepCtl* ctl,
                                                                    uint32_t* status) {
@@ -203,7 +205,10 @@ __global__ __launch_bounds__(kFusedThreads) void khop_first_kernel(GraphView<Off
             const uint32_t d = (uint32_t)d0 + u * kFusedThreads, q = fastdiv(d, div_m), j = d - q * div_m.d;
             live += (uint32_t)__popcll(__ballot(v[u] >= 0 && j == 0u));
             v[u] = ND_NULL_VERTEX;
-            if (deg[u] > 0u) v[u] = g.col[rs[u] + mulhi32(draw4(seed, sample_base + q, j, 0u, 0u).r0, deg[u])];
+            if (deg[u] > 0u) {
+                const uint64_t e = rs[u] + mulhi32(draw4(seed, sample_base + q, j, 0u, 0u).r0, deg[u]);
+                v[u] = PACKED ? packed_entry(packed, (uint32_t)e) : g.col[e];
+            }
         }
 #pragma unroll
         for (uint32_t u = 0; u < kInFlight; ++u)
@@ -651,6 +656,21 @@ bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t 
     return w * fanout[k - 1] < (1ll << 31);
 }
 
+// Whether a call is faster over the packed columns: where its draws fetch a line each or two and are many.  The m draws of
+// a short row share its lines anyway, and then only the instructions of the unpacking are felt.  Measured with
+// [25,10], [10,25], [20], [15,10,5], [7,13], [5,5], [10,10] and [8,8,4] on twelve graphs, plain time over packed time
+// (both with the better kind of store): from 6 M draws on and a mean degree of 6/5 of the last fanout 0.97 to 1.35
+// ([8,8,4] on 3 M vertices the least, [15,10,5] on R-MAT 18 the most), below it 0.81 to 1.0 ([10,25] at a mean degree of 20
+// and 29 0.81 and 0.83, [20] at 16 0.91); fewer draws 0.91 to 1.1 there, from 200 K on 0.97 to 1.39 at mean degrees
+// of 207 and 487, below that 0.96 to 1.03.
+bool khop_reads_packed(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
+    if (!gr.links) return false;
+    int64_t draws = S;
+    for (int32_t i = 0; i < k; ++i) draws *= fanout[i];  // below 2^31 by the call's plan
+    return (draws >= 6000000 && 5 * gr.E >= 6 * (int64_t)fanout[k - 1] * gr.V) ||
+           (draws >= 200000 && gr.E >= 128 * gr.V);
+}
+
 // Draws of the last hop from which a call's outputs leave past the caches, which then hold more of the graph: every
 // vertex of R-MAT 22, [25,10], 1.05 G draws, 3,220 us and 3,058 like this; 400 M draws of [25,10] on R-MAT 18 979 and 891,
 // over weights on 57 K vertices 1,070 and 1,041, on 2 M alike.  A batch that L2 holds (1,024 roots) is faster through it
@@ -676,6 +696,7 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     const FusedShape f = fused_shape(gr, k, W, S);
     FusedArgs a{};
     a.links = gr.links;
+    a.packed = d.packed;
     a.seed = d.seed;
     a.sample_base = d.sample_base;
     a.S = (uint32_t)S;
@@ -703,7 +724,11 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     const bool pairs = khop_in_pairs(a.m[k - 1], step_out[k - 1]);
     const bool past = S * W[k - 1] >= kPastCaches && (pairs || gr.E <= kPastCachesOneByOne);
 #define ND_FUSED_LAUNCH_R(STRIDE, R, PAST, OFFT)                                                                  \
-    hipLaunchKernelGGL((khop_fused_kernel<STRIDE, R, PAST, OFFT>), grid, block, f.lds, stream, view_of<OFFT>(gr), a)
+    do {                                                                                                          \
+        auto* kernel = a.packed.bytes ? &khop_fused_kernel<STRIDE, R, PAST, true, OFFT>                           \
+                                      : &khop_fused_kernel<STRIDE, R, PAST, false, OFFT>;                         \
+        hipLaunchKernelGGL(kernel, grid, block, f.lds, stream, view_of<OFFT>(gr), a);                             \
+    } while (0)
 #define ND_FUSED_LAUNCH(STRIDE, OFFT)                           \
     do {                                                        \
         if (pairs && past) ND_FUSED_LAUNCH_R(STRIDE, 2, true, OFFT);       \
@@ -732,12 +757,17 @@ int khop_first(const Graph& gr, const DrawArgs& d, int32_t m, int64_t S, const i
     if (groups > (int64_t)gr.num_cus * 16) groups = (int64_t)gr.num_cus * 16;
     const FastDiv div_m = make_fastdiv((uint32_t)m);
     mark_phase(ND_PHASE_SAMPLE_SP, stream);
-    if (gr.off64)
-        hipLaunchKernelGGL(khop_first_kernel<int64_t>, dim3((unsigned)groups), dim3(kFusedThreads), 0, stream,
-                           view_of<int64_t>(gr), d.seed, d.sample_base, roots, n, div_m, out, ctl, status);
-    else
-        hipLaunchKernelGGL(khop_first_kernel<int32_t>, dim3((unsigned)groups), dim3(kFusedThreads), 0, stream,
-                           view_of<int32_t>(gr), d.seed, d.sample_base, roots, n, div_m, out, ctl, status);
+#define ND_FIRST_LAUNCH(PACKED, OFFT)                                                                              \
+    hipLaunchKernelGGL((khop_first_kernel<PACKED, OFFT>), dim3((unsigned)groups), dim3(kFusedThreads), 0, stream,  \
+                       view_of<OFFT>(gr), d.packed, d.seed, d.sample_base, roots, n, div_m, out, ctl, status)
+    if (gr.off64) {
+        if (d.packed.bytes) ND_FIRST_LAUNCH(true, int64_t);
+        else ND_FIRST_LAUNCH(false, int64_t);
+    } else {
+        if (d.packed.bytes) ND_FIRST_LAUNCH(true, int32_t);
+        else ND_FIRST_LAUNCH(false, int32_t);
+    }
+#undef ND_FIRST_LAUNCH
     ND_HIP_CHECK(hipGetLastError());
     return ND_OK;
 }

@@ -23,6 +23,7 @@ struct DrawArgs {
     int32_t lds_policy;
     const int32_t* prev_transit;  // node2vec: previous transit of every sample
     int32_t* out;                 // this step's output array
+    PackedCols packed;            // k-hop: what the sub-wavefront class and the fused kernel read, where it is there
 };
 
 // Device arrays and launch bounds of one transit-parallel step.
@@ -81,11 +82,13 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
               hipStream_t stream);
 
 // All hops of a k-hop call in one launch (nd_khop.hip).  fits: the graph has links, the rows of a
-// sample's widest hop with children fit LDS, and grouping by transit would not be faster; groups: workgroups, hence flags and rows of live counts.
+// sample's widest hop with children fit LDS, and grouping by transit would not be faster; reads_packed: the call, grouped
+// or not, is faster over the packed columns; groups: workgroups, hence flags and rows of live counts.
 // status_out (may be null): receives the status word when the roots are few enough for one
 // workgroup to look at (kKhopStatusRoots).
 constexpr int64_t kKhopStatusRoots = 8192;
 bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S);
+bool khop_reads_packed(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S);
 int64_t khop_fused_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S);
 int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_t k, int64_t S, const int32_t* roots,
                int32_t* const* step_out, char* ws, uint64_t o_flags, uint64_t o_parts, uint32_t* status_out,

@@ -135,7 +135,7 @@ __device__ __forceinline__ PairCtx load_pair(const GraphView<OffT>& g,
     return load_pair_row<HEAVY>(g, heavy_bits, load_pair_key(keys, vals, pi, P));
 }
 
-template <int DRAW, typename OffT>
+template <int DRAW, bool PACKED, typename OffT>
 __device__ __forceinline__ int32_t draw_pair(const GraphView<OffT>& g, const DrawArgs& a,
                                              const PairCtx& c, uint32_t jj) {
     if (DRAW == kDrawUniform) {
@@ -146,7 +146,7 @@ __device__ __forceinline__ int32_t draw_pair(const GraphView<OffT>& g, const Dra
         const Rand4 r = draw4(a.seed, a.sample_base + s, slot, a.step, 0u);
         const bool live = c.mine && c.deg > 0u && !(a.ppr_thr != 0 && (uint64_t)r.r3 < a.ppr_thr);
         const uint64_t e = live ? c.rs + mulhi32(r.r0, c.deg) : 0ull;
-        const int32_t u = g.col[e];
+        const int32_t u = PACKED ? packed_entry(a.packed, (uint32_t)e) : g.col[e];
         return live ? u : ND_NULL_VERTEX;
     }
     if (!c.mine || c.deg == 0) return ND_NULL_VERTEX;
@@ -157,7 +157,7 @@ __device__ __forceinline__ int32_t draw_pair(const GraphView<OffT>& g, const Dra
 
 // The loop of the sub-wavefront kernel.  HEAVY: some transits of this step belong to the
 // workgroup / grid class and must be skipped (looked up in the bitmap).
-template <int DRAW, bool HEAVY, typename OffT>
+template <int DRAW, bool PACKED, bool HEAVY, typename OffT>
 __device__ __forceinline__ void sub_loop(const GraphView<OffT>& g, const DrawArgs& a, uint32_t P,
                                          const int32_t* __restrict__ keys,
                                          const int32_t* __restrict__ vals,
@@ -201,7 +201,7 @@ __device__ __forceinline__ void sub_loop(const GraphView<OffT>& g, const DrawArg
                 nxt[u] = load_pair_row<HEAVY>(g, heavy_bits, key1[u]);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) res[u] = draw_pair<DRAW>(g, a, cur[u], jj);
+            for (int u = 0; u < U; ++u) res[u] = draw_pair<DRAW, PACKED>(g, a, cur[u], jj);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (cur[u].mine) a.out[cur[u].q * a.m + jj] = res[u];  // below 2^31 by the call's plan
@@ -216,7 +216,7 @@ __device__ __forceinline__ void sub_loop(const GraphView<OffT>& g, const DrawArg
             const uint32_t pi = fastdiv(d, a.div_m);
             const uint32_t jj = d - pi * a.m;
             const PairCtx c = load_pair<HEAVY>(g, keys, vals, heavy_bits, pi, P);
-            const int32_t res = draw_pair<DRAW>(g, a, c, jj);
+            const int32_t res = draw_pair<DRAW, PACKED>(g, a, c, jj);
             if (c.mine) a.out[c.q * a.m + jj] = res;
         }
     }
@@ -280,7 +280,7 @@ __device__ __forceinline__ void workgroup_draws(const GraphView<OffT>& g, const 
 // cursor runs out.  Then it turns into four independent 256-lane groups of the lane-per-draw
 // loop over all pairs (sub-wavefront class), which skips the pairs of transits marked in
 // heavy_bits.  A forced class runs only its half.
-template <int DRAW, typename OffT>
+template <int DRAW, bool PACKED, typename OffT>
 __global__ __launch_bounds__(kWgThreads) void sample_tp_kernel(
     GraphView<OffT> g, DrawArgs a, SchedParams sp, StepCtl* __restrict__ ctl,
     const int32_t* __restrict__ keys, const int32_t* __restrict__ vals,
@@ -327,9 +327,9 @@ __global__ __launch_bounds__(kWgThreads) void sample_tp_kernel(
         const uint32_t block = (threadIdx.x >> 8) * gridDim.x + blockIdx.x;
         // no transit went to the other classes this step: nothing to look up in the bitmap
         if (heavy_bits != nullptr && (ctl->n_wg | ctl->n_chunks) != 0u)
-            sub_loop<DRAW, true>(g, a, P, keys, vals, heavy_bits, pairs_per_block, tid, block, blocks);
+            sub_loop<DRAW, PACKED, true>(g, a, P, keys, vals, heavy_bits, pairs_per_block, tid, block, blocks);
         else
-            sub_loop<DRAW, false>(g, a, P, keys, vals, heavy_bits, pairs_per_block, tid, block, blocks);
+            sub_loop<DRAW, PACKED, false>(g, a, P, keys, vals, heavy_bits, pairs_per_block, tid, block, blocks);
     }
 }
 
@@ -351,7 +351,9 @@ int launch_tp(const Graph& gr, const DrawArgs& a, const SchedParams& sp, const T
     uint32_t ppb = a.m <= 256u ? 256u / a.m : 0u;
     if (ppb * a.m < 231u) ppb = 0u;
     mark_phase(lanes ? ND_PHASE_SAMPLE_SUB : ND_PHASE_SAMPLE_WG, stream);
-    hipLaunchKernelGGL((sample_tp_kernel<DRAW, OffT>), dim3((unsigned)blocks), dim3(kWgThreads), 0,
+    auto* kernel = &sample_tp_kernel<DRAW, false, OffT>;
+    if (DRAW == kDrawUniform && a.packed.bytes) kernel = &sample_tp_kernel<DRAW, DRAW == kDrawUniform, OffT>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kWgThreads), 0,
                        stream, g, a, sp, t.ctl, t.keys, t.vals, t.g_key, t.g_start, t.list_wg,
                        t.chunk_gid, t.chunk_idx, (uint32_t)t.cap_wg, (uint32_t)t.cap_chunks,
                        sp.force_class == ND_CLASS_AUTO ? (const uint32_t*)t.heavy_bits : nullptr, ppb,

@@ -607,3 +607,46 @@ def test_layer_samples_over_weights_that_leave_the_totals(n):
     for a, b, w in zip(*outs, want):
         assert torch.equal(a, b)
         assert np.array_equal(a[n * (S - 2):].cpu().numpy(), np.asarray(w).reshape(-1))
+
+
+@pytest.mark.parametrize("weighted,int64_offsets", [(False, False), (False, True), (True, False)])
+@pytest.mark.parametrize("V", [128, 129, 256, 257, 1025, 4096])
+def test_khop_over_packed_columns(V, weighted, int64_offsets):
+    """Dense graphs, whose columns are read in as many bits as a vertex takes (7 to 12): rows that start at any bit, a
+    last row that ends with the array, the largest vertex in it; one draw or two per lane, one hop to three."""
+    rng = np.random.default_rng(V)
+    rows = [np.unique(np.append(rng.integers(0, V, 4000 if V < 300 else 190), [V - 1, 0][:1 + v % 2])) for v in range(V)]
+    off = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64 if int64_offsets else np.int32)
+    col = np.concatenate(rows).astype(np.int32)
+    assert col.size >= 128 * V
+    w = (1.0 + rng.random(col.size)).astype(np.float32) if weighted else None
+    dg, og = B.nd_graph_create(off, col, w), oracle.OracleGraph(off, col, w)
+    for fanout, S in (([25, 10], 900), ([7, 13], 2300), ([211], 1000), ([15, 10, 5], 300)):
+        roots = _roots(V, S, 3)
+        want = oracle.khop(og, roots, fanout, seed=8, sample_id_base=4)
+        got, _ = gpu_sample(dg, B.ND_KHOP, roots, 8, num_steps=len(fanout), fanout=fanout, sample_id_base=4)
+        assert_steps_equal(got, want, f"khop {fanout} V={V}")
+
+
+@pytest.mark.parametrize("V", [1 << 25, (1 << 25) + 1])
+def test_khop_at_the_widest_packed_columns(V):
+    """25 bits, the most that one load of four bytes holds at every bit of a byte, and a vertex more, where the columns
+    stay as they are: against the sample-parallel kernel, which reads those."""
+    v = torch.arange(V, device="cuda:0")
+    other = (v * 2654435761 + 12345) % V
+    other = torch.where(other == v, (v + 1) % V, other)
+    col = torch.stack([torch.minimum(v, other), torch.maximum(v, other)], 1).view(-1).to(torch.int32)
+    off = (torch.arange(V + 1, device="cuda:0") * 2).to(torch.int32)
+    del v, other
+    dg = B.nd_graph_create(off, col)
+    r = torch.randint(0, V, (6_000_000,), device="cuda:0", dtype=torch.int32)
+    r[:1000] = torch.arange(V - 1000, V, device="cuda:0", dtype=torch.int32)
+    outs = []
+    for mode in (B.ND_MODE_TRANSIT_PARALLEL, B.ND_MODE_SAMPLE_PARALLEL):
+        s = B.Sampler(dg, B.ND_KHOP, B.nd_params_init(num_steps=2, fanout=[1, 1], mode=mode), r.numel())
+        outs.append([o.clone() for o in s.run(r, 13)])
+        torch.cuda.synchronize()
+        s.status()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+        assert int(a.min()) >= 0
