@@ -13,19 +13,19 @@
 // Output is one CSR over the rows (sample, transit slot).  A row lists the new
 // slots j whose vertex is a neighbour of the row's transit, ordered by (vertex
 // id, j) - the order a walk down the ascending adjacency list meets them - so
-// the result is unique.  To make that order cheap the sample's (vertex, slot)
-// pairs are sorted once in LDS (a radix sort); the hash table maps a vertex to
-// its run in the sorted list.  A table entry is one 32-bit word (fingerprint of
-// the vertex, start and length of the run) in a table twice the number of
-// slots; a fingerprint match is confirmed against the sorted list.
+// the result is unique.  A hash table maps a vertex to its slots, which lie together and ascending.
 //
-// Nine adjacency entries in ten are of no sample vertex, and the kernel is bound as much by
-// instruction issue as by the 4 bytes per entry it streams.  So an entry first tests one bit of a 65,536-bit
-// map of the sample's vertices (no loop, no divergence); the few that pass are packed, in order,
-// into a queue of the wavefront in LDS, and the table is probed by a full wavefront of queued
-// entries at a time.
+// Nine adjacency entries in ten are of no sample vertex, and the kernel is bound by instruction issue
+// (scalar instructions as much as vector ones) before the 4 bytes per entry it streams.  So an entry first tests one
+// bit of a 65,536-bit map of the sample's vertices (no loop, no divergence); the few that pass are packed, in order,
+// into a queue of the wavefront in LDS, and the table is probed by a full wavefront of queued entries at a time.
+// Whether there are as many is asked once for two or four loads of 64 entries, whose looks at the map then wait for LDS
+// together, and full steps have code of their own, without a test of where the list ends.  Counting pass of 4,096
+// samples of 2,048 transits and vertices (10 GB of lists): 2.12 ms with one load at a time and the lists' places fetched
+// one after the other, 1.46 like this (6.9 TB/s; the loads alone, without the test, 1.44; loads of 16 bytes per lane
+// 1.47).  The filling pass is at 2.16 (3.08 so), of which its stores are 0.65.
 //
-// The sample's transit slots are sorted by vertex as well: a vertex that several slots hold (layer
+// The sample's transit slots are grouped by vertex as well: a vertex that several slots hold (layer
 // samples hold well-connected vertices many times over) is streamed once, and what is found goes to
 // the row of each of those slots.  The wavefronts take the distinct transits from a counter.
 //
@@ -41,15 +41,11 @@ namespace nd {
 
 namespace {
 
-constexpr int kEdgeThreads = 1024;  // two workgroups (78 KB of LDS each) fill a CU's 32 wave slots
-constexpr int kBitWords = 2048;     // the vertex map: 65,536 bits, indexed by the vertex id folded to 16 bits
-constexpr uint32_t kQueueCap = 64 + 64;        // fewer than 64 left over plus a quarter step's entries
-constexpr uint32_t kOutCap = 64 + 64;          // filling pass: edges of the current transit not yet written
-constexpr int kMaxSlots = 2048;  // new vertices per sample (ND_MAX_EDGE_SLOTS)
-constexpr int kChunk = 2048;     // transit slots of a sample that are sorted and de-duplicated together
-constexpr size_t kEdgeLdsBytes = (size_t)kMaxSlots * 8 + (size_t)2 * kMaxSlots * 4 +
-                                 (size_t)(kEdgeThreads / 64) * (kQueueCap + kOutCap) * 4 + (size_t)kChunk * 8 +
-                                 (size_t)kChunk * 2;
+constexpr int kEdgeThreads = 1024;  // two workgroups (77 KB of LDS each) fill a CU's 32 wave slots
+constexpr int kBitWords = 2048;     // the vertex map: 65,536 bits
+constexpr int kMaxSlots = 2048;     // new vertices per sample (ND_MAX_EDGE_SLOTS)
+constexpr int kTable = 2 * kMaxSlots;
+constexpr int kChunk = 2048;        // transit slots of a sample that are grouped together
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
@@ -58,26 +54,48 @@ struct EdgeArgs {
     const int32_t* transits;  // [S][n_prev]
     const int32_t* sampled;   // [S][m]
     uint32_t n_prev, m;
-    uint32_t m2;              // power of two >= m
-    uint32_t hash_shift;      // 32 - log2(2 * m2)
+    uint32_t table;           // places of the vertices' table: a power of two, at least 2 m
+    uint32_t shift;           // 32 - log2(table)
     int32_t* counts;          // count pass: [S * n_prev]
     const int64_t* row_ptr;   // fill pass
     int32_t* edge_slot;
     int64_t capacity;
     uint32_t* status;
-    int vertex_bits;          // bits of the largest vertex id
 };
 
-// Table entry: bits 0-10 first position of the vertex's run in the sorted list, bits 11-22 the
-// run's length (1..2048), bits 23-31 a fingerprint of the vertex.  All ones = empty (no run is
-// 4,095 long).
-constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+// What a workgroup keeps in LDS.  PIECES: wavefront loads of 64 entries between two looks at the queue's fill.
+template <bool FILL>
+struct EdgeLds {
+    static constexpr int kPieces = FILL ? 2 : 4;
+    static constexpr uint32_t kQueue = 64 + 64 * kPieces;  // fewer than 64 left over, the entries of the pieces, a spare place
+    static constexpr uint32_t kOut = 64 + 64;              // filling pass: edges of the current item not yet written
+    uint32_t bits[kBitWords];       // bit set: a vertex of the sample may be there
+    uint32_t keys[kTable];          // the sample's vertices, hashed; kNoKey = free
+    uint16_t first[kTable + 8];     // slots of the vertices in the places before (while they are counted: in this place)
+    union {
+        uint32_t t_keys[2 * kChunk];                        // the chunk's transits, hashed; then, per distinct transit:
+        struct { uint32_t rs[kChunk], deg[kChunk]; } item;  // its list: low word of the start, length
+    };
+    uint16_t t_first[kChunk];       // its first place in t_slot, and from bit 11 on the start's bits from 32 on
+    uint16_t t_slot[kChunk];        // the chunk's live slots, those of one transit together
+    uint16_t slot[FILL ? kMaxSlots : 2];                    // the sample's slots, those of one vertex together and ascending
+    uint16_t out[FILL ? (kEdgeThreads / 64) * kOut : 2];    // per wavefront: edges waiting to be written
+    union {
+        uint32_t queue[(kEdgeThreads / 64) * kQueue];       // per wavefront: entries that passed the bit test
+        uint16_t t_count[2 * kChunk];                       // while transits are grouped: slots, then the item, per place
+    };
+    uint64_t scan[kEdgeThreads / 64 + 1];
+    uint32_t items, live;           // distinct transits and live slots of the chunk
+    uint32_t next;                  // next item to hand out
+};
+static_assert(sizeof(EdgeLds<true>) <= 80 * 1024 && sizeof(EdgeLds<false>) <= 80 * 1024, "two workgroups per compute unit");
+
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 __device__ __forceinline__ uint32_t hash_vertex(int32_t v) { return (uint32_t)v * 0x9E3779B1u; }
-__device__ __forceinline__ uint32_t fingerprint(uint32_t h) { return (h >> 9) & 0x1FFu; }
-// The vertex's bit in the 65,536-bit map: the id folded to 16 bits.  Two shifts and an exclusive or,
-// where the multiplicative hash costs a quarter-rate multiply per adjacency entry, and neighbouring
-// ids - an ascending adjacency list is full of them - read the same or neighbouring words of LDS.
-__device__ __forceinline__ uint32_t map_bit(int32_t v) { return ((uint32_t)v ^ ((uint32_t)v >> 16)) & 0xFFFFu; }
+// The vertex's bit in the map: bits 2-12 of its id name the word (an AND gives its place in bytes), the others the
+// bit, counted from the top, so that the test is a shift and a sign.
+__device__ __forceinline__ uint32_t map_word(int32_t v) { return ((uint32_t)v & 0x1FFCu) >> 2; }
+__device__ __forceinline__ uint32_t map_bit(int32_t v) { return (((uint32_t)v << 3) + ((uint32_t)v >> 13)) & 31u; }
 
 // one wavefront: its LDS operations complete in order; keeps the compiler from moving them
 __device__ __forceinline__ void wave_lds_order() {
@@ -85,78 +103,18 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Sorts the n2 (a power of two, at most 2 * kEdgeThreads) keys (vertex << 32 | slot) of an LDS array
-// by vertex; the slots arrive ascending and the sort is stable, so the keys end ascending.  Every
-// thread of the workgroup calls it, after a barrier that made the keys visible, and it ends with
-// one.  An LSD radix sort over the vertex's bits plus one (missing keys are all ones and must end
-// behind the largest vertex), 8 bits per pass: a wavefront owns 128 consecutive keys, ranks them
-// with one ballot per digit bit, the per-wavefront digit counts are scanned, and the keys, which
-// sit in registers meanwhile, go back to their places.  Three passes for 4 M vertices where a
-// bitonic network takes 66 compare-exchange steps (54 us per workgroup through LDS, 32 us in
-// registers with lane exchanges: more than streaming the adjacency lists of 64 transits).
-// hist: kEdgeThreads / 64 rows of 256 counters; digit_start: 256 entries; scan_tmp: for the scan.
-__device__ __forceinline__ void sort_keys_lds(uint64_t* keys, uint32_t n2, uint32_t tid, int vertex_bits,
-                                              uint32_t* hist, uint32_t* digit_start, uint32_t* scan_tmp) {
-    constexpr uint32_t T = (uint32_t)kEdgeThreads;
-    const bool two = n2 > T;  // the same for the whole workgroup
-    const uint32_t wave = tid >> 6, lane = tid & 63u;
-    const uint32_t per_wave = two ? 128u : 64u;
-    const uint32_t at0 = wave * per_wave + lane, at1 = at0 + 64u;
-    uint32_t* my_hist = hist + wave * 256u;
-    const int total_bits = vertex_bits + 1;
-    const int passes = (total_bits + 7) / 8;
-    int shift = 0;
-    for (int pass = 0; pass < passes; ++pass) {
-        const int bits = total_bits / passes + (pass >= passes - total_bits % passes ? 1 : 0);
-        const uint32_t dmask = (1u << bits) - 1u;
-        const uint64_t k0 = at0 < n2 ? keys[at0] : ~0ull;
-        const uint64_t k1 = (two && at1 < n2) ? keys[at1] : ~0ull;
-        for (uint32_t i = lane; i < 256u; i += 64u) my_hist[i] = 0u;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t d0 = ((uint32_t)(k0 >> 32) >> shift) & dmask;
-        const uint32_t d1 = ((uint32_t)(k1 >> 32) >> shift) & dmask;
-        uint32_t r0, r1 = 0;
-        {
-            const uint64_t peers = digit_peers(d0, ~0ull, bits);
-            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-            const uint32_t old = my_hist[d0];  // read by all lanes before the lowest peer writes it
-            if (below == 0u) my_hist[d0] = old + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            r0 = old + below;
-        }
-        if (two) {
-            const uint64_t peers = digit_peers(d1, ~0ull, bits);
-            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-            const uint32_t old = my_hist[d1];
-            if (below == 0u) my_hist[d1] = old + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            r1 = old + below;
-        }
-        __syncthreads();
-        uint32_t cnt = 0;
-        if (tid < (1u << bits)) {  // per digit: exclusive scan over the wavefronts, in place
-#pragma unroll
-            for (uint32_t w = 0; w < T / 64u; ++w) {
-                const uint32_t t = hist[w * 256u + tid];
-                hist[w * 256u + tid] = cnt;
-                cnt += t;
-            }
-        }
-        uint32_t total;
-        const uint32_t ex = block_exclusive_scan<uint32_t, kEdgeThreads>(cnt, scan_tmp, &total);
-        if (tid < (1u << bits)) digit_start[tid] = ex;
-        __syncthreads();
-        // every key is in a register: the array can be overwritten
-        if (at0 < n2) keys[digit_start[d0] + my_hist[d0] + r0] = k0;
-        if (two && at1 < n2) keys[digit_start[d1] + my_hist[d1] + r1] = k1;
-        __syncthreads();
-        shift += bits;
+// Puts v (>= 0) into a table of at least twice as many places as vertices and adds one to its 16-bit count; the place
+// in the low half of the result, in the high half how many came before.
+__device__ __forceinline__ uint32_t count_key(uint32_t* keys, uint16_t* counts, uint32_t mask, uint32_t shift, int32_t v) {
+    uint32_t pos = hash_vertex(v) >> shift;
+    for (;;) {  // ends: the table is never full
+        const uint32_t old = atomicCAS(&keys[pos], kNoKey, (uint32_t)v);
+        if (old == kNoKey || old == (uint32_t)v) break;
+        pos = (pos + 1u) & mask;
     }
+    const uint32_t half = (pos & 1u) * 16u;  // at most 2,048 per count: no carry into the other half
+    const uint32_t before = atomicAdd((uint32_t*)counts + (pos >> 1), 1u << half) >> half;
+    return pos | (before << 16);
 }
 
 // Two workgroups of 1,024 threads per compute unit are eight wavefronts per SIMD.  That takes at most
@@ -166,218 +124,243 @@ __device__ __forceinline__ void sort_keys_lds(uint64_t* keys, uint32_t n2, uint3
 template <typename OffT, bool FILL>
 __global__ __launch_bounds__(kEdgeThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
-    extern __shared__ __align__(16) unsigned char s_dyn[];
-    uint64_t* s_sorted = (uint64_t*)s_dyn;                // [kMaxSlots] (vertex << 32 | slot), ascending; ~0 = none
-    uint32_t* table = (uint32_t*)(s_sorted + kMaxSlots);  // [2 * kMaxSlots] entries as described above
-    int32_t* s_queue = (int32_t*)(table + 2 * kMaxSlots);  // per wavefront: entries that passed the bit test
-    int32_t* s_out = s_queue + (kEdgeThreads / 64) * kQueueCap;  // per wavefront: edges waiting to be written
-    uint64_t* s_trans = (uint64_t*)(s_out + (kEdgeThreads / 64) * kOutCap);  // [kChunk] (transit << 32 | slot), sorted
-    uint16_t* s_heads = (uint16_t*)(s_trans + kChunk);    // [kChunk] where each distinct transit starts in s_trans
-    // bit set: some sample vertex hashes here.  Declared statically so that its address is a constant
-    // of the instruction that reads it (one read per adjacency entry).
-    __shared__ uint32_t s_bits[kBitWords];
-    __shared__ uint32_t s_scan[kEdgeThreads / 64 + 1];
-    __shared__ uint32_t s_items[3];                       // distinct transits and live slots of the chunk; next item to hand out
-    // Adjacency loads in flight per lane and step: eight where the kernel then still fits 64 vector
-    // registers (two workgroups per compute unit), four in the filling pass over 64-bit offsets.
-    constexpr int kEdgeUnroll = (FILL && sizeof(OffT) == 8) ? 4 : 8;
+    using Lds = EdgeLds<FILL>;
+    __shared__ Lds s;
+    constexpr uint32_t T = (uint32_t)kEdgeThreads;
+    constexpr int kPieces = Lds::kPieces;
+    // Adjacency loads in flight per lane and step
+    constexpr int kEdgeUnroll = 8;
     constexpr uint32_t kBatch = 64 * kEdgeUnroll;  // adjacency entries a wavefront takes per step
     const uint32_t b = blockIdx.x;
     const uint32_t tid = threadIdx.x;
-    const uint32_t mask = 2u * a.m2 - 1u;
-    const int32_t* sampled = a.sampled + (uint64_t)b * a.m;
-    bool bad = false;
-
-    for (uint32_t i = tid; i < a.m2; i += kEdgeThreads) {
-        uint64_t key = ~0ull;
-        if (i < a.m) {
-            int32_t v = sampled[i];
-            if (v >= g.V || v < ND_NULL_VERTEX) {
-                bad = true;
-                v = ND_NULL_VERTEX;
-            }
-            if (v >= 0) key = ((uint64_t)(uint32_t)v << 32) | i;
-        }
-        s_sorted[i] = key;
-    }
-    for (uint32_t i = tid; i < 2u * a.m2; i += kEdgeThreads) table[i] = kEmpty;
-    for (uint32_t i = tid; i < (uint32_t)kBitWords; i += kEdgeThreads) s_bits[i] = 0u;
-    __syncthreads();
-
-    sort_keys_lds(s_sorted, a.m2, tid, a.vertex_bits, (uint32_t*)s_queue, (uint32_t*)s_heads, s_scan);
-
-    // the first entry of every run of equal vertices puts the run into the table (the table has
-    // twice as many places as there can be runs, so the probe loops end)
-    for (uint32_t k = tid; k < a.m2; k += kEdgeThreads) {
-        const uint64_t key = s_sorted[k];
-        if (key == ~0ull) continue;
-        const int32_t v = (int32_t)(key >> 32);
-        if (k > 0 && (int32_t)(s_sorted[k - 1] >> 32) == v) continue;
-        uint32_t lo = k + 1, hi = a.m2;  // first position after k whose vertex differs
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if ((int32_t)(s_sorted[mid] >> 32) == v) lo = mid + 1;
-            else hi = mid;
-        }
-        const uint32_t h = hash_vertex(v);
-        const uint32_t entry = (fingerprint(h) << 23) | ((lo - k) << 11) | k;
-        uint32_t pos = h >> a.hash_shift;
-        while (atomicCAS(&table[pos], kEmpty, entry) != kEmpty) pos = (pos + 1u) & mask;
-        const uint32_t bi = map_bit(v);
-        atomicOr(&s_bits[bi >> 5], 0x80000000u >> (bi & 31u));  // counted from the top: the test is a shift and a sign
-    }
-    __syncthreads();
-
-    // ---- The sample's transits, kChunk slots at a time, are sorted by vertex in LDS: layer samples
-    // hold well-connected vertices many times over (569 distinct among the 2,048 transits of the
-    // benchmark's second step), and a vertex's adjacency list is streamed once for all the slots
-    // that hold it.  The wavefronts then take one distinct transit each at a time.
-    // Everything about such an item is the same in all lanes of its wavefront and is kept in scalar
-    // registers.  The loop runs over steps of up to kBatch entries of a list; the entries of the next
-    // step (the same item's or the next item's) and the offsets of the item after are requested
-    // before the current step is worked on.
     const int lane = lane_id();
     const uint32_t wave = wave_uniform((uint32_t)wave_id());
-    int32_t* queue = s_queue + wave * kQueueCap;
-    int32_t* obuf = s_out + wave * kOutCap;
+    const uint32_t mask = a.table - 1u;
     const uint64_t row0 = (uint64_t)b * a.n_prev;
+    bool bad = false;
+    auto checked = [&](int32_t v) -> int32_t {  // NULL instead of what is no vertex
+        const bool out = v >= g.V || v < ND_NULL_VERTEX;
+        bad |= out;
+        return out ? ND_NULL_VERTEX : v;
+    };
+    uint32_t* queue = s.queue + wave * Lds::kQueue;
+    uint16_t* obuf = s.out + (FILL ? wave * Lds::kOut : 0u);
 
     for (uint32_t chunk0 = 0; chunk0 < a.n_prev; chunk0 += (uint32_t)kChunk) {
+        // ---- The sample's vertices (once) and kChunk transit slots at a time are grouped by a hash table each: layer
+        // samples hold well-connected vertices many times over (569 distinct among the 2,048 transits of the
+        // benchmark's second step), and a vertex's adjacency list is streamed once for all the slots that hold it.
+        // Groups need no order among each other, so this takes a table's insertions and one scan of its places where a
+        // sort by vertex took three passes (4,096 samples of 64 transits and 2,048 vertices, 2,400 entries to stream:
+        // the counting pass 245 us with sorts, 135 like this).
+        const bool first = chunk0 == 0;
         const uint32_t n_chunk = a.n_prev - chunk0 < (uint32_t)kChunk ? a.n_prev - chunk0 : (uint32_t)kChunk;
-        uint32_t n2 = 64;
-        while (n2 < n_chunk) n2 <<= 1;
-        for (uint32_t i = tid; i < n2; i += kEdgeThreads) {
-            uint64_t key = ~0ull;
-            if (i < n_chunk) {
-                int32_t v = a.transits[row0 + chunk0 + i];
-                if (v >= g.V || v < ND_NULL_VERTEX) {
-                    bad = true;
-                    v = ND_NULL_VERTEX;
+        uint32_t t_table = 128, t_shift = 25;
+        while (t_table < 2u * n_chunk) {
+            t_table <<= 1;
+            --t_shift;
+        }
+        int32_t v[2], t[2];
+#pragma unroll
+        for (uint32_t e = 0; e < 2u; ++e) {
+            const uint32_t i = tid + e * T;
+            v[e] = t[e] = ND_NULL_VERTEX;
+            if (first && i < a.m) v[e] = checked(a.sampled[(uint64_t)b * a.m + i]);
+            if (i < n_chunk) t[e] = checked(a.transits[row0 + chunk0 + i]);
+            if (!FILL && i < n_chunk && t[e] < 0) a.counts[row0 + chunk0 + i] = 0;  // a slot without a transit has no edges
+        }
+        bool edges[2] = {true, true};  // filling pass: the counting pass found edges for this slot
+        if (FILL) {
+#pragma unroll
+            for (uint32_t e = 0; e < 2u; ++e)
+                if (t[e] >= 0) {
+                    const int64_t* r = a.row_ptr + row0 + chunk0 + tid + e * T;
+                    edges[e] = r[0] != r[1];
                 }
-                if (v >= 0) key = ((uint64_t)(uint32_t)v << 32) | (chunk0 + i);
-                else if (!FILL) a.counts[row0 + chunk0 + i] = 0;  // a slot without a transit has no edges
+        }
+        const uint4 none = make_uint4(kNoKey, kNoKey, kNoKey, kNoKey);
+        if (first) {
+            for (uint32_t i = tid; i < a.table / 4u; i += T) {
+                reinterpret_cast<uint4*>(s.keys)[i] = none;
+                reinterpret_cast<uint2*>(s.first)[i] = make_uint2(0u, 0u);
             }
-            s_trans[i] = key;
+            for (uint32_t i = tid; i < (uint32_t)kBitWords; i += T) s.bits[i] = 0u;
+        }
+        for (uint32_t i = tid; i < t_table / 4u; i += T) {
+            reinterpret_cast<uint4*>(s.t_keys)[i] = none;
+            reinterpret_cast<uint2*>(s.t_count)[i] = make_uint2(0u, 0u);
         }
         __syncthreads();
-        sort_keys_lds(s_trans, n2, tid, a.vertex_bits, (uint32_t*)s_queue, (uint32_t*)s_heads, s_scan);
-        {   // where the distinct transits start (two positions per thread: n2 <= 2 * kEdgeThreads)
-            bool head[2];
-            uint32_t mine = 0, live = 0;
+        uint32_t vp[2] = {0u, 0u}, tp[2] = {0u, 0u};  // place, and how many of the vertex came before
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const uint32_t i = tid * 2u + (uint32_t)e;
-                head[e] = false;
-                if (i < n2 && s_trans[i] != ~0ull) {
-                    ++live;
-                    head[e] = i == 0 || (uint32_t)(s_trans[i - 1] >> 32) != (uint32_t)(s_trans[i] >> 32);
-                }
-                mine += head[e] ? 1u : 0u;
+        for (uint32_t e = 0; e < 2u; ++e) {
+            if (v[e] >= 0) vp[e] = count_key(s.keys, s.first, mask, a.shift, v[e]);
+            if (t[e] >= 0) tp[e] = count_key(s.t_keys, s.t_count, t_table - 1u, t_shift, t[e]);
+        }
+        __syncthreads();
+        {   // four places of each table per thread
+            uint4 vk = none, tk = none;
+            uint2 vc = make_uint2(0u, 0u), tc = make_uint2(0u, 0u);
+            if (first && tid < a.table / 4u) {
+                vk = reinterpret_cast<const uint4*>(s.keys)[tid];
+                vc = reinterpret_cast<const uint2*>(s.first)[tid];
             }
-            // one scan for both counts (each at most 2,048): heads in the low half, live slots in the high
-            uint32_t total;
-            uint32_t at = block_exclusive_scan<uint32_t, kEdgeThreads>(mine | (live << 16), s_scan, &total) & 0xFFFFu;
+            if (tid < t_table / 4u) {
+                tk = reinterpret_cast<const uint4*>(s.t_keys)[tid];
+                tc = reinterpret_cast<const uint2*>(s.t_count)[tid];
+            }
+            const uint32_t vkey[4] = {vk.x, vk.y, vk.z, vk.w}, tkey[4] = {tk.x, tk.y, tk.z, tk.w};
+            const uint32_t vcnt[4] = {vc.x & 0xFFFFu, vc.x >> 16, vc.y & 0xFFFFu, vc.y >> 16};
+            const uint32_t tcnt[4] = {tc.x & 0xFFFFu, tc.x >> 16, tc.y & 0xFFFFu, tc.y >> 16};
+            // one scan for the three sums (each at most 2,048): the sample's slots, the chunk's live slots and its items
+            uint64_t mine = 0, total;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                mine += (uint64_t)vcnt[j] | ((uint64_t)tcnt[j] << 16) | ((uint64_t)(tcnt[j] > 0u ? 1u : 0u) << 32);
+            const uint64_t ex = block_exclusive_scan<uint64_t, kEdgeThreads>(mine, s.scan, &total);
+            if (first && tid < a.table / 4u) {
+                uint32_t at = (uint32_t)ex & 0xFFFFu;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    s.first[tid * 4u + (uint32_t)j] = (uint16_t)at;
+                    at += vcnt[j];
+                    if (vkey[j] != kNoKey)
+                        atomicOr(&s.bits[map_word((int32_t)vkey[j])], 0x80000000u >> map_bit((int32_t)vkey[j]));
+                }
+                if (tid == a.table / 4u - 1u) s.first[a.table] = (uint16_t)at;
+            }
+            if (tid < t_table / 4u) {
+                uint32_t at = (uint32_t)(ex >> 16) & 0xFFFFu, it = (uint32_t)(ex >> 32);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (tcnt[j] == 0u) continue;
+                    const uint64_t rs = (uint64_t)g.off[tkey[j]];
+                    s.item.rs[it] = (uint32_t)rs;
+                    s.item.deg[it] = row_length(g, (int32_t)tkey[j], rs);
+                    // a device holds fewer than 2^37 columns (512 GiB)
+                    s.t_first[it] = (uint16_t)(at | ((uint32_t)(rs >> 32) << 11));
+                    s.t_count[tid * 4u + (uint32_t)j] = (uint16_t)it;
+                    at += tcnt[j];
+                    ++it;
+                }
+            }
             if (tid == 0) {
-                s_items[0] = total & 0xFFFFu;
-                s_items[1] = total >> 16;
-                s_items[2] = 0;
+                s.live = (uint32_t)(total >> 16) & 0xFFFFu;
+                s.items = (uint32_t)(total >> 32);
+                s.next = 0;
             }
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-                if (head[e]) s_heads[at++] = (uint16_t)(tid * 2u + (uint32_t)e);
         }
         __syncthreads();
-        const uint32_t n_items = wave_uniform(s_items[0]);
-        const uint32_t n_live = wave_uniform(s_items[1]);  // the live slots are the first n_live of s_trans
+#pragma unroll
+        for (uint32_t e = 0; e < 2u; ++e) {
+            if (t[e] >= 0) {
+                const uint32_t it = s.t_count[tp[e] & 0xFFFFu], before = tp[e] >> 16;
+                s.t_slot[(s.t_first[it] & 0x7FFu) + before] = (uint16_t)(tid + e * T);
+                if (FILL && before == 0u && !edges[e]) s.item.deg[it] = 0u;  // nothing to look for
+            }
+            if (FILL && v[e] >= 0) s.slot[s.first[vp[e] & 0xFFFFu] + (vp[e] >> 16)] = (uint16_t)(tid + e * T);
+        }
+        if (FILL && first) {  // the slots of a vertex, in any order yet: each counts the lower ones
+            __syncthreads();
+            uint32_t at[2] = {0u, 0u};
+#pragma unroll
+            for (uint32_t e = 0; e < 2u; ++e)
+                if (v[e] >= 0) {
+                    const uint32_t k = s.first[vp[e] & 0xFFFFu], end = s.first[(vp[e] & 0xFFFFu) + 1u];
+                    at[e] = k;
+                    for (uint32_t i = k; end - k > 1u && i < end; ++i) at[e] += s.slot[i] < tid + e * T ? 1u : 0u;
+                }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t e = 0; e < 2u; ++e)
+                if (v[e] >= 0) s.slot[at[e]] = (uint16_t)(tid + e * T);
+        }
+        __syncthreads();
+        const uint32_t n_items = wave_uniform(s.items);
+        const uint32_t n_live = wave_uniform(s.live);  // the live slots are the first n_live of t_slot
+        const uint64_t row1 = row0 + chunk0;
 
-        // the item whose entries are being requested: positions [p0, p1) of s_trans hold its slots
-        // the wavefronts take the items in order from a counter: lists differ in length by orders of
-        // magnitude, and a fixed share per wavefront leaves most of them waiting for the slowest
+        // ---- The wavefronts take the items from a counter: lists differ in length by orders of magnitude, and a fixed
+        // share per wavefront leaves most of them waiting for the slowest.  Everything about an item is the same in all
+        // lanes of its wavefront and is kept in scalar registers.  The loop runs over steps of up to kBatch entries of a
+        // list; the entries of the next step (the same item's or the next item's) are requested before the current
+        // step is worked on.
         auto claim = [&]() -> uint32_t {
             uint32_t i = 0;
-            if (lane == 0) i = atomicAdd(&s_items[2], 1u);
+            if (lane == 0) i = atomicAdd(&s.next, 1u);
             return wave_uniform(i);
         };
         uint32_t item = claim();
-        uint32_t item_next = claim();  // its offsets are requested while `item` is worked on
-        uint32_t p0 = 0, p1 = 0;
-        uint64_t rs = 0;            // where its adjacency list starts
+        uint32_t item_next = claim();
+        uint32_t p0 = 0, p1 = 0;    // positions [p0, p1) of t_slot hold the slots of the item being requested
+        uint64_t rs = 0;            // where its list starts
         uint32_t deg = 0;           // how long it is (0: nothing to stream); a list has fewer than 2^31 entries
         uint32_t e0 = 0;            // the next entry of it to request
-        // one item ahead: offsets (FILL: row pointers of its first slot) requested
-        OffT off_a0 = 0, off_a1 = 0;
-        int64_t rp_a0 = 0, rp_a1 = 0;
-        auto slots_of = [&](uint32_t it, uint32_t* first, uint32_t* last) {
-            *first = s_heads[it];
-            *last = it + 1u < n_items ? (uint32_t)s_heads[it + 1u] : n_live;
-        };
-        auto request_a = [&](uint32_t it) {  // offsets and row pointers of item `it`
-            off_a0 = off_a1 = 0;
-            rp_a0 = rp_a1 = 0;
-            if (it < n_items) {
-                const uint64_t key = s_trans[s_heads[it]];
-                const int32_t v = wave_uniform((int32_t)(uint32_t)(key >> 32));
-                off_a0 = g.off[v];
-                off_a1 = g.off[v + 1];
-                if constexpr (FILL) {
-                    const uint32_t slot = wave_uniform((uint32_t)key);
-                    rp_a0 = a.row_ptr[row0 + slot];
-                    rp_a1 = a.row_ptr[row0 + slot + 1];
-                }
-            }
-        };
-        bool no_edges = false;  // FILL: the counting pass found nothing for this item
-        auto adopt = [&]() {     // the item ahead becomes the item being requested
-            rs = wave_uniform((uint64_t)off_a0);
-            deg = (uint32_t)(wave_uniform((uint64_t)off_a1) - rs);
-            if constexpr (FILL) {
-                no_edges = wave_uniform(rp_a1) == wave_uniform(rp_a0);
-                if (no_edges) deg = 0;
-            }
+        // Filling pass: the chunk's rows lie together, in at most 16 MB, so that a place among them is a 32-bit offset (in
+        // bytes), and a store beyond them or the capacity is one that the buffer drops.
+        int64_t base = 0;
+        uint32_t bytes = 0;
+        if constexpr (FILL) {
+            base = a.row_ptr[row1];
+            const int64_t end = a.row_ptr[row1 + n_chunk] < a.capacity ? a.row_ptr[row1 + n_chunk] : a.capacity;
+            const int64_t room = end > base ? (end - base) * 4 : 0;
+            bytes = room < 0x7FFFFFFCll ? (uint32_t)room : 0x7FFFFFFCu;
+        }
+        const auto rows = __builtin_amdgcn_make_buffer_rsrc(a.edge_slot + (bytes > 0u ? base : 0), 0, (int)bytes, 0x00027000);
+        uint32_t my_row = 0, row_next = 0;  // filling pass: where the row of the item's slot number `lane` starts
+        auto adopt = [&]() {        // `item` becomes the item being requested
             e0 = 0;
-            if (item < n_items) slots_of(item, &p0, &p1);
-            request_a(item_next);
+            deg = 0;
+            if (item < n_items) {
+                const uint32_t f = wave_uniform((uint32_t)s.t_first[item]);
+                rs = ((uint64_t)(f >> 11) << 32) | wave_uniform(s.item.rs[item]);
+                deg = wave_uniform(s.item.deg[item]);
+                p0 = f & 0x7FFu;
+                p1 = item + 1u < n_items ? wave_uniform((uint32_t)s.t_first[item + 1u]) & 0x7FFu : n_live;
+                if (FILL && deg > 0u && p0 + (uint32_t)lane < p1) row_next = (uint32_t)(a.row_ptr[row1 + s.t_slot[p0 + (uint32_t)lane]] - base) * 4u;
+            }
         };
         // an item without entries to stream: its slots' counts are 0 (counting pass), nothing else
-        auto skip_empty_items = [&]() {
-            while (item < n_items && deg == 0) {
-                if constexpr (!FILL)
-                    for (uint32_t d = p0 + (uint32_t)lane; d < p1; d += 64u)
-                        a.counts[row0 + (uint32_t)s_trans[d]] = 0;
+        auto next_item = [&]() {
+            do {
                 item = item_next;
                 item_next = claim();
                 adopt();
-            }
+                if (!FILL && item < n_items && deg == 0u)
+                    for (uint32_t d = p0 + (uint32_t)lane; d < p1; d += 64u) a.counts[row1 + s.t_slot[d]] = 0;
+            } while (item < n_items && deg == 0u);
         };
         auto request_entries = [&](int32_t (&u)[kEdgeUnroll]) {
             const int32_t* p = g.col + rs + e0;
             const uint32_t left = deg - e0;
-            const uint32_t cnt = left < kBatch ? left : kBatch;
-            if (cnt == kBatch) {  // a full step, the common case: nothing to test
+            if (left >= kBatch) {  // a full step, the common case: nothing to test
 #pragma unroll
                 for (int r = 0; r < kEdgeUnroll; ++r) u[r] = p[r * 64 + lane];
                 return;
             }
 #pragma unroll
             for (int r = 0; r < kEdgeUnroll; ++r) {
-                u[r] = ND_NULL_VERTEX;
                 // the test is the same in all lanes; inside the last 64 entries a lane past the end
                 // reads the last entry again instead of branching (and drops it when it looks at it:
                 // looking at it here would wait for each load in turn)
-                if ((uint32_t)r * 64u < cnt) {
+                if ((uint32_t)r * 64u < left) {
                     const uint32_t e = (uint32_t)r * 64u + (uint32_t)lane;
-                    u[r] = p[e < cnt ? e : cnt - 1u];
+                    u[r] = p[e < left ? e : left - 1u];
                 }
             }
         };
 
-        request_a(item);
         adopt();
-        skip_empty_items();
+        if (item < n_items && deg == 0u) {
+            if (!FILL)
+                for (uint32_t d = p0 + (uint32_t)lane; d < p1; d += 64u) a.counts[row1 + s.t_slot[d]] = 0;
+            next_item();
+        }
         int32_t u_next[kEdgeUnroll];
 #pragma unroll
         for (int r = 0; r < kEdgeUnroll; ++r) u_next[r] = 0;
         if (item < n_items) request_entries(u_next);
+        my_row = row_next;
 
         uint32_t queued = 0;  // entries in the queue (the same in all lanes)
         uint32_t count = 0;   // counting pass: my share of the item's edges
@@ -393,77 +376,62 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                 // for these entries placed after those requests would wait for them as well
                 asm volatile("" : "+v"(u[r]));
             }
-            const uint32_t left = deg - e0;
-            const uint32_t cnt = left < kBatch ? left : kBatch;
-            const bool row_ends = left <= kBatch;
+            const uint32_t cnt = deg - e0;
+            const bool row_ends = cnt <= kBatch;
             const uint32_t q0 = p0, q1 = p1;  // the slots of the item being worked on
             // ---- request the next step's entries before working on this one
-            if (row_ends) {
-                item = item_next;
-                item_next = claim();
-                adopt();
-                skip_empty_items();
-            } else {
-                e0 += kBatch;
-            }
+            if (row_ends) next_item();
+            else e0 += kBatch;
             if (item < n_items) request_entries(u_next);
 
-            // ---- entries that pass the bit test join the queue, in order, 64 at a time; the table is
-            // probed by 64 queued entries at a time (by what is left when the item ends).
+            // ---- entries that pass the bit test join the queue, in order; the table is probed by 64 queued entries at a
+            // time (by what is left when the item ends).
             // Filling pass: the edges found are collected in obuf, in order, and leave 64 at a time, one
             // coalesced store per slot that holds the item's transit.
-            auto write_out = [&](uint32_t nf) {  // the first nf (at most 64) entries of obuf, to every row of the item
-                const int32_t val = (uint32_t)lane < nf ? obuf[lane] : 0;
+            // The first nf (at most 64) entries of obuf, to every row of the item: a store per row whose place is one scalar
+            // (4,096 samples of 2,048 transits and vertices: 2.35 ms with 64-bit places and their bounds per lane, 2.16 like this;
+            // two to eight short rows per store 2.18, and stores held back until after the next wait 2.5).
+            auto write_out = [&](uint32_t nf) {
+                const int32_t val = (uint32_t)lane < nf ? (int32_t)obuf[lane] : 0;
                 for (uint32_t d0 = q0; d0 < q1; d0 += 64u) {
                     // the rows of up to 64 slots at a time: their starts come by one load, a lane per slot
                     const uint32_t nd = q1 - d0 < 64u ? q1 - d0 : 64u;
-                    int64_t my_row = 0;
-                    if ((uint32_t)lane < nd) my_row = a.row_ptr[row0 + (uint32_t)s_trans[d0 + lane]];
-                    for (uint32_t dd = 0; dd < nd; ++dd) {
-                        const int64_t wbase =
-                            (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(my_row >> 32), dd) << 32) |
-                                      (uint32_t)__builtin_amdgcn_readlane((int)my_row, dd)) + done;
-                        if ((uint32_t)lane < nf && wbase + lane < a.capacity) a.edge_slot[wbase + lane] = val;
+                    uint32_t row = my_row;
+                    if (d0 > q0 && (uint32_t)lane < nd) row = (uint32_t)(a.row_ptr[row1 + s.t_slot[d0 + (uint32_t)lane]] - base) * 4u;
+                    row += done * 4u;
+                    if (__ballot((uint32_t)lane < nd && row + nf * 4u > bytes) == 0ull) {
+                        if ((uint32_t)lane < nf)
+                            for (uint32_t dd = 0; dd < nd; ++dd)
+                                __builtin_amdgcn_raw_buffer_store_b32(val, rows, lane * 4, __builtin_amdgcn_readlane((int)row, (int)dd), 0);
+                    } else {  // the capacity ends in or before one of these rows
+                        for (uint32_t dd = 0; dd < nd; ++dd) {
+                            const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)row, (int)dd) + (uint32_t)lane * 4u;
+                            if ((uint32_t)lane < nf && to < bytes) __builtin_amdgcn_raw_buffer_store_b32(val, rows, (int)to, 0, 0);
+                        }
                     }
                 }
                 done += nf;
             };
-#pragma unroll
-            for (int r = 0; r < kEdgeUnroll; ++r) {
-                const bool in_step = cnt == kBatch || (uint32_t)r * 64u < cnt;  // the same for the whole wavefront
-                if (in_step) {
-                    const uint32_t bi = map_bit(u[r]);
-                    const bool pass = (int32_t)(s_bits[bi >> 5] << (bi & 31u)) < 0;
-                    // The lanes past the list's end (its last step only) are struck from the votes, a
-                    // scalar operation, and not from `pass`: such a lane that passes writes to the place
-                    // after the last live entry (at most the spare one), which nothing reads.
-                    const uint32_t live = cnt - (uint32_t)r * 64u;
-                    const uint64_t votes = __ballot(pass) & (live >= 64u ? ~0ull : (1ull << live) - 1ull);
-                    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(votes >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)votes, queued));
-                    // no branch: a lane that does not pass writes to the queue's spare last place
-                    queue[pass ? at : kQueueCap - 1u] = u[r];
-                    queued += (uint32_t)__popcll(votes);
+            auto leave = [&]() {  // a full wavefront of edges leaves, the rest moves to the front
+                wave_lds_order();
+                if (ofill >= 64u) {
+                    write_out(64u);
+                    const uint16_t moved = (uint32_t)lane < ofill - 64u ? obuf[64 + lane] : (uint16_t)0;
+                    wave_lds_order();
+                    if ((uint32_t)lane < ofill - 64u) obuf[lane] = moved;
+                    ofill -= 64u;
                     wave_lds_order();
                 }
-                const bool last = row_ends && r == kEdgeUnroll - 1;
-                while (queued >= 64u || (last && queued > 0u)) {
-                // 64 queued entries (or, at the item's end, what is left)
-                const uint32_t n = queued < 64u ? queued : 64u;
-                const int32_t v = (uint32_t)lane < n ? queue[lane] : ND_NULL_VERTEX;
+            };
+            auto probe = [&](uint32_t from, uint32_t n) {  // n (at most 64) queued entries
+                const int32_t w = (uint32_t)lane < n ? (int32_t)queue[from + (uint32_t)lane] : ND_NULL_VERTEX;
                 uint32_t c = 0, k = 0;
-                if (v >= 0) {
-                    const uint32_t h = hash_vertex(v);
-                    const uint32_t fp = fingerprint(h);
-                    uint32_t pos = h >> a.hash_shift;
-                    uint32_t en;
-                    while ((en = table[pos]) != kEmpty) {  // ends: the table is never full
-                        if ((en >> 23) == fp && (int32_t)(s_sorted[en & 0x7FFu] >> 32) == v) {
-                            k = en & 0x7FFu;
-                            c = (en >> 11) & 0xFFFu;
-                            break;
-                        }
-                        pos = (pos + 1u) & mask;
+                if (w >= 0) {
+                    uint32_t pos = hash_vertex(w) >> a.shift, key;
+                    while ((key = s.keys[pos]) != (uint32_t)w && key != kNoKey) pos = (pos + 1u) & mask;  // never full
+                    if (key == (uint32_t)w) {
+                        k = s.first[pos];
+                        c = s.first[pos + 1u] - k;
                     }
                 }
                 if constexpr (FILL) {
@@ -475,17 +443,9 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                     const uint32_t ex = incl - c;
                     if (total <= 64u && __ballot(c > 8u) == 0ull) {
                         for (uint32_t i = 0; __ballot(i < c) != 0ull; ++i)
-                            if (i < c) obuf[ofill + ex + i] = (int32_t)(uint32_t)s_sorted[k + i];
+                            if (i < c) obuf[ofill + ex + i] = s.slot[k + i];
                         ofill += total;
-                        wave_lds_order();
-                        if (ofill >= 64u) {
-                            write_out(64u);
-                            const int32_t moved = (uint32_t)lane < ofill - 64u ? obuf[64 + lane] : 0;
-                            wave_lds_order();
-                            if ((uint32_t)lane < ofill - 64u) obuf[lane] = moved;
-                            ofill -= 64u;
-                            wave_lds_order();
-                        }
+                        leave();
                     } else {
                         for (uint32_t base = 0; base < total; base += 64u) {
                             const uint32_t p = base + lane;
@@ -497,47 +457,82 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                             const uint32_t ok = __shfl(k, (int)owner, 64);
                             const uint32_t oex = __shfl(ex, (int)owner, 64);
                             const uint32_t nb = total - base < 64u ? total - base : 64u;
-                            if (p < total) obuf[ofill + lane] = (int32_t)(uint32_t)s_sorted[ok + (p - oex)];
+                            if (p < total) obuf[ofill + lane] = s.slot[ok + (p - oex)];
                             ofill += nb;
-                            wave_lds_order();
-                            if (ofill >= 64u) {
-                                write_out(64u);
-                                const int32_t moved = (uint32_t)lane < ofill - 64u ? obuf[64 + lane] : 0;
-                                wave_lds_order();
-                                if ((uint32_t)lane < ofill - 64u) obuf[lane] = moved;
-                                ofill -= 64u;
-                                wave_lds_order();
-                            }
+                            leave();
                         }
                     }
                 } else {
                     count += c;
                 }
-                // what is left of the queue moves to the front
-                const uint32_t rest = queued - n;
-                const int32_t moved = (uint32_t)lane < rest ? queue[n + lane] : 0;
-                wave_lds_order();
-                if ((uint32_t)lane < rest) queue[lane] = moved;
-                queued = rest;
-                wave_lds_order();
-                }
-                if (last) {  // the item ends
-                    if constexpr (!FILL) {
-                        const uint32_t incl = wave_inclusive_scan(count, lane);
-                        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-                        for (uint32_t d = q0 + (uint32_t)lane; d < q1; d += 64u)
-                            a.counts[row0 + (uint32_t)s_trans[d]] = (int32_t)total;
-                        count = 0;
-                    } else {
-                        if (ofill > 0u) write_out(ofill);
-                        ofill = 0;
-                        done = 0;
+            };
+            auto pieces = [&](auto full) {
+                constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+                for (int r0 = 0; r0 < kEdgeUnroll; r0 += kPieces) {
+                    if (!FULL && (uint32_t)r0 * 64u >= cnt) break;  // the same for the whole wavefront
+                    uint32_t word[kPieces];
+#pragma unroll
+                    for (int r = 0; r < kPieces; ++r) word[r] = s.bits[map_word(u[r0 + r])];
+#pragma unroll
+                    for (int r = 0; r < kPieces; ++r) {
+                        const bool pass = (int32_t)(word[r] << map_bit(u[r0 + r])) < 0;
+                        uint64_t votes = __ballot(pass);
+                        if (!FULL) {
+                            // The lanes past the list's end are struck from the votes and not from `pass`: such a lane that
+                            // passes writes to the place after the last live entry (at most the spare one), which
+                            // nothing reads.
+                            const uint32_t at = (uint32_t)(r0 + r) * 64u, live = cnt > at ? cnt - at : 0u;
+                            votes &= live >= 64u ? ~0ull : (1ull << live) - 1ull;
+                        }
+                        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(votes >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)votes, queued));
+                        // no branch: a lane that does not pass writes to the queue's spare last place
+                        queue[pass ? at : Lds::kQueue - 1u] = (uint32_t)u[r0 + r];
+                        queued += (uint32_t)__popcll(votes);
+                    }
+                    if (queued >= 64u) {
+                        wave_lds_order();
+                        uint32_t from = 0;
+                        do {
+                            probe(from, 64u);
+                            from += 64u;
+                        } while (queued - from >= 64u);
+                        // what is left of the queue moves to the front
+                        queued -= from;
+                        const uint32_t moved = (uint32_t)lane < queued ? queue[from + (uint32_t)lane] : 0u;
+                        wave_lds_order();
+                        if ((uint32_t)lane < queued) queue[lane] = moved;
                         wave_lds_order();
                     }
                 }
+            };
+            if (cnt >= kBatch) pieces(std::true_type{});
+            else pieces(std::false_type{});
+            if (row_ends) {  // the item ends
+                if (queued > 0u) {
+                    wave_lds_order();
+                    probe(0u, queued);
+                    queued = 0;
+                }
+                if constexpr (!FILL) {
+                    const uint32_t incl = wave_inclusive_scan(count, lane);
+                    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                    for (uint32_t d = q0 + (uint32_t)lane; d < q1; d += 64u) a.counts[row1 + s.t_slot[d]] = (int32_t)total;
+                    count = 0;
+                } else {
+                    if (ofill > 0u) {
+                        wave_lds_order();
+                        write_out(ofill);
+                    }
+                    ofill = 0;
+                    done = 0;
+                    my_row = row_next;
+                }
+                wave_lds_order();
             }
         }
-        __syncthreads();  // the chunk's sorted transits are replaced by the next chunk's
+        __syncthreads();  // the chunk's transits and the queues' LDS are replaced by the next chunk's
     }
     if (bad && a.status) atomicOr(a.status, 1u);
 }
@@ -598,43 +593,23 @@ __global__ __launch_bounds__(kScanThreads) void scan_write_kernel(const int32_t*
 
 inline int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 
-inline uint32_t pow2_at_least(uint32_t x) {
-    uint32_t p = 64;
-    while (p < x) p <<= 1;
-    return p;
-}
-
-inline EdgeArgs make_args(const Graph& gr, const int32_t* transits, int32_t n_prev, const int32_t* sampled,
+inline EdgeArgs make_args(const int32_t* transits, int32_t n_prev, const int32_t* sampled,
                           int32_t m) {
     EdgeArgs a{};
     a.transits = transits;
     a.sampled = sampled;
     a.n_prev = (uint32_t)n_prev;
     a.m = (uint32_t)m;
-    a.m2 = pow2_at_least((uint32_t)m);
-    uint32_t lg = 0;
-    while ((1u << lg) < 2u * a.m2) ++lg;
-    a.hash_shift = 32u - lg;
-    a.vertex_bits = 1;
-    while (a.vertex_bits < 31 && (1ll << a.vertex_bits) < gr.V) ++a.vertex_bits;
+    a.table = 128;
+    a.shift = 25;
+    while (a.table < 2u * (uint32_t)m) {
+        a.table <<= 1;
+        --a.shift;
+    }
     return a;
 }
 
 }  // namespace
-
-// Dynamic LDS above the 64 KB default has to be allowed once per kernel; done when a graph is
-// created so that the entry points themselves only launch.
-int edges_prepare() {
-#define ND_EDGES_ALLOW(OFFT, FILL)                                                              \
-    ND_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&edges_kernel<OFFT, FILL>),  \
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kEdgeLdsBytes))
-    ND_EDGES_ALLOW(int64_t, true);
-    ND_EDGES_ALLOW(int64_t, false);
-    ND_EDGES_ALLOW(int32_t, true);
-    ND_EDGES_ALLOW(int32_t, false);
-#undef ND_EDGES_ALLOW
-    return ND_OK;
-}
 
 size_t edges_workspace_bytes(int64_t num_samples, int32_t n_prev) {
     const int64_t rows = num_samples * (int64_t)n_prev;
@@ -653,15 +628,15 @@ int edges_count(const Graph& gr, const int32_t* transits, int32_t n_prev, const 
     const int64_t tiles = scan_tiles(rows);
     hipLaunchKernelGGL(edges_clear_status_kernel, dim3(1), dim3(1), 0, stream, status);
     if (num_samples > 0) {
-        EdgeArgs a = make_args(gr, transits, n_prev, sampled, m);
+        EdgeArgs a = make_args(transits, n_prev, sampled, m);
         a.counts = counts;
         a.status = status;
         if (gr.off64)
             hipLaunchKernelGGL((edges_kernel<int64_t, false>), dim3((unsigned)num_samples),
-                               dim3(kEdgeThreads), kEdgeLdsBytes, stream, view_of<int64_t>(gr), a);
+                               dim3(kEdgeThreads), 0, stream, view_of<int64_t>(gr), a);
         else
             hipLaunchKernelGGL((edges_kernel<int32_t, false>), dim3((unsigned)num_samples),
-                               dim3(kEdgeThreads), kEdgeLdsBytes, stream, view_of<int32_t>(gr), a);
+                               dim3(kEdgeThreads), 0, stream, view_of<int32_t>(gr), a);
         hipLaunchKernelGGL(scan_sums_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, stream, counts,
                            rows, sums);
     }
@@ -676,17 +651,17 @@ int edges_fill(const Graph& gr, const int32_t* transits, int32_t n_prev, const i
                int32_t m, int64_t num_samples, const int64_t* row_ptr, int32_t* edge_slot,
                int64_t capacity, hipStream_t stream) {
     if (num_samples == 0) return ND_OK;
-    EdgeArgs a = make_args(gr, transits, n_prev, sampled, m);
+    EdgeArgs a = make_args(transits, n_prev, sampled, m);
     a.row_ptr = row_ptr;
     a.edge_slot = edge_slot;
     a.capacity = capacity;
     a.status = nullptr;
     if (gr.off64)
         hipLaunchKernelGGL((edges_kernel<int64_t, true>), dim3((unsigned)num_samples), dim3(kEdgeThreads),
-                           kEdgeLdsBytes, stream, view_of<int64_t>(gr), a);
+                           0, stream, view_of<int64_t>(gr), a);
     else
         hipLaunchKernelGGL((edges_kernel<int32_t, true>), dim3((unsigned)num_samples), dim3(kEdgeThreads),
-                           kEdgeLdsBytes, stream, view_of<int32_t>(gr), a);
+                           0, stream, view_of<int32_t>(gr), a);
     ND_HIP_CHECK(hipGetLastError());
     return ND_OK;
 }

@@ -148,3 +148,50 @@ def test_edges_among_the_vertices_of_one_step():
     members[rng.random(members.shape) < 0.03] = -1
     ptr = _compare(g, members, members)
     assert ptr[-1] > 0
+
+
+@pytest.mark.parametrize("n_prev", [150, 2300])
+def test_an_edge_array_that_ends_anywhere_is_filled_up_to_there(n_prev):
+    """Rows are stored as offsets inside the rows of a chunk of slots: arrays that end before, in and after rows of
+    transits that one slot holds, or 70 slots do, in the first chunk and (2,300 slots) in the second."""
+    g = _small
+    dg, _ = device_graph(g)
+    rng = np.random.default_rng(5)
+    tr = rng.integers(0, g.V, (2, n_prev)).astype(np.int32)
+    hub = int(np.argmax(np.diff(g.row_offsets)))
+    tr[:, rng.permutation(n_prev)[:70]] = hub
+    sv = np.concatenate([g.col_indices[rng.integers(0, g.E, (2, 300))], g.col_indices[g.row_offsets[hub]:][:40][None].repeat(2, 0)], 1)
+    tr, sv = (torch.as_tensor(x.astype(np.int32), device="cuda:0") for x in (tr, sv))
+    row_ptr, full = B.layer_edges(dg, tr, sv)
+    ends = [0, 1, 2, 63, 64, 65] + [int(row_ptr[i]) + d for i in (n_prev // 2, n_prev - 1, n_prev, n_prev + 1) for d in (-1, 0, 1, 30)]
+    if n_prev > 2048:
+        ends += [int(row_ptr[i]) + d for i in (2047, 2048, n_prev + 2048) for d in (-1, 0, 1)]
+    for end in sorted({e for e in ends if 0 <= e <= full.numel()} | {full.numel() - 1}):
+        short = torch.full((full.numel(),), -7, dtype=torch.int32, device="cuda:0")
+        B.nd_layer_edges_fill(dg, tr, sv, row_ptr, short[:end])
+        torch.cuda.synchronize()
+        assert torch.equal(short[:end], full[:end]) and bool((short[end:] == -7).all()), end
+
+
+def test_lists_that_start_beyond_four_billion_entries():
+    """The places of lists are kept as 32 bits and five more: 4.3 G entries, rows on both sides of 2^32."""
+    V, degree = 70_000, 62_000
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GB of free device memory")
+    col = torch.arange(degree, dtype=torch.int32, device="cuda:0").repeat(V)
+    for shift in range(1, 8):                                # row v holds the vertices from v % 8 on
+        col.view(V, degree)[shift::8] += shift
+    dg = B.nd_graph_create(torch.arange(V + 1, device="cuda:0") * degree, col)
+    del col
+    last = (1 << 32) // degree
+    rng = np.random.default_rng(9)
+    tr = np.array([[0, last - 1, last, last + 1, V - 1, last, 5], [V - 1, V - 2, 3, last, -1, 7, last + 8]], dtype=np.int32)
+    sv = rng.integers(0, 9, (2, 40)).astype(np.int32)
+    sv[:, 20:] = rng.integers(degree - 4, degree + 9, (2, 20))
+    row_ptr, slots = B.layer_edges(dg, torch.as_tensor(tr, device="cuda:0"), torch.as_tensor(sv, device="cuda:0"))
+    row_ptr, slots = row_ptr.cpu().numpy(), slots.cpu().numpy()
+    for i, t in enumerate(tr.reshape(-1)):
+        row = sv[i // tr.shape[1]]
+        first = t % 8
+        want = [j for j in np.lexsort((np.arange(row.size), row)) if t >= 0 and first <= row[j] < degree + first]
+        assert slots[row_ptr[i]:row_ptr[i + 1]].tolist() == want, (i, t)
