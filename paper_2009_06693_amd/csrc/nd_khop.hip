@@ -10,6 +10,8 @@
 #include "nd_draw.h"
 #include "nd_group.h"
 
+#include <type_traits>
+
 namespace nd {
 
 namespace {
@@ -273,6 +275,10 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     constexpr uint32_t SUBS = THREADS <= 64 ? 64 / THREADS : 1;  // groups (samples in flight) per workgroup
     constexpr int kLanes = THREADS <= 64 ? THREADS : 64;         // lanes of a group within one wavefront
+    // Who holds a vertex is found in passes (see settle) by whole wavefronts.  Half a one's 32 slots rarely share a bucket,
+    // and its compare-and-swap loops are shorter than two passes (every vertex of R-MAT 22, [25]: 1,152 us, 1,203 with
+    // passes); several wavefronts would need two barriers for each.
+    constexpr bool kPasses = THREADS == 64;
     __shared__ uint32_t s_live[ND_MAX_FANOUT_STEPS];
     __shared__ uint32_t q_fill[2];            // queue lengths of a group of several wavefronts
     const uint32_t sub = threadIdx.x / (uint32_t)THREADS;
@@ -281,7 +287,7 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
     unsigned char* mem = s_raw + (size_t)sub * unique_group_bytes(a.slots, a.rows);
     uint2* rows_a = (uint2*)mem;
     uint2* rows_b = rows_a + a.rows;
-    // A bucket names the slot whose vertex it stands for: j = slot j holds the vertex, kOpen + j = slot j
+    // A bucket names the slot whose vertex it stands for.  By compare and swap: j = slot j holds the vertex, kOpen + j = slot j
     // is the lowest that proposes it so far.  (Keys and claims apart took twice the LDS, and with it a
     // quarter of the wavefronts a compute unit can hold.)
     constexpr uint32_t kOpen = 4096u, kFree = 0xFFFFFFFFu;
@@ -323,11 +329,56 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
             uint32_t buckets = 64;                  // power of two, at least 2 W
             while (buckets < 2u * W) buckets <<= 1;
             const uint32_t mask = buckets - 1u;
+            // In passes: a bucket holds the lowest key of those who came to it, a key being the pass and the slot, so that who
+            // came in an earlier pass stays.  Whoever finds itself in its bucket holds its vertex, whoever finds a slot of the
+            // same vertex has lost, and who finds another vertex goes on to its next bucket in the next pass (the
+            // sequence depends on the vertex only, so that equal vertices meet).  Nothing is marked afterwards, a pass is
+            // an LDS minimum without a result and two reads, and the few that the first pass leaves are packed before the
+            // second (R-MAT 22, every vertex, [25,10], 4 draws: 4,685 us with compare and swap, 4,460 like this; 1,024
+            // vertices of 57 K 19.1 and 15.8).
+            uint32_t pass = 0;
+            auto bucket_of = [&](int32_t c) -> uint32_t { return ((uint32_t)c * 2654435761u >> 15) & mask; };
+            // a pass has put its keys: 1 slot j holds c, 2 it has lost, 0 neither
+            auto verdict = [&](uint32_t b, int32_t c, uint32_t j) -> uint32_t {
+                const uint32_t w = table[b] & (kOpen - 1u);
+                return w == j ? 1u : s_res[w] == c ? 2u : 0u;
+            };
+            // up to `n` slots per lane that come together; open[i] tells who does, won[i] receives who holds its vertex.
+            // `step` buckets of the sequences have been looked at, b[i] is the next.
+            auto settle = [&](auto count, uint32_t limit, const uint32_t* j, const int32_t* c, uint32_t* b, bool* open, bool* won,
+                              uint32_t step) {
+                constexpr int N = decltype(count)::value;
+                bool more;
+                do {
+                    ++pass;
+                    ++step;
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        if ((uint32_t)i * (uint32_t)THREADS >= limit) break;
+                        if (open[i]) atomicMin(&table[b[i]], (pass << 12) + j[i]);  // at most 64 rounds of 512 passes
+                    }
+                    group_sync<THREADS>();
+                    more = false;
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        if ((uint32_t)i * (uint32_t)THREADS >= limit) break;
+                        if (open[i]) {
+                            const uint32_t v = verdict(b[i], c[i], j[i]);
+                            won[i] = v == 1u;
+                            open[i] = v == 0u;
+                            b[i] = (b[i] + step) & mask;
+                        }
+                        more |= open[i];
+                    }
+                    group_sync<THREADS>();
+                } while (group_any<kLanes>(more, group_lanes));  // ends: there are more buckets than vertices
+            };
+            // By compare and swap:
             // proposes vertex c for slot j (s_res[j] is c already, for every proposer); returns the bucket of
             // c.  The table never holds more than W distinct vertices in at least 2 W buckets, so a free or
             // matching bucket is found long before the probe bound.
             auto propose = [&](int32_t c, uint32_t j) -> uint32_t {
-                uint32_t b = ((uint32_t)c * 2654435761u >> 15) & mask;
+                uint32_t b = bucket_of(c);
                 for (uint32_t probe = 0; probe < buckets; ++probe) {
                     const uint32_t old = atomicCAS(&table[b], kFree, kOpen + j);
                     if (old == kFree) break;
@@ -391,34 +442,82 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
                     if ((uint32_t)t * (uint32_t)THREADS < W && j < W) s_res[j] = cand[t];
                 }
                 group_sync<THREADS>();
+                if constexpr (kPasses) {
 #pragma unroll
-                for (int t = 0; t < PER; ++t) {
-                    if ((uint32_t)t * (uint32_t)THREADS >= W) break;
-                    if (cand[t] >= 0) where[t] |= propose(cand[t], tix + (uint32_t)t * (uint32_t)THREADS);
-                }
-                group_sync<THREADS>();
-#pragma unroll
-                for (int t = 0; t < PER; ++t) {
-                    won[t] = false;
-                    if ((uint32_t)t * (uint32_t)THREADS >= W) continue;
-                    won[t] = cand[t] >= 0 && table[where[t] & 0xFFFFu] == kOpen + tix + (uint32_t)t * (uint32_t)THREADS;
-                }
-                group_sync<THREADS>();              // every claim has been read
-                // a winner marks its bucket as held: whoever proposes that vertex later loses; a loser queues
-#pragma unroll
-                for (int t = 0; t < PER; ++t) {
-                    if ((uint32_t)t * (uint32_t)THREADS >= W) break;
-                    const uint32_t j = tix + (uint32_t)t * (uint32_t)THREADS;
-                    if (won[t]) {
-                        table[where[t] & 0xFFFFu] = j;
-                        atomicAdd(&p_held[where[t] >> 16], 1u);
-                    } else if (j < W) {
-                        s_res[j] = ND_NULL_VERTEX;
-                        if (!last) next[j] = make_uint2(0u, 0u);
+                    for (int t = 0; t < PER; ++t) {   // the first pass, all slots at once
+                        if ((uint32_t)t * (uint32_t)THREADS >= W) break;
+                        if (cand[t] >= 0) {
+                            where[t] |= bucket_of(cand[t]);
+                            atomicMin(&table[where[t] & 0xFFFFu], tix + (uint32_t)t * (uint32_t)THREADS);
+                        }
                     }
-                    const bool open = cand[t] >= 0 && !won[t];
-                    const uint32_t at = group_reserve<THREADS>(open, group_lanes, &fill, &q_fill[0]);
-                    if (open) queue[0][at] = (uint16_t)j;
+                    group_sync<THREADS>();
+                    uint32_t undecided = 0;   // packed in the other queue, ascending
+#pragma unroll
+                    for (int t = 0; t < PER; ++t) {
+                        if ((uint32_t)t * (uint32_t)THREADS >= W) break;
+                        const uint32_t j = tix + (uint32_t)t * (uint32_t)THREADS;
+                        uint32_t v = 2u;
+                        if (cand[t] >= 0) v = verdict(where[t] & 0xFFFFu, cand[t], j);
+                        if (v == 1u) atomicAdd(&p_held[where[t] >> 16], 1u);
+                        const uint32_t later = group_reserve<THREADS>(v == 0u, group_lanes, &undecided, nullptr);
+                        if (v == 0u) queue[1][later] = (uint16_t)j;
+                        const bool lost = v == 2u && cand[t] >= 0;
+                        const uint32_t at = group_reserve<THREADS>(lost, group_lanes, &fill, nullptr);
+                        if (lost) queue[0][at] = (uint16_t)j;
+                        if (v == 2u && j < W) {
+                            s_res[j] = ND_NULL_VERTEX;
+                            if (!last) next[j] = make_uint2(0u, 0u);
+                        }
+                    }
+                    group_sync<THREADS>();
+                    if (THREADS >= 64) undecided = wave_uniform(undecided);
+                    for (uint32_t e0 = 0; e0 < undecided; e0 += (uint32_t)THREADS) {  // a fifth where W fills half the table
+                        bool open = e0 + tix < undecided, held = false;
+                        const bool mine = open;
+                        const uint32_t j = mine ? queue[1][e0 + tix] : 0u;
+                        const int32_t c = mine ? s_res[j] : ND_NULL_VERTEX;
+                        uint32_t b = (bucket_of(c) + 1u) & mask;
+                        settle(std::integral_constant<int, 1>{}, 1u, &j, &c, &b, &open, &held, 1u);
+                        if (held) atomicAdd(&p_held[fastdiv(j, a.div_m[hop])], 1u);
+                        const bool lost = mine && !held;
+                        const uint32_t at = group_reserve<THREADS>(lost, group_lanes, &fill, nullptr);
+                        if (lost) {
+                            queue[0][at] = (uint16_t)j;
+                            s_res[j] = ND_NULL_VERTEX;
+                            if (!last) next[j] = make_uint2(0u, 0u);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int t = 0; t < PER; ++t) {
+                        if ((uint32_t)t * (uint32_t)THREADS >= W) break;
+                        if (cand[t] >= 0) where[t] |= propose(cand[t], tix + (uint32_t)t * (uint32_t)THREADS);
+                    }
+                    group_sync<THREADS>();
+#pragma unroll
+                    for (int t = 0; t < PER; ++t) {
+                        won[t] = false;
+                        if ((uint32_t)t * (uint32_t)THREADS >= W) continue;
+                        won[t] = cand[t] >= 0 && table[where[t] & 0xFFFFu] == kOpen + tix + (uint32_t)t * (uint32_t)THREADS;
+                    }
+                    group_sync<THREADS>();              // every claim has been read
+                    // a winner marks its bucket as held: whoever proposes that vertex later loses; a loser queues
+#pragma unroll
+                    for (int t = 0; t < PER; ++t) {
+                        if ((uint32_t)t * (uint32_t)THREADS >= W) break;
+                        const uint32_t j = tix + (uint32_t)t * (uint32_t)THREADS;
+                        if (won[t]) {
+                            table[where[t] & 0xFFFFu] = j;
+                            atomicAdd(&p_held[where[t] >> 16], 1u);
+                        } else if (j < W) {
+                            s_res[j] = ND_NULL_VERTEX;
+                            if (!last) next[j] = make_uint2(0u, 0u);
+                        }
+                        const bool open = cand[t] >= 0 && !won[t];
+                        const uint32_t at = group_reserve<THREADS>(open, group_lanes, &fill, &q_fill[0]);
+                        if (open) queue[0][at] = (uint16_t)j;
+                    }
                 }
             }
             if (THREADS > 64 && tix == 0) q_fill[1] = 0;
@@ -468,13 +567,20 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
                                 }
                                 if (open) s_res[j] = c;
                                 group_sync<kLanes>();
+                                bool win = false;
                                 uint32_t at = 0;
-                                if (open) at = propose(c, j);
-                                group_sync<kLanes>();
-                                const bool win = open && table[at] == kOpen + j;
-                                group_sync<kLanes>();          // every claim has been read
+                                if constexpr (kPasses) {
+                                    bool come = open;
+                                    at = bucket_of(c);
+                                    settle(std::integral_constant<int, 1>{}, 1u, &j, &c, &at, &come, &win, 0u);
+                                } else {
+                                    if (open) at = propose(c, j);
+                                    group_sync<kLanes>();
+                                    win = open && table[at] == kOpen + j;
+                                    group_sync<kLanes>();          // every claim has been read
+                                    if (win) table[at] = j;
+                                }
                                 if (win) {
-                                    table[at] = j;
                                     if (!last) next[j] = cr;
                                     atomicAdd(&p_held[pj], 1u);
                                 } else if (open) {
@@ -518,25 +624,37 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
                     if (!last) next[j] = crow;
                 }
                 group_sync<THREADS>();
+                if constexpr (kPasses) {
+                    uint32_t b[PER];
+                    bool come[PER];
 #pragma unroll
-                for (int p = 0; p < PER; ++p) {
-                    if ((uint32_t)p * (uint32_t)THREADS >= L) break;
-                    if (cand[p] >= 0) where[p] |= propose(cand[p], jq[p]);
-                }
-                group_sync<THREADS>();
+                    for (int p = 0; p < PER; ++p) {
+                        won[p] = false;
+                        come[p] = cand[p] >= 0;
+                        b[p] = bucket_of(cand[p]);
+                    }
+                    settle(std::integral_constant<int, PER>{}, L, jq, cand, b, come, won, 0u);
+                } else {
 #pragma unroll
-                for (int p = 0; p < PER; ++p) {
-                    won[p] = false;
-                    if ((uint32_t)p * (uint32_t)THREADS >= L) continue;
-                    won[p] = cand[p] >= 0 && table[where[p] & 0xFFFFu] == kOpen + jq[p];
+                    for (int p = 0; p < PER; ++p) {
+                        if ((uint32_t)p * (uint32_t)THREADS >= L) break;
+                        if (cand[p] >= 0) where[p] |= propose(cand[p], jq[p]);
+                    }
+                    group_sync<THREADS>();
+#pragma unroll
+                    for (int p = 0; p < PER; ++p) {
+                        won[p] = false;
+                        if ((uint32_t)p * (uint32_t)THREADS >= L) continue;
+                        won[p] = cand[p] >= 0 && table[where[p] & 0xFFFFu] == kOpen + jq[p];
+                    }
+                    group_sync<THREADS>();          // every claim has been read
                 }
-                group_sync<THREADS>();          // every claim has been read
                 fill = 0;
 #pragma unroll
                 for (int p = 0; p < PER; ++p) {
                     if ((uint32_t)p * (uint32_t)THREADS >= L) break;
                     if (won[p]) {
-                        table[where[p] & 0xFFFFu] = jq[p];
+                        if (!kPasses) table[where[p] & 0xFFFFu] = jq[p];
                         atomicAdd(&p_held[where[p] >> 16], 1u);
                     }
                     const bool open = cand[p] >= 0 && !won[p];

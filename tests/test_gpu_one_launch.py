@@ -650,3 +650,24 @@ def test_khop_at_the_widest_packed_columns(V):
     for a, b in zip(*outs):
         assert torch.equal(a, b)
         assert int(a.min()) >= 0
+
+
+@pytest.mark.parametrize("fanout", [[200], [60], [25, 9]])
+def test_unique_neighbours_whose_vertices_share_one_bucket(fanout):
+    """Rows of vertices that the kernels' hash sends to one bucket in 512: a pass for every one of them."""
+    v = np.arange(200_000, dtype=np.uint32)
+    same = v[((v * np.uint32(2654435761)) >> 15) & 511 == 77][:300].astype(np.int32)
+    V, n = 200_000, same.size
+    assert n == 300
+    rows = {int(r): np.sort(same[r % 7:]) for r in range(40)}
+    rows.update({int(s): np.sort(same[i % 5::2]) for i, s in enumerate(same) if int(s) >= 40})
+    off = np.zeros(V + 1, dtype=np.int64)
+    for r, c in rows.items():
+        off[r + 1] = c.size
+    off = np.cumsum(off)
+    col = np.concatenate([rows[r] for r in sorted(rows)]).astype(np.int32)
+    dg, og = B.nd_graph_create(off, col), oracle.OracleGraph(off, col)
+    roots = np.arange(40, dtype=np.int32)
+    want = oracle.khop(og, roots, fanout, seed=3, unique_rounds=6)
+    got, _ = gpu_sample(dg, B.ND_KHOP, roots, 3, num_steps=len(fanout), fanout=fanout, unique_rounds=6)
+    assert_steps_equal(got, want, f"{fanout}")
