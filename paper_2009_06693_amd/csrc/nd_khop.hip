@@ -269,7 +269,8 @@ __host__ __device__ inline uint32_t unique_group_bytes(uint32_t slots, uint32_t 
     return (bytes + 15u) & ~15u;
 }
 
-template <int STRIDE, typename OffT, int THREADS, int PER>
+// PAST: outputs go past the caches.
+template <int STRIDE, typename OffT, int THREADS, int PER, bool PAST = false>
 __global__ __launch_bounds__(THREADS <= 64 ? 64 : THREADS, THREADS <= 64 ? 8 : 4)
 void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
     extern __shared__ __align__(16) unsigned char s_raw[];
@@ -323,7 +324,8 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
             uint2* next = (hop & 1) ? rows_a : rows_b;
             int32_t* out_row = a.out[hop] + (uint64_t)s * W;
             if (!any) {  // uniform: nothing to draw in this hop and those after it
-                for (uint32_t j = tix; j < W; j += (uint32_t)THREADS) out_row[j] = ND_NULL_VERTEX;
+                const int32_t none = ND_NULL_VERTEX;
+                for (uint32_t j = tix; j < W; j += (uint32_t)THREADS) store_run<1, PAST>(out_row + j, &none);
                 continue;
             }
             uint32_t buckets = 64;                  // power of two, at least 2 W
@@ -677,7 +679,7 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
             uint32_t got = 0;
             for (uint32_t j = tix; j < W; j += (uint32_t)THREADS) {
                 const int32_t v = s_res[j];
-                out_row[j] = v;
+                store_run<1, PAST>(out_row + j, &v);
                 got += (uint32_t)__popcll(__ballot(v >= 0) & group_lanes);
                 if (!last) alive |= next[j].y > 0u ? 1 : 0;
             }
@@ -792,12 +794,16 @@ bool khop_reads_packed(const Graph& gr, const int32_t* fanout, int32_t k, int64_
 // Draws of the last hop from which a call's outputs leave past the caches, which then hold more of the graph: every
 // vertex of R-MAT 22, [25,10], 1.05 G draws, 3,220 us and 3,058 like this; 400 M draws of [25,10] on R-MAT 18 979 and 891,
 // over weights on 57 K vertices 1,070 and 1,041, on 2 M alike.  A batch that L2 holds (1,024 roots) is faster through it
-// (8.6 and 8.8), and calls of 1 to 64 M draws are alike.  Outputs that leave one by one (odd fanouts) go past the
+// (8.6 and 8.8).  Outputs that leave one by one (odd fanouts) go past the
 // caches only where the L2s, of 4 MB each, hold the entries between them: 400 M draws on 57 K vertices (6 MB of
 // entries) [7,13] 1,258 and 1,221, [15,10,5] 2,390 and 2,352, on R-MAT 18 (16 MB) 1,156 and 1,186, 2,114 and 2,096; not
 // on R-MAT 22 (275 MB) with 1,520 and 1,581 for [7,13], 2,637 and 2,719 for [5,5], 2,703 and 2,727 for [15,10,5], nor on 2 M
 // vertices (128 MB): 1,985 and 2,022, 3,883 and 3,983, 3,122 and 3,141.
+//
+// In pairs and after a hop that reads links they do so from 6 M draws on: of eight fanouts on twelve graphs with 6 to 64 M draws,
+// with and without packed columns, none slower, up to 13 % faster ([25,10] of 131,072 vertices of R-MAT 22 112 us and 97).
 constexpr int64_t kPastCaches = 64 << 20;
+constexpr int64_t kPastCachesPairs = 6000000;
 constexpr int64_t kPastCachesOneByOne = 8 << 20;  // entries: 32 MB
 
 int64_t khop_fused_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
@@ -840,7 +846,8 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     mark_phase(ND_PHASE_SAMPLE_SUB, stream);
     const dim3 grid((unsigned)f.groups), block(kFusedThreads);
     const bool pairs = khop_in_pairs(a.m[k - 1], step_out[k - 1]);
-    const bool past = S * W[k - 1] >= kPastCaches && (pairs || gr.E <= kPastCachesOneByOne);
+    const bool past = pairs ? S * W[k - 1] >= (k > 1 ? kPastCachesPairs : kPastCaches)
+                            : S * W[k - 1] >= kPastCaches && gr.E <= kPastCachesOneByOne;
 #define ND_FUSED_LAUNCH_R(STRIDE, R, PAST, OFFT)                                                                  \
     do {                                                                                                          \
         auto* kernel = a.packed.bytes ? &khop_fused_kernel<STRIDE, R, PAST, true, OFFT>                           \
@@ -924,6 +931,11 @@ UniqueShape unique_shape(const Graph& gr, const int32_t* fanout, int32_t k, int6
     return u;
 }
 constexpr size_t kUniqueLdsMost = 128 << 10;
+// Slots of the last hop from which the outputs of groups inside a wavefront leave past the caches, which then hold more of
+// the graph: every vertex of R-MAT 22, [25,10], 4,460 us and 4,340, one draw per slot 3,550 and 3,390, [25] 1,152 and
+// 1,127, 1 M vertices of [60] 400 and 380.  From 8,192 samples of [25,10] on never slower, over eleven fanouts on three
+// graphs; 1,024 samples up to 2 % slower.
+constexpr int64_t kUniquePast = 2 << 20;
 }  // namespace
 
 // At most ND_MAX_UNIQUE_SLOTS slots per sample and hop (the call's plan has checked).
@@ -963,15 +975,21 @@ int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32
     a.o_flags = o_flags;
     a.o_parts = o_parts;
     mark_phase(ND_PHASE_UNIQUE, stream);
+    const bool past = S * W[k - 1] >= kUniquePast;
+#define ND_UNIQUE_ONE(STRIDE, OFFT, THREADS, PER)                                                                  \
+    do {                                                                                                           \
+        auto* kernel = past ? &khop_unique_kernel<STRIDE, OFFT, THREADS, PER, true> : &khop_unique_kernel<STRIDE, OFFT, THREADS, PER>; \
+        hipLaunchKernelGGL(kernel, dim3((unsigned)u.groups), dim3(64), u.lds, stream, view_of<OFFT>(gr), a);       \
+    } while (0)
 #define ND_UNIQUE_GO(STRIDE, OFFT, THREADS, PER)                                                                   \
-    hipLaunchKernelGGL((khop_unique_kernel<STRIDE, OFFT, THREADS, PER>), dim3((unsigned)u.groups), dim3(THREADS <= 64 ? 64 : THREADS), u.lds, \
+    hipLaunchKernelGGL((khop_unique_kernel<STRIDE, OFFT, THREADS, PER>), dim3((unsigned)u.groups), dim3(THREADS), u.lds, \
                        stream, view_of<OFFT>(gr), a)
 #define ND_UNIQUE_SIZE(STRIDE, OFFT)                                    \
     do {                                                                \
-        if (u.slots <= 32) ND_UNIQUE_GO(STRIDE, OFFT, 32, 1);           \
-        else if (u.slots <= 64) ND_UNIQUE_GO(STRIDE, OFFT, 64, 1);      \
-        else if (u.slots <= 128) ND_UNIQUE_GO(STRIDE, OFFT, 64, 2);     \
-        else if (u.slots <= 256) ND_UNIQUE_GO(STRIDE, OFFT, 64, 4);     \
+        if (u.slots <= 32) ND_UNIQUE_ONE(STRIDE, OFFT, 32, 1);          \
+        else if (u.slots <= 64) ND_UNIQUE_ONE(STRIDE, OFFT, 64, 1);     \
+        else if (u.slots <= 128) ND_UNIQUE_ONE(STRIDE, OFFT, 64, 2);    \
+        else if (u.slots <= 256) ND_UNIQUE_ONE(STRIDE, OFFT, 64, 4);    \
         else if (u.threads == 128 && u.slots <= 512) ND_UNIQUE_GO(STRIDE, OFFT, 128, 4); \
         else if (u.threads == 128) ND_UNIQUE_GO(STRIDE, OFFT, 128, 8);  \
         else if (u.slots <= 512) ND_UNIQUE_GO(STRIDE, OFFT, 256, 2);    \

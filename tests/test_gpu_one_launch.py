@@ -671,3 +671,14 @@ def test_unique_neighbours_whose_vertices_share_one_bucket(fanout):
     want = oracle.khop(og, roots, fanout, seed=3, unique_rounds=6)
     got, _ = gpu_sample(dg, B.ND_KHOP, roots, 3, num_steps=len(fanout), fanout=fanout, unique_rounds=6)
     assert_steps_equal(got, want, f"{fanout}")
+
+
+@pytest.mark.parametrize("fanout,draws,rounds", [([3, 6], 6_000_000, 0), ([9, 4], 6_000_000, 0), ([32], 2 << 20, 3),
+                                                 ([20, 3], 2 << 20, 3), ([11, 11], 2 << 20, 3), ([25, 10], 2 << 20, 3)])
+def test_first_calls_whose_outputs_leave_past_the_caches(graph, fanout, draws, rounds):
+    """Pairs of draws from 6 M on, unique neighbours (half a wavefront and whole ones) from 2 M slots on: against halves."""
+    g, dg, _ = graph
+    S = -(-draws // int(np.prod(fanout)))
+    r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
+    for whole, halves in _whole_and_halves(dg, B.ND_KHOP, S, r, num_steps=len(fanout), fanout=fanout, unique_rounds=rounds):
+        assert torch.equal(whole, torch.cat(halves))
