@@ -879,7 +879,9 @@ int khop_first(const Graph& gr, const DrawArgs& d, int32_t m, int64_t S, const i
     const uint32_t n = (uint32_t)(S * m);  // below 2^31
     const int64_t per = kFusedThreads * 4;
     int64_t groups = (n + per - 1) / per;
-    if (groups > (int64_t)gr.num_cus * 16) groups = (int64_t)gr.num_cus * 16;
+    // Half of what a unit holds: each group adds to the counter of live pairs, and 233 K roots of 25 draws leave
+    // after 5.6 rounds (the whole call 497 us, 502 to 507 with 2, 8 or 16 per unit).
+    if (groups > (int64_t)gr.num_cus * 4) groups = (int64_t)gr.num_cus * 4;
     const FastDiv div_m = make_fastdiv((uint32_t)m);
     mark_phase(ND_PHASE_SAMPLE_SP, stream);
 #define ND_FIRST_LAUNCH(PACKED, OFFT)                                                                              \

@@ -682,3 +682,29 @@ def test_first_calls_whose_outputs_leave_past_the_caches(graph, fanout, draws, r
     r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
     for whole, halves in _whole_and_halves(dg, B.ND_KHOP, S, r, num_steps=len(fanout), fanout=fanout, unique_rounds=rounds):
         assert torch.equal(whole, torch.cat(halves))
+
+
+@pytest.mark.parametrize("app,S,kw", [(B.ND_KHOP, 30_000, dict(num_steps=2, fanout=[25, 10])),
+                                      (B.ND_KHOP, 30_000, dict(num_steps=2, fanout=[25, 57])),
+                                      (B.ND_KHOP, 30_000, dict(num_steps=2, fanout=[25, 3], sched_sub_max=64)),
+                                      (B.ND_DEEPWALK, 800_001, dict(num_steps=2, use_weights=1)),
+                                      (B.ND_NODE2VEC, 800_001, dict(num_steps=3, p=0.5, q=2.0))])
+def test_many_pairs_are_shared_out_by_neighbourhoods(graph, app, S, kw):
+    """More pairs than 256 for each group of lanes: whole pairs per round, draws that cross a round's end (57), some
+    transits in the other classes; against the sample-parallel kernel."""
+    g, dg, _ = graph
+    kw = dict(kw, use_weights=int(bool(kw.get("use_weights")) and g.weights is not None))
+    if "sched_sub_max" not in kw:
+        kw["sched_force_class"] = B.ND_CLASS_SUBWAVE
+    r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
+    outs = []
+    for mode in (dict(mode=B.ND_MODE_SAMPLE_PARALLEL), {}):
+        use = {k: v for k, v in kw.items() if not (mode and k.startswith("sched"))}
+        s = B.Sampler(dg, app, B.nd_params_init(**use, **mode), S)
+        outs.append([o.clone() for o in s.run(r, 17)])
+        torch.cuda.synchronize()
+        s.status()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    if app == B.ND_KHOP:
+        assert int((outs[0][0] >= 0).sum()) >= 2048 * 256
