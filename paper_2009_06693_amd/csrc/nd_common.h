@@ -99,6 +99,8 @@ struct Graph {
     int device = 0;
     int num_cus = 256;
     int64_t max_degree = 0;
+    int64_t empty_rows = 0;
+    uint64_t* filled = nullptr; // a bit per vertex: its row has entries (behind the offsets)
     // E links, each followed by its WeightLink on a weighted graph; null when E >= 2^31 or when the
     // device had no room for them (walks then take the window kernel)
     Link* links = nullptr;

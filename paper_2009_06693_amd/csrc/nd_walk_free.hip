@@ -40,6 +40,7 @@ struct FreeArgs {
     uint32_t b_ret, b_com, b_far, b_max;
     int32_t max_attempts, use_weights;
     uint32_t R;                // multi-dimensional walk: roots per sample
+    const uint64_t* filled;    // ... a bit per vertex, whether its row has entries (FILLED)
     int32_t* state;            // ... and where they go when more steps follow, else null
     WsHeader* hdr;
     uint32_t* flags;           // per workgroup: a root was outside [0, V) (launches of the first steps)
@@ -570,7 +571,11 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
 // lane: a step that picks a root no earlier one of the 64 picked reads it from the sample's roots
 // in LDS, the others wait for the last earlier step with the same root - two to four rounds for 64 steps
 // and 100 roots, where step after step is 64 chains of three dependent fetches.
-template <int STRIDE, typename OffT, int WAVES>
+// Many samples are bound by the rate of scattered requests to memory (41,943 samples of 100 roots and steps on R-MAT 22:
+// 5.6 M of them in 116 us, two in three for the offsets of a root's row).  KEEP: later steps find the rows of roots that
+// earlier ones moved in LDS (108 us).  FILLED: a bit per vertex, which the L2s hold, says which rows are empty (96 us).
+// All 100 steps at once, two per lane, took 110: more instructions per round.
+template <int STRIDE, typename OffT, int WAVES, bool KEEP, bool FILLED = false>
 __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g, FreeArgs a) {
     extern __shared__ uint32_t s_dyn[];
     constexpr uint32_t T = WAVES * 64;
@@ -579,8 +584,10 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
     const uint32_t R = a.R;
     const uint32_t wave = wave_uniform((uint32_t)wave_id());
     const int lane = lane_id();
-    int32_t* state = (int32_t*)s_dyn + wave * R * 3u;  // the roots of my sample
+    int32_t* state = (int32_t*)s_dyn + wave * R * (KEEP ? 5u : 3u);  // the roots of my sample
     uint32_t* picked = (uint32_t*)state + R;           // per root: which of the 64 steps pick it (two words)
+    uint32_t* rows = picked + 2u * R;                  // KEEP: the root's row, its length kUnknown until a step has looked
+    constexpr uint32_t kUnknown = 0xFFFFFFFFu;         // a row has fewer than 2^31 entries
     const uint32_t s0 = a.s_first + blockIdx.x * WAVES, s = s0 + wave;
     const bool mine = s < a.S;
     bool bad = false;
@@ -596,6 +603,7 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
         state[i] = v;
         picked[2u * i] = 0u;
         picked[2u * i + 1u] = 0u;
+        if (KEEP) rows[2u * i + 1u] = kUnknown;
     }
     for (uint32_t i = threadIdx.x; i < (uint32_t)kFreeChunk; i += T) s_live[i] = 0;
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
@@ -616,10 +624,16 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
         uint32_t ars = 0, adeg = 0;
         if (step && pred < 0) {
             av = state[pick];
-            if (av >= 0) {
-                const uint64_t rs = (uint64_t)g.off[av];
-                ars = (uint32_t)rs;
-                adeg = row_length(g, av, rs);
+            adeg = KEEP ? rows[2u * pick + 1u] : kUnknown;
+            if (adeg != kUnknown) {
+                ars = rows[2u * pick];
+            } else {
+                adeg = 0u;
+                if (av >= 0 && (!FILLED || ((a.filled[(uint32_t)av >> 6] >> (av & 63)) & 1ull) != 0ull)) {
+                    const uint64_t rs = (uint64_t)g.off[av];
+                    ars = (uint32_t)rs;
+                    adeg = row_length(g, av, rs);
+                }
             }
         }
         bool had = false;
@@ -644,7 +658,13 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
             }
         }
         if (step) {
-            if ((same >> lane) == 1ull) state[pick] = av;  // the last of the 64 steps that picked this root
+            if ((same >> lane) == 1ull) {  // the last of the 64 steps that picked this root
+                state[pick] = av;
+                if (KEEP) {
+                    rows[2u * pick] = ars;
+                    rows[2u * pick + 1u] = adeg;
+                }
+            }
             picked[2u * pick] = 0u;
             picked[2u * pick + 1u] = 0u;
             if (had) atomicAdd(&s_live[si], 1u);
@@ -666,12 +686,32 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
         for (uint32_t i = (uint32_t)lane; i < R; i += 64u) a.state[(uint64_t)s * R + i] = state[i];
 }
 
+// Whether rows are looked up in the bits first: where a quarter of them is empty, the offsets are more than an L2 holds and
+// the wavefronts are more than the chip holds.  41,943 samples of 100 steps on R-MAT 22 (47 % empty) 108 us without and 96
+// like this, 300 samples 7.5 and 7.7; on R-MAT 18 (1 MB of offsets) 132.2 and 133.8; on 3 M vertices of which few are
+// alone 97 and 103.
+bool mrw_reads_filled(const Graph& gr, uint32_t S) {
+    return 4 * gr.empty_rows >= gr.V && gr.V * (gr.off64 ? 8 : 4) >= (8 << 20) && S >= 8192u;
+}
+
+constexpr size_t kMrwLds = 48 << 10;
+
 template <int WAVES, typename OffT>
 void launch_mrw(const Graph& gr, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
     const dim3 grid(groups), block(WAVES * 64);
-    const size_t lds = (size_t)WAVES * a.R * 12;  // at most 48 KB
-    if (gr.wq) hipLaunchKernelGGL((mrw_free_kernel<2, OffT, WAVES>), grid, block, lds, stream, view_of<OffT>(gr), a);
-    else hipLaunchKernelGGL((mrw_free_kernel<1, OffT, WAVES>), grid, block, lds, stream, view_of<OffT>(gr), a);
+    const size_t lds = (size_t)WAVES * a.R * 12, lds_keep = (size_t)WAVES * a.R * 20;  // the first is within kMrwLds
+    const bool keep = a.n_steps > 64u && lds_keep <= kMrwLds, filled = keep && mrw_reads_filled(gr, a.S);
+    const GraphView<OffT> g = view_of<OffT>(gr);
+#define ND_MRW_LAUNCH(STRIDE)                                                                             \
+    do {                                                                                                  \
+        auto* kernel = filled ? &mrw_free_kernel<STRIDE, OffT, WAVES, true, true>                         \
+                       : keep ? &mrw_free_kernel<STRIDE, OffT, WAVES, true>                               \
+                              : &mrw_free_kernel<STRIDE, OffT, WAVES, false>;                             \
+        hipLaunchKernelGGL(kernel, grid, block, keep ? lds_keep : lds, stream, g, a);                     \
+    } while (0)
+    if (gr.wq) ND_MRW_LAUNCH(2);
+    else ND_MRW_LAUNCH(1);
+#undef ND_MRW_LAUNCH
 }
 
 // Samples (wavefronts) per workgroup: sixteen, whose outputs then leave in runs of 64 bytes, as long as
@@ -815,6 +855,7 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.max_attempts = d.max_attempts;
     a.use_weights = d.use_weights;
     a.R = mrw_R;
+    a.filled = gr.filled;
     a.hdr = (WsHeader*)ws;
     a.flags = (uint32_t*)(ws + o_flags);
     a.parts = (uint32_t*)(ws + o_parts);

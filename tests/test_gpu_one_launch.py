@@ -708,3 +708,45 @@ def test_many_pairs_are_shared_out_by_neighbourhoods(graph, app, S, kw):
         assert torch.equal(a, b)
     if app == B.ND_KHOP:
         assert int((outs[0][0] >= 0).sum()) >= 2048 * 256
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("V,int64_offsets,S,R", [((1 << 20) + 37, True, 8200, 9), (1 << 21, False, 8192, 5)])
+def test_multi_dimensional_walk_where_rows_are_empty(V, int64_offsets, S, R, weighted):
+    """Half of the rows are empty, the last one as well as the one before, and which they are is looked up in bits: many
+    samples of 100 steps, whose roots are picked before and after step 64, against the oracle."""
+    rng = np.random.default_rng(V)
+    deg = rng.integers(1, 4, V)
+    deg[rng.random(V) < 0.5] = 0
+    deg[:3], deg[-2:] = (0, 1, 0), (2, 0)
+    off = np.concatenate([[0], np.cumsum(deg)])
+    n = int(off[-1])
+    # ascending within a row: a start and steps of at least one
+    start, gap = rng.integers(0, V - 8, V), rng.integers(1, 4, V)
+    row = np.repeat(np.arange(V), deg)
+    col = (start[row] + gap[row] * (np.arange(n) - off[:-1][row])).astype(np.int32)
+    off = off.astype(np.int64 if int64_offsets else np.int32)
+    w = (1.0 + rng.random(n)).astype(np.float32) if weighted else None
+    dg, og = B.nd_graph_create(off, col, w), oracle.OracleGraph(off, col, w)
+    roots = rng.integers(0, V, S * R, dtype=np.int32)
+    roots[::13] = -1
+    roots[1::17], roots[2::17] = V - 1, V - 2
+    want = oracle.multirw(og, roots, R, 100, seed=5)
+    got, _ = gpu_sample(dg, B.ND_MULTIRW, roots, 5, num_steps=100, roots_per_sample=R)
+    assert_steps_equal(got, list(want), f"V={V}")
+
+
+@pytest.mark.parametrize("V", [1, 63, 64, 65, 257])
+def test_offsets_of_few_rows(V):
+    """Errors in the offsets, and none, where rows fill a wavefront or a workgroup and where they do not."""
+    col = np.zeros(1, np.int32)
+    for v in {0, V // 2, V - 1}:  # the only entry is of row v
+        off = (np.arange(V + 1) > v).astype(np.int64)
+        dg = B.nd_graph_create(off, col)
+        got, _ = gpu_sample(dg, B.ND_DEEPWALK, np.arange(V, dtype=np.int32), 1, num_steps=1)
+        assert got[0].tolist() == [0 if i == v else -1 for i in range(V)]
+        for at, by in ((V, 1), (0, 1), (v, 2), (v + 1, -2)):
+            bad = off.copy()
+            bad[at] += by
+            with pytest.raises(B.NdError):
+                B.nd_graph_create(bad, col)
