@@ -227,7 +227,8 @@ int nd_graph_info(const nd_graph* g, int64_t* V, int64_t* E, int* has_weights,
  * without it, and do not use it where it is there.  For layer sampling with
  * use_weights it is the sum of every row's weights (8 bytes per vertex).  For k-hop
  * calls of 6 M draws and more (200 K on dense graphs) it is the columns in as many
- * bits as a vertex takes, up to 25.  A caller
+ * bits as a vertex takes, up to 25.  For multi-dimensional walks of 8,192 samples
+ * and more on large graphs with many empty rows it is a bit per vertex.  A caller
  * who wants the memory more than the speed asks for the weighted calls' sizes with
  * use_weights = 0, which are the same.  No other call of this function touches
  * the device.

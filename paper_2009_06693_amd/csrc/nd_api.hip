@@ -523,6 +523,8 @@ int nd_sample_query(const nd_graph* h, int app, const nd_params* params, int64_t
     else if (params->use_weights && pl.free_walk && walk_uses_cells(*h->g, pl.S)) graph_need_cells(*h->g);
     else if (params->use_weights && pl.layer_fused) graph_need_totals(*h->g);
     else if (pl.packed) graph_need_packed(*h->g);
+    else if (app == ND_MULTIRW && pl.free_walk && mrw_reads_filled(*h->g, pl.S, pl.k, (uint32_t)params->roots_per_sample))
+        graph_need_filled(*h->g);
     if (num_steps) *num_steps = pl.k;
     if (step_len) {
         for (int i = 0; i < pl.k; ++i) {

@@ -100,7 +100,6 @@ struct Graph {
     int num_cus = 256;
     int64_t max_degree = 0;
     int64_t empty_rows = 0;
-    uint64_t* filled = nullptr; // a bit per vertex: its row has entries (behind the offsets)
     // E links, each followed by its WeightLink on a weighted graph; null when E >= 2^31 or when the
     // device had no room for them (walks then take the window kernel)
     Link* links = nullptr;
@@ -112,12 +111,16 @@ struct Graph {
     mutable std::atomic<uint64_t*> totals{nullptr};
     // E columns in packed_bits(V) bits: built when the sizes of a k-hop call that reads them are first asked for
     mutable std::atomic<uint8_t*> packed{nullptr};
+    // A bit per vertex, whether its row has entries: built when the sizes of a multi-dimensional walk that looks
+    // (mrw_reads_filled) are first asked for
+    mutable std::atomic<uint64_t*> filled{nullptr};
     mutable std::mutex extra_mutex;
 };
 void graph_need_rowset(const Graph& g);
 void graph_need_totals(const Graph& g);
 void graph_need_cells(const Graph& g);
 void graph_need_packed(const Graph& g);
+void graph_need_filled(const Graph& g);
 
 // Is u in the row of v?  Every row owns a hash table of at least 2 deg + 1 places in groups of four
 // (16 bytes), open addressing by groups, empty places -1: one fetch answers most questions where a

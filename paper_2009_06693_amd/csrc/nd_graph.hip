@@ -23,12 +23,12 @@ enum : uint32_t {
     kBadRowTotal = 64u   // a row's quantised weights sum to 2^39 or more
 };
 
-// Checks the offsets, and finds the longest row, how many rows are empty and, a bit per row, which are not.
+// Checks the offsets, and finds the longest row and how many rows are empty.
 // found: [0] flags, [2..3] the longest row, [4..5] the empty rows.  One atomic per workgroup and word: atomics on one word
 // take 12 ns each (4.2 M rows: 102 us with one per wavefront, 39 like this).
 template <typename OffT>
 __global__ __launch_bounds__(256) void check_offsets_kernel(const OffT* __restrict__ off, int64_t V, int64_t E,
-                                                            uint32_t* __restrict__ found, uint64_t* __restrict__ filled) {
+                                                            uint32_t* __restrict__ found) {
     __shared__ unsigned long long s_max;
     __shared__ uint32_t s_empty, s_bad;
     if (threadIdx.x == 0) {
@@ -38,20 +38,13 @@ __global__ __launch_bounds__(256) void check_offsets_kernel(const OffT* __restri
     __syncthreads();
     uint32_t bad = 0, empty = 0;
     unsigned long long mx = 0;
-    for (int64_t v0 = (int64_t)blockIdx.x * 256; v0 < V; v0 += (int64_t)gridDim.x * 256) {
-        const int64_t v = v0 + threadIdx.x;
-        bool some = false;
-        if (v < V) {
-            if (v == 0 && off[0] != 0) bad |= kBadFirst;
-            if (v == 0 && (int64_t)off[V] != E) bad |= kBadLast;
-            const int64_t a = (int64_t)off[v], b = (int64_t)off[v + 1];
-            if (a > b || a < 0 || b > E) bad |= kBadMonotone;
-            else if ((unsigned long long)(b - a) > mx) mx = (unsigned long long)(b - a);
-            some = b > a;
-            empty += some ? 0u : 1u;
-        }
-        const uint64_t votes = __ballot(some);
-        if (lane_id() == 0 && v < V) filled[v >> 6] = votes;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
+        if (v == 0 && off[0] != 0) bad |= kBadFirst;
+        if (v == 0 && (int64_t)off[V] != E) bad |= kBadLast;
+        const int64_t a = (int64_t)off[v], b = (int64_t)off[v + 1];
+        if (a > b || a < 0 || b > E) bad |= kBadMonotone;
+        else if ((unsigned long long)(b - a) > mx) mx = (unsigned long long)(b - a);
+        empty += a == b ? 1u : 0u;
     }
     for (int d = 32; d >= 1; d >>= 1) {
         const unsigned long long o = __shfl_xor(mx, d, 64);
@@ -255,6 +248,16 @@ __global__ __launch_bounds__(256) void build_totals_kernel(const OffT* __restric
     }
 }
 
+// A bit per vertex, whether its row has entries.
+template <typename OffT>
+__global__ __launch_bounds__(256) void build_filled_kernel(const OffT* __restrict__ off, int64_t V, uint64_t* __restrict__ filled) {
+    for (int64_t v0 = (int64_t)blockIdx.x * 256; v0 < V; v0 += (int64_t)gridDim.x * 256) {
+        const int64_t v = v0 + threadIdx.x;
+        const uint64_t votes = __ballot(v < V && off[v + 1] > off[v]);
+        if (lane_id() == 0 && v < V) filled[v >> 6] = votes;
+    }
+}
+
 // The packed columns, a 32-bit word per thread: the entries that have a bit in it, two to four where bits >= 11.  Reads
 // come from the caches, which neighbouring words share.
 __global__ __launch_bounds__(256) void build_packed_kernel(const int32_t* __restrict__ col, int64_t E, uint32_t bits,
@@ -310,6 +313,7 @@ void free_graph(Graph* g) {
     (void)hipFree(g->cells.load());
     (void)hipFree(g->totals.load());
     (void)hipFree(g->packed.load());
+    (void)hipFree(g->filled.load());
     delete g;
 }
 
@@ -319,7 +323,7 @@ int validate_and_build(Graph* g, const float* w_dev, uint32_t* flags_dev, hipStr
     int64_t blocks = (g->V + threads - 1) / threads;
     if (blocks > (int64_t)g->num_cus * 4) blocks = (int64_t)g->num_cus * 4;
     hipLaunchKernelGGL(check_offsets_kernel<OffT>, dim3((unsigned)blocks), dim3(threads), 0, stream,
-                       (const OffT*)g->off, g->V, g->E, flags_dev, g->filled);
+                       (const OffT*)g->off, g->V, g->E, flags_dev);
     ND_HIP_CHECK(hipGetLastError());
     struct {
         uint32_t flags, unused;
@@ -392,9 +396,7 @@ int graph_create(Graph** out, int64_t V, int64_t E, const void* off, int off64, 
         const size_t off_bytes = (size_t)(V + 1) * (off64 ? 8 : 4);
         const size_t e_alloc = (size_t)(E > 0 ? E : 1);
         const hipMemcpyKind kind = src_is_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-        const size_t filled_at = (off_bytes + 7) / 8 * 8;
-        ND_HIP_CHECK(hipMalloc(&g->off, filled_at + ((size_t)V + 63) / 64 * 8));
-        g->filled = (uint64_t*)((char*)g->off + filled_at);
+        ND_HIP_CHECK(hipMalloc(&g->off, off_bytes));
         ND_HIP_CHECK(hipMalloc((void**)&g->col, e_alloc * 4));
         ND_HIP_CHECK(hipMalloc((void**)&flags_dev, 256));
         ND_HIP_CHECK(hipMemsetAsync(flags_dev, 0, 256, stream));
@@ -484,6 +486,17 @@ void graph_need_totals(const Graph& g) {
         else
             hipLaunchKernelGGL(build_totals_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.cumq,
                                g.V, totals);
+    });
+}
+
+// Which rows have entries: a bit per vertex.
+void graph_need_filled(const Graph& g) {
+    const dim3 grid((unsigned)g.num_cus * 8u);
+    need_extra(g, g.filled, ((size_t)g.V + 63) / 64 * 8, [&](uint64_t* filled, hipStream_t stream) {
+        if (g.off64)
+            hipLaunchKernelGGL(build_filled_kernel<int64_t>, grid, dim3(256), 0, stream, (const int64_t*)g.off, g.V, filled);
+        else
+            hipLaunchKernelGGL(build_filled_kernel<int32_t>, grid, dim3(256), 0, stream, (const int32_t*)g.off, g.V, filled);
     });
 }
 

@@ -398,7 +398,10 @@ void khop_unique_kernel(GraphView<OffT> g, UniqueFusedArgs a) {
             if (THREADS > 64 && tix == 0) q_fill[0] = 0;
             // what a slot draws: an entry of the parent's row (its link where the hop has children)
             auto fetch = [&](uint2 row, uint32_t j, uint32_t attempt, uint2* row_out) -> int32_t {
-                const Rand4 r = draw4(a.seed, a.sample_base + s, j, (uint32_t)hop, attempt);
+                // Joined exclusive ors make a call of few samples, by four wavefronts each, longer: 56 of [15,10,5] with 8
+                // draws 30.6 us and 31.9 with them, 200 with 4 draws 22.2 and 22.6; two wavefronts gain (100,000 on
+                // R-MAT 22 692 and 684).
+                const Rand4 r = draw4<THREADS != 256>(a.seed, a.sample_base + s, j, (uint32_t)hop, attempt);
                 const uint64_t e = (uint64_t)row.x + mulhi32(r.r0, row.y);
                 *row_out = make_uint2(0u, 0u);
                 if (last) return g.col[e];

@@ -20,18 +20,21 @@ struct Rand4 {
 // a ^ b ^ c in one instruction, which the compiler (ROCm 7.2) does not choose by itself.  A generator call is ten
 // rounds of two multiplications and two of these, each waiting for the one before: 296 cycles alone on a SIMD with two
 // exclusive ors in their place, 202 like this; 199 and 162 cycles of issue where eight wavefronts share the SIMD.
+// JOINED false: two instructions after all, for a kernel that was measured to be the faster for it.
+template <bool JOINED>
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
-    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+    return JOINED ? (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96) : a ^ b ^ c;
 }
 
+template <bool JOINED = true>
 __device__ __forceinline__ Rand4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+        const uint32_t n0 = xor3<JOINED>((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = xor3<JOINED>((uint32_t)(p0 >> 32), c3, k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -43,9 +46,10 @@ __device__ __forceinline__ Rand4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
 }
 
 // Counter layout of every draw: (sample id, slot within the sample, step, attempt).
+template <bool JOINED = true>
 __device__ __forceinline__ Rand4 draw4(uint64_t seed, uint32_t sample_id, uint32_t slot,
                                        uint32_t step, uint32_t attempt) {
-    return philox4x32_10(sample_id, slot, step, attempt, (uint32_t)seed, (uint32_t)(seed >> 32));
+    return philox4x32_10<JOINED>(sample_id, slot, step, attempt, (uint32_t)seed, (uint32_t)(seed >> 32));
 }
 
 __device__ __forceinline__ uint32_t mulhi32(uint32_t a, uint32_t b) { return __umulhi(a, b); }

@@ -74,6 +74,7 @@ int walk_windows(const Graph& gr, int draw, bool multirw, const DrawArgs& d, int
 // multi-dimensional walk, whose roots pass through mrw_state where the call takes several launches.  The
 // call's header, one flag per workgroup (o_flags) and the live walks per workgroup and step (o_parts)
 // go to the workspace.
+bool mrw_reads_filled(const Graph& gr, int64_t S, int32_t num_steps, uint32_t R);
 int64_t walk_free_groups(int64_t S, int32_t num_steps, bool node2vec, uint32_t mrw_R);
 bool walk_uses_cells(const Graph& gr, int64_t S);  // DeepWalk and PPR over edge weights, where the cells are there
 int64_t walk_free_state_bytes(int64_t S, int32_t num_steps, uint32_t mrw_R);

@@ -686,21 +686,14 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
         for (uint32_t i = (uint32_t)lane; i < R; i += 64u) a.state[(uint64_t)s * R + i] = state[i];
 }
 
-// Whether rows are looked up in the bits first: where a quarter of them is empty, the offsets are more than an L2 holds and
-// the wavefronts are more than the chip holds.  41,943 samples of 100 steps on R-MAT 22 (47 % empty) 108 us without and 96
-// like this, 300 samples 7.5 and 7.7; on R-MAT 18 (1 MB of offsets) 132.2 and 133.8; on 3 M vertices of which few are
-// alone 97 and 103.
-bool mrw_reads_filled(const Graph& gr, uint32_t S) {
-    return 4 * gr.empty_rows >= gr.V && gr.V * (gr.off64 ? 8 : 4) >= (8 << 20) && S >= 8192u;
-}
-
 constexpr size_t kMrwLds = 48 << 10;
+size_t mrw_keep_lds(int waves, uint32_t R) { return (size_t)waves * R * 20; }
 
 template <int WAVES, typename OffT>
 void launch_mrw(const Graph& gr, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
     const dim3 grid(groups), block(WAVES * 64);
-    const size_t lds = (size_t)WAVES * a.R * 12, lds_keep = (size_t)WAVES * a.R * 20;  // the first is within kMrwLds
-    const bool keep = a.n_steps > 64u && lds_keep <= kMrwLds, filled = keep && mrw_reads_filled(gr, a.S);
+    const size_t lds = (size_t)WAVES * a.R * 12, lds_keep = mrw_keep_lds(WAVES, a.R);  // the first is within kMrwLds
+    const bool keep = a.n_steps > 64u && lds_keep <= kMrwLds, filled = keep && a.filled != nullptr;
     const GraphView<OffT> g = view_of<OffT>(gr);
 #define ND_MRW_LAUNCH(STRIDE)                                                                             \
     do {                                                                                                  \
@@ -807,6 +800,19 @@ static int attempt_lanes(int64_t S, const DrawArgs& d) {
     return S <= kFewAttemptWalks && accepted < 0.75 ? kAttemptLanes : 1;
 }
 
+// Later steps of a launch find rows in LDS that earlier ones left.
+static bool mrw_keeps_rows(int32_t num_steps, uint32_t R) {
+    return num_steps > 64 && mrw_keep_lds(mrw_waves(R), R) <= kMrwLds;
+}
+
+// Whether rows are looked up in the bits first: where a quarter of them is empty, the offsets are more than an L2 holds and
+// the wavefronts are more than the chip holds.  41,943 samples of 100 steps on R-MAT 22 (47 % empty) 108 us without and 96
+// like this, 300 samples 7.5 and 7.7; on R-MAT 18 (1 MB of offsets) 132.2 and 133.8; on 3 M vertices of which few are
+// alone 97 and 103.
+bool mrw_reads_filled(const Graph& gr, int64_t S, int32_t num_steps, uint32_t R) {
+    return 4 * gr.empty_rows >= gr.V && gr.V * (gr.off64 ? 8 : 4) >= (8 << 20) && S >= 8192 && mrw_keeps_rows(num_steps, R);
+}
+
 // Walks per workgroup; lanes: attempts at once of a node2vec call, 0 for the others.
 static int64_t samples_per_group(int64_t S, int lanes, uint32_t mrw_R) {
     if (mrw_R > 0) return mrw_waves(mrw_R);
@@ -855,7 +861,7 @@ int walk_free(const Graph& gr, int draw, const DrawArgs& d, int64_t S, int32_t n
     a.max_attempts = d.max_attempts;
     a.use_weights = d.use_weights;
     a.R = mrw_R;
-    a.filled = gr.filled;
+    a.filled = mrw_R > 0 && mrw_reads_filled(gr, S, num_steps, mrw_R) ? gr.filled.load(std::memory_order_acquire) : nullptr;
     a.hdr = (WsHeader*)ws;
     a.flags = (uint32_t*)(ws + o_flags);
     a.parts = (uint32_t*)(ws + o_parts);
