@@ -32,8 +32,8 @@ HBM_PEAK_GBS = 8000.0
 # from above.  Source: the counter table in profiles/one_launch_routes_rocprofv3.md.  None where not
 # profiled.
 MEASURED_TRAFFIC_BYTES = {
-    ("c5_khop", "khop_fused_kernel"): 22318600192,     # 17,135,604 KiB fetched + 4,659,904 KiB written
-    ("c5_deepwalk", "walk_free_kernel"): 29912658944,  # 27,565,350 KiB fetched + 1,646,231 KiB written
+    ("c5_khop", "khop_fused_kernel"): 19968795648,     # 14,869,094 KiB fetched + 4,631,683 KiB written
+    ("c5_deepwalk", "walk_free_kernel"): 29908805632,  # 27,561,580 KiB fetched + 1,646,238 KiB written
 }
 
 WORKLOADS = {
