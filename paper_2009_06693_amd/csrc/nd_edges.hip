@@ -19,6 +19,9 @@
 // (scalar instructions as much as vector ones) before the 4 bytes per entry it streams.  So an entry first tests one
 // bit of a 65,536-bit map of the sample's vertices (no loop, no divergence); the few that pass are packed, in order,
 // into a queue of the wavefront in LDS, and the table is probed by a full wavefront of queued entries at a time.
+// The map's bits are hashed from the whole id: 512 samples of 2,048 transits and vertices on a graph whose ids are
+// multiples of 64, where bits of the id let 39 % of the entries pass, count in 674 us (2,070) and fill in 866 (2,200), with
+// ids in 64 blocks 2^16 apart 705 (2,720) and 894 (3,480); on relabelled ids both are as fast.
 // Whether there are as many is asked once for two or four loads of 64 entries, whose looks at the map then wait for LDS
 // together, and full steps have code of their own, without a test of where the list ends.  Counting pass of 4,096
 // samples of 2,048 transits and vertices (10 GB of lists): 2.12 ms with one load at a time and the lists' places fetched
@@ -35,6 +38,7 @@
 
 #include "nd_common.h"
 #include "nd_edges.h"
+#include "nd_places.h"
 #include "nd_wave.h"
 
 namespace nd {
@@ -92,10 +96,6 @@ static_assert(sizeof(EdgeLds<true>) <= 80 * 1024 && sizeof(EdgeLds<false>) <= 80
 
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 __device__ __forceinline__ uint32_t hash_vertex(int32_t v) { return (uint32_t)v * 0x9E3779B1u; }
-// The vertex's bit in the map: bits 2-12 of its id name the word (an AND gives its place in bytes), the others the
-// bit, counted from the top, so that the test is a shift and a sign.
-__device__ __forceinline__ uint32_t map_word(int32_t v) { return ((uint32_t)v & 0x1FFCu) >> 2; }
-__device__ __forceinline__ uint32_t map_bit(int32_t v) { return (((uint32_t)v << 3) + ((uint32_t)v >> 13)) & 31u; }
 
 // one wavefront: its LDS operations complete in order; keeps the compiler from moving them
 __device__ __forceinline__ void wave_lds_order() {
@@ -224,8 +224,10 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                 for (int j = 0; j < 4; ++j) {
                     s.first[tid * 4u + (uint32_t)j] = (uint16_t)at;
                     at += vcnt[j];
-                    if (vkey[j] != kNoKey)
-                        atomicOr(&s.bits[map_word((int32_t)vkey[j])], 0x80000000u >> map_bit((int32_t)vkey[j]));
+                    if (vkey[j] != kNoKey) {
+                        const uint32_t h = edge_map_hash((int32_t)vkey[j]);
+                        atomicOr(&s.bits[edge_map_word(h)], 0x80000000u >> edge_map_bit(h));
+                    }
                 }
                 if (tid == a.table / 4u - 1u) s.first[a.table] = (uint16_t)at;
             }
@@ -473,10 +475,10 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                     if (!FULL && (uint32_t)r0 * 64u >= cnt) break;  // the same for the whole wavefront
                     uint32_t word[kPieces];
 #pragma unroll
-                    for (int r = 0; r < kPieces; ++r) word[r] = s.bits[map_word(u[r0 + r])];
+                    for (int r = 0; r < kPieces; ++r) word[r] = s.bits[edge_map_word(edge_map_hash(u[r0 + r]))];
 #pragma unroll
                     for (int r = 0; r < kPieces; ++r) {
-                        const bool pass = (int32_t)(word[r] << map_bit(u[r0 + r])) < 0;
+                        const bool pass = (int32_t)(word[r] << edge_map_bit(edge_map_hash(u[r0 + r]))) < 0;
                         uint64_t votes = __ballot(pass);
                         if (!FULL) {
                             // The lanes past the list's end are struck from the votes and not from `pass`: such a lane that
