@@ -50,6 +50,7 @@ constexpr int kBitWords = 2048;     // the vertex map: 65,536 bits
 constexpr int kMaxSlots = 2048;     // new vertices per sample (ND_MAX_EDGE_SLOTS)
 constexpr int kTable = 2 * kMaxSlots;
 constexpr int kChunk = 2048;        // transit slots of a sample that are grouped together
+constexpr uint32_t kRun = 64;       // slots of a vertex up to which each of them looks at all the others
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
@@ -91,6 +92,7 @@ struct EdgeLds {
     uint64_t scan[kEdgeThreads / 64 + 1];
     uint32_t items, live;           // distinct transits and live slots of the chunk
     uint32_t next;                  // next item to hand out
+    uint32_t long_runs;             // filling pass: a vertex of the sample is held by more than kRun slots
 };
 static_assert(sizeof(EdgeLds<true>) <= 80 * 1024 && sizeof(EdgeLds<false>) <= 80 * 1024, "two workgroups per compute unit");
 
@@ -120,7 +122,8 @@ __device__ __forceinline__ uint32_t count_key(uint32_t* keys, uint16_t* counts, 
 // Two workgroups of 1,024 threads per compute unit are eight wavefronts per SIMD.  That takes at most
 // 64 vector registers and, on this register file (800 scalar registers per SIMD), at most 96 scalar
 // registers per wavefront: left to itself the compiler uses more scalar registers than that, which
-// silently halves the occupancy, so the bound is stated (the surplus goes to lanes of a vector register).
+// silently halves the occupancy, so the bound is stated (the surplus goes to lanes of a vector register; of the set-up's
+// vector registers 2 and, in the filling pass, 12 go to memory, none of the loop's).
 template <typename OffT, bool FILL>
 __global__ __launch_bounds__(kEdgeThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
@@ -185,6 +188,7 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                 reinterpret_cast<uint2*>(s.first)[i] = make_uint2(0u, 0u);
             }
             for (uint32_t i = tid; i < (uint32_t)kBitWords; i += T) s.bits[i] = 0u;
+            if (FILL && tid == 0) s.long_runs = 0u;
         }
         for (uint32_t i = tid; i < t_table / 4u; i += T) {
             reinterpret_cast<uint4*>(s.t_keys)[i] = none;
@@ -224,6 +228,7 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
                 for (int j = 0; j < 4; ++j) {
                     s.first[tid * 4u + (uint32_t)j] = (uint16_t)at;
                     at += vcnt[j];
+                    if (FILL && vcnt[j] > kRun) s.long_runs = 1u;
                     if (vkey[j] != kNoKey) {
                         const uint32_t h = edge_map_hash((int32_t)vkey[j]);
                         atomicOr(&s.bits[edge_map_word(h)], 0x80000000u >> edge_map_bit(h));
@@ -263,14 +268,37 @@ void edges_kernel(GraphView<OffT> g, EdgeArgs a) {
             if (FILL && v[e] >= 0) s.slot[s.first[vp[e] & 0xFFFFu] + (vp[e] >> 16)] = (uint16_t)(tid + e * T);
         }
         if (FILL && first) {  // the slots of a vertex, in any order yet: each counts the lower ones
+            // Of more than kRun slots in a bitmap of theirs, 2,048 bits in the queues' LDS: every such run has a multiple of kRun
+            // among its places, and the first one names its bitmap (512 samples of 64 transits and 2,048 slots that all hold
+            // one vertex, no edges: 167 us when each slot looks at every other, 32 like this, 20 with different vertices).
+            constexpr uint32_t kWords = kMaxSlots / 32;
+            static_assert(kMaxSlots / kRun * kWords * 4 <= sizeof(s.queue), "a bitmap for every multiple");
             __syncthreads();
+            const bool long_runs = wave_uniform(s.long_runs) != 0u;
+            if (long_runs) {
+                for (uint32_t i = tid; i < kMaxSlots / kRun * kWords; i += T) s.queue[i] = 0u;
+                __syncthreads();
+#pragma unroll
+                for (uint32_t e = 0; e < 2u; ++e)
+                    if (v[e] >= 0) {
+                        const uint32_t k = s.first[vp[e] & 0xFFFFu], end = s.first[(vp[e] & 0xFFFFu) + 1u];
+                        if (end - k > kRun) atomicOr(&s.queue[(k + kRun - 1u) / kRun * kWords + ((tid + e * T) >> 5)], 1u << (tid & 31u));
+                    }
+                __syncthreads();
+            }
             uint32_t at[2] = {0u, 0u};
 #pragma unroll
             for (uint32_t e = 0; e < 2u; ++e)
                 if (v[e] >= 0) {
-                    const uint32_t k = s.first[vp[e] & 0xFFFFu], end = s.first[(vp[e] & 0xFFFFu) + 1u];
+                    const uint32_t k = s.first[vp[e] & 0xFFFFu], end = s.first[(vp[e] & 0xFFFFu) + 1u], slot = tid + e * T;
                     at[e] = k;
-                    for (uint32_t i = k; end - k > 1u && i < end; ++i) at[e] += s.slot[i] < tid + e * T ? 1u : 0u;
+                    if (long_runs && end - k > kRun) {
+                        const uint32_t* map = s.queue + (k + kRun - 1u) / kRun * kWords;
+                        for (uint32_t w = 0; w < slot >> 5; ++w) at[e] += (uint32_t)__popc(map[w]);
+                        at[e] += (uint32_t)__popc(map[slot >> 5] & ((1u << (slot & 31u)) - 1u));
+                    } else {
+                        for (uint32_t i = k; end - k > 1u && i < end; ++i) at[e] += s.slot[i] < slot ? 1u : 0u;
+                    }
                 }
             __syncthreads();
 #pragma unroll

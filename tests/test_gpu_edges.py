@@ -195,3 +195,51 @@ def test_lists_that_start_beyond_four_billion_entries():
         first = t % 8
         want = [j for j in np.lexsort((np.arange(row.size), row)) if t >= 0 and first <= row[j] < degree + first]
         assert slots[row_ptr[i]:row_ptr[i + 1]].tolist() == want, (i, t)
+
+
+def _fill_time(dg, transits, sampled):
+    """The least time of a filling pass, ms."""
+    S, n = transits.shape
+    row_ptr = torch.empty(S * n + 1, dtype=torch.int64, device="cuda:0")
+    ws = torch.empty(max(B.nd_layer_edges_workspace_bytes(S, n), 256), dtype=torch.uint8, device="cuda:0")
+    B.nd_layer_edges_count(dg, transits, sampled, row_ptr, ws)
+    assert int(row_ptr[-1]) == 0
+    slots = torch.empty(1, dtype=torch.int32, device="cuda:0")
+    marks = [torch.cuda.Event(enable_timing=True) for _ in range(12)]
+    for m in marks:
+        B.nd_layer_edges_fill(dg, transits, sampled, row_ptr, slots)
+        m.record()
+    torch.cuda.synchronize()
+    return min(a.elapsed_time(b) for a, b in zip(marks, marks[1:]))
+
+
+def test_a_vertex_in_every_slot_is_ordered_about_as_fast_as_different_ones():
+    """Leaves of a star and no edges between them, so that a filling pass is its preparation: each slot that looks at
+    every other one of its vertex took 167 us where different vertices take 19 and a bitmap per vertex 32.  Three times
+    is between."""
+    V = 4001
+    g = inputs.from_edges(V, [(0, v) for v in range(1, V)] + [(v, 0) for v in range(1, V)])
+    dg, _ = device_graph(g)
+    S = 512
+    tr = (1 + torch.arange(S * 64, device="cuda:0") % (V - 1)).to(torch.int32).view(S, 64)
+    different = _fill_time(dg, tr, torch.arange(1, 2049, device="cuda:0", dtype=torch.int32).repeat(S, 1))
+    one = _fill_time(dg, tr, torch.full((S, 2048), 7, device="cuda:0", dtype=torch.int32))
+    print(f"[times] different vertices {different:.4f} ms, one {one:.4f} ms", flush=True)
+    assert one < 3 * different
+
+
+@pytest.mark.parametrize("runs", [[2048], [65, 64, 63, 66], [1023, 1025], [65] * 31 + [33], [128, 129, 1, 64, 700, 2]])
+def test_slots_of_a_vertex_leave_in_order_whatever_their_number(runs):
+    """Runs around 64 slots, up to which each slot looks at the others, as many longer ones as there can be, and all slots."""
+    g = _small
+    hub = int(np.argmax(np.diff(g.row_offsets)))
+    nbrs = g.col_indices[g.row_offsets[hub]:g.row_offsets[hub + 1]]
+    assert nbrs.size >= len(runs)
+    rng = np.random.default_rng(len(runs))
+    sampled = np.full((3, 2048), -1, dtype=np.int32)
+    for row in sampled:
+        row[rng.permutation(2048)[:sum(runs)]] = np.repeat(rng.permutation(nbrs)[:len(runs)], runs)
+    transits = rng.integers(0, g.V, (3, 2100)).astype(np.int32)
+    transits[:, ::700] = hub
+    ptr = _compare(g, transits, sampled)
+    assert ptr[1] - ptr[0] == sum(runs)
