@@ -27,6 +27,7 @@
 #include "nd_common.h"
 #include "nd_philox.h"
 #include "nd_wave.h"
+#include "nd_places.h"
 #include "nd_sample.h"
 #include "nd_draw.h"
 #include "nd_group.h"
@@ -155,6 +156,10 @@ __device__ __forceinline__ int32_t draw_pair(const GraphView<OffT>& g, const Dra
                                (DRAW == kDrawNode2vec && a.use_weights) ? g.wq + c.rs : nullptr);
 }
 
+// Independent pairs in flight per lane of the sub-wavefront kernel (the looping draws gain nothing from a second one).
+template <int DRAW>
+constexpr int kPairsInFlight = DRAW == kDrawUniform ? 2 : 1;
+
 // The loop of the sub-wavefront kernel.  HEAVY: some transits of this step belong to the
 // workgroup / grid class and must be skipped (looked up in the bitmap).
 template <int DRAW, bool PACKED, bool HEAVY, typename OffT>
@@ -165,8 +170,7 @@ __device__ __forceinline__ void sub_loop(const GraphView<OffT>& g, const DrawArg
                                          uint32_t tid, uint32_t block, uint32_t blocks) {
     // tid, block, blocks: position of this lane in a grid of 256-lane groups (four of them share
     // one workgroup of the launch)
-    // independent pairs in flight per lane (the looping draws gain nothing from a second one)
-    constexpr int U = DRAW == kDrawUniform ? 2 : 1;
+    constexpr int U = kPairsInFlight<DRAW>;
     if (pairs_per_block != 0u) {
         // A workgroup round covers pairs_per_block whole pairs: a lane keeps its draw index jj
         // and walks over pairs, so no division sits in the loop.  U pairs are fetched before the
@@ -287,7 +291,8 @@ __global__ __launch_bounds__(kWgThreads) void sample_tp_kernel(
     const int32_t* __restrict__ g_key, const int32_t* __restrict__ g_start,
     const int32_t* __restrict__ list_wg, const int32_t* __restrict__ chunk_gid,
     const int32_t* __restrict__ chunk_idx, uint32_t cap_wg, uint32_t cap_chunks,
-    const uint32_t* __restrict__ heavy_bits, uint32_t pairs_per_block, int do_heavy, int do_lanes) {
+    const uint32_t* __restrict__ heavy_bits, uint32_t pairs_per_block, uint32_t neighbours_from,
+    int do_heavy, int do_lanes) {
     constexpr uint32_t cap = StageCap<DRAW>::value;
     __shared__ int32_t lds_col[cap];
     __shared__ uint64_t lds_cum[DRAW == kDrawWeighted ? cap : 1];
@@ -320,16 +325,9 @@ __global__ __launch_bounds__(kWgThreads) void sample_tp_kernel(
     if (do_lanes) {  // no barrier from here on
         const uint32_t P = ctl->P;
         const uint32_t tid = threadIdx.x & 255u;
-        // Four 256-lane groups per workgroup; group i of workgroup b is number i * gridDim.x + b,
-        // so that neighbouring rounds go to different workgroups (CUs) and a small step still
-        // uses every CU.
+        // Four 256-lane groups per workgroup
         const uint32_t blocks = gridDim.x * (kWgThreads / 256);
-        uint32_t block = (threadIdx.x >> 8) * gridDim.x + blockIdx.x;
-        // Many rounds: the groups of an XCD (workgroups go to the eight in turn) are neighbours, so that the pairs of a
-        // transit meet its row in one L2, as a rule even in one L1.  5.8 M pairs of 10 draws, mean degree 487, bound by the
-        // requests to memory (half of them stores of 40 bytes): 317 us with neighbours on different XCDs, 297 like this.
-        if (gridDim.x % 8u == 0u && P / 256u >= blocks)
-            block = (blockIdx.x % 8u) * (blocks / 8u) + blockIdx.x / 8u * (kWgThreads / 256) + (threadIdx.x >> 8);
+        const uint32_t block = first_block(blockIdx.x, threadIdx.x >> 8, gridDim.x, P >= neighbours_from);
         // no transit went to the other classes this step: nothing to look up in the bitmap
         if (heavy_bits != nullptr && (ctl->n_wg | ctl->n_chunks) != 0u)
             sub_loop<DRAW, PACKED, true>(g, a, P, keys, vals, heavy_bits, pairs_per_block, tid, block, blocks);
@@ -355,6 +353,9 @@ int launch_tp(const Graph& gr, const DrawArgs& a, const SchedParams& sp, const T
     // whole pairs per 256-lane round when that idles under a tenth of the lanes
     uint32_t ppb = a.m <= 256u ? 256u / a.m : 0u;
     if (ppb * a.m < 231u) ppb = 0u;
+    const uint32_t groups = (uint32_t)blocks * (kWgThreads / 256);
+    const uint32_t per_round = ppb != 0u ? groups * ppb * kPairsInFlight<DRAW> : groups * 256u / a.m;
+    const uint32_t neighbours_from = pairs_of_neighbours(a.m, (uint32_t)blocks, per_round);
     mark_phase(lanes ? ND_PHASE_SAMPLE_SUB : ND_PHASE_SAMPLE_WG, stream);
     auto* kernel = &sample_tp_kernel<DRAW, false, OffT>;
     if (DRAW == kDrawUniform && a.packed.bytes) kernel = &sample_tp_kernel<DRAW, DRAW == kDrawUniform, OffT>;
@@ -362,7 +363,7 @@ int launch_tp(const Graph& gr, const DrawArgs& a, const SchedParams& sp, const T
                        stream, g, a, sp, t.ctl, t.keys, t.vals, t.g_key, t.g_start, t.list_wg,
                        t.chunk_gid, t.chunk_idx, (uint32_t)t.cap_wg, (uint32_t)t.cap_chunks,
                        sp.force_class == ND_CLASS_AUTO ? (const uint32_t*)t.heavy_bits : nullptr, ppb,
-                       heavy ? 1 : 0, lanes ? 1 : 0);
+                       neighbours_from, heavy ? 1 : 0, lanes ? 1 : 0);
     ND_HIP_CHECK(hipGetLastError());
     return ND_OK;
 }

@@ -15,6 +15,12 @@ extern "C" void edge_bits(const int32_t* v, int64_t n, int32_t* bit) {
         bit[i] = (int32_t)(nd::edge_map_word(h) * 32u + nd::edge_map_bit(h));
     }
 }
+extern "C" int blocks_of_groups(uint32_t pairs, uint32_t per_pair, uint32_t workgroups, uint32_t per_round, uint32_t* block) {
+    const bool next = pairs >= nd::pairs_of_neighbours(per_pair, workgroups, per_round);
+    for (uint32_t w = 0; w < workgroups; ++w)
+        for (uint32_t g = 0; g < 4; ++g) block[w * 4 + g] = nd::first_block(w, g, workgroups, next);
+    return next;
+}
 """
 
 
@@ -61,3 +67,27 @@ def test_few_vertices_share_a_bit_of_the_edge_map_whatever_the_ids_structure(pla
         in_map[bits[held]] = True
         rates.append(in_map[bits[others]].mean())
     assert np.mean(rates) < 3 * 2048 / 65536
+
+
+@pytest.mark.parametrize("workgroups", [1, 7, 8, 100, 504, 512])
+@pytest.mark.parametrize("per_pair,in_flight", [(1, 1), (1, 2), (2, 2), (3, 2), (5, 2), (10, 2), (25, 2), (100, 1), (300, 2)])
+def test_groups_of_lanes_take_each_block_once_and_few_rounds_use_every_xcd(places, workgroups, per_pair, in_flight):
+    """A block of pairs per group and round, workgroup w on XCD w % 8: no XCD has much more than the mean, at any number
+    of draws (half a round on four of the eight: 1.25 to 1.45 times the time of the draws, one per pair by weights).  A
+    round that is nearly empty weighs a third where there are three before it, and all there is where it is alone."""
+    groups = 4 * workgroups
+    whole = 256 // per_pair
+    per_group = whole * in_flight if whole * per_pair >= 231 else 256 / per_pair  # pairs per round
+    block = np.empty(groups, dtype=np.uint32)
+    orders = set()
+    for rounds in (0.3, 0.5, 0.75, 1.0, 1.25, 1.5, 2.1, 2.98, 3.0, 3.2, 5.5, 20.0):
+        pairs = max(1, int(rounds * groups * per_group))
+        orders.add(places.blocks_of_groups(pairs, per_pair, workgroups, int(groups * per_group),
+                                           block.ctypes.data_as(ctypes.c_void_p)))
+        assert np.array_equal(np.sort(block), np.arange(groups))
+        blocks = int(-(-pairs // per_group))                           # block b, b + groups, b + 2 groups, ... are a group's
+        load = np.zeros(8)
+        np.add.at(load, (np.arange(groups) // 4) % 8, np.maximum(0, -(-(blocks - block.astype(np.int64)) // groups)))
+        if workgroups % 8 == 0 and blocks >= 8 * 4:
+            assert load.max() <= (1.34 if rounds > 3 else 1.13) * load.mean(), (rounds, load)
+    assert orders == ({0, 1} if workgroups % 8 == 0 and per_pair >= 5 else {0})
