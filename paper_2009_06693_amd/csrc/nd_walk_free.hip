@@ -573,7 +573,7 @@ __global__ __launch_bounds__(THREADS) void walk_free_n2v_kernel(GraphView<OffT> 
 // and 100 roots, where step after step is 64 chains of three dependent fetches.
 // Many samples are bound by the rate of scattered requests to memory (41,943 samples of 100 roots and steps on R-MAT 22:
 // 5.6 M of them in 116 us, two in three for the offsets of a root's row).  KEEP: later steps find the rows of roots that
-// earlier ones moved in LDS (108 us).  FILLED: a bit per vertex, which the L2s hold, says which rows are empty (96 us).
+// earlier ones moved in LDS (108 us).  FILLED: a bit per vertex, which the L2s hold, says which rows are empty (97 us).
 // All 100 steps at once, two per lane, took 110: more instructions per round.
 template <int STRIDE, typename OffT, int WAVES, bool KEEP, bool FILLED = false>
 __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g, FreeArgs a) {
@@ -686,32 +686,47 @@ __global__ __launch_bounds__(WAVES * 64) void mrw_free_kernel(GraphView<OffT> g,
         for (uint32_t i = (uint32_t)lane; i < R; i += 64u) a.state[(uint64_t)s * R + i] = state[i];
 }
 
+// Samples (wavefronts) per workgroup: sixteen, whose outputs then leave in runs of 64 bytes, as long as
+// their roots fit 48 KB of LDS (two workgroups per compute unit and room for a third).  20,000 samples of 100 steps
+// with one, four and sixteen: 75, 60 and 59 us with 100 roots each, 80, 67 and 63 with 256; up to 5,000 samples
+// they are alike.
+int mrw_waves(uint32_t R) { return R <= 256u ? 16 : R <= 1024u ? 4 : 1; }
+
+// Later steps of a launch find rows in LDS that earlier ones left: a second round of 64 steps, and LDS for the rows, no
+// more than the roots alone may take (154 to 256 roots per sample pass that; rows in more LDS have not been timed).
 constexpr size_t kMrwLds = 48 << 10;
 size_t mrw_keep_lds(int waves, uint32_t R) { return (size_t)waves * R * 20; }
+bool mrw_may_keep_rows(int32_t n_steps, uint32_t R) { return n_steps > 64 && mrw_keep_lds(mrw_waves(R), R) <= kMrwLds; }
+
+int64_t offsets_bytes(const Graph& gr) { return gr.V * (gr.off64 ? 8 : 4); }
+
+// ... and is the faster for it where the offsets are what an L2 holds or more, and the second round is half full.  Time
+// without over time with kept rows, 100 roots, 16 to 41,943 samples: 70 steps 0.97 to 1.00 on seven graphs of 0.2 to 33 MB
+// of offsets, 80 steps 0.97 to 1.02, 96 0.98 to 1.05, 100 0.97 to 1.08, 128 1.00 to 1.09 (from 8,192 samples and 4 MB on
+// 96 1.01 to 1.05, 100 1.02 to 1.08); offsets of 0.2 and 1 MB 0.97 to 0.99 at 30 and 100 roots and any number of steps
+// (4 roots 1.00 to 1.02), of 2 MB 0.98 to 1.02.
+bool mrw_keeps_rows(const Graph& gr, int32_t n_steps, uint32_t R) {
+    return mrw_may_keep_rows(n_steps, R) && n_steps >= 96 && offsets_bytes(gr) >= (4 << 20);
+}
 
 template <int WAVES, typename OffT>
 void launch_mrw(const Graph& gr, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
     const dim3 grid(groups), block(WAVES * 64);
-    const size_t lds = (size_t)WAVES * a.R * 12, lds_keep = mrw_keep_lds(WAVES, a.R);  // the first is within kMrwLds
-    const bool keep = a.n_steps > 64u && lds_keep <= kMrwLds, filled = keep && a.filled != nullptr;
+    const size_t lds = (size_t)WAVES * a.R * 12;  // within kMrwLds
+    const bool filled = a.filled != nullptr && mrw_may_keep_rows((int32_t)a.n_steps, a.R);
+    const bool keep = filled || mrw_keeps_rows(gr, (int32_t)a.n_steps, a.R);
     const GraphView<OffT> g = view_of<OffT>(gr);
 #define ND_MRW_LAUNCH(STRIDE)                                                                             \
     do {                                                                                                  \
         auto* kernel = filled ? &mrw_free_kernel<STRIDE, OffT, WAVES, true, true>                         \
                        : keep ? &mrw_free_kernel<STRIDE, OffT, WAVES, true>                               \
                               : &mrw_free_kernel<STRIDE, OffT, WAVES, false>;                             \
-        hipLaunchKernelGGL(kernel, grid, block, keep ? lds_keep : lds, stream, g, a);                     \
+        hipLaunchKernelGGL(kernel, grid, block, keep ? mrw_keep_lds(WAVES, a.R) : lds, stream, g, a);       \
     } while (0)
     if (gr.wq) ND_MRW_LAUNCH(2);
     else ND_MRW_LAUNCH(1);
 #undef ND_MRW_LAUNCH
 }
-
-// Samples (wavefronts) per workgroup: sixteen, whose outputs then leave in runs of 64 bytes, as long as
-// their roots fit 48 KB of LDS (two workgroups per compute unit and room for a third).  20,000 samples of 100 steps
-// with one, four and sixteen: 75, 60 and 59 us with 100 roots each, 80, 67 and 63 with 256; up to 5,000 samples
-// they are alike.
-int mrw_waves(uint32_t R) { return R <= 256u ? 16 : R <= 1024u ? 4 : 1; }
 
 template <typename OffT>
 void launch_few(const Graph& gr, int draw, const FreeArgs& a, uint32_t groups, hipStream_t stream) {
@@ -800,17 +815,20 @@ static int attempt_lanes(int64_t S, const DrawArgs& d) {
     return S <= kFewAttemptWalks && accepted < 0.75 ? kAttemptLanes : 1;
 }
 
-// Later steps of a launch find rows in LDS that earlier ones left.
-static bool mrw_keeps_rows(int32_t num_steps, uint32_t R) {
-    return num_steps > 64 && mrw_keep_lds(mrw_waves(R), R) <= kMrwLds;
-}
-
-// Whether rows are looked up in the bits first: where a quarter of them is empty, the offsets are more than an L2 holds and
-// the wavefronts are more than the chip holds.  41,943 samples of 100 steps on R-MAT 22 (47 % empty) 108 us without and 96
-// like this, 300 samples 7.5 and 7.7; on R-MAT 18 (1 MB of offsets) 132.2 and 133.8; on 3 M vertices of which few are
-// alone 97 and 103.
+// Whether rows are looked up in the bits first: each empty row then costs no fetch, each other one a look more.  The more
+// roots a sample has the more of its looks go past the kept rows, and the fewer empty rows it takes.  Time without
+// over time with bits, 100 steps, 8, 16 and 32 MB of offsets, 8,192, 12,000 and 41,943 samples:
+//   empty rows   30 %          35 %          40 %          45 %          50 %          70 %
+//   16 roots     0.98 to 1.01  0.99 to 1.01  0.99 to 1.01  0.99 to 1.02  0.99 to 1.02  1.00 to 1.04
+//   30 roots     0.98 to 1.00  0.99 to 1.01  0.99 to 1.02  1.00 to 1.02  1.00 to 1.03  1.04 to 1.10
+//   60 roots     0.98 to 1.02  0.99 to 1.03  1.00 to 1.04  1.02 to 1.07  1.04 to 1.08  1.09 to 1.16
+//   100 roots    0.99 to 1.03  1.00 to 1.05  1.01 to 1.07  1.03 to 1.08  1.05 to 1.10  1.12 to 1.21
+//   150 roots    0.99 to 1.05  1.01 to 1.07  1.02 to 1.09  1.04 to 1.12  1.06 to 1.13  1.15 to 1.25
+// R-MAT 22 (47 %), 100 roots: 8,192 samples 1.13, 41,943 1.12 (70 steps, against none kept, 1.10 and 1.08), 4,000 1.03, 1,000
+// 0.96.  Half of the rows empty, 4 MB 1.02 to 1.10, 2 MB 0.98 to 1.09.
 bool mrw_reads_filled(const Graph& gr, int64_t S, int32_t num_steps, uint32_t R) {
-    return 4 * gr.empty_rows >= gr.V && gr.V * (gr.off64 ? 8 : 4) >= (8 << 20) && S >= 8192 && mrw_keeps_rows(num_steps, R);
+    return R >= 30u && mrw_may_keep_rows(num_steps, R) && S >= 8192 && offsets_bytes(gr) >= (8 << 20) &&
+           700 * gr.empty_rows >= (int64_t)(345u - (R < 150u ? R : 150u)) * gr.V;
 }
 
 // Walks per workgroup; lanes: attempts at once of a node2vec call, 0 for the others.

@@ -17,7 +17,8 @@
  * allocations of the queries fail); query_roots=N (sizes are asked for N roots; the call keeps its own); left=B (of the device's memory, B bytes are free when the first query
  * is made); device=D (current during the queries; the graph lies on device 0, and memory taken on another
  * is counted as elsewhere and ends the program with status 4); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
- * and prints "unused STATS_RC STATUS_RC").  A call that does not return within 20 seconds ends the program with SIGALRM. */
+ * and prints "unused STATS_RC STATUS_RC"); empty=N (so many of the rows have no entries, as the kernel that checks the
+ * offsets would have found).  A call that does not return within 20 seconds ends the program with SIGALRM. */
 #define _GNU_SOURCE
 #include <stdio.h>
 #include <stdlib.h>
@@ -33,6 +34,7 @@ typedef struct { void* p; size_t n; } Block;
 static Block blocks[256];
 static int n_blocks, fail_malloc, trace, device, elsewhere;
 static size_t live_bytes, free_limit;
+static uint64_t empty_rows;
 static struct { const void* f; const char* name; } kernels[1024];
 static int n_kernels;
 
@@ -68,6 +70,7 @@ int hipMemGetInfo(size_t* avail, size_t* total) {
 int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* stream) {
     (void)stream;
     if (kind == 2) memcpy(d, s, n);
+    if (kind == 2 && n == 24) ((uint64_t*)d)[2] = empty_rows;  /* flags, the longest row, the empty rows */
     return 0;
 }
 int hipMemsetAsync(void* d, int v, size_t n, void* s) { (void)d; (void)v; (void)n; (void)s; return 0; }
@@ -140,6 +143,7 @@ int main(int argc, char** argv) {
         else if (!strcmp(n, "queries")) queries = atoi(v);
         else if (!strcmp(n, "query_roots")) query_roots = atoll(v);
         else if (!strcmp(n, "left")) left = atoll(v);
+        else if (!strcmp(n, "empty")) empty_rows = (uint64_t)atoll(v);
         else if (!strcmp(n, "device")) query_device = atoi(v);
         else return 2;
     }

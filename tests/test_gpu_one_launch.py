@@ -736,6 +736,29 @@ def test_multi_dimensional_walk_where_rows_are_empty(V, int64_offsets, S, R, wei
     assert_steps_equal(got, list(want), f"V={V}")
 
 
+@pytest.mark.parametrize("V,int64_offsets,R,steps", [((1 << 20) + 37, True, 30, 100), (1 << 21, False, 100, 70),
+                                                     (1 << 21, False, 100, 200)])
+def test_multi_dimensional_walk_of_many_roots_where_rows_are_empty(V, int64_offsets, R, steps):
+    """As many roots as it takes for the bits of empty rows to be read (the routes are pinned on the host): one launch whose
+    second round is short, and two of which the second has both rounds."""
+    rng = np.random.default_rng(V + R)
+    deg = rng.integers(1, 4, V)
+    deg[rng.random(V) < 0.5] = 0
+    deg[:3], deg[-2:] = (0, 1, 0), (2, 0)
+    off = np.concatenate([[0], np.cumsum(deg)])
+    start, gap = rng.integers(0, V - 8, V), rng.integers(1, 4, V)
+    row = np.repeat(np.arange(V), deg)
+    col = (start[row] + gap[row] * (np.arange(off[-1]) - off[:-1][row])).astype(np.int32)
+    off = off.astype(np.int64 if int64_offsets else np.int32)
+    dg, og = B.nd_graph_create(off, col), oracle.OracleGraph(off, col)
+    roots = rng.integers(0, V, 8192 * R, dtype=np.int32)
+    roots[::13] = -1
+    roots[1::17], roots[2::17] = V - 1, V - 2
+    want = oracle.multirw(og, roots, R, steps, seed=6)
+    got, _ = gpu_sample(dg, B.ND_MULTIRW, roots, 6, num_steps=steps, roots_per_sample=R)
+    assert_steps_equal(got, list(want), f"V={V}")
+
+
 @pytest.mark.parametrize("V", [1, 63, 64, 65, 257])
 def test_offsets_of_few_rows(V):
     """Errors in the offsets, and none, where rows fill a wavefront or a workgroup and where they do not."""

@@ -1,6 +1,7 @@
 """What calls do on the host - argument checks, plans, sizes, the kernels they launch - without a GPU:
 the library runs against stand-ins for the HIP functions (host_calls.c) and no kernel executes."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -152,3 +153,37 @@ def test_khop_outputs_that_leave_one_by_one_pass_the_caches_of_small_graphs_only
     of [7, 13] on R-MAT 22: 1,581 us one by one past the caches, 1,520 through them)."""
     got = program(B.ND_KHOP, samples, V=1_000_000, E=E, fanout=[fanout], weighted=weighted)
     assert got["static"] == [0] and f"khop_fused_kernelILi{1 + weighted}E{kernel}" in got["launches"][0]
+
+
+def _mrw_kernels(got):
+    """Of each launch of a multi-dimensional walk, whether rows stay in LDS and whether bits are looked up."""
+    found = [re.search(r"mrw_free_kernelILi\dElLi\d+ELb(\d)ELb(\d)E", k) for k in got["launches"]]
+    return [m.groups() for m in found if m]
+
+
+@pytest.mark.parametrize("V,roots,steps,kept", [
+    (1 << 19, 100, 96, [1]), ((1 << 19) - 1, 100, 96, [0]), (1 << 19, 100, 95, [0]), (1 << 19, 4, 100, [1]),
+    (1 << 22, 100, 64, [0]), (1 << 22, 100, 70, [0]), (57_000, 100, 128, [0]), (1 << 22, 100, 223, [1, 0]),
+    (1 << 22, 100, 224, [1, 1]), (1 << 19, 153, 100, [1]), (1 << 19, 154, 100, [0]), (1 << 19, 614, 100, [1]),
+    (1 << 19, 615, 100, [0])])
+@pytest.mark.parametrize("samples", [16, 8192])
+def test_rows_of_moved_roots_stay_where_they_are_looked_at_again(program, V, roots, steps, kept, samples):
+    """From half of a second round of 64 steps on and from 4 MB of offsets (100 roots, 70 steps 8.63 us where rows stay
+    and 8.41 without, 1 MB of offsets 9.26 and 9.06), as far as they fit 48 KB."""
+    got = program(B.ND_MULTIRW, samples * roots, V=V, num_steps=steps, roots_per_sample=roots)
+    assert got["static"] == [0] and _mrw_kernels(got) == [(str(k), "0") for k in kept]
+
+
+@pytest.mark.parametrize("V,empty,roots,samples,steps,bits", [
+    (1 << 20, 0.351, 100, 8192, 100, [1]), (1 << 20, 0.349, 100, 8192, 100, [0]), ((1 << 20) - 1, 0.5, 100, 8192, 100, [0]),
+    (1 << 20, 0.5, 100, 8191, 100, [0]), (1 << 20, 0.451, 30, 8192, 100, [1]), (1 << 20, 0.449, 30, 8192, 100, [0]),
+    (1 << 20, 0.9, 29, 8192, 100, [0]), (1 << 20, 0.41, 60, 8192, 70, [1]), (1 << 20, 0.9, 60, 8192, 64, [0]),
+    (1 << 20, 0.5, 100, 8192, 192, [1, 0]), (1 << 20, 0.28, 614, 8192, 100, [1]), (1 << 20, 0.27, 614, 8192, 100, [0]),
+    (1 << 20, 0.9, 154, 8192, 100, [0])])
+def test_bits_tell_empty_rows_where_enough_of_them_are(program, V, empty, roots, samples, steps, bits):
+    """The fewer roots a sample has the more rows have to be empty, from 8,192 samples and 8 MB of offsets on (30 roots,
+    41,943 samples, a quarter empty: 3 % slower with bits).  They are made when sizes are asked for and are a bit per vertex."""
+    got = program(B.ND_MULTIRW, samples * roots, V=V, empty=int(empty * V), num_steps=steps, roots_per_sample=roots)
+    assert [int(b) for _, b in _mrw_kernels(got)] == bits
+    assert all(k == "1" for k, b in _mrw_kernels(got) if b == "1")
+    assert got["allocated"] == [(V + 1) * 8 + 4000 * 4 + 4000 * 16 + ((V + 63) // 64 * 8 if any(bits) else 0)]
