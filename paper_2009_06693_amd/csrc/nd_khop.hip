@@ -803,11 +803,23 @@ bool khop_reads_packed(const Graph& gr, const int32_t* fanout, int32_t k, int64_
 // on R-MAT 22 (275 MB) with 1,520 and 1,581 for [7,13], 2,637 and 2,719 for [5,5], 2,703 and 2,727 for [15,10,5], nor on 2 M
 // vertices (128 MB): 1,985 and 2,022, 3,883 and 3,983, 3,122 and 3,141.
 //
-// In pairs and after a hop that reads links they do so from 6 M draws on: of eight fanouts on twelve graphs with 6 to 64 M draws,
-// with and without packed columns, none slower, up to 13 % faster ([25,10] of 131,072 vertices of R-MAT 22 112 us and 97).
+// In pairs and after a hop that reads links, and where neighbours are unique, they do so from 24 M draws on (96 MB) where the
+// last-level cache, of 256 MB, does not hold them together with the entries.  Who reads them next has to be counted in:
+// the call alone is faster past the caches from 6 M draws on (up to 6 %), but outputs that the last-level cache would
+// have held then come from memory.  Time through the caches over time past them, the call alone and with a copy of
+// the last hop, a maximum per sample, the gathered records and a look-up per vertex behind it:
+//   57 K vertices, 2 M entries, [25,10]: 48 MB 1.02, with those 0.95, 0.97, 0.86, 1.00; 128 MB 1.02, 1.00, 0.97, 0.93, 1.00;
+//     200 MB 1.03, 1.07, 0.97, 1.03, 0.94; 256 MB 1.05, 1.03, 1.04, 1.04, 1.01
+//   R-MAT 20, 30 M entries, 48 MB 1.02, 0.94, 0.99, 0.90, 0.99; 128 MB 1.03, 1.06, 0.99, 1.01, 0.98; 200 MB 1.02, 1.02, 1.02,
+//     1.02, 0.99
+//   R-MAT 22, 69 M entries, 48 MB 1.02, 0.94, 0.96, 0.89, 1.00; 80 MB 1.03, 1.05, 0.98, 0.94, 0.99; 100 MB 1.08, 1.06, 1.00, 1.00,
+//     0.99; 128 MB 1.14, 1.04, 1.02, 1.04, 1.00; 256 MB 1.19, 1.05, 1.04, 1.05, 1.04
+// and [10,10], [15,10,4] and unique neighbours alike ([25,10], 57 K vertices, 80 MB 1.00, 0.97, 0.99, 0.92, 0.99; R-MAT 22, 48 MB
+// 1.03, 0.97, 0.99, 0.91, 1.00, 128 MB 1.04, 1.02, 0.99, 1.00, 0.99).
 constexpr int64_t kPastCaches = 64 << 20;
-constexpr int64_t kPastCachesPairs = 6000000;
+constexpr int64_t kPastCachesPairs = 24000000;
 constexpr int64_t kPastCachesOneByOne = 8 << 20;  // entries: 32 MB
+bool last_level_is_passed(const Graph& gr, int64_t draws) { return draws >= kPastCachesPairs && draws + gr.E >= (64 << 20); }
 
 int64_t khop_fused_groups(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
     int64_t W[ND_MAX_FANOUT_STEPS];
@@ -849,8 +861,9 @@ int khop_fused(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32_
     mark_phase(ND_PHASE_SAMPLE_SUB, stream);
     const dim3 grid((unsigned)f.groups), block(kFusedThreads);
     const bool pairs = khop_in_pairs(a.m[k - 1], step_out[k - 1]);
-    const bool past = pairs ? S * W[k - 1] >= (k > 1 ? kPastCachesPairs : kPastCaches)
-                            : S * W[k - 1] >= kPastCaches && gr.E <= kPastCachesOneByOne;
+    const int64_t draws = S * W[k - 1];
+    const bool past = pairs ? draws >= kPastCaches || (k > 1 && last_level_is_passed(gr, draws))
+                            : draws >= kPastCaches && gr.E <= kPastCachesOneByOne;
 #define ND_FUSED_LAUNCH_R(STRIDE, R, PAST, OFFT)                                                                  \
     do {                                                                                                          \
         auto* kernel = a.packed.bytes ? &khop_fused_kernel<STRIDE, R, PAST, true, OFFT>                           \
@@ -936,11 +949,6 @@ UniqueShape unique_shape(const Graph& gr, const int32_t* fanout, int32_t k, int6
     return u;
 }
 constexpr size_t kUniqueLdsMost = 128 << 10;
-// Slots of the last hop from which the outputs of groups inside a wavefront leave past the caches, which then hold more of
-// the graph: every vertex of R-MAT 22, [25,10], 4,460 us and 4,340, one draw per slot 3,550 and 3,390, [25] 1,152 and
-// 1,127, 1 M vertices of [60] 400 and 380.  From 8,192 samples of [25,10] on never slower, over eleven fanouts on three
-// graphs; 1,024 samples up to 2 % slower.
-constexpr int64_t kUniquePast = 2 << 20;
 }  // namespace
 
 // At most ND_MAX_UNIQUE_SLOTS slots per sample and hop (the call's plan has checked).
@@ -980,7 +988,9 @@ int khop_unique(const Graph& gr, const DrawArgs& d, const int32_t* fanout, int32
     a.o_flags = o_flags;
     a.o_parts = o_parts;
     mark_phase(ND_PHASE_UNIQUE, stream);
-    const bool past = S * W[k - 1] >= kUniquePast;
+    // outputs of groups inside a wavefront: every vertex of R-MAT 22, [25,10], 4,460 us and 4,340, one draw per slot 3,550 and 3,390,
+    // [25] 1,152 and 1,127, 1 M vertices of [60] 400 and 380
+    const bool past = last_level_is_passed(gr, S * W[k - 1]);
 #define ND_UNIQUE_ONE(STRIDE, OFFT, THREADS, PER)                                                                  \
     do {                                                                                                           \
         auto* kernel = past ? &khop_unique_kernel<STRIDE, OFFT, THREADS, PER, true> : &khop_unique_kernel<STRIDE, OFFT, THREADS, PER>; \

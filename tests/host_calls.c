@@ -18,7 +18,8 @@
  * is made); device=D (current during the queries; the graph lies on device 0, and memory taken on another
  * is counted as elsewhere and ends the program with status 4); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
  * and prints "unused STATS_RC STATUS_RC"); empty=N (so many of the rows have no entries, as the kernel that checks the
- * offsets would have found).  A call that does not return within 20 seconds ends the program with SIGALRM. */
+ * offsets would have found); workspace=1 (the call is made through nd_sample with the scratch it asks for, and "call RC"
+ * comes in the place of "static RC").  A call that does not return within 20 seconds ends the program with SIGALRM. */
 #define _GNU_SOURCE
 #include <stdio.h>
 #include <stdlib.h>
@@ -121,7 +122,7 @@ int main(int argc, char** argv) {
     free_limit = (size_t)atoll(argv[4]);
     nd_params p;
     nd_params_init(&p);
-    int fail = 0, unused = -1, queries = 1, query_device = 0;
+    int fail = 0, unused = -1, queries = 1, query_device = 0, workspace = 0;
     long long left = -1, query_roots = roots;
     for (int i = 7; i < argc; ++i) {
         char* eq = strchr(argv[i], '=');
@@ -144,6 +145,7 @@ int main(int argc, char** argv) {
         else if (!strcmp(n, "query_roots")) query_roots = atoll(v);
         else if (!strcmp(n, "left")) left = atoll(v);
         else if (!strcmp(n, "empty")) empty_rows = (uint64_t)atoll(v);
+        else if (!strcmp(n, "workspace")) workspace = atoi(v);
         else if (!strcmp(n, "device")) query_device = atoi(v);
         else return 2;
     }
@@ -166,7 +168,8 @@ int main(int argc, char** argv) {
     static int32_t* out[ND_MAX_WALK_STEPS];
     for (int i = 0; i < ND_MAX_WALK_STEPS; ++i) out[i] = any;
     trace = 1;
-    printf("static %d\n", nd_sample_static(g, app, &p, any, roots, 1, out, any, NULL));
+    if (workspace) printf("call %d\n", nd_sample(g, app, &p, any, roots, 1, out, reserve(ws), ws, NULL));
+    else printf("static %d\n", nd_sample_static(g, app, &p, any, roots, 1, out, any, NULL));
     trace = 0;
     if (unused >= 0) {
         const size_t n = 1 << 20;

@@ -673,13 +673,19 @@ def test_unique_neighbours_whose_vertices_share_one_bucket(fanout):
     assert_steps_equal(got, want, f"{fanout}")
 
 
-@pytest.mark.parametrize("fanout,draws,rounds", [([3, 6], 6_000_000, 0), ([9, 4], 6_000_000, 0), ([32], 2 << 20, 3),
-                                                 ([20, 3], 2 << 20, 3), ([11, 11], 2 << 20, 3), ([25, 10], 2 << 20, 3)])
-def test_first_calls_whose_outputs_leave_past_the_caches(graph, fanout, draws, rounds):
-    """Pairs of draws from 6 M on, unique neighbours (half a wavefront and whole ones) from 2 M slots on: against halves."""
-    g, dg, _ = graph
-    S = -(-draws // int(np.prod(fanout)))
-    r = torch.from_numpy(_roots(g.V, S, 3)).cuda()
+@pytest.mark.parametrize("fanout,rounds", [([3, 6], 0), ([9, 4], 0), ([32], 3), ([20, 3], 3), ([11, 11], 3), ([25, 10], 3)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_first_calls_whose_outputs_leave_past_the_caches(fanout, rounds, wide):
+    """24 M draws in pairs, and as many unique neighbours (half a wavefront and whole ones), over 44 M entries, with which they
+    are more than the last-level cache holds: against halves, which are below the line."""
+    V, degree = 2_000_000, 22
+    v = torch.arange(V, device="cuda:0")
+    col = (v[:, None] + 1 + 977 * torch.arange(degree, device="cuda:0")) % V
+    col = col.sort(1).values.view(-1).to(torch.int32)
+    off = torch.arange(V + 1, device="cuda:0") * degree
+    dg = B.nd_graph_create(off if wide else off.to(torch.int32), col)
+    S = -(-24_000_000 // int(np.prod(fanout)))
+    r = torch.from_numpy(_roots(V, S, 3)).cuda()
     for whole, halves in _whole_and_halves(dg, B.ND_KHOP, S, r, num_steps=len(fanout), fanout=fanout, unique_rounds=rounds):
         assert torch.equal(whole, torch.cat(halves))
 

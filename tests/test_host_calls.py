@@ -187,3 +187,22 @@ def test_bits_tell_empty_rows_where_enough_of_them_are(program, V, empty, roots,
     assert [int(b) for _, b in _mrw_kernels(got)] == bits
     assert all(k == "1" for k, b in _mrw_kernels(got) if b == "1")
     assert got["allocated"] == [(V + 1) * 8 + 4000 * 4 + 4000 * 16 + ((V + 63) // 64 * 8 if any(bits) else 0)]
+
+
+@pytest.mark.parametrize("fanout,rounds", [([25, 10], 0), ([15, 10, 4], 0), ([25, 10], 3), ([30], 3)])
+@pytest.mark.parametrize("draws,E,past", [(24_000_000, 44_000_000, True), (24_000_000, 43_000_000, False),
+                                          (23_990_000, 120_000_000, False), (32_000_000, 36_000_000, True),
+                                          (32_000_000, 35_000_000, False), (67_500_000, 4000, True), (66_000_000, 4000, False)])
+def test_outputs_that_the_last_level_cache_holds_stay_in_it(program, fanout, rounds, draws, E, past):
+    """A copy of 48 MB of outputs behind the call that wrote them took 6 % longer, call included, and their records 14 %, when
+    they had gone to memory (57 K vertices, [25,10]).  They pass the caches from 24 M draws on, if 256 MB do not hold
+    them and the entries."""
+    per = 1
+    for f in fanout:
+        per *= f
+    got = program(B.ND_KHOP, -(-draws // per), V=4_000_000, E=E, fanout=fanout, unique_rounds=rounds,
+                  workspace=1)
+    assert got["call"] == [0]
+    name = [k for k in got["launches"] if "khop" in k][0]
+    flag = re.search(r"khop_unique_kernelILi\dElLi\d+ELi\dELb(\d)E" if rounds else r"khop_fused_kernelILi\dELi2ELb(\d)E", name).group(1)
+    assert flag == str(int(past)), got["launches"]
