@@ -226,11 +226,17 @@ int nd_graph_info(const nd_graph* g, int64_t* V, int64_t* E, int* has_weights,
  * number on graphs of up to 58 M entries: more walks on larger graphs are faster
  * without it, and do not use it where it is there.  For layer sampling with
  * use_weights it is the sum of every row's weights (8 bytes per vertex).  For k-hop
- * calls of 6 M draws and more (200 K on dense graphs) it is the columns in as many
- * bits as a vertex takes, up to 25.  For multi-dimensional walks of 8,192 samples
- * and more on large graphs with many empty rows it is a bit per vertex.  A caller
- * who wants the memory more than the speed asks for the weighted calls' sizes with
- * use_weights = 0, which are the same.  No other call of this function touches
+ * with replacement it is the columns in as many bits as a vertex takes, where that is
+ * 25 at most (bits * E / 8 bytes, below 4 GB): for calls of 6 M draws of the last hop
+ * and more on graphs whose mean degree is at least 6/5 of the last fanout, and of
+ * 200 K and more where it is at least 128.  For multi-dimensional walks of more than
+ * 64 steps, 30 and more roots per sample and 8,192 and more samples, on graphs with
+ * 8 MB of offsets and more of which (345 - roots) / 700 and more of the rows are empty
+ * (from 150 roots on 0.28), it is a bit per vertex.  All this stays with the graph
+ * until it is destroyed.  A caller who wants the memory more than the speed asks for the
+ * weighted calls' sizes with use_weights = 0 and for those of k-hop with
+ * sched_window = -1, which are the same; node2vec's tables and the bits are not
+ * declined that way.  No other call of this function touches
  * the device.
  */
 int nd_sample_query(const nd_graph* g, int app, const nd_params* params, int64_t num_roots,

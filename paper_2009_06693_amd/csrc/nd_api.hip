@@ -47,6 +47,7 @@ struct Plan {
     int window = 0;            // walks grouped per window of this many samples (0: GPU-wide grouping)
     uint32_t heavy_min = 64;   // pairs of one transit in a window from which the workgroup class serves it
     bool free_walk = false;    // walks over the graph's links, one lane per walk (nd_walk_free.hip)
+    bool may_fuse = false;     // k-hop: the call, or the same one with sched_window = 0, takes one launch
     bool fused = false;        // k-hop: all hops in one launch (nd_khop.hip)
     bool first_free = false;   // k-hop that groups: its first hop does not
     bool packed = false;       // k-hop: draws read the packed columns, where they are there
@@ -210,7 +211,8 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     }
     pl->max_slots = 0;
     pl->max_out = 0;
-    const bool khop_default = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden && p->sched_window == 0;
+    const bool khop_tp = app == ND_KHOP && p->mode == ND_MODE_TRANSIT_PARALLEL && !overridden;
+    const bool khop_default = khop_tp && p->sched_window == 0;
     int64_t planned = -1;  // slots that the last sort plan was made for
     double guard = 1.0;
     for (int i = 0; i < pl->k; ++i) {
@@ -241,9 +243,10 @@ int check_params(const Graph& g, int app, const nd_params* p, int64_t num_roots,
     pl->layer_fused = app == ND_LAYER && g.links != nullptr;
     // a call without samples draws nothing, and its fanouts have no bound that a shape could be made from
     pl->first_free = khop_default && p->unique_rounds == 0 && g.links && pl->S <= g.V;
-    pl->fused = khop_default && pl->S > 0 &&
-                (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
-                                      : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
+    pl->may_fuse = khop_tp && pl->S > 0 &&
+                   (p->unique_rounds > 0 ? khop_unique_fits(g, p->fanout, p->num_steps)
+                                         : khop_fused_fits(g, p->fanout, p->num_steps, pl->S));
+    pl->fused = khop_default && pl->may_fuse;
     pl->packed = khop_default && p->unique_rounds == 0 && khop_reads_packed(g, p->fanout, p->num_steps, pl->S);
     return ND_OK;
 }
@@ -290,7 +293,7 @@ void layout(Plan* pl, const Graph& g, const nd_params* p) {
         pl->bit_words = (V + 31) / 32;
         pl->o_bits = o; o = align_up(o + (size_t)pl->bit_words * 4);
     }
-    if (pl->fused) {  // inside what the call may use when it groups
+    if (pl->may_fuse) {  // inside what the call uses when it groups, and with either window the same size in all
         const size_t groups = (size_t)(p->unique_rounds > 0 ? khop_unique_groups(g, p->fanout, pl->k, pl->S)
                                                             : khop_fused_groups(g, p->fanout, pl->k, pl->S));
         size_t f = pl->o_ctl;

@@ -19,7 +19,7 @@
  * is counted as elsewhere and ends the program with status 4); unused=B (asks for the statistics and the status of a workspace of bytes B that no call has used,
  * and prints "unused STATS_RC STATUS_RC"); empty=N (so many of the rows have no entries, as the kernel that checks the
  * offsets would have found); workspace=1 (the call is made through nd_sample with the scratch it asks for, and "call RC"
- * comes in the place of "static RC").  A call that does not return within 20 seconds ends the program with SIGALRM. */
+ * comes in the place of "static RC"); query_window=N (sizes are asked for with that sched_window; the call keeps its own).  A call that does not return within 20 seconds ends the program with SIGALRM. */
 #define _GNU_SOURCE
 #include <stdio.h>
 #include <stdlib.h>
@@ -122,7 +122,7 @@ int main(int argc, char** argv) {
     free_limit = (size_t)atoll(argv[4]);
     nd_params p;
     nd_params_init(&p);
-    int fail = 0, unused = -1, queries = 1, query_device = 0, workspace = 0;
+    int fail = 0, unused = -1, queries = 1, query_device = 0, workspace = 0, query_window = 0, own_window = 1;
     long long left = -1, query_roots = roots;
     for (int i = 7; i < argc; ++i) {
         char* eq = strchr(argv[i], '=');
@@ -145,6 +145,7 @@ int main(int argc, char** argv) {
         else if (!strcmp(n, "query_roots")) query_roots = atoll(v);
         else if (!strcmp(n, "left")) left = atoll(v);
         else if (!strcmp(n, "empty")) empty_rows = (uint64_t)atoll(v);
+        else if (!strcmp(n, "query_window")) { query_window = atoi(v); own_window = 0; }
         else if (!strcmp(n, "workspace")) workspace = atoi(v);
         else if (!strcmp(n, "device")) query_device = atoi(v);
         else return 2;
@@ -160,7 +161,9 @@ int main(int argc, char** argv) {
     fail_malloc = fail;
     if (left >= 0) free_limit = live_bytes + (size_t)left;
     device = query_device;
-    for (int i = 0; i < queries; ++i) rc = nd_sample_query(g, app, &p, query_roots, &steps, lens, &ws);
+    nd_params asked = p;
+    if (!own_window) asked.sched_window = query_window;
+    for (int i = 0; i < queries; ++i) rc = nd_sample_query(g, app, &asked, query_roots, &steps, lens, &ws);
     fail_malloc = 0;
     printf("query %d %zu %d\n", rc, ws, steps);
     printf("device %d\n", device);

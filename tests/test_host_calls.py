@@ -206,3 +206,24 @@ def test_outputs_that_the_last_level_cache_holds_stay_in_it(program, fanout, rou
     name = [k for k in got["launches"] if "khop" in k][0]
     flag = re.search(r"khop_unique_kernelILi\dElLi\d+ELi\dELb(\d)E" if rounds else r"khop_fused_kernelILi\dELi2ELb(\d)E", name).group(1)
     assert flag == str(int(past)), got["launches"]
+
+
+def _packed(V, E):
+    """Bytes of the packed columns."""
+    return -(-E // 32) * max(1, (V - 1).bit_length()) * 4 + 4
+
+
+def _graph_bytes(V, E):
+    return (V + 1) * 8 + E * 4 + E * 16
+
+
+@pytest.mark.parametrize("fanout,samples,V,E", [([25, 10], 30_000, 100_000, 2_000_000), ([1 << 20], 6, 1 << 20, 160 << 20),
+                                                ([15, 10, 5], 9000, 57_000, 1_600_000), ([2, 10], 10_000, 1000, 128_000),
+                                                ([4000], 50, 1000, 128_000), ([10, 10], 1_000_000, 1_000_000, 120_000_000)])
+def test_sizes_of_khop_asked_for_with_the_groups_of_all_samples_build_nothing(program, fanout, samples, V, E):
+    """A way to decline the packed columns: the sizes are the same, and the call reads the columns as they are."""
+    same = program(B.ND_KHOP, samples, V=V, E=E, fanout=fanout, workspace=1)
+    got = program(B.ND_KHOP, samples, V=V, E=E, fanout=fanout, workspace=1, query_window=-1)
+    assert got["query"] == same["query"] and got["call"] == same["call"] == [0]
+    assert got["allocated"] == [_graph_bytes(V, E)] and same["allocated"] == [_graph_bytes(V, E) + _packed(V, E)]
+    assert len(got["launches"]) == len(same["launches"])
