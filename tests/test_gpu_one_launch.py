@@ -628,6 +628,27 @@ def test_khop_over_packed_columns(V, weighted, int64_offsets):
         assert_steps_equal(got, want, f"khop {fanout} V={V}")
 
 
+@pytest.mark.parametrize("int64_offsets", [False, True])
+@pytest.mark.parametrize("V", [2, 3, 4, 5, 9, 17, 33, 64])
+def test_khop_over_packed_columns_of_few_bits(V, int64_offsets):
+    """1 to 6 bits, of which up to 32 entries lie in a word: every row but one holds every vertex, 6 M draws, as many per parent
+    as such rows allow; against the sample-parallel kernel, which reads the columns as they are."""
+    rows = [np.arange(V)] * (V - 1) + [np.array([V - 1])]
+    off = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64 if int64_offsets else np.int32)
+    dg = B.nd_graph_create(off, np.concatenate(rows).astype(np.int32))
+    last = max(1, 5 * int(off[-1]) // (6 * V))
+    r = torch.from_numpy(_roots(V, -(-6_000_000 // (3 * last)), 5)).cuda()
+    outs = []
+    for mode in (B.ND_MODE_TRANSIT_PARALLEL, B.ND_MODE_SAMPLE_PARALLEL):
+        s = B.Sampler(dg, B.ND_KHOP, B.nd_params_init(num_steps=2, fanout=[3, last], mode=mode), r.numel())
+        outs.append([o.clone() for o in s.run(r, 14)])
+        torch.cuda.synchronize()
+        s.status()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    assert int(outs[0][1].max()) == V - 1 and int(outs[0][1][outs[0][1] >= 0].min()) == 0
+
+
 @pytest.mark.parametrize("V", [1 << 25, (1 << 25) + 1])
 def test_khop_at_the_widest_packed_columns(V):
     """25 bits, the most that one load of four bytes holds at every bit of a byte, and a vertex more, where the columns

@@ -217,6 +217,38 @@ def _graph_bytes(V, E):
     return (V + 1) * 8 + E * 4 + E * 16
 
 
+@pytest.mark.parametrize("fanout,samples,V,E,packed", [
+    ([6, 10], 100_000, 1000, 12_000, True), ([6, 10], 99_999, 1000, 12_000, False),      # 6 M draws
+    ([6, 10], 100_000, 1000, 11_999, False), ([6, 9], 111_112, 1000, 10_800, True),      # 6/5 of the last fanout
+    ([6, 9], 111_112, 1000, 10_799, False), ([2, 10], 10_000, 1000, 128_000, True),
+    ([2, 10], 9_999, 1000, 128_000, False), ([2, 10], 10_000, 1000, 127_999, False),     # 200 K draws, degree 128
+    ([200], 1000, 1000, 128_000, True), ([1, 1], 6_000_000, 1 << 25, 3 << 24, True),     # 25 bits
+    ([1, 1], 6_000_000, (1 << 25) + 1, (3 << 24) + 2, False)])
+def test_khop_reads_packed_columns_where_draws_are_many_and_rows_long(program, fanout, samples, V, E, packed):
+    """Both sides of each line of the rule, by the kernels that are launched and by the memory that the query takes."""
+    got = program(B.ND_KHOP, samples, V=V, E=E, fanout=fanout, workspace=1)
+    assert got["call"] == [0] and got["allocated"] == [_graph_bytes(V, E) + (_packed(V, E) if packed else 0)]
+    reads = [re.search(r"khop_fused_kernelILi1ELi\dELb\dELb(\d)E", k) for k in got["launches"]]
+    assert [m.group(1) for m in reads if m] == [str(int(packed))], got["launches"]
+
+
+def test_grouped_khop_reads_packed_columns_too(program):
+    """The first hop, which is not grouped, and the sub-wavefront class of the second."""
+    V, E = 1_000_000, 120_000_000
+    got = program(B.ND_KHOP, V, V=V, E=E, fanout=[10, 10], workspace=1)
+    assert got["call"] == [0] and got["allocated"] == [_graph_bytes(V, E) + _packed(V, E)]
+    first = [k for k in got["launches"] if "khop_first" in k]
+    second = [k for k in got["launches"] if "sample_tp_kernel" in k]
+    assert len(first) == 1 and "ILb1E" in first[0] and len(second) == 1 and "ILi0ELb1E" in second[0]
+
+
+def test_packed_columns_are_taken_from_a_quarter_of_the_free_memory(program):
+    V, E = 1000, 128_000
+    for left, packed in ((4 * _packed(V, E), _packed(V, E)), (4 * _packed(V, E) - 1, 0)):
+        got = program(B.ND_KHOP, 10_000, V=V, E=E, fanout=[2, 10], left=left, workspace=1)
+        assert got["call"] == [0] and got["allocated"] == [_graph_bytes(V, E) + packed]
+
+
 @pytest.mark.parametrize("fanout,samples,V,E", [([25, 10], 30_000, 100_000, 2_000_000), ([1 << 20], 6, 1 << 20, 160 << 20),
                                                 ([15, 10, 5], 9000, 57_000, 1_600_000), ([2, 10], 10_000, 1000, 128_000),
                                                 ([4000], 50, 1000, 128_000), ([10, 10], 1_000_000, 1_000_000, 120_000_000)])
