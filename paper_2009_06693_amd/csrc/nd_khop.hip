@@ -119,13 +119,14 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
             const uint32_t end = begin + share < pieces ? begin + share : pieces;
             for (uint32_t d0 = begin + tid; d0 < end; d0 += kInFlight * T) {
                 uint2 row[kInFlight];
-                uint32_t e[kInFlight][R], word[kInFlight][R];
+                uint32_t e[kInFlight][R];
+                int32_t v[kInFlight][R];
 #pragma unroll
                 for (uint32_t u = 0; u < kInFlight; ++u) {
                     const uint32_t d = (d0 + u * T) * R;
                     row[u] = d0 + u * T < end ? rows[fastdiv(d, a.div_m[hop])] : make_uint2(0u, 0u);
-#pragma unroll
-                    for (uint32_t i = 0; i < R; ++i) e[u][i] = 0u;
+                    if (PACKED)
+                        for (uint32_t i = 0; i < R; ++i) e[u][i] = 0u;
                     // the draws of a sample without live parents are neighbours: whole wavefronts skip this
                     if (row[u].y > 0u) {
                         const uint32_t s = fastdiv(d, a.div_w[hop]);
@@ -140,18 +141,15 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
                 for (uint32_t u = 0; u < kInFlight; ++u)
 #pragma unroll
                     for (uint32_t i = 0; i < R; ++i) {
-                        word[u][i] = (uint32_t)ND_NULL_VERTEX;
-                        if (row[u].y > 0u) word[u][i] = PACKED ? packed_word(a.packed, e[u][i], &e[u][i]) : (uint32_t)g.col[e[u][i]];
+                        v[u][i] = ND_NULL_VERTEX;
+                        if (row[u].y > 0u) v[u][i] = PACKED ? (int32_t)packed_word(a.packed, e[u][i], &e[u][i]) : g.col[e[u][i]];
                     }
 #pragma unroll
                 for (uint32_t u = 0; u < kInFlight; ++u) {
-                    int32_t v[R];
-#pragma unroll
-                    for (uint32_t i = 0; i < R; ++i) {
-                        v[i] = (int32_t)word[u][i];
-                        if (PACKED) v[i] = row[u].y > 0u ? packed_vertex(a.packed, word[u][i], e[u][i]) : ND_NULL_VERTEX;
-                    }
-                    if (d0 + u * T < end) store_run<R, PAST>(out + (d0 + u * T) * R, v);
+                    if (PACKED)
+                        for (uint32_t i = 0; i < R; ++i)
+                            v[u][i] = row[u].y > 0u ? packed_vertex(a.packed, (uint32_t)v[u][i], e[u][i]) : ND_NULL_VERTEX;
+                    if (d0 + u * T < end) store_run<R, PAST>(out + (d0 + u * T) * R, v[u]);
                 }
             }
         }
