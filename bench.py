@@ -32,7 +32,7 @@ HBM_PEAK_GBS = 8000.0
 # from above.  Source: the counter table in profiles/one_launch_routes_rocprofv3.md.  None where not
 # profiled.
 MEASURED_TRAFFIC_BYTES = {
-    ("c5_khop", "khop_fused_kernel"): 19968795648,     # 14,869,094 KiB fetched + 4,631,683 KiB written
+    ("c5_khop", "khop_fused_kernel"): 19990791168,     # 14,867,272 KiB fetched + 4,654,985 KiB written
     ("c5_deepwalk", "walk_free_kernel"): 29908805632,  # 27,561,580 KiB fetched + 1,646,238 KiB written
 }
 

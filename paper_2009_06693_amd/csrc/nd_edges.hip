@@ -26,7 +26,8 @@
 // together, and full steps have code of their own, without a test of where the list ends.  Counting pass of 4,096
 // samples of 2,048 transits and vertices (10 GB of lists): 2.12 ms with one load at a time and the lists' places fetched
 // one after the other, 1.46 like this (6.9 TB/s; the loads alone, without the test, 1.44; loads of 16 bytes per lane
-// 1.47).  The filling pass is at 2.16 (3.08 so), of which its stores are 0.65.
+// 1.47).  L2 serves one look in eight, and vector instructions issue in 0.89 of the cycles.  The filling pass is at 2.02
+// (3.08 so), of which its stores are 0.65.
 //
 // The sample's transit slots are grouped by vertex as well: a vertex that several slots hold (layer
 // samples hold well-connected vertices many times over) is streamed once, and what is found goes to

@@ -173,7 +173,8 @@ __global__ __launch_bounds__(kFusedThreads) void khop_fused_kernel(GraphView<Off
 
 // The first hop of a call that groups its later ones: roots as a rule differ, so that grouping them by transit finds
 // nothing to share, and their draws leave in order.  Bound by the lines of the rows.  233 K roots of 25 draws, mean
-// degree 487: 85 us, 133 with the grouping (a sort, four kernels of groups and classes, 74 for the draws).
+// degree 487: 66 us over packed columns, 71 with the gap to the next launch and 87 so over plain ones; 133 with the grouping
+// (a sort, four kernels of groups and classes, 74 for the draws over plain columns).
 template <bool PACKED, typename OffT>
 __global__ __launch_bounds__(kFusedThreads) void khop_first_kernel(GraphView<OffT> g, PackedCols packed, uint64_t seed, uint32_t sample_base,
                                                                    const int32_t* __restrict__ roots, uint32_t n,
@@ -760,14 +761,15 @@ void slots_per_sample(const int32_t* fanout, int32_t k, int64_t* W) {
 // Whether the fused kernel takes the call.  Its limits are the rows in LDS and the links.  Its cost is one
 // scattered fetch per line a pair's draws touch, whatever other pairs touch; grouping by transit fetches a
 // line once for all its draws and pays for it with the sort and with scattered stores.  Measured from
-// all, a tenth and a fiftieth of the vertices of eleven graphs with fanouts [25,10], [10,10], [10,25], [20] and
-// [15,10,5]: grouping wins, by up to 1.6x, on dense graphs (rows that ten draws
+// all, a tenth and a fiftieth of the vertices of twelve graphs with fanouts [25,10], [10,10], [10,25], [20],
+// [15,10,5], [7,13], [8,8,4] and [5,5]: grouping wins, by up to 1.7x, on dense graphs (rows that ten draws
 // rarely share a line of) with many pairs per vertex and enough draws to pay for its launches; elsewhere it
-// loses, by up to 11x.  Near the lines, over links and grouped: mean degree 149, 10 pairs per vertex, 23 M draws 279
-// and 239 us, 58 M 441 and 358; degree 203, 25 pairs, 14 M 161 and 131, 10 pairs, 14 M 113 and 110; degree 93, 10 pairs,
-// 26 M 251 and 248, 66 M 421 and 384, 25 pairs, 66 M 550 and 522; degree 82, 25 pairs, 66 M 481 and 500; degree 862, 25
-// pairs, 5 M 87 and 88; degree 487, 15 pairs, 17 M 357 and 400; degree 60, 25 pairs, 58 M 419 and 456.  The lines are where
-// they were before the first hop went ungrouped; what they leave on the slower side is at most 12 %.
+// loses, by up to 6x from 1 M draws on.  Near the lines, over links and grouped: mean degree 152, 10 pairs per vertex, 23 M
+// draws 255 and 173 us, 58 M 402 and 319; degree 211, 25 pairs, 14 M 127 and 120, 10 pairs, 14 M 88 and 104; degree 98,
+// 10 pairs, 26 M 228 and 197, 25 pairs, 66 M 471 and 481; degree 84, 25 pairs, 66 M 433 and 469; degree 1059, 25 pairs,
+// 5 M 78 and 78; degree 487, 15 pairs, 17 M 343 and 341, 7 pairs, 21 M 301 and 217; degree 61, 25 pairs, 58 M 342 and 418; degree
+// 58, 10 pairs, 100 M 933 and 767.  The lines were drawn on times of earlier kernels of both routes; they now leave up to
+// 39 % (7 pairs per vertex, mean degrees of 152 and 487) and 22 % (the last one).
 bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
     if (!gr.links) return false;
     int64_t pairs = S;
@@ -787,11 +789,9 @@ bool khop_fused_fits(const Graph& gr, const int32_t* fanout, int32_t k, int64_t 
 
 // Whether a call is faster over the packed columns: where its draws fetch a line each or two and are many.  The m draws of
 // a short row share its lines anyway, and then only the instructions of the unpacking are felt.  Measured with
-// [25,10], [10,25], [20], [15,10,5], [7,13], [5,5], [10,10] and [8,8,4] on twelve graphs, plain time over packed time
-// (both with the better kind of store): from 6 M draws on and a mean degree of 6/5 of the last fanout 0.97 to 1.35
-// ([8,8,4] on 3 M vertices the least, [15,10,5] on R-MAT 18 the most), below it 0.81 to 1.0 ([10,25] at a mean degree of 20
-// and 29 0.81 and 0.83, [20] at 16 0.91); fewer draws 0.91 to 1.1 there, from 200 K on 0.97 to 1.39 at mean degrees
-// of 207 and 487, below that 0.96 to 1.03.
+// [25,10], [10,10], [10,25], [20], [15,10,5], [7,13], [8,8,4] and [5,5] on twelve graphs, plain time over packed time: where the rule
+// reads them 1.01 ([8,8,4] on the dense graph) to 1.45 ([10,25], 57 K vertices of mean degree 211); elsewhere 0.94
+// ([10,25] at a mean degree of 29) to 1.26 (6 M draws of [10,25], mean degree 61).
 bool khop_reads_packed(const Graph& gr, const int32_t* fanout, int32_t k, int64_t S) {
     if (!gr.links) return false;
     int64_t draws = S;
