@@ -25,9 +25,10 @@ constexpr uint32_t edge_map_bit(uint32_t hash) { return (hash >> 26) & 31u; }
 //   10 draws 0.87, 0.94, 1.08, 1.00;  25 draws 0.94, 0.96, 1.07, 1.07;  300 draws 1.00, 1.02, 1.04, 1.10.
 // 5.8 M pairs of 10 draws, mean degree 487 (57 rounds): 317 us in turn, 297 like this.
 constexpr uint32_t kNeighbourRounds = 3, kNeighbourDraws = 5;
-// The number of pairs from which a launch has its groups next to each other; pairs_per_round: of all its groups.
-constexpr uint32_t pairs_of_neighbours(uint32_t per_pair, uint32_t workgroups, uint32_t pairs_per_round) {
-    return workgroups % 8u == 0u && per_pair >= kNeighbourDraws ? kNeighbourRounds * pairs_per_round : 0xFFFFFFFFu;
+// The number of pairs from which a launch has its groups next to each other; draws_per_round: of all its groups.
+constexpr uint32_t pairs_of_neighbours(uint32_t per_pair, uint32_t workgroups, uint32_t draws_per_round) {
+    return workgroups % 8u == 0u && per_pair >= kNeighbourDraws ? (kNeighbourRounds * draws_per_round + per_pair - 1u) / per_pair
+                                                                : 0xFFFFFFFFu;
 }
 // Which block of the first round group `group` (0-3) of workgroup `workgroup` takes.
 constexpr uint32_t first_block(uint32_t workgroup, uint32_t group, uint32_t workgroups, bool next_to_each_other) {

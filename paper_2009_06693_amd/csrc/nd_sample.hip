@@ -354,8 +354,8 @@ int launch_tp(const Graph& gr, const DrawArgs& a, const SchedParams& sp, const T
     uint32_t ppb = a.m <= 256u ? 256u / a.m : 0u;
     if (ppb * a.m < 231u) ppb = 0u;
     const uint32_t groups = (uint32_t)blocks * (kWgThreads / 256);
-    const uint32_t per_round = ppb != 0u ? groups * ppb * kPairsInFlight<DRAW> : groups * 256u / a.m;
-    const uint32_t neighbours_from = pairs_of_neighbours(a.m, (uint32_t)blocks, per_round);
+    const uint32_t lanes_used = ppb != 0u ? ppb * kPairsInFlight<DRAW> * a.m : 256u;
+    const uint32_t neighbours_from = pairs_of_neighbours(a.m, (uint32_t)blocks, groups * lanes_used);
     mark_phase(lanes ? ND_PHASE_SAMPLE_SUB : ND_PHASE_SAMPLE_WG, stream);
     auto* kernel = &sample_tp_kernel<DRAW, false, OffT>;
     if (DRAW == kDrawUniform && a.packed.bytes) kernel = &sample_tp_kernel<DRAW, DRAW == kDrawUniform, OffT>;
